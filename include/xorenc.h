@@ -222,13 +222,12 @@ XORENC_API int32_t xorenc_encode(int32_t m, int32_t n, int32_t n_in, int32_t q, 
 
 /*
  * Encoder on the GPU with the fewest patches (Section 5.2, minimising n_patch for small n_in): for
- * every slice all 2^n_in inputs of the XOR-gate network are tried and one whose output differs from
- * the quantised bits on the fewest care positions is kept; among equals the smallest input read as
- * an integer (bit j = x_j).  Patches are the remaining mismatches.  Arguments, outputs, workspace and
- * stream behaviour exactly as xorenc_encode.  Work is l * 2^n_in network evaluations per plane, one slice per
- * lane and all of a slice's inputs in one kernel (about 3 * 10^12 evaluations per second on one MI355X: a million
- * slices take 20 ms at n_in = 16 and several seconds at n_in = 24): XORENC_EUNSUPPORTED for
- * n_in > XORENC_EXH_MAX_N_IN.
+ * every slice the input of the XOR-gate network whose output differs from the quantised bits on the fewest care
+ * positions; among equals the smallest input read as an integer (bit j = x_j).  Patches are the remaining
+ * mismatches.  Arguments, outputs, workspace and stream behaviour exactly as xorenc_encode, eight kernels.  Slices
+ * that can be encoded without patches cost what they cost in xorenc_encode; on the others all 2^n_in inputs are
+ * tried (1.4 * 10^13 network evaluations per second on one MI355X at n_out = 64, 6 * 10^12 at 192 and 256).
+ * XORENC_EUNSUPPORTED for n_in > XORENC_EXH_MAX_N_IN.
  */
 #define XORENC_EXH_MAX_N_IN 24
 XORENC_API int32_t xorenc_encode_exhaustive(int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,

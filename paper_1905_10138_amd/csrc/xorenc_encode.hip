@@ -9,13 +9,13 @@
 // the last care bit, back-substitution with every free variable 0 gives w^c, which is the
 // solution the reduced row-echelon form of the accepted rows yields.
 //
-// Second encoder (Section 5.2, minimising n_patch for small n_in): every one of the 2^n_in inputs is
-// tried on every slice and the one with the fewest mismatched care bits is kept.  All lanes walk the
-// inputs in the same (Gray code) order, so the output of the XOR-gate network for the current input
-// is wave-uniform and is kept up to date with one XOR of a column of M per step; a lane only counts
-// the mismatches on its own slice.  Ties go to the smallest input read as an integer.
+// Second encoder (Section 5.2, minimising n_patch for small n_in): the input with the fewest mismatched care bits,
+// the smallest one read as an integer among equals.  A slice on which Algorithm 1 drops nothing has a solution
+// without mismatches, and back-substitution gives the smallest such input: its pivots are the columns that are not
+// sums of lower columns, so a free variable (a sum of lower columns) can be 0 whatever the higher variables are and
+// a pivot variable is determined by the higher ones.  Only the other slices are searched: they are listed, and
+// every one of the 2^n_in inputs is tried on them as a matrix product on the matrix cores (exhaustive_search_kernel).
 #include <hip/hip_runtime.h>
-#include <type_traits>
 
 #include <mutex>
 
@@ -57,24 +57,32 @@ struct EncParams {
   uint64_t *pbits;      // [q][n_slots] patch bitmaps (workspace)
   uint32_t *counts;     // [q*n_units] patches per unit (workspace)
   int64_t n_slots, n_eslots;
-  int32_t n_units, n_in, q, J, spr, espr;
+  int32_t n_units, n_in, q, J;
   uint32_t M_rows[XORENC_MAX_N_OUT];
 };
 
-__global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P) {
+// Position of the first word of slice `gid` (plane-major eslot index) in [q][n_slots] arrays of words: eslot =
+// (rb*espr + S)*32 + rr, word w of the slice is slot ((rb*espr + S)*J + w)*32 + rr, and n_slots = J*n_eslots.
+__device__ inline int64_t first_word(int64_t gid, int J) { return (gid >> 5) * J * 32 + (gid & 31); }
+
+// SEARCH: first pass of the encoder with the fewest patches.  The low half of a slice's first patch word becomes its
+// key: the solution x (below 2^24) when nothing was dropped, otherwise all ones, and the slice joins the list, whose
+// entry i is the high half of the first patch word of slice i; *list_len counts them.  The pass covers the slices from
+// `first` (a multiple of 32) to `end`, and the list holds numbers relative to `first` (32 bits).
+template <bool SEARCH>
+__global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P, int64_t first, int64_t end,
+                                                                   uint32_t *list_len) {
   __shared__ uint32_t basis[XORENC_MAX_N_IN][ENC_THREADS];
   const int tid = threadIdx.x;
-  const int64_t gid = (int64_t)blockIdx.x * ENC_THREADS + tid;  // (plane, slice) flattened, slices in eslot order
-  const int64_t total = (int64_t)P.q * P.n_eslots;
-  const bool valid = gid < total;
+  // (plane, slice) flattened, slices in eslot order
+  const int64_t gid = first + (int64_t)blockIdx.x * ENC_THREADS + tid;
+  const bool valid = gid < end;
   const int64_t eslot = valid ? gid % P.n_eslots : 0;
   const int p = valid ? (int)(gid / P.n_eslots) : 0;
-  // eslot = (rb*espr + S)*32 + rr; word w of the slice is slot (rb*spr + S*J + w)*32 + rr
   const int rr = (int)(eslot & 31);
-  const int64_t eu = eslot >> 5;
-  const int64_t rb = eu / P.espr, S = eu % P.espr;
-  const int64_t unit0 = rb * P.spr + S * P.J;
+  const int64_t unit0 = (eslot >> 5) * P.J;
 
+  bool dropped = false;
   uint32_t have = 0;     // bit j: a basis row with pivot j exists
   uint32_t rhsbits = 0;  // bit j: right-hand side of that row
   for (int w = 0; w < P.J; ++w) {  // uniform; care bits in ascending position over the whole slice
@@ -103,12 +111,15 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P)
       have |= 1u << piv;
       rhsbits |= rhs << piv;
     }
-    if (valid) P.pbits[(int64_t)p * P.n_slots + slot] = patches;
-    // patches per unit = sum over the 32 lanes that share it (n_eslots is a multiple of 32)
-    int cnt = __builtin_popcountll(patches);
+    dropped = dropped || patches != 0;
+    if constexpr (!SEARCH) {
+      if (valid) P.pbits[(int64_t)p * P.n_slots + slot] = patches;
+      // patches per unit = sum over the 32 lanes that share it (n_eslots is a multiple of 32)
+      int cnt = __builtin_popcountll(patches);
 #pragma unroll
-    for (int o = 16; o >= 1; o >>= 1) cnt += __shfl_down(cnt, o, 32);
-    if (valid && rr == 0) P.counts[(int64_t)p * P.n_units + unit0 + w] = (uint32_t)cnt;
+      for (int o = 16; o >= 1; o >>= 1) cnt += __shfl_down(cnt, o, 32);
+      if (valid && rr == 0) P.counts[(int64_t)p * P.n_units + unit0 + w] = (uint32_t)cnt;
+    }
   }
   // back-substitution, free variables = 0, highest pivot first
   uint32_t x = 0;
@@ -121,6 +132,21 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P)
     x |= v << j;
   }
   store_enc_unit(P.enc, (int64_t)p * P.n_eslots + eslot, P.n_in, x, valid);
+  if constexpr (SEARCH) {
+    uint32_t *const halves = reinterpret_cast<uint32_t *>(P.pbits);
+    if (valid) halves[2 * first_word(gid, P.J)] = dropped ? 0xffffffffu : x;
+    const uint64_t listed = __ballot(valid && dropped);
+    if (listed) {
+      const int lane = tid & 63, leader = __builtin_ctzll(listed);
+      uint32_t base = 0;
+      if (lane == leader) base = atomicAdd(list_len, (uint32_t)__builtin_popcountll(listed));
+      base = (uint32_t)__shfl((int)base, leader, 64);
+      if (valid && dropped) {
+        const int64_t at = first + base + __builtin_popcountll(listed & ((1ull << lane) - 1ull));
+        halves[2 * first_word(at, P.J) + 1] = (uint32_t)(gid - first);
+      }
+    }
+  }
 }
 
 struct ExhParams {
@@ -130,94 +156,191 @@ struct ExhParams {
   uint64_t *pbits;
   uint32_t *counts;
   int64_t n_slots, n_eslots;
-  int32_t n_units, n_in, q, spr, espr;
+  int32_t n_units, n_in, q;
   uint64_t Mcol[XORENC_MAX_J][XORENC_EXH_MAX_N_IN];  // [w][j]: bit i = M[64 w + i][j]
+  uint64_t used[XORENC_MAX_J];                       // [w]: bit i = row 64 w + i of M is not zero
 };
 
-// WIDE: more than 16 input bits, where the pair (mismatches, input) no longer fits one 32-bit word.
-template <int J, bool WIDE>
-__global__ __launch_bounds__(ENC_THREADS) void exhaustive_slices_kernel(ExhParams P) {
-  const int tid = threadIdx.x;
-  const int64_t gid = (int64_t)blockIdx.x * ENC_THREADS + tid;
-  const int64_t total = (int64_t)P.q * P.n_eslots;
-  const bool valid = gid < total;
-  const int64_t eslot = valid ? gid % P.n_eslots : 0;
-  const int p = valid ? (int)(gid / P.n_eslots) : 0;
-  const int rr = (int)(eslot & 31);
-  const int64_t eu = eslot >> 5;
-  const int64_t rb = eu / P.espr, S = eu % P.espr;
-  const int64_t unit0 = rb * P.spr + S * J;
+typedef __attribute__((ext_vector_type(8))) int32_t i32x8;
 
-  uint64_t care[J], want[J];
+__global__ void exhaustive_reset_kernel(uint32_t *list_len) { *list_len = 0; }
+
+// All 2^n_in inputs on the listed slices, 128 slices and 2^c consecutive inputs per item of work of a wave.
+//
+// With A[x][i] = (-1)^(output bit i of the network for input x) and B[i][s] = -(-1)^(wanted bit i of slice s) on care
+// bits, 0 elsewhere, (A B)[x][s] = 2 mismatches - care bits: a product on the matrix cores in FP4, 32 inputs x 32
+// slices x 64 bits per instruction.  A's block scale is 2^14 and the accumulator starts at the input's number in its
+// tile (and the shift that keeps it positive), so a result plus 32 * tile is a float that holds the pair (mismatches,
+// input) exactly (2 * 2^14 * 256 + 2^15 < 2^24; all terms are integers) and its minimum is the answer: half a v_min3_u32
+// on the bit patterns per input and slice.  Rows of M
+// that are zero mismatch or match whatever the input is and stay out, so that at most half of the care bits can
+// be mismatched at the minimum and a key (mismatches + 1) << 24 | input fits 32 bits.  Tiles are visited in Gray code
+// order: one column of M flips the signs of A (4 XORs per 64 bits, shared by the four slice tiles).
+//
+// Bound: VALU issue beside the matrix instructions.  Every slice of 16384 x 4096, n_out = 192, n_in = 20 used to be
+// searched, one slice per lane, at 2J AND, 2J XOR and 2J population counts per input: 219 ms for the call, 0.35 ms now
+// (16384 x 4096 with half of the weights kept, n_out = 64, n_in = 16, where nearly every slice is searched: 14 and 5 ms).
+// The width of an item falls from 2^15 to 2^10 inputs when there are too few slices to give every wave eight items.
+template <int J>
+__global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhParams P, int64_t first,
+                                                                          const uint32_t *list_len) {
+  constexpr int NS = 4;                                   // slice tiles of a wave
+  constexpr int COLS = XORENC_EXH_MAX_N_IN - 5;           // columns that change from tile to tile
+  constexpr int kShift = J * 64 << 14;                    // keeps the accumulators positive
+  __shared__ uint4 flip_s[COLS][J][2];                    // sign bits of column 5 + c, per half of a word
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, rl = lane & 31;
+  auto sign_bits = [](uint32_t y, int d) { return ((y >> d) & 0x11111111u) << 3; };
+  for (int i = tid; i < COLS * J * 2; i += ENC_THREADS) {
+    const int c = i / (2 * J), w = (i >> 1) % J, h = i & 1;
+    const uint32_t y = (uint32_t)(P.Mcol[w][5 + c] >> (32 * h));
+    flip_s[c][w][h] = make_uint4(sign_bits(y, 0), sign_bits(y, 1), sign_bits(y, 2), sign_bits(y, 3));
+  }
+  __syncthreads();
+  const uint32_t n_list = *list_len;
+  const int64_t groups = ((int64_t)n_list + 32 * NS - 1) / (32 * NS);
+  const int64_t waves = (int64_t)gridDim.x * (ENC_THREADS / 64);
+  int c = P.n_in < 15 ? (P.n_in > 5 ? P.n_in : 5) : 15;
+  while (c > 10 && (groups << (P.n_in - c)) < 8 * waves) --c;
+  const int chunk_bits = P.n_in > c ? P.n_in - c : 0;
+  const uint32_t tiles = 1u << (c - 5);
+
+  const uint32_t *const halves = reinterpret_cast<const uint32_t *>(P.pbits);
+  uint32_t *const keys = reinterpret_cast<uint32_t *>(P.pbits);
+  // row rl of A for the inputs 0..31 (columns beyond n_in are zero: with n_in = 4 the inputs 16..31 repeat 0..15)
+  uint32_t base[J];
 #pragma unroll
   for (int w = 0; w < J; ++w) {
-    const int64_t slot = (unit0 + w) * 32 + rr;
-    care[w] = valid ? P.mask[slot] : 0ull;
-    want[w] = valid ? (P.planes[(int64_t)p * P.n_slots + slot] & care[w]) : 0ull;
+    base[w] = 0;
+#pragma unroll
+    for (int j = 0; j < 5; ++j)
+      base[w] ^= ((rl >> j) & 1) ? (uint32_t)(P.Mcol[w][j] >> (32 * g)) : 0u;
   }
-  // wave-uniform state: the current input x and its output y
-  uint32_t x = 0;
-  uint64_t y[J], c0[J], c1[J], c2[J];
+  f32x16 number;
 #pragma unroll
-  for (int w = 0; w < J; ++w) {
-    y[w] = 0;
-    c0[w] = P.Mcol[w][0];
-    c1[w] = P.Mcol[w][1];
-    c2[w] = P.Mcol[w][2];
-  }
-  // (mismatches << 16) | x, or (mismatches << 32) | x: the minimum is the fewest patches, then the smallest x
-  typename std::conditional<WIDE, uint64_t, uint32_t>::type best = WIDE ? ~0ull : 0xffffffffu;
-  auto flip = [&](int j, const uint64_t(&col)[J]) {
-    x ^= 1u << j;
+  for (int i = 0; i < 16; ++i) number[i] = (float)(kShift + 8 * (i / 4) + 4 * g + i % 4);
+
+  for (int64_t item = (int64_t)blockIdx.x * (ENC_THREADS / 64) + (tid >> 6); item < (groups << chunk_bits);
+       item += waves) {  // uniform per wave
+    const int64_t group = item >> chunk_bits;
+    const uint32_t chunk = (uint32_t)(item & ((1 << chunk_bits) - 1));
+    // ---- the four slice tiles: column rl of tile t is list entry group*128 + 32 t + rl
+    i32x8 b[NS][J];
+    uint32_t care_bits[NS];
+    int64_t gid[NS];
 #pragma unroll
-    for (int w = 0; w < J; ++w) y[w] ^= col[w];
-  };
-  auto eval = [&]() {
-    uint32_t cnt = 0;
+    for (int t = 0; t < NS; ++t) {
+      const int64_t li = group * (32 * NS) + 32 * t + rl;
+      const bool valid = li < n_list;
+      gid[t] = first + (valid ? (int64_t)halves[2 * first_word(first + li, J) + 1] : 0);
+      const int64_t word = first_word(gid[t], J);  // in [q][n_slots]
+      const int64_t mask_word = word - gid[t] / P.n_eslots * P.n_slots;
+      care_bits[t] = 0;
 #pragma unroll
-    for (int w = 0; w < J; ++w) cnt += (uint32_t)__builtin_popcountll((y[w] & care[w]) ^ want[w]);
-    if constexpr (WIDE) {
-      const uint64_t key = ((uint64_t)cnt << 32) | x;
-      best = key < best ? key : best;
-    } else {
-      best = min(best, (cnt << 16) | x);
+      for (int w = 0; w < J; ++w) {
+        uint32_t care = reinterpret_cast<const uint32_t *>(P.mask)[2 * (mask_word + 32 * w) + g];
+        const uint32_t want = reinterpret_cast<const uint32_t *>(P.planes)[2 * (word + 32 * w) + g];
+        care &= (uint32_t)(P.used[w] >> (32 * g));
+        if (!valid) care = 0;
+        care_bits[t] += __builtin_popcount(care);
+        const uint32_t minus = care & ~want;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) b[t][w][d] = (int32_t)((((care >> d) & 0x11111111u) << 1) | sign_bits(minus, d));
+#pragma unroll
+        for (int d = 4; d < 8; ++d) b[t][w][d] = 0;
+      }
+      care_bits[t] += (uint32_t)__shfl_xor((int)care_bits[t], 32, 64);
     }
-  };
-  // Gray code walk: step k flips bit ctz(k); inside a group of 8 steps the flipped bits are
-  // 0 1 0 2 0 1 0, and only the step into the next group needs a column chosen at run time.
-  const uint32_t groups = (1u << P.n_in) >> 3;  // n_in >= 4 (checked by the entry point): at least two groups
-  for (uint32_t g = 0; g < groups; ++g) {
-    if (g) {
-      const int j = __builtin_ctz(g) + 3;
-      uint64_t cj[J];
+    // ---- A of the chunk's first tile
+    const uint32_t tile0 = chunk << (c - 5);
+    i32x8 a[J];
 #pragma unroll
-      for (int w = 0; w < J; ++w) cj[w] = P.Mcol[w][j];
-      flip(j, cj);
+    for (int w = 0; w < J; ++w) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) a[w][d] = (int32_t)(0x22222222u | sign_bits(base[w], d));
+#pragma unroll
+      for (int d = 4; d < 8; ++d) a[w][d] = 0;
     }
-    eval();
-    flip(0, c0); eval();
-    flip(1, c1); eval();
-    flip(0, c0); eval();
-    flip(2, c2); eval();
-    flip(0, c0); eval();
-    flip(1, c1); eval();
-    flip(0, c0); eval();
+    auto flip = [&](int col) {
+#pragma unroll
+      for (int w = 0; w < J; ++w) {
+        const uint4 f = flip_s[col][w][g];
+        a[w][0] ^= (int32_t)f.x;
+        a[w][1] ^= (int32_t)f.y;
+        a[w][2] ^= (int32_t)f.z;
+        a[w][3] ^= (int32_t)f.w;
+      }
+    };
+    for (uint32_t bits = tile0; bits; bits &= bits - 1) flip(__builtin_ctz(bits));  // uniform
+    uint32_t best[NS];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) best[t] = 0xffffffffu;
+    for (uint32_t i = 0; i < tiles; ++i) {          // uniform
+      const float offset = (float)(32u * (i ^ (i >> 1)));
+      f32x16 d[NS];
+#pragma unroll
+      for (int t = 0; t < NS; ++t) {
+        d[t] = number;
+#pragma unroll
+        for (int w = 0; w < J; ++w)
+          d[t] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[w], b[t][w], d[t], 4, 4, 0, 127 + 14, 0, 127);
+      }
+      if (i + 1 < tiles) flip(__builtin_ctz(i + 1));
+#pragma unroll
+      for (int t = 0; t < NS; ++t) {
+        // (positive floats order like their bit patterns; integer minima need no NaN handling)
+        uint32_t v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = __float_as_uint(d[t][k]);
+        const uint32_t m0 = min(min(v[0], v[1]), v[2]), m1 = min(min(v[3], v[4]), v[5]),
+                       m2 = min(min(v[6], v[7]), v[8]), m3 = min(min(v[9], v[10]), v[11]),
+                       m4 = min(min(v[12], v[13]), v[14]);
+        const uint32_t m = min(min(min(m0, m1), m2), min(min(m3, m4), v[15]));
+        best[t] = min(best[t], __float_as_uint(__uint_as_float(m) + offset));
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+      const float v = __uint_as_float(min(best[t], (uint32_t)__shfl_xor((int)best[t], 32, 64))) - (float)kShift;
+      const int64_t li = group * (32 * NS) + 32 * t + rl;
+      if (g == 0 && li < n_list) {
+        const int32_t pair = (int32_t)v + (int32_t)(care_bits[t] << 14);  // mismatches << 15 | input inside the chunk
+        const uint32_t x = (chunk << c) | (uint32_t)(pair & 0x7fff);
+        atomicMin(keys + 2 * first_word(gid[t], J), ((uint32_t)(pair >> 15) + 1u) << 24 | x);
+      }
+    }
   }
-  const uint32_t xb = WIDE ? (uint32_t)best : (uint32_t)best & 0xffffu;
-  // output of the chosen input, patches = mismatched care bits
+}
+
+// Keys -> patch words, patches per unit, and the encrypted bits of the slices that were searched.
+template <int J>
+__global__ __launch_bounds__(ENC_THREADS) void exhaustive_finish_kernel(ExhParams P, int64_t first, int64_t end) {
+  const int64_t gid = first + (int64_t)blockIdx.x * ENC_THREADS + threadIdx.x;
+  const bool valid = gid < end;
+  const int64_t word = first_word(valid ? gid : first, J);  // in [q][n_slots]
+  const uint32_t key = valid ? (uint32_t)P.pbits[word] : 0u;
+  const uint32_t x = key & 0xffffffu;
+  const bool searched = key >= 1u << 24;
+  const bool any = __ballot(searched) != 0ull;  // uniform
 #pragma unroll
   for (int w = 0; w < J; ++w) {
-    uint64_t yb = 0;
-    for (int j = 0; j < P.n_in; ++j) yb ^= ((xb >> j) & 1u) ? P.Mcol[w][j] : 0ull;
-    const uint64_t patches = (yb & care[w]) ^ want[w];
-    const int64_t slot = (unit0 + w) * 32 + rr;
-    if (valid) P.pbits[(int64_t)p * P.n_slots + slot] = patches;
+    uint64_t patches = 0;
+    if (any) {
+      uint64_t y = 0;
+      for (int j = 0; j < P.n_in; ++j) y ^= ((x >> j) & 1u) ? P.Mcol[w][j] : 0ull;
+      if (searched) {
+        const int64_t p = gid / P.n_eslots;
+        patches = (y ^ P.planes[word + 32 * w]) & P.mask[word + 32 * w - p * P.n_slots];
+      }
+    }
+    if (valid) P.pbits[word + 32 * w] = patches;
     int cnt = __builtin_popcountll(patches);
+    if (any) {
 #pragma unroll
-    for (int o = 16; o >= 1; o >>= 1) cnt += __shfl_down(cnt, o, 32);
-    if (valid && rr == 0) P.counts[(int64_t)p * P.n_units + unit0 + w] = (uint32_t)cnt;
+      for (int o = 16; o >= 1; o >>= 1) cnt += __shfl_down(cnt, o, 32);
+    }
+    if (valid && (gid & 31) == 0) P.counts[(gid >> 5) * J + w] = (uint32_t)cnt;
   }
-  store_enc_unit(P.enc, (int64_t)p * P.n_eslots + eslot, P.n_in, xb, valid);
+  if (any) store_enc_unit(P.enc, gid, P.n_in, x, valid);
 }
 
 // Exclusive scan of counts[0..n) into off[0..n] in three launches and without extra memory.  A block
@@ -364,60 +487,69 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
   const unsigned eblocks = (unsigned)((slices + ENC_THREADS - 1) / ENC_THREADS);
   const unsigned blocks = (unsigned)((total + ENC_THREADS - 1) / ENC_THREADS);
   const int J = n_out / 64;
-  if (exhaustive) {
-    ExhParams P;
-    P.mask = mask;
-    P.planes = planes;
-    P.enc = enc_out;
-    P.pbits = pbits;
-    P.counts = counts;
-    P.n_slots = sz.n_slots;
-    P.n_eslots = sz.n_eslots;
-    P.n_units = (int32_t)sz.n_units;
-    P.n_in = n_in;
-    P.q = q;
-    P.spr = (int32_t)sz.spr;
-    P.espr = (int32_t)sz.espr;
-    for (int w = 0; w < XORENC_MAX_J; ++w)
+  EncParams P;
+  P.mask = mask;
+  P.planes = planes;
+  P.enc = enc_out;
+  P.pbits = pbits;
+  P.counts = counts;
+  P.n_slots = sz.n_slots;
+  P.n_eslots = sz.n_eslots;
+  P.n_units = (int32_t)sz.n_units;
+  P.n_in = n_in;
+  P.q = q;
+  P.J = J;
+  for (int i = 0; i < XORENC_MAX_N_OUT; ++i) P.M_rows[i] = i < n_out ? M_rows[i] : 0u;
+  if (!exhaustive) {
+    hipLaunchKernelGGL(encode_slices_kernel<false>, dim3(eblocks), dim3(ENC_THREADS), 0, st, P, (int64_t)0, slices, nullptr);
+  } else {
+    ExhParams E;
+    E.mask = mask;
+    E.planes = planes;
+    E.enc = enc_out;
+    E.pbits = pbits;
+    E.counts = counts;
+    E.n_slots = sz.n_slots;
+    E.n_eslots = sz.n_eslots;
+    E.n_units = (int32_t)sz.n_units;
+    E.n_in = n_in;
+    E.q = q;
+    for (int w = 0; w < XORENC_MAX_J; ++w) {
+      E.used[w] = 0;
+      for (int i = 0; i < 64; ++i) E.used[w] |= (uint64_t)(P.M_rows[64 * w + i] != 0) << i;
       for (int j = 0; j < XORENC_EXH_MAX_N_IN; ++j) {
         uint64_t col = 0;
-        if (w < J && j < n_in)
-          for (int i = 0; i < 64; ++i) col |= (uint64_t)((M_rows[64 * w + i] >> j) & 1u) << i;
-        P.Mcol[w][j] = col;
-      }
-    const dim3 eg(eblocks), eb(ENC_THREADS);
-    if (n_in <= 16) {
-      switch (J) {
-        case 1: hipLaunchKernelGGL((exhaustive_slices_kernel<1, false>), eg, eb, 0, st, P); break;
-        case 2: hipLaunchKernelGGL((exhaustive_slices_kernel<2, false>), eg, eb, 0, st, P); break;
-        case 3: hipLaunchKernelGGL((exhaustive_slices_kernel<3, false>), eg, eb, 0, st, P); break;
-        default: hipLaunchKernelGGL((exhaustive_slices_kernel<4, false>), eg, eb, 0, st, P); break;
-      }
-    } else {
-      switch (J) {
-        case 1: hipLaunchKernelGGL((exhaustive_slices_kernel<1, true>), eg, eb, 0, st, P); break;
-        case 2: hipLaunchKernelGGL((exhaustive_slices_kernel<2, true>), eg, eb, 0, st, P); break;
-        case 3: hipLaunchKernelGGL((exhaustive_slices_kernel<3, true>), eg, eb, 0, st, P); break;
-        default: hipLaunchKernelGGL((exhaustive_slices_kernel<4, true>), eg, eb, 0, st, P); break;
+        for (int i = 0; i < 64; ++i) col |= (uint64_t)((P.M_rows[64 * w + i] >> j) & 1u) << i;
+        E.Mcol[w][j] = col;
       }
     }
-  } else {
-    EncParams P;
-    P.mask = mask;
-    P.planes = planes;
-    P.enc = enc_out;
-    P.pbits = pbits;
-    P.counts = counts;
-    P.n_slots = sz.n_slots;
-    P.n_eslots = sz.n_eslots;
-    P.n_units = (int32_t)sz.n_units;
-    P.n_in = n_in;
-    P.q = q;
-    P.J = J;
-    P.spr = (int32_t)sz.spr;
-    P.espr = (int32_t)sz.espr;
-    for (int i = 0; i < XORENC_MAX_N_OUT; ++i) P.M_rows[i] = i < n_out ? M_rows[i] : 0u;
-    hipLaunchKernelGGL(encode_slices_kernel, dim3(eblocks), dim3(ENC_THREADS), 0, st, P);
+    uint32_t *const list_len = patch_off_out;  // free until the scan, which overwrites every entry
+    const int64_t range = (int64_t)1 << 31;  // slices of a pass: list entries are 32-bit numbers
+    for (int64_t first = 0; first < slices; first += range) {
+      const int64_t end = slices - first < range ? slices : first + range;
+      const dim3 eg((unsigned)((end - first + ENC_THREADS - 1) / ENC_THREADS)), eb(ENC_THREADS);
+      const dim3 sg(J == 1 ? 1024 : J == 2 ? 768 : 512);  // search: the workgroups that are resident walk over the items
+      hipLaunchKernelGGL(exhaustive_reset_kernel, dim3(1), dim3(1), 0, st, list_len);
+      hipLaunchKernelGGL(encode_slices_kernel<true>, eg, eb, 0, st, P, first, end, list_len);
+      switch (J) {
+        case 1:
+          hipLaunchKernelGGL(exhaustive_search_kernel<1>, sg, eb, 0, st, E, first, list_len);
+          hipLaunchKernelGGL(exhaustive_finish_kernel<1>, eg, eb, 0, st, E, first, end);
+          break;
+        case 2:
+          hipLaunchKernelGGL(exhaustive_search_kernel<2>, sg, eb, 0, st, E, first, list_len);
+          hipLaunchKernelGGL(exhaustive_finish_kernel<2>, eg, eb, 0, st, E, first, end);
+          break;
+        case 3:
+          hipLaunchKernelGGL(exhaustive_search_kernel<3>, sg, eb, 0, st, E, first, list_len);
+          hipLaunchKernelGGL(exhaustive_finish_kernel<3>, eg, eb, 0, st, E, first, end);
+          break;
+        default:
+          hipLaunchKernelGGL(exhaustive_search_kernel<4>, sg, eb, 0, st, E, first, list_len);
+          hipLaunchKernelGGL(exhaustive_finish_kernel<4>, eg, eb, 0, st, E, first, end);
+          break;
+      }
+    }
   }
   const int nscan = (int)((n_counts + SCAN_BLOCK - 1) / SCAN_BLOCK);
   hipLaunchKernelGGL(scan_local_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, counts, patch_off_out, (int)n_counts);

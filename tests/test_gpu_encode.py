@@ -169,3 +169,39 @@ def test_patch_capacity_overflow_is_reported_and_retried():
     L = xe.encode(wl.m, wl.n, 8, 1, M_rows, mask, planes, torch.from_numpy(wl.alpha).to(dev), patch_capacity=2)
     assert L.patch.numel() == int(enc.n_patch.sum())
     assert xe.check_packed(L.to_host()) == 0
+
+
+@pytest.mark.parametrize("m,n_out,n_in,q,zero_rows", [
+    # 32 slices per tile, 128 per item of work: one slice short of, exactly and one slice beyond them
+    (1, 64, 4, 1, True), (31, 64, 5, 1, False), (127, 64, 6, 1, True), (128, 128, 7, 1, True), (129, 192, 8, 1, False),
+    (129, 256, 10, 2, True), (65, 256, 11, 3, True), (257, 64, 12, 4, False)])
+def test_fewest_patches_when_every_slice_is_searched(m, n_out, n_in, q, zero_rows):
+    """Nearly every weight kept, so that no slice has a solution without mismatches and all of them go through the search
+    over 2^n_in inputs; rows of the network that are zero (their care bits match or mismatch whatever the input is) or
+    equal; an all-pruned row next to them.  Compared bit for bit with the oracle's search."""
+    import torch
+    import paper_1905_10138_amd as xe
+    from oracle import encoder
+    rng = np.random.default_rng(1000 * n_out + 10 * n_in + m)
+    n = n_out - 3
+    keep = np.zeros((m, n_out), dtype=bool)
+    keep[:, :n] = rng.random((m, n)) < 0.9
+    keep[m // 2] = m == 1
+    keep[:, n:] = False
+    planes = (rng.random((q, m, n_out)) < 0.5) & keep
+    M = rng.integers(0, 2, size=(n_out, n_in), dtype=np.uint8)
+    if zero_rows:
+        M[::7] = 0
+        M[1::9] = M[2]
+    alpha = np.ones((q, m), np.float32)
+    enc = encoder.encode(keep, planes, alpha, M, n, exhaustive=True)
+    dev = torch.device("cuda:0")
+    words = lambda a: torch.from_numpy(xe.pack_bits(a[:, :n], n_out).view(np.int64))
+    M_rows = (M.astype(np.uint64) << np.arange(n_in, dtype=np.uint64)).sum(axis=1).astype(np.uint32)
+    L = xe.encode_exhaustive(m, n, n_in, q, M_rows, words(keep).to(dev), torch.stack([words(p) for p in planes]).to(dev),
+                             torch.from_numpy(alpha).to(dev), n_out=n_out)
+    w_c, _, n_patch, d_patch = xe.unpack(L.to_host())
+    ow, _, onp, odp, _ = paper_format_arrays(enc)
+    assert np.array_equal(w_c, ow)
+    assert np.array_equal(n_patch, onp)
+    assert np.array_equal(d_patch, odp)
