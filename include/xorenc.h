@@ -213,7 +213,8 @@ XORENC_API int32_t xorenc_pack_bits(int32_t m, int32_t n, int32_t n_out, const u
  *              must compare patch_off_out[q*n_units] (the true total) with patch_capacity after the
  *              stream has run, and retry with a larger buffer if it is larger.
  *   workspace  DEV  uint64[q*n_slots] + uint32[q*n_units] bytes, 8-byte aligned (scratch, contents undefined after)
- * Five kernels are enqueued on hip_stream (slices, three for the offset scan, patch entries); nothing synchronises.
+ * Two kernels are enqueued on hip_stream (slices; offsets and patch entries), three more for a scan from 8.4 million
+ * slices on; nothing synchronises.
  */
 XORENC_API int32_t xorenc_encode(int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out, const uint32_t *M_rows,
                                  const uint64_t *mask, const uint64_t *planes, uint8_t *enc_out,
@@ -224,7 +225,7 @@ XORENC_API int32_t xorenc_encode(int32_t m, int32_t n, int32_t n_in, int32_t q, 
  * Encoder on the GPU with the fewest patches (Section 5.2, minimising n_patch for small n_in): for
  * every slice the input of the XOR-gate network whose output differs from the quantised bits on the fewest care
  * positions; among equals the smallest input read as an integer (bit j = x_j).  Patches are the remaining
- * mismatches.  Arguments, outputs, workspace and stream behaviour exactly as xorenc_encode, eight kernels.  Slices
+ * mismatches.  Arguments, outputs, workspace and stream behaviour exactly as xorenc_encode, three more kernels.  Slices
  * that can be encoded without patches cost what they cost in xorenc_encode; on the others all 2^n_in inputs are
  * tried (1.4 * 10^13 network evaluations per second on one MI355X at n_out = 64, 6 * 10^12 at 192 and 256).
  * XORENC_EUNSUPPORTED for n_in > XORENC_EXH_MAX_N_IN.

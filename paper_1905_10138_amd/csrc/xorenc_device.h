@@ -50,6 +50,13 @@ static __device__ inline uint32_t load_enc(const uint8_t *enc, int64_t e, int n_
 // of the wave must call this; lanes whose `valid` is false write nothing.
 static __device__ inline void store_enc_unit(uint8_t *enc, int64_t e, int n_in, uint32_t x, bool valid) {
   const int rr = (int)(threadIdx.x & 31);
+  uint32_t *const d = reinterpret_cast<uint32_t *>(enc) + ((e - rr) >> 5) * n_in;
+  if ((n_in & (n_in - 1)) == 0) {  // uniform: 32/n_in whole fields per dword, gathered by neighbours
+    uint32_t word = x << ((rr * n_in) & 31);
+    for (int o = 1; o * n_in < 32; o <<= 1) word |= (uint32_t)__shfl_xor((int)word, o, 32);
+    if (valid && ((rr * n_in) & 31) == 0) d[(rr * n_in) >> 5] = word;
+    return;
+  }
   const int lo_bit = 32 * rr;             // this lane composes dword rr of the run (if rr < n_in)
   const int first = lo_bit / n_in;        // first field that reaches into it
   uint32_t word = 0;
@@ -60,10 +67,7 @@ static __device__ inline void store_enc_unit(uint8_t *enc, int64_t e, int n_in, 
     const int pos = k * n_in - lo_bit;    // where field k starts relative to this dword
     if (k < 32 && pos < 32) word |= pos >= 0 ? (xk << pos) : (xk >> (-pos));
   }
-  if (valid && rr < n_in) {
-    uint32_t *d = reinterpret_cast<uint32_t *>(enc);
-    d[((e - rr) >> 5) * n_in + rr] = word;
-  }
+  if (valid && rr < n_in) d[rr] = word;
 }
 
 static __device__ inline uint32_t f32_to_bf16_rne(float f) {

@@ -50,102 +50,175 @@ int32_t static_scratch_address(void **out) {
   return XORENC_OK;
 }
 
+constexpr int ENC_UNITS = ENC_THREADS / 32;  // 32-slice groups of a workgroup
+
+// The patch counts that the slices leave for the offsets live where the workspace has 4 bytes per unit and plane:
+// 2-byte counts (a unit has at most 2048 patches), and totals per counting block, the ENC_UNITS * J units that a
+// workgroup covers in one plane, in flattened (plane, block) order.
+struct Counts {
+  uint16_t *unit;     // [q*n_units]
+  uint32_t *block;    // [q*n_blocks]
+  uint32_t *scanned;  // [q*n_blocks + 1]: exclusive sums of `block` (only when there are many blocks)
+  int32_t n_units, n_blocks;
+};
+
 struct EncParams {
   const uint64_t *mask;
   const uint64_t *planes;
   uint8_t *enc;
-  uint64_t *pbits;      // [q][n_slots] patch bitmaps (workspace)
-  uint32_t *counts;     // [q*n_units] patches per unit (workspace)
+  uint64_t *pbits;      // [q][n_slots] patch bitmaps (workspace); only units with patches are written and read
+  Counts counts;
   int64_t n_slots, n_eslots;
-  int32_t n_units, n_in, q, J;
+  int32_t n_in, J;
   uint32_t M_rows[XORENC_MAX_N_OUT];
 };
 
-// Position of the first word of slice `gid` (plane-major eslot index) in [q][n_slots] arrays of words: eslot =
-// (rb*espr + S)*32 + rr, word w of the slice is slot ((rb*espr + S)*J + w)*32 + rr, and n_slots = J*n_eslots.
-__device__ inline int64_t first_word(int64_t gid, int J) { return (gid >> 5) * J * 32 + (gid & 31); }
+// First word of slice `eslot` = (rb*espr + S)*32 + rr of a plane: word w of it is slot ((rb*espr + S)*J + w)*32 + rr.
+__device__ inline int64_t first_word(int64_t eslot, int J) { return (eslot >> 5) * J * 32 + (eslot & 31); }
 
-// SEARCH: first pass of the encoder with the fewest patches.  The low half of a slice's first patch word becomes its
-// key: the solution x (below 2^24) when nothing was dropped, otherwise all ones, and the slice joins the list, whose
-// entry i is the high half of the first patch word of slice i; *list_len counts them.  The pass covers the slices from
-// `first` (a multiple of 32) to `end`, and the list holds numbers relative to `first` (32 bits).
-template <bool SEARCH>
-__global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P, int64_t first, int64_t end,
+// A pass over the slices [first, first + n) of every plane (n a multiple of 32, n*q < 2^32) numbers them plane by
+// plane, entry = plane*n + slice - first; this is the first word of one in [q][n_slots].
+__device__ inline int64_t entry_word(uint32_t entry, int64_t first, uint32_t n, int64_t n_slots, int J) {
+  const uint32_t p = entry / n;
+  return p * n_slots + first_word(first + (entry - p * n), J);
+}
+
+// Patches of the 32 slices of a unit (one per lane of a half wave): count for the unit and its block, bitmaps if there
+// are any.  Every lane of the wave calls this with the same w; `block_total` is LDS.
+__device__ inline void put_patches(uint64_t *pbits, const Counts &c, int p, int64_t slot, uint64_t patches, bool valid,
+                                   uint32_t *block_total) {
+  uint32_t cnt = 0;
+  if (__ballot(patches != 0)) {  // uniform
+    cnt = (uint32_t)__builtin_popcountll(patches);
+#pragma unroll
+    for (int o = 16; o >= 1; o >>= 1) cnt += (uint32_t)__shfl_xor((int)cnt, o, 32);
+    if (valid && cnt) pbits[slot] = patches;
+  }
+  if (valid && (threadIdx.x & 31) == 0) {
+    c.unit[(int64_t)p * c.n_units + (slot - (int64_t)p * c.n_units * 32) / 32] = (uint16_t)cnt;
+    if (cnt) atomicAdd(block_total, cnt);
+  }
+}
+
+// Algorithm 1.  The planes share the mask, so the coefficients of a slice's equations, which of them join the basis
+// and the pivots are the same for all planes: one elimination with Q right-hand sides, which travel in the bits above
+// the n_in coefficients of a row (PACKED: n_in + Q <= 32) or as bits per pivot in a register per plane.
+//
+// Bound: the chain of dependent LDS reads of a reduction (one per set pivot) and the longest of 64 slices in a wave.
+// The network's rows are read from LDS (they used to be fetched from the kernel arguments with a vector load per
+// equation), and the basis takes n_in KB of LDS instead of 32.  16384 x 4096, two planes, n_in = 8: 24 us; 45 us with
+// one elimination per plane and rows from the arguments.
+//
+// SEARCH: first pass of the encoder with the fewest patches, over the slices [first, first + n).  The low half of a
+// slice's first patch word becomes its key: the solution x (below 2^24) when nothing was dropped, otherwise all ones,
+// and the slice joins the list, whose entry i is the high half of the first patch word of slice i of the pass's
+// numbering; *list_len counts them.
+template <int Q, bool PACKED, bool SEARCH>
+__global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P, int64_t first, int64_t n,
                                                                    uint32_t *list_len) {
-  __shared__ uint32_t basis[XORENC_MAX_N_IN][ENC_THREADS];
+  extern __shared__ uint32_t enc_lds[];  // [n_in][ENC_THREADS] basis, then the 64 J rows of the network
+  __shared__ uint32_t block_total[Q];
+  uint32_t *const rows = enc_lds + P.n_in * ENC_THREADS;
   const int tid = threadIdx.x;
-  // (plane, slice) flattened, slices in eslot order
-  const int64_t gid = first + (int64_t)blockIdx.x * ENC_THREADS + tid;
-  const bool valid = gid < end;
-  const int64_t eslot = valid ? gid % P.n_eslots : 0;
-  const int p = valid ? (int)(gid / P.n_eslots) : 0;
-  const int rr = (int)(eslot & 31);
-  const int64_t unit0 = (eslot >> 5) * P.J;
+  for (int i = tid; i < 64 * P.J; i += ENC_THREADS) rows[i] = P.M_rows[i];
+  if (tid < Q) block_total[tid] = 0;
+  const int64_t rel = (int64_t)blockIdx.x * ENC_THREADS + tid;
+  const bool valid = rel < n;
+  const int64_t eslot = first + (valid ? rel : 0);
+  const int64_t slot0 = first_word(eslot, P.J);
+  const int n_in = P.n_in;
+  const uint32_t coefs = n_in < 32 ? (1u << n_in) - 1u : 0xffffffffu;
+  uint32_t *const basis = enc_lds + tid;  // row with pivot j at basis[j * ENC_THREADS]
+  __syncthreads();
 
-  bool dropped = false;
-  uint32_t have = 0;     // bit j: a basis row with pivot j exists
-  uint32_t rhsbits = 0;  // bit j: right-hand side of that row
+  uint32_t have = 0;         // bit j: a basis row with pivot j exists
+  uint32_t rhsbits[Q] = {};  // !PACKED: bit j = right-hand side of that row
+  bool dropped[Q] = {};
   for (int w = 0; w < P.J; ++w) {  // uniform; care bits in ascending position over the whole slice
-    const int64_t slot = (unit0 + w) * 32 + rr;
+    const int64_t slot = slot0 + 32 * w;
     uint64_t care = valid ? P.mask[slot] : 0ull;
-    const uint64_t bits = valid ? P.planes[(int64_t)p * P.n_slots + slot] : 0ull;
-    uint64_t patches = 0;
+    uint64_t bits[Q], patches[Q];
+#pragma unroll
+    for (int p = 0; p < Q; ++p) {
+      bits[p] = valid ? P.planes[p * P.n_slots + slot] : 0ull;
+      patches[p] = 0;
+    }
     while (care) {
       const int i = __builtin_ctzll(care);
       care &= care - 1;
-      uint32_t row = P.M_rows[64 * w + i];
-      uint32_t rhs = (uint32_t)((bits >> i) & 1);
+      uint32_t row = rows[64 * w + i];
+      uint32_t rhs = 0;  // bit p: plane p
+#pragma unroll
+      for (int p = 0; p < Q; ++p) rhs |= (uint32_t)((bits[p] >> i) & 1) << p;
+      if constexpr (PACKED) row |= rhs << n_in;
       uint32_t t = row & have;
-      while (t) {  // reduce, ascending pivots
+      while (t) {  // reduce, ascending pivots (a basis row has no bit below its pivot)
         const int j = __builtin_ctz(t);
-        row ^= basis[j][tid];
-        rhs ^= (rhsbits >> j) & 1u;
-        t = row & have & ~((2u << j) - 1u);
+        row ^= basis[j * ENC_THREADS];
+        if constexpr (!PACKED) {
+#pragma unroll
+          for (int p = 0; p < Q; ++p) rhs ^= ((rhsbits[p] >> j) & 1u) << p;
+        }
+        t = row & have;
       }
-      if (row == 0) {
-        if (rhs) patches |= 1ull << i;  // 0 ... 0 | 1: unsolvable, the equation is dropped
+      if ((row & coefs) == 0) {  // 0 ... 0 | rhs: the equation is dropped where that is 1
+        if constexpr (PACKED) rhs = row >> n_in;
+#pragma unroll
+        for (int p = 0; p < Q; ++p) patches[p] |= (uint64_t)((rhs >> p) & 1u) << i;
         continue;
       }
       const int piv = __builtin_ctz(row);
-      basis[piv][tid] = row;
+      basis[piv * ENC_THREADS] = row;
       have |= 1u << piv;
-      rhsbits |= rhs << piv;
-    }
-    dropped = dropped || patches != 0;
-    if constexpr (!SEARCH) {
-      if (valid) P.pbits[(int64_t)p * P.n_slots + slot] = patches;
-      // patches per unit = sum over the 32 lanes that share it (n_eslots is a multiple of 32)
-      int cnt = __builtin_popcountll(patches);
+      if constexpr (!PACKED) {
 #pragma unroll
-      for (int o = 16; o >= 1; o >>= 1) cnt += __shfl_down(cnt, o, 32);
-      if (valid && rr == 0) P.counts[(int64_t)p * P.n_units + unit0 + w] = (uint32_t)cnt;
+        for (int p = 0; p < Q; ++p) rhsbits[p] |= ((rhs >> p) & 1u) << piv;
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < Q; ++p) {
+      dropped[p] = dropped[p] || patches[p] != 0;
+      if constexpr (!SEARCH)
+        put_patches(P.pbits, P.counts, p, p * P.n_slots + slot, patches[p], valid, block_total + p);
     }
   }
   // back-substitution, free variables = 0, highest pivot first
-  uint32_t x = 0;
+  uint32_t x[Q] = {};
   uint32_t t = have;
   while (t) {
     const int j = 31 - __builtin_clz(t);
     t &= ~(1u << j);
-    const uint32_t others = basis[j][tid] & x;  // pivots above j already solved; free ones are 0
-    const uint32_t v = ((rhsbits >> j) & 1u) ^ (__builtin_popcount(others) & 1u);
-    x |= v << j;
+    const uint32_t row = basis[j * ENC_THREADS];
+#pragma unroll
+    for (int p = 0; p < Q; ++p) {
+      const uint32_t others = row & coefs & x[p];  // pivots above j already solved; free ones are 0
+      const uint32_t rhs = PACKED ? row >> (n_in + p) : rhsbits[p] >> j;
+      x[p] |= ((rhs ^ (uint32_t)__builtin_popcount(others)) & 1u) << j;
+    }
   }
-  store_enc_unit(P.enc, (int64_t)p * P.n_eslots + eslot, P.n_in, x, valid);
+#pragma unroll
+  for (int p = 0; p < Q; ++p) store_enc_unit(P.enc, p * P.n_eslots + eslot, n_in, x[p], valid);
   if constexpr (SEARCH) {
     uint32_t *const halves = reinterpret_cast<uint32_t *>(P.pbits);
-    if (valid) halves[2 * first_word(gid, P.J)] = dropped ? 0xffffffffu : x;
-    const uint64_t listed = __ballot(valid && dropped);
-    if (listed) {
-      const int lane = tid & 63, leader = __builtin_ctzll(listed);
-      uint32_t base = 0;
-      if (lane == leader) base = atomicAdd(list_len, (uint32_t)__builtin_popcountll(listed));
-      base = (uint32_t)__shfl((int)base, leader, 64);
-      if (valid && dropped) {
-        const int64_t at = first + base + __builtin_popcountll(listed & ((1ull << lane) - 1ull));
-        halves[2 * first_word(at, P.J) + 1] = (uint32_t)(gid - first);
+#pragma unroll
+    for (int p = 0; p < Q; ++p) {
+      const bool search = valid && dropped[p];
+      if (valid) halves[2 * (p * P.n_slots + slot0)] = search ? 0xffffffffu : x[p];
+      const uint64_t listed = __ballot(search);
+      if (listed) {
+        const int lane = tid & 63, leader = __builtin_ctzll(listed);
+        uint32_t base = 0;
+        if (lane == leader) base = atomicAdd(list_len, (uint32_t)__builtin_popcountll(listed));
+        base = (uint32_t)__shfl((int)base, leader, 64);
+        if (search) {
+          const uint32_t at = base + (uint32_t)__builtin_popcountll(listed & ((1ull << lane) - 1ull));
+          halves[2 * entry_word(at, first, (uint32_t)n, P.n_slots, P.J) + 1] = (uint32_t)(p * n + rel);
+        }
       }
     }
+  } else {
+    __syncthreads();
+    if (tid < Q) P.counts.block[tid * P.counts.n_blocks + blockIdx.x] = block_total[tid];
   }
 }
 
@@ -154,9 +227,9 @@ struct ExhParams {
   const uint64_t *planes;
   uint8_t *enc;
   uint64_t *pbits;
-  uint32_t *counts;
+  Counts counts;
   int64_t n_slots, n_eslots;
-  int32_t n_units, n_in, q;
+  int32_t n_in;
   uint64_t Mcol[XORENC_MAX_J][XORENC_EXH_MAX_N_IN];  // [w][j]: bit i = M[64 w + i][j]
   uint64_t used[XORENC_MAX_J];                       // [w]: bit i = row 64 w + i of M is not zero
 };
@@ -182,7 +255,7 @@ __global__ void exhaustive_reset_kernel(uint32_t *list_len) { *list_len = 0; }
 // (16384 x 4096 with half of the weights kept, n_out = 64, n_in = 16, where nearly every slice is searched: 14 and 5 ms).
 // The width of an item falls from 2^15 to 2^10 inputs when there are too few slices to give every wave eight items.
 template <int J>
-__global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhParams P, int64_t first,
+__global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhParams P, int64_t first, int64_t n,
                                                                           const uint32_t *list_len) {
   constexpr int NS = 4;                                   // slice tiles of a wave
   constexpr int COLS = XORENC_EXH_MAX_N_IN - 5;           // columns that change from tile to tile
@@ -226,19 +299,19 @@ __global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhPa
     // ---- the four slice tiles: column rl of tile t is list entry group*128 + 32 t + rl
     i32x8 b[NS][J];
     uint32_t care_bits[NS];
-    int64_t gid[NS];
+    int64_t word[NS];                                     // first word of the slice in [q][n_slots]
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
       const int64_t li = group * (32 * NS) + 32 * t + rl;
       const bool valid = li < n_list;
-      gid[t] = first + (valid ? (int64_t)halves[2 * first_word(first + li, J) + 1] : 0);
-      const int64_t word = first_word(gid[t], J);  // in [q][n_slots]
-      const int64_t mask_word = word - gid[t] / P.n_eslots * P.n_slots;
+      const uint32_t entry = valid ? halves[2 * entry_word((uint32_t)li, first, (uint32_t)n, P.n_slots, J) + 1] : 0u;
+      word[t] = entry_word(entry, first, (uint32_t)n, P.n_slots, J);
+      const int64_t mask_word = word[t] - entry / (uint32_t)n * P.n_slots;
       care_bits[t] = 0;
 #pragma unroll
       for (int w = 0; w < J; ++w) {
         uint32_t care = reinterpret_cast<const uint32_t *>(P.mask)[2 * (mask_word + 32 * w) + g];
-        const uint32_t want = reinterpret_cast<const uint32_t *>(P.planes)[2 * (word + 32 * w) + g];
+        const uint32_t want = reinterpret_cast<const uint32_t *>(P.planes)[2 * (word[t] + 32 * w) + g];
         care &= (uint32_t)(P.used[w] >> (32 * g));
         if (!valid) care = 0;
         care_bits[t] += __builtin_popcount(care);
@@ -305,42 +378,40 @@ __global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhPa
       if (g == 0 && li < n_list) {
         const int32_t pair = (int32_t)v + (int32_t)(care_bits[t] << 14);  // mismatches << 15 | input inside the chunk
         const uint32_t x = (chunk << c) | (uint32_t)(pair & 0x7fff);
-        atomicMin(keys + 2 * first_word(gid[t], J), ((uint32_t)(pair >> 15) + 1u) << 24 | x);
+        atomicMin(keys + 2 * word[t], ((uint32_t)(pair >> 15) + 1u) << 24 | x);
       }
     }
   }
 }
 
-// Keys -> patch words, patches per unit, and the encrypted bits of the slices that were searched.
+// Keys -> patches, their counts, and the encrypted bits of the slices that were searched.  One plane per grid row.
 template <int J>
-__global__ __launch_bounds__(ENC_THREADS) void exhaustive_finish_kernel(ExhParams P, int64_t first, int64_t end) {
-  const int64_t gid = first + (int64_t)blockIdx.x * ENC_THREADS + threadIdx.x;
-  const bool valid = gid < end;
-  const int64_t word = first_word(valid ? gid : first, J);  // in [q][n_slots]
+__global__ __launch_bounds__(ENC_THREADS) void exhaustive_finish_kernel(ExhParams P, int64_t first, int64_t n) {
+  __shared__ uint32_t block_total;
+  if (threadIdx.x == 0) block_total = 0;
+  const int64_t rel = (int64_t)blockIdx.x * ENC_THREADS + threadIdx.x;
+  const int p = blockIdx.y;
+  const bool valid = rel < n;
+  const int64_t eslot = first + (valid ? rel : 0);
+  const int64_t slot = first_word(eslot, J), word = p * P.n_slots + slot;
   const uint32_t key = valid ? (uint32_t)P.pbits[word] : 0u;
   const uint32_t x = key & 0xffffffu;
   const bool searched = key >= 1u << 24;
   const bool any = __ballot(searched) != 0ull;  // uniform
+  __syncthreads();
 #pragma unroll
   for (int w = 0; w < J; ++w) {
     uint64_t patches = 0;
     if (any) {
       uint64_t y = 0;
       for (int j = 0; j < P.n_in; ++j) y ^= ((x >> j) & 1u) ? P.Mcol[w][j] : 0ull;
-      if (searched) {
-        const int64_t p = gid / P.n_eslots;
-        patches = (y ^ P.planes[word + 32 * w]) & P.mask[word + 32 * w - p * P.n_slots];
-      }
+      if (searched) patches = (y ^ P.planes[word + 32 * w]) & P.mask[slot + 32 * w];
     }
-    if (valid) P.pbits[word + 32 * w] = patches;
-    int cnt = __builtin_popcountll(patches);
-    if (any) {
-#pragma unroll
-      for (int o = 16; o >= 1; o >>= 1) cnt += __shfl_down(cnt, o, 32);
-    }
-    if (valid && (gid & 31) == 0) P.counts[(gid >> 5) * J + w] = (uint32_t)cnt;
+    put_patches(P.pbits, P.counts, p, word + 32 * w, patches, valid, &block_total);
   }
-  if (any) store_enc_unit(P.enc, gid, P.n_in, x, valid);
+  if (any) store_enc_unit(P.enc, p * P.n_eslots + eslot, P.n_in, x, valid);
+  __syncthreads();
+  if (threadIdx.x == 0) P.counts.block[p * P.counts.n_blocks + (int)(first / ENC_THREADS) + blockIdx.x] = block_total;
 }
 
 // Exclusive scan of counts[0..n) into off[0..n] in three launches and without extra memory.  A block
@@ -430,28 +501,115 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_add_kernel(uint32_t *off, i
     if (first + i < n && !(tid == 0 && i == 0)) off[first + i] += add;
 }
 
-__global__ __launch_bounds__(ENC_THREADS) void emit_patches_kernel(const uint64_t *pbits, const uint32_t *off,
-                                                                  uint16_t *patch, int64_t capacity,
-                                                                  int64_t total_slots) {
-  const int64_t gid = (int64_t)blockIdx.x * ENC_THREADS + threadIdx.x;
-  const bool valid = gid < total_slots;
-  uint64_t w = valid ? pbits[gid] : 0ull;
-  const int cnt = __builtin_popcountll(w);
-  // exclusive prefix of cnt inside the 32-lane unit
-  int incl = cnt;
+// Offsets of the units' patch lists and the lists themselves.  A workgroup covers `per` counting blocks (at most
+// EMIT_UNITS units); where its lists start is the sum of the blocks before it, which it adds up itself (SCANNED: reads
+// from the scanned totals).  Adding them up reads 4 bytes per ENC_UNITS * J units and workgroup from the L2 (16384 x
+// 4096, two planes: 64 KB at most) and replaces three scan launches; beyond kDirectBlocks blocks the scan is cheaper.
+constexpr int EMIT_UNITS = 128;
+constexpr int kDirectBlocks = 32768;
+
+template <bool SCANNED>
+__global__ __launch_bounds__(ENC_THREADS) void emit_patches_kernel(const uint64_t *pbits, Counts C, int q, int64_t n_slots,
+                                                                  int units_per_block, int per, uint32_t *off,
+                                                                  uint16_t *patch, int64_t capacity) {
+  __shared__ uint32_t wsum[ENC_THREADS / 64], start_s[EMIT_UNITS];
+  __shared__ int64_t slot_s[EMIT_UNITS];  // first bitmap of a unit with patches, -1 for the others
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_all = q * C.n_blocks;
+  const int block0 = blockIdx.x * per;
+  // unit of this thread (tid < EMIT_UNITS): flattened block, plane, unit of the plane
+  const int blk = block0 + tid / units_per_block;
+  const int p = min(blk, n_all - 1) / C.n_blocks;
+  const int64_t u = (int64_t)(blk - p * C.n_blocks) * units_per_block + tid % units_per_block;
+  const bool mine = tid < per * units_per_block && blk < n_all && u < C.n_units;
+  const uint32_t cnt = mine ? C.unit[(int64_t)p * C.n_units + u] : 0u;
+  uint32_t before = 0;  // patches of earlier workgroups
+  if constexpr (SCANNED) {
+    before = C.scanned[block0];
+  } else {
+    int i = tid;
+    for (; i + 7 * ENC_THREADS < block0; i += 8 * ENC_THREADS) {
+      uint32_t v[8];
 #pragma unroll
-  for (int o = 1; o < 32; o <<= 1) {
-    const int v = __shfl_up(incl, o, 32);
-    if ((threadIdx.x & 31) >= o) incl += v;
+      for (int k = 0; k < 8; ++k) v[k] = C.block[i + k * ENC_THREADS];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) before += v[k];
+    }
+    for (; i < block0; i += ENC_THREADS) before += C.block[i];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) before += (uint32_t)__shfl_xor((int)before, o, 64);
+    if (lane == 0) wsum[wave] = before;
+    __syncthreads();
+    before = 0;
+#pragma unroll
+    for (int w = 0; w < ENC_THREADS / 64; ++w) before += wsum[w];
+    __syncthreads();
   }
-  if (!valid || !w) return;
-  int64_t pos = (int64_t)off[gid >> 5] + (incl - cnt);
-  const uint32_t rr = (uint32_t)(gid & 31);
-  while (w) {
-    const int bit = __builtin_ctzll(w);
-    w &= w - 1;
-    if (pos < capacity) patch[pos] = (uint16_t)((rr << 6) | bit);
-    ++pos;
+  uint32_t incl = cnt;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t up = (uint32_t)__shfl_up((int)incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  if (wave == 1) incl += wsum[0];  // (the units sit in the first two waves)
+  const uint32_t start = before + incl - cnt;
+  if (tid < EMIT_UNITS) {
+    start_s[tid] = start;
+    slot_s[tid] = cnt ? p * n_slots + u * 32 : -1;
+  }
+  if (mine) {
+    off[(int64_t)p * C.n_units + u] = start;
+    if (p == q - 1 && u == C.n_units - 1) off[(int64_t)q * C.n_units] = start + cnt;
+  }
+  __syncthreads();
+  // a half wave per unit; the bitmaps of its units are requested together
+  const int rr = tid & 31, t0 = tid >> 5;
+  uint64_t bits[EMIT_UNITS / ENC_UNITS];
+#pragma unroll
+  for (int k = 0; k < EMIT_UNITS / ENC_UNITS; ++k) {
+    const int64_t slot = slot_s[t0 + k * ENC_UNITS];
+    bits[k] = slot >= 0 ? pbits[slot + rr] : 0ull;
+  }
+#pragma unroll
+  for (int k = 0; k < EMIT_UNITS / ENC_UNITS; ++k) {
+    uint64_t w = bits[k];
+    if (!__ballot(w != 0)) continue;  // uniform
+    const int c = __builtin_popcountll(w);
+    int inc = c;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+      const int v = __shfl_up(inc, o, 32);
+      if (rr >= o) inc += v;
+    }
+    int64_t pos = (int64_t)start_s[t0 + k * ENC_UNITS] + (inc - c);
+    while (w) {
+      const int bit = __builtin_ctzll(w);
+      w &= w - 1;
+      if (pos < capacity) patch[pos] = (uint16_t)((rr << 6) | bit);
+      ++pos;
+    }
+  }
+}
+
+template <int Q, bool SEARCH>
+void launch_slices(const EncParams &P, int64_t first, int64_t n, uint32_t *list_len, hipStream_t st) {
+  const dim3 grid((unsigned)((n + ENC_THREADS - 1) / ENC_THREADS));
+  const size_t lds = ((size_t)P.n_in * ENC_THREADS + 64 * P.J) * sizeof(uint32_t);
+  if (P.n_in + Q <= 32)
+    hipLaunchKernelGGL((encode_slices_kernel<Q, true, SEARCH>), grid, dim3(ENC_THREADS), lds, st, P, first, n, list_len);
+  else
+    hipLaunchKernelGGL((encode_slices_kernel<Q, false, SEARCH>), grid, dim3(ENC_THREADS), lds, st, P, first, n, list_len);
+}
+
+template <bool SEARCH>
+void launch_slices_q(int q, const EncParams &P, int64_t first, int64_t n, uint32_t *list_len, hipStream_t st) {
+  switch (q) {
+    case 1: launch_slices<1, SEARCH>(P, first, n, list_len, st); break;
+    case 2: launch_slices<2, SEARCH>(P, first, n, list_len, st); break;
+    case 3: launch_slices<3, SEARCH>(P, first, n, list_len, st); break;
+    default: launch_slices<4, SEARCH>(P, first, n, list_len, st); break;
   }
 }
 
@@ -481,39 +639,45 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
   for (int i = 0; i < n_out; ++i)
     if (n_in < 32 && (M_rows[i] >> n_in)) return XORENC_EINVAL;
   uint64_t *pbits = static_cast<uint64_t *>(workspace);
-  uint32_t *counts = reinterpret_cast<uint32_t *>(pbits + total);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  const int64_t slices = (int64_t)q * sz.n_eslots;
-  const unsigned eblocks = (unsigned)((slices + ENC_THREADS - 1) / ENC_THREADS);
-  const unsigned blocks = (unsigned)((total + ENC_THREADS - 1) / ENC_THREADS);
   const int J = n_out / 64;
+  Counts C;
+  C.n_units = (int32_t)sz.n_units;
+  C.n_blocks = (int32_t)((sz.n_eslots + ENC_THREADS - 1) / ENC_THREADS);
+  const int n_blocks = q * C.n_blocks;
+  const bool scan = n_blocks > kDirectBlocks;
+  // The workspace's 4 bytes per unit and plane hold 2 bytes per unit and 4 per block (8 where the totals are scanned,
+  // which takes thousands of blocks): a block has at least eight units or is the only one of its plane, so they fit
+  // from two units per plane on.  With one unit the counts lie in the offsets, which one workgroup writes after
+  // reading them.
+  unsigned char *const area = reinterpret_cast<unsigned char *>(pbits + total);
+  const int64_t unit_bytes = sz.n_units > 1 ? (2 * n_counts + 3) / 4 * 4 : 0;
+  C.unit = sz.n_units > 1 ? reinterpret_cast<uint16_t *>(area) : reinterpret_cast<uint16_t *>(patch_off_out);
+  C.block = reinterpret_cast<uint32_t *>(area + unit_bytes);
+  C.scanned = scan ? C.block + n_blocks : nullptr;
   EncParams P;
   P.mask = mask;
   P.planes = planes;
   P.enc = enc_out;
   P.pbits = pbits;
-  P.counts = counts;
+  P.counts = C;
   P.n_slots = sz.n_slots;
   P.n_eslots = sz.n_eslots;
-  P.n_units = (int32_t)sz.n_units;
   P.n_in = n_in;
-  P.q = q;
   P.J = J;
   for (int i = 0; i < XORENC_MAX_N_OUT; ++i) P.M_rows[i] = i < n_out ? M_rows[i] : 0u;
   if (!exhaustive) {
-    hipLaunchKernelGGL(encode_slices_kernel<false>, dim3(eblocks), dim3(ENC_THREADS), 0, st, P, (int64_t)0, slices, nullptr);
+    launch_slices_q<false>(q, P, 0, sz.n_eslots, nullptr, st);
   } else {
     ExhParams E;
     E.mask = mask;
     E.planes = planes;
     E.enc = enc_out;
     E.pbits = pbits;
-    E.counts = counts;
+    E.counts = C;
     E.n_slots = sz.n_slots;
     E.n_eslots = sz.n_eslots;
-    E.n_units = (int32_t)sz.n_units;
     E.n_in = n_in;
-    E.q = q;
     for (int w = 0; w < XORENC_MAX_J; ++w) {
       E.used[w] = 0;
       for (int i = 0; i < 64; ++i) E.used[w] |= (uint64_t)(P.M_rows[64 * w + i] != 0) << i;
@@ -523,40 +687,48 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
         E.Mcol[w][j] = col;
       }
     }
-    uint32_t *const list_len = patch_off_out;  // free until the scan, which overwrites every entry
-    const int64_t range = (int64_t)1 << 31;  // slices of a pass: list entries are 32-bit numbers
-    for (int64_t first = 0; first < slices; first += range) {
-      const int64_t end = slices - first < range ? slices : first + range;
-      const dim3 eg((unsigned)((end - first + ENC_THREADS - 1) / ENC_THREADS)), eb(ENC_THREADS);
+    // free until the last kernel overwrites every entry (behind the counts where those are in the offsets too)
+    uint32_t *const list_len = patch_off_out + q * sz.n_units;
+    const int64_t range = (int64_t)1 << 29;  // slices of a pass: list entries are 32-bit numbers
+    for (int64_t first = 0; first < sz.n_eslots; first += range) {
+      const int64_t n_pass = sz.n_eslots - first < range ? sz.n_eslots - first : range;
+      const dim3 eb(ENC_THREADS), fg((unsigned)((n_pass + ENC_THREADS - 1) / ENC_THREADS), (unsigned)q);
       const dim3 sg(J == 1 ? 1024 : J == 2 ? 768 : 512);  // search: the workgroups that are resident walk over the items
       hipLaunchKernelGGL(exhaustive_reset_kernel, dim3(1), dim3(1), 0, st, list_len);
-      hipLaunchKernelGGL(encode_slices_kernel<true>, eg, eb, 0, st, P, first, end, list_len);
+      launch_slices_q<true>(q, P, first, n_pass, list_len, st);
       switch (J) {
         case 1:
-          hipLaunchKernelGGL(exhaustive_search_kernel<1>, sg, eb, 0, st, E, first, list_len);
-          hipLaunchKernelGGL(exhaustive_finish_kernel<1>, eg, eb, 0, st, E, first, end);
+          hipLaunchKernelGGL(exhaustive_search_kernel<1>, sg, eb, 0, st, E, first, n_pass, list_len);
+          hipLaunchKernelGGL(exhaustive_finish_kernel<1>, fg, eb, 0, st, E, first, n_pass);
           break;
         case 2:
-          hipLaunchKernelGGL(exhaustive_search_kernel<2>, sg, eb, 0, st, E, first, list_len);
-          hipLaunchKernelGGL(exhaustive_finish_kernel<2>, eg, eb, 0, st, E, first, end);
+          hipLaunchKernelGGL(exhaustive_search_kernel<2>, sg, eb, 0, st, E, first, n_pass, list_len);
+          hipLaunchKernelGGL(exhaustive_finish_kernel<2>, fg, eb, 0, st, E, first, n_pass);
           break;
         case 3:
-          hipLaunchKernelGGL(exhaustive_search_kernel<3>, sg, eb, 0, st, E, first, list_len);
-          hipLaunchKernelGGL(exhaustive_finish_kernel<3>, eg, eb, 0, st, E, first, end);
+          hipLaunchKernelGGL(exhaustive_search_kernel<3>, sg, eb, 0, st, E, first, n_pass, list_len);
+          hipLaunchKernelGGL(exhaustive_finish_kernel<3>, fg, eb, 0, st, E, first, n_pass);
           break;
         default:
-          hipLaunchKernelGGL(exhaustive_search_kernel<4>, sg, eb, 0, st, E, first, list_len);
-          hipLaunchKernelGGL(exhaustive_finish_kernel<4>, eg, eb, 0, st, E, first, end);
+          hipLaunchKernelGGL(exhaustive_search_kernel<4>, sg, eb, 0, st, E, first, n_pass, list_len);
+          hipLaunchKernelGGL(exhaustive_finish_kernel<4>, fg, eb, 0, st, E, first, n_pass);
           break;
       }
     }
   }
-  const int nscan = (int)((n_counts + SCAN_BLOCK - 1) / SCAN_BLOCK);
-  hipLaunchKernelGGL(scan_local_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, counts, patch_off_out, (int)n_counts);
-  hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(1024), 0, st, patch_off_out, (int)n_counts, nscan);
-  hipLaunchKernelGGL(scan_add_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, patch_off_out, (int)n_counts);
-  hipLaunchKernelGGL(emit_patches_kernel, dim3(blocks), dim3(ENC_THREADS), 0, st, pbits, patch_off_out, patch_out,
-                     patch_capacity, total);
+  const int units_per_block = ENC_UNITS * J, per = EMIT_UNITS / units_per_block;
+  const dim3 emit_grid((unsigned)((n_blocks + per - 1) / per));
+  if (scan) {
+    const int nscan = (n_blocks + SCAN_BLOCK - 1) / SCAN_BLOCK;
+    hipLaunchKernelGGL(scan_local_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, C.block, C.scanned, n_blocks);
+    hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(1024), 0, st, C.scanned, n_blocks, nscan);
+    hipLaunchKernelGGL(scan_add_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, C.scanned, n_blocks);
+    hipLaunchKernelGGL(emit_patches_kernel<true>, emit_grid, dim3(ENC_THREADS), 0, st, pbits, C, q, sz.n_slots,
+                       units_per_block, per, patch_off_out, patch_out, patch_capacity);
+  } else {
+    hipLaunchKernelGGL(emit_patches_kernel<false>, emit_grid, dim3(ENC_THREADS), 0, st, pbits, C, q, sz.n_slots,
+                       units_per_block, per, patch_off_out, patch_out, patch_capacity);
+  }
   return xorenc_internal_check_launch();
 }
 

@@ -205,3 +205,38 @@ def test_fewest_patches_when_every_slice_is_searched(m, n_out, n_in, q, zero_row
     assert np.array_equal(w_c, ow)
     assert np.array_equal(n_patch, onp)
     assert np.array_equal(d_patch, odp)
+
+
+@pytest.mark.parametrize("name,m,n,n_out,n_in,S", [
+    # one unit per plane; two; a counting block (eight 32-row groups of one slice) short, full and one over; the last
+    # widths whose right-hand sides fit above the coefficients of a row, and the first that do not (q = 1, 2, 3)
+    ("large_q2", 20, 50, 64, 8, 0.5), ("lstm", 33, 64, 64, 24, 0.3), ("large_q2", 224, 64, 64, 8, 0.7),
+    ("large_q2", 256, 64, 64, 8, 0.7), ("large_q2", 257, 128, 128, 12, 0.7), ("large_q1", 64, 300, 64, 31, 0.4),
+    ("large_q1", 64, 300, 64, 32, 0.4), ("large_q2", 64, 300, 64, 30, 0.4), ("large_q2", 64, 300, 64, 31, 0.4),
+    ("lstm", 64, 300, 192, 29, 0.7), ("lstm", 64, 300, 192, 30, 0.7)])
+def test_encoder_counting_blocks_and_right_hand_sides(name, m, n, n_out, n_in, S):
+    wl, enc = encoded_workload(name, m, n, S=S, n_out=n_out, n_in=n_in)
+    _check_against_oracle(wl, enc)
+
+
+def test_encoder_with_more_counting_blocks_than_one_workgroup_adds_up():
+    """8.4 million slices: the totals of the counting blocks are scanned by kernels of their own.  Offsets and lists are
+    checked through the decoder (every kept bit of every plane comes back) and the number of patches."""
+    import torch
+    import paper_1905_10138_amd as xe
+    dev = torch.device("cuda:0")
+    m, n, q, n_in = 32800, 4096, 4, 8
+    sz = xe.get_sizes(m, n, n_in, q)
+    assert q * -(-sz["n_eslots"] // 256) > 32768
+    g = torch.Generator(device=dev)
+    g.manual_seed(7)
+    words = lambda *shape: torch.randint(-2**63, 2**63 - 1, shape, dtype=torch.int64, device=dev, generator=g)
+    mask = words(sz["n_slots"]) & words(sz["n_slots"]) & words(sz["n_slots"]) & words(sz["n_slots"])   # one in sixteen kept
+    planes = words(q, sz["n_slots"])
+    M_rows = np.random.default_rng(3).integers(1, 256, size=64).astype(np.uint32)
+    L = xe.encode(m, n, n_in, q, M_rows, mask, planes, torch.ones((q, m), dtype=torch.float32, device=dev))
+    off = L.patch_off.cpu().numpy().view(np.uint32)
+    assert off[0] == 0 and np.all(np.diff(off.astype(np.int64)) >= 0) and off[-1] == L.patch.numel() > 100000
+    got = xe.decode(L, xe.OUT_PLANES).view(q, m // 32, 32, n // 64)
+    want = (planes & mask).view(q, m // 32, n // 64, 32).transpose(2, 3)
+    assert torch.equal(got, want)
