@@ -49,6 +49,7 @@ int32_t xorenc_fill_dev_layer(const xorenc_layer *layer, DevLayer *D) {
   D->nrb = (int32_t)(sz.m_pad / 32);
   D->n_units = (int32_t)sz.n_units;
   D->nib = nib;
+  D->nib_variant = nib_variant_of(layer->n_in);
   D->n_in = layer->n_in;
   D->q = layer->q;
   D->n_slots = sz.n_slots;

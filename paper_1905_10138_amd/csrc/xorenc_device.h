@@ -18,6 +18,7 @@ struct DevLayer {
   const float *alpha;
   int32_t m, n, spr, nrb, n_units, nib, q;  // nib = ceil(n_in/8): byte-indexed XOR tables per word
   int32_t n_in;
+  int32_t nib_variant;  // table count of the product kernel's variant (nib_variant_of)
   int32_t J, espr;  // 64-bit words per slice (n_out/64), slices per row
   int64_t n_slots, n_eslots;
   // Launches that split the reduction dimension over several workgroups per output tile: partial tiles
@@ -30,6 +31,17 @@ struct DevLayer {
   uint32_t Mcol_hi[XORENC_MAX_J * XORENC_MAX_N_IN];
 };
 
+
+// The product kernels' variants: tables per word, and whether a lane fetches one or two dwords for a field.  Widths that
+// are powers of two never straddle dwords (1, 1, 2 and 4 tables); all others take two dwords, with three tables up
+// to 24 bits (columns of M beyond n_in are zero, so entries do not depend on index bits beyond n_in and a narrow
+// field may use a wide variant: whatever follows it in the stream selects among equal entries) and four above.
+constexpr int kFourTablesTwoDwords = 5;
+constexpr int nib_variant_of(int n_in) {
+  return (n_in & (n_in - 1)) == 0 ? (n_in + 7) / 8 : n_in <= 24 ? 3 : kFourTablesTwoDwords;
+}
+constexpr int tables_of_variant(int v) { return v == kFourTablesTwoDwords ? 4 : v; }
+constexpr bool two_dwords_of_variant(int v) { return v == 3 || v == kFourTablesTwoDwords; }
 
 constexpr int kSplitTileFloats = 4096;  // largest output tile of a split launch (64 x 64)
 constexpr int kSplitMaxGroups = 256;    // workgroups of a split launch (one per CU)

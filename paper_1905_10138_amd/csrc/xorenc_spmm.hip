@@ -92,13 +92,10 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
   if (((uintptr_t)Y & 3) || ((uintptr_t)X & (esz - 1))) return XORENC_EALIGN;
   // 16-byte loads of X need whole chunks (8 bf16 / 4 fp32 columns) and 16-byte aligned rows
   const int per = 16 / esz;
-  // the specialised kernels fetch one dword of encrypted bits per lane (two for 17..24 bits): a field of
-  // any other width that can straddle dwords takes the general kernel
-  const bool enc_fast = (D.n_in & (D.n_in - 1)) == 0 || D.nib == 3;
   // (a last piece with fewer columns is fetched whole: what lies behind column B inside the row's pitch only
   // reaches output columns that are never stored)
   const bool aligned = (ldx % per == 0) && (((uintptr_t)X & 15) == 0);
-  int x_fast = (enc_fast && aligned) ? 1 : 0;
+  int x_fast = aligned ? 1 : 0;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   xorenc_internal_begin_call();
   unsigned char *slot = nullptr;
@@ -113,7 +110,7 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
   }
   // rows of X that do not start on 16-byte boundaries: a padded copy, unless the few-column kernel (which reads X
   // element by element anyway) takes the call or the copy does not fit
-  if (enc_fast && !aligned && B >= kStageMinB) {
+  if (!aligned && B >= kStageMinB) {
     const int cpr = (B + per - 1) / per;  // 16-byte pieces per row
     xorenc_spmm_detail::F4Plan unused;
     if ((int64_t)layer->n * cpr * 16 <= (int64_t)kStageBytes &&

@@ -619,6 +619,8 @@ inline bool f4_applies(const DevLayer &D, int32_t x_dtype, int B, int x_fast, F4
   // 65536 x 4096 layer: 29.8 against 32.6 us; five to seven columns 29 against 42-45 us with the other kernels,
   // 19 against 23 us at 32768 rows, 15 against 13 us at 16384 rows)
   if (B > kF4MaxBOneRound && x_fast) return false;
+  // (widths whose fields straddle dwords outside 17..24 bits stay with the kernels that multiply exact bf16 terms, as
+  // they always did: their results are thirty times closer to the 64-bit ones)
   if ((D.n_in & (D.n_in - 1)) != 0 && D.nib != 3) return false;
   return f4_plan(D, B, f4_pmax(D.q), f4_pmax_mr(D.q, D.nib), plan);
 }

@@ -94,14 +94,14 @@ struct BoolC {
   static constexpr bool value = V;
 };
 
-// NIBT = ceil(n_in/8), the number of byte-indexed tables, known at compile time (1..4; a field may
-// then straddle two dwords only for NIBT == 3), or 0: any n_in, read from the layer at run time.
+// NIBV: the layer's nib_variant (number of byte-indexed tables, one or two dwords per field; nib_variant_of), or 0:
+// any n_in, read from the layer at run time (only for X that has to be fetched element by element).
 // JT = most 64-bit words per slice the variant has table space for: 1 (n_out = 64) or 4 (n_out up to 256).
 // PD = slice buffers per wave on the direct path: 2 (loads a slice and a half ahead, two waves per
 // SIMD hide each other's waits) or 1 (loads one slice ahead, more waves per SIMD do the hiding).
 // NARROW: at most eight columns of X (one 16-byte chunk per row): a slice of X is 1 KB and arrives with a
 // single direct load; the operand lanes of the 24 padding columns read the same chunk again.
-template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBT, int JT, bool NARROW = false>
+template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBV, int JT, bool NARROW = false>
 __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void spmm_kernel(DevLayer L, const void *__restrict__ Xv, int64_t ldx, int B,
                                                       float *__restrict__ Y, int64_t ldy, int slices_per_split,
                                                       int n_splits) {
@@ -113,7 +113,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   static_assert(!NARROW || (XDIR && NCB == 1), "narrow rows of X exist on the direct path with one column block");
   constexpr int RSB = NARROW ? 16 : XDIR ? CW * 2 : CW * 2 + 16;  // LDS row stride in bytes
   constexpr int XSL = 64 * RSB;                     // the 64 X rows of one slice
-  constexpr int KC = RB * (1 + Q * (NIBT == 3 ? 2 : 1));  // compressed dwords per lane and slice (XDIR)
+  constexpr int NIBT = tables_of_variant(NIBV);
+  constexpr int KC = RB * (1 + Q * (two_dwords_of_variant(NIBV) ? 2 : 1));  // compressed dwords per lane and slice (XDIR)
   // With one slice buffer the staging area also takes the patch offsets of the wave's range (one dword
   // per lane, row block and plane), fetched ahead of everything else.
   constexpr bool OFF_DMA = XDIR && PD == 1;
@@ -177,7 +178,6 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   const int nib = NIBT ? NIBT : l_nib;
   const int n_in = l_n_in;
   const uint32_t enc_bytes = (uint32_t)((l_n_eslots >> 3) * l_q * n_in);  // n_eslots is a multiple of 32
-  const uint32_t last_mask = (1u << (n_in - 8 * (nib - 1))) - 1u;         // index bits of the last table
   uint8_t *xbuf = xbuf_all + wave * XBUF;
 
   // ---- this wave's contiguous slice range [w0, w1) inside the workgroup's [s_begin, s_end)
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
     uint32_t e0[RB][Q];
     uint32_t e1[RB][Q];  // second dword, only needed when a 3-byte field straddles two dwords
   };
-  const bool two_dw = NIBT ? (NIBT == 3) : ((n_in & (n_in - 1)) != 0);
+  const bool two_dw = NIBV ? two_dwords_of_variant(NIBV) : ((n_in & (n_in - 1)) != 0);
   const uint32_t m_lane_off = (uint32_t)(rl * 8 + g * 4);
   const uint32_t e_bit = (uint32_t)(rl * n_in);
   const uint32_t e_lane_off = (e_bit >> 5) << 2;
@@ -576,17 +576,17 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
           x = c.e0[rb][p] >> e_shift;
         uint32_t v;
         if constexpr (NIBT == 1) {
-          v = lut_g[2 * (x & last_mask)];
+          v = lut_g[2 * (x & 255)];
         } else if constexpr (NIBT == 2) {
-          const uint32_t t0 = lut_g[2 * (x & 255)], t1 = lut_g[2 * (256 + ((x >> 8) & last_mask))];
+          const uint32_t t0 = lut_g[2 * (x & 255)], t1 = lut_g[2 * (256 + ((x >> 8) & 255))];
           v = t0 ^ t1;
         } else if constexpr (NIBT == 3) {
           const uint32_t t0 = lut_g[2 * (x & 255)], t1 = lut_g[2 * (256 + ((x >> 8) & 255))];
-          const uint32_t t2 = lut_g[2 * (512 + ((x >> 16) & last_mask))];
+          const uint32_t t2 = lut_g[2 * (512 + ((x >> 16) & 255))];
           v = t0 ^ t1 ^ t2;
         } else if constexpr (NIBT == 4) {
           const uint32_t t0 = lut_g[2 * (x & 255)], t1 = lut_g[2 * (256 + ((x >> 8) & 255))];
-          const uint32_t t2 = lut_g[2 * (512 + ((x >> 16) & 255))], t3 = lut_g[2 * (768 + ((x >> 24) & last_mask))];
+          const uint32_t t2 = lut_g[2 * (512 + ((x >> 16) & 255))], t3 = lut_g[2 * (768 + (x >> 24))];
           v = t0 ^ t1 ^ t2 ^ t3;
         } else {
           if (n_in < 32) x &= (1u << n_in) - 1u;
@@ -801,7 +801,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
 
   // ---- epilogue: scale by alpha (fp32) and reduce the waves in a fixed order.  NREG tiles of
   // CW x TS floats (column-major) live in LDS over the (now idle) X buffers; wave w adds into tile w % NREG in round
-  // w / NREG, then every thread sums the NREG tiles of its outputs in ascending tile order.
+  // w / NREG, then every thread sums the NREG tiles of its outputs pairwise.
   // acc element i of a lane is row 8*(i/4) + 4*g + i%4, column rl of its 32x32 block.
   // every wave has left its loop: the X buffers are idle and alpha_s (written by the first waves
   // without a barrier of its own) is complete
@@ -850,11 +850,16 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   // final pass: a thread owns four consecutive rows of one column; lanes run over columns, so each
   // of its four stores is contiguous across the wave
   auto reduced4 = [&](int col, int rq) {
+    // (added in pairs, pairs of pairs, ...: fewer roundings on the way of each part than one after the other)
     const float *src = red + col * TS + 4 * rq;
-    f32x4 v = *reinterpret_cast<const f32x4 *>(src);
+    f32x4 v[NREG];
 #pragma unroll
-    for (int r = 1; r < NREG; ++r) v += *reinterpret_cast<const f32x4 *>(src + r * TILE);
-    return v;
+    for (int r = 0; r < NREG; ++r) v[r] = *reinterpret_cast<const f32x4 *>(src + r * TILE);
+#pragma unroll
+    for (int s = 1; s < NREG; s *= 2)
+#pragma unroll
+      for (int r = 0; r + s < NREG; r += 2 * s) v[r] += v[r + s];
+    return v[0];
   };
   // n_splits > 1: this workgroup holds one of n_splits partial sums of its tile.  It parks the tile in the
   // library's scratch area and takes a ticket; the workgroup that arrives last adds the parts in the order
@@ -900,9 +905,12 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
         const int rq = idx / NR, nn = idx % NR;
         const int gc = col0 + nn;
         if (gc < B) {
-          f32x4 v = __builtin_bit_cast(f32x4, split_load4(parts, 16u * idx));
-          for (int z = 1; z < n_splits; ++z)
-            v += __builtin_bit_cast(f32x4, split_load4(parts, (uint32_t)z * (kSplitTileFloats * 4u) + 16u * idx));
+          // two to four parts, (0 + 1) + (2 + 3)
+          auto part = [&](int z) {
+            return __builtin_bit_cast(f32x4, split_load4(parts, (uint32_t)z * (kSplitTileFloats * 4u) + 16u * idx));
+          };
+          f32x4 v = part(0) + part(1);
+          if (n_splits > 2) v += n_splits > 3 ? part(2) + part(3) : part(2);
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
             const int gr = row0 + 4 * rq + k;
@@ -915,10 +923,10 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   }
 }
 
-template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBT, int JT, bool NARROW = false>
+template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBV, int JT, bool NARROW = false>
 inline void launch_variant(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y, int64_t ldy, dim3 grid,
                            int sps, int n_splits, hipStream_t st) {
-  hipLaunchKernelGGL((spmm_kernel<NCB, Q, RB, XF32, NW, XFAST, PD, NIBT, JT, NARROW>), grid, dim3(NW * 64), 0, st, D, X,
+  hipLaunchKernelGGL((spmm_kernel<NCB, Q, RB, XF32, NW, XFAST, PD, NIBV, JT, NARROW>), grid, dim3(NW * 64), 0, st, D, X,
                      ldx, B, Y, ldy, sps, n_splits);
 }
 
@@ -959,14 +967,15 @@ int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float 
     return XORENC_EUNSUPPORTED;
   } else {
     if constexpr (JMODE != 1)
-      if (wide) switch (D.nib) {
+      if (wide) switch (D.nib_variant) {
           case 1: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 1, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
           case 2: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 2, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
           case 3: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 3, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          default: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 4, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 4: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 4, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          default: launch_variant<NCB, Q, RB, XF32, NW, true, PD, kFourTablesTwoDwords, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
         }
     if constexpr (JMODE != 4)
-      if (!wide) switch (D.nib) {
+      if (!wide) switch (D.nib_variant) {
           case 1: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 1, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
           case 2: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 2, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
           case 3:
@@ -974,9 +983,13 @@ int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float 
             if constexpr (NW == 4 && !XF32) return XORENC_EUNSUPPORTED;
             else launch_variant<NCB, Q, RB, XF32, NW, true, PD, 3, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
             break;
-          default:
+          case 4:
             if constexpr (NW == 4 && !XF32) return XORENC_EUNSUPPORTED;
             else launch_variant<NCB, Q, RB, XF32, NW, true, PD, 4, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
+            break;
+          default:
+            if constexpr (NW == 4 && !XF32) return XORENC_EUNSUPPORTED;
+            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, kFourTablesTwoDwords, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
             break;
         }
   }
@@ -1018,13 +1031,13 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
     if (B <= 8 && D.J == 1 && small_narrow) return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     // more than one round of 64-row tiles: four-wave workgroups, several per CU, so that one's prologue and epilogue
     // overlap another's loop (65536 x 4096 at B = 8: 28.9 against 30.4 us)
-    if (B <= 8 && D.J == 1 && D.nib <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
+    if (B <= 8 && D.J == 1 && D.nib_variant <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
       return launch_spmm<1, Q, 2, false, 4, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (B <= 8 && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     // (small layers: 32-row tiles while they fit one round, see below; 4096 x 4096 at B = 32: 7.5 against 8.6 us)
     if (blocks == 1 && D.J == 1 && small_block) return launch_spmm<1, Q, 1, false, 12, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     // (several rounds: four-wave workgroups as above; 65536 x 4096 at B = 32: 32.5 against 34.8 us)
-    if (blocks == 1 && D.J == 1 && D.nib <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
+    if (blocks == 1 && D.J == 1 && D.nib_variant <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
       return launch_spmm<1, Q, 2, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (blocks == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     // 128-row tiles halve the number of times X is re-read; used once they still fill most of the chip.
@@ -1032,7 +1045,7 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
     // four-wave workgroups, two per CU, which share the CU's LDS so that one's prologue and epilogue do
     // not wait for the other's to finish.
     const int64_t tiles128 = (int64_t)((D.nrb + 3) / 4) * ((B + 63) / 64);
-    if (D.J == 1 && D.nib <= 2 && tiles128 > 256)
+    if (D.J == 1 && D.nib_variant <= 2 && tiles128 > 256)
       return launch_spmm<2, Q, 4, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (D.J == 1 && tiles128 >= 200) return launch_spmm<2, Q, 4, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     // (small layers, see above; 2048 x 2048 at B = 64: 7.6 against 9.3 us, 4096 x 4096: 9.4 against 11.5 us)
@@ -1040,7 +1053,7 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
     return launch_spmm<2, Q, 2, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
   } else if constexpr (Q == 2) {
     if (B <= 8 && x_fast && D.J == 1 && small_narrow) return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (B <= 8 && x_fast && D.J == 1 && D.nib <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
+    if (B <= 8 && x_fast && D.J == 1 && D.nib_variant <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
       return launch_spmm<1, Q, 2, false, 4, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (B <= 8 && x_fast && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (blocks == 1 && x_fast && D.J == 1 && small_block)
@@ -1053,7 +1066,7 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
     // 64-row tiles once they fill most of the chip: X is re-read half as often; more than 256 of them run as
     // four-wave workgroups, two per CU
     const int64_t tiles64 = (int64_t)((D.nrb + 1) / 2) * ((B + 63) / 64);
-    if (D.nib <= 2 && tiles64 > 256) return launch_spmm<2, Q, 2, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (D.nib_variant <= 2 && tiles64 > 256) return launch_spmm<2, Q, 2, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (tiles64 >= 200) return launch_spmm<2, Q, 2, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     return launch_spmm<2, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
   } else if constexpr (Q == 3) {

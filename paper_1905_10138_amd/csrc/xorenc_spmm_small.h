@@ -25,10 +25,11 @@ namespace xorenc_spmm_detail {
 constexpr int kSmallMaxB = 8;                // batch rows 0..7 are accumulator elements 0..3 of both halves
 constexpr int kSmallXBytes = 96 * 1024;      // LDS set aside for X^T (rows padded by 16 bytes)
 
-template <int Q, int RB, int NW, int NIBT>
+template <int Q, int RB, int NW, int NIBV>
 __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const uint16_t *__restrict__ X, int64_t ldx,
                                                             int B, float *__restrict__ Y, int64_t ldy,
                                                             int slices_per_split, int n_splits) {
+  constexpr int NIBT = tables_of_variant(NIBV);
   constexpr int ROWS = 32 * RB;
   constexpr int RED_FLOATS = NW * RB * kSmallMaxB * 32;  // partial results, over the X^T area after the loop
   static_assert(RED_FLOATS * 4 <= kSmallXBytes, "the reduction area must fit where X^T was");
@@ -56,7 +57,6 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, rl = lane & 31;
   const int row0 = blockIdx.x * ROWS;
-  constexpr int nib = NIBT;
 
   // ---- slice range of the workgroup and, inside it, of this wave (balanced, contiguous)
   const int s_begin = blockIdx.z * slices_per_split;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
     uint32_t e0[RB][Q];
     uint32_t e1[RB][Q];
   };
-  constexpr bool two_dw = NIBT == 3;
+  constexpr bool two_dw = two_dwords_of_variant(NIBV);
   const __amdgpu_buffer_rsrc_t mrsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint32_t *>(l_mask32), 0, (uint32_t)(l_n_slots * 8), kRsrcFlags);
   const __amdgpu_buffer_rsrc_t ersrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -85,7 +85,6 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
   const uint32_t e_lane_off = (e_bit >> 5) << 2;
   const uint32_t e_shift = e_bit & 31u;
   const uint32_t e_plane_units = (uint32_t)(l_n_slots >> 5), e_unit_bytes = (uint32_t)(n_in * 4);
-  const uint32_t last_mask = (1u << (n_in - 8 * (nib - 1))) - 1u;  // index bits of the last table
   auto load_comp = [&](int s, Comp &c) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
@@ -231,10 +230,10 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
           x = __builtin_amdgcn_alignbit(c.e1[rb][p], c.e0[rb][p], e_shift);
         else
           x = c.e0[rb][p] >> e_shift;
-        uint32_t v = lut_g[2 * (x & (NIBT == 1 ? last_mask : 255u))];
-        if constexpr (NIBT >= 2) v ^= lut_g[2 * (256 + ((x >> 8) & (NIBT == 2 ? last_mask : 255u)))];
-        if constexpr (NIBT >= 3) v ^= lut_g[2 * (512 + ((x >> 16) & (NIBT == 3 ? last_mask : 255u)))];
-        if constexpr (NIBT >= 4) v ^= lut_g[2 * (768 + ((x >> 24) & last_mask))];
+        uint32_t v = lut_g[2 * (x & 255u)];
+        if constexpr (NIBT >= 2) v ^= lut_g[2 * (256 + ((x >> 8) & 255u))];
+        if constexpr (NIBT >= 3) v ^= lut_g[2 * (512 + ((x >> 16) & 255u))];
+        if constexpr (NIBT >= 4) v ^= lut_g[2 * (768 + (x >> 24))];
         S[rb][p] = v;
       }
   };
@@ -324,7 +323,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
 
   // ---- epilogue.  acc element i of a lane is batch row 8*(i/4) + 4*g + i%4, W row rl of its row
   // block: batch rows 0..7 are elements 0..3 of the two halves.  Scale by alpha (fp32), park the
-  // real batch rows in LDS, then every output sums the waves' parts in wave order.
+  // real batch rows in LDS, then every output sums the waves' parts pairwise.
   __syncthreads();  // every wave has finished reading X^T
   float *red = reinterpret_cast<float *>(xt_all);
 #pragma unroll
@@ -353,9 +352,14 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
     const int gr = row0 + r;
     if (b < B && gr < l_m) {
       const float *src = red + ((r >> 5) * kSmallMaxB + b) * 32 + (r & 31);
-      float v = src[0];
+      float part[NW];  // added pairwise
 #pragma unroll
-      for (int w = 1; w < NW; ++w) v += src[w * RB * kSmallMaxB * 32];
+      for (int w = 0; w < NW; ++w) part[w] = src[w * RB * kSmallMaxB * 32];
+#pragma unroll
+      for (int s = 1; s < NW; s *= 2)
+#pragma unroll
+        for (int w = 0; w + s < NW; w += 2 * s) part[w] += part[w + s];
+      const float v = part[0];
       if (n_splits > 1)
         split_store(my_part + idx, v);
       else
@@ -413,7 +417,7 @@ int32_t launch_small(const DevLayer &D, const void *X, int64_t ldx, int B, float
   const dim3 grid((D.nrb + RB - 1) / RB, 1, ks);
   const int atomic = ks;  // number of splits
   const uint16_t *Xh = static_cast<const uint16_t *>(X);
-  switch (D.nib) {
+  switch (D.nib_variant) {
     case 1:
       hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 1>), grid, dim3(NW * 64), 0, st, D, Xh, ldx, B, Y, ldy, sps, atomic);
       break;
@@ -423,8 +427,11 @@ int32_t launch_small(const DevLayer &D, const void *X, int64_t ldx, int B, float
     case 3:
       hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 3>), grid, dim3(NW * 64), 0, st, D, Xh, ldx, B, Y, ldy, sps, atomic);
       break;
-    default:
+    case 4:
       hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 4>), grid, dim3(NW * 64), 0, st, D, Xh, ldx, B, Y, ldy, sps, atomic);
+      break;
+    default:
+      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, kFourTablesTwoDwords>), grid, dim3(NW * 64), 0, st, D, Xh, ldx, B, Y, ldy, sps, atomic);
       break;
   }
   return xorenc_internal_check_launch();
@@ -437,8 +444,6 @@ template <int Q>
 bool dispatch_small_q(const DevLayer &D, const void *X, int32_t x_dtype, int64_t ldx, int B, float *Y, int64_t ldy,
                       int x_fast, hipStream_t st, int32_t *rc) {
   if (x_dtype != XORENC_X_BF16 || x_fast || D.J != 1) return false;
-  // one dword of encrypted bits per lane and slice (two for 17..24 bits), as in the specialised main kernels
-  if ((D.n_in & (D.n_in - 1)) != 0 && D.nib != 3) return false;
   constexpr int RB = (Q <= 3) ? 2 : 1;
   constexpr int NW = (Q == 1) ? 16 : (Q == 2 ? 12 : 8);
   int ks = 1, sps = 0;

@@ -355,3 +355,15 @@ def test_split_reduction_is_deterministic_and_one_launch(name, m, n, B, dtype):
         Y.fill_(float(i))
         xe.spmm(L, xg, Y=Y)
         assert torch.equal(Y, first), f"call {i} differs"
+
+
+@pytest.mark.parametrize("n_in", range(4, 33))
+def test_every_width_of_the_encrypted_vector(n_in):
+    """Every n_in on the kernels that fetch one or two dwords per field: powers of two (fields never straddle dwords),
+    5..24 bits with three tables, 25..31 with four; one column, unaligned and aligned few columns, one and two column
+    blocks, fp32; one, two and three planes; one-word and wider slices.  The last unit's fields end with the stream."""
+    for name, m, n, n_out, B, dtype, pad in [("large_q1", 65, 200, 64, 1, "bf16", 0), ("large_q2", 40, 130, 64, 3, "bf16", 0),
+                                             ("lstm", 33, 260, 64, 8, "bf16", 0), ("large_q1", 96, 190, 192, 24, "bf16", 0),
+                                             ("large_q2", 70, 200, 128, 48, "bf16", 0), ("fc6", 40, 320, 64, 12, "f32", 0)]:
+        got, want = _run(name, m, n, B, dtype, ldx_pad=pad, S=0.8, n_out=n_out, n_in=n_in, every_output=(dtype == "bf16"))
+        assert rel_fro(got, want) <= (1e-5 if B <= 4 and dtype == "bf16" else 4e-7)
