@@ -367,3 +367,50 @@ def test_every_width_of_the_encrypted_vector(n_in):
                                              ("large_q2", 70, 200, 128, 48, "bf16", 0), ("fc6", 40, 320, 64, 12, "f32", 0)]:
         got, want = _run(name, m, n, B, dtype, ldx_pad=pad, S=0.8, n_out=n_out, n_in=n_in, every_output=(dtype == "bf16"))
         assert rel_fro(got, want) <= (1e-5 if B <= 4 and dtype == "bf16" else 4e-7)
+
+
+@pytest.mark.parametrize("name,m,n,n_out,n_in,B,S", [
+    # one plane, 256 x 128 tiles: full and ragged rows and columns, reductions of 1, 2, 5 and 17 slices
+    ("large_q1", 16384, 64, 64, 8, 1024, None), ("large_q1", 16300, 100, 64, 13, 1016, None),
+    ("large_q1", 16130, 300, 64, 5, 1024, 0.85), ("large_q1", 16384, 1088, 64, 27, 1024, 0.8),
+    ("large_q1", 15000, 400, 256, 31, 1000, 0.85), ("large_q1", 16384, 600, 192, 20, 512, 0.9),
+    # two planes: two reduction groups (256 tiles of 128 x 128; odd and even numbers of slices, one slice for two
+    # groups) and one group (512 tiles and more)
+    ("large_q2", 16384, 64, 64, 8, 256, None), ("large_q2", 16290, 320, 64, 16, 248, 0.85),
+    ("large_q2", 16384, 390, 128, 12, 250, 0.9), ("large_q2", 16384, 200, 64, 24, 1000, 0.8),
+    # three and four planes, 128 x 64 tiles
+    ("lstm", 6000, 200, 64, 24, 256, None), ("lstm", 5990, 330, 192, 20, 1000, 0.9),
+    # patch lists longer than a staged chunk and than one trip of the scatter
+    ("large_q1", 16384, 1100, 64, 4, 1024, 0.8), ("large_q2", 16384, 700, 64, 4, 256, 0.7)])
+def test_many_columns_and_rows(name, m, n, n_out, n_in, B, S):
+    """Calls whose tiles fill the chip: waves on top of each other share the slices of X, compressed words are staged four
+    slices at a time and patches scattered into flip words.  Every output element by element."""
+    got, want = _run(name, m, n, B, "bf16", S=S, n_out=n_out, n_in=n_in, every_output=True)
+    assert rel_fro(got, want) <= 2e-7
+
+
+def test_many_columns_with_a_patch_list_at_an_odd_address_and_four_planes():
+    """Entries are 2-byte aligned while the staging loads are 4-byte ones; four planes; Y with a leading dimension; the
+    rows of X in parts that fit the staging area (an odd leading dimension)."""
+    import dataclasses
+    import torch
+    import paper_1905_10138_amd as xe
+    from oracle import encoder
+    from synth_inputs import CONFIGS, make_workload
+    wl = make_workload(dataclasses.replace(CONFIGS["lstm"], q=4, n_in=8, S=0.85), m=6000, n=330)
+    enc = encoder.encode(wl.keep, wl.planes, wl.alpha, wl.M, wl.n)
+    L = pack_encoded(enc).to(torch.device("cuda:0"))
+    buf = torch.zeros(L.patch.numel() + 3, dtype=torch.int16, device="cuda:0")
+    for B, pad in ((256, 0), (1000, 3)):
+        stored, exact = draw_X(wl.n, B, "bf16", 5)
+        x = torch.zeros((wl.n, B + pad), dtype=torch.int16)
+        x[:, :B] = torch.from_numpy(stored.view(np.int16))
+        xg = x.view(torch.bfloat16).to("cuda:0")[:, :B]
+        want = decoder.spmm_f64(enc, exact)
+        for shift in (0, 1):
+            L.patch = buf[shift:shift + L.patch.numel()].copy_(L.patch.clone())
+            Y = torch.full((wl.m, B + 5), 3.0, dtype=torch.float32, device="cuda:0")
+            xe.spmm(L, xg, Y=Y[:, :B])
+            got = Y.cpu().numpy()
+            assert_every_output_close(got[:, :B], want, enc, exact)
+            assert np.all(got[:, B:] == 3.0)
