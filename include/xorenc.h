@@ -275,8 +275,9 @@ XORENC_API int32_t xorenc_decode(const xorenc_layer *layer, int32_t out_kind, vo
  * split exactly into three bf16 terms, so the fp32 path keeps fp32 accuracy on the matrix cores.
  * The same bits in Y for the same inputs on every call: sums are formed in a fixed order.  One kernel launch per
  * call, two when the rows of X do not start on 16-byte boundaries (ldx not a multiple of 8 bf16 / 4 fp32 values, or
- * such a base address) and X has at least five columns and at most 4 MiB with its rows padded to whole 16-byte
- * pieces: a first kernel then copies X into a staging area inside the library, and the product reads the copy
+ * such a base address) and X has at least five columns: a first kernel then copies X into a 4 MiB staging area inside
+ * the library with its rows padded to whole 16-byte pieces, and the product reads the copy; an X that needs more is
+ * copied and multiplied in parts of its columns, two launches each (n <= 32768; larger n are read element by element)
  * (the fast kernels fetch X in 16-byte pieces).  For small layers the launch splits the reduction dimension over
  * several workgroups per output tile; their partial tiles meet in a scratch area, and the workgroup that finishes
  * last adds them in the order of their slice ranges.  Staging and scratch areas live in device memory that the

@@ -16,7 +16,8 @@
 // on 16-byte boundaries.  When the caller's X does not (a leading dimension that is not a multiple of eight bf16 or
 // four fp32 values, or an odd base address) and it fits, a small kernel copies it into the staging area with padded
 // rows first (one more launch, about 2 us) and the product runs on the copy (B = 33: 16 against 43 us, B = 65: 25
-// against 170 us on a 16384 x 4096 layer); larger X take the element-wise kernels.
+// against 170 us on a 16384 x 4096 layer); larger X are copied and multiplied in parts
+// (4096 x 9216, two planes, B = 1023: 2700 us on the element-wise kernels, 278 us).
 namespace {
 constexpr int kSplitSlots = 4;
 constexpr size_t kSplitPartBytes = (size_t)kSplitMaxGroups * kSplitTileFloats * sizeof(float);  // 4 MiB
@@ -95,7 +96,6 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
   // (a last piece with fewer columns is fetched whole: what lies behind column B inside the row's pitch only
   // reaches output columns that are never stored)
   const bool aligned = (ldx % per == 0) && (((uintptr_t)X & 15) == 0);
-  int x_fast = aligned ? 1 : 0;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   xorenc_internal_begin_call();
   unsigned char *slot = nullptr;
@@ -108,26 +108,37 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
     D.split_part = reinterpret_cast<float *>(slot);
     D.split_ticket = reinterpret_cast<uint32_t *>(slot + kSplitPartBytes);
   }
+  auto product = [&](const void *Xp, int64_t ld, int32_t cols, float *Yp, int fast) -> int32_t {
+    switch (layer->q) {
+      case 1: return xorenc_spmm_dispatch_q1(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
+      case 2: return xorenc_spmm_dispatch_q2(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
+      case 3: return xorenc_spmm_dispatch_q3(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
+      default: return xorenc_spmm_dispatch_q4(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
+    }
+  };
   // rows of X that do not start on 16-byte boundaries: a padded copy, unless the few-column kernel (which reads X
-  // element by element anyway) takes the call or the copy does not fit
+  // element by element anyway) takes the call.  A copy that does not fit the staging area is made and multiplied a part
+  // of the columns at a time (parts of nearly equal width, at least 64 columns of the area each: n <= 32768).
   if (!aligned && B >= kStageMinB) {
-    const int cpr = (B + per - 1) / per;  // 16-byte pieces per row
+    const int64_t fit = (int64_t)(kStageBytes / ((size_t)layer->n * 16)) * per / 64 * 64;  // columns, in whole 64s
+    const bool whole = (int64_t)layer->n * ((B + per - 1) / per) * 16 <= (int64_t)kStageBytes;
     xorenc_spmm_detail::F4Plan unused;
-    if ((int64_t)layer->n * cpr * 16 <= (int64_t)kStageBytes &&
-        !xorenc_spmm_detail::f4_applies(D, x_dtype, B, 0, &unused)) {
+    if ((whole || fit > 0) && !xorenc_spmm_detail::f4_applies(D, x_dtype, B, 0, &unused)) {
+      const int64_t parts = whole ? 1 : (B + fit - 1) / fit;
+      const int part = whole ? B : (int)((B + parts - 1) / parts + 7) / 8 * 8;
       unsigned char *stage = slot + kSplitPartBytes + kSplitTicketBytes;
-      const int64_t pieces = (int64_t)layer->n * cpr;
-      hipLaunchKernelGGL(stage_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
-                         static_cast<const unsigned char *>(X), ldx, (int)layer->n, (int)B, esz, cpr, stage);
-      X = stage;
-      ldx = (int64_t)cpr * per;
-      x_fast = 1;
+      for (int c0 = 0; c0 < B; c0 += part) {
+        const int cols = min(part, B - c0);
+        const int cpr = (cols + per - 1) / per;  // 16-byte pieces per row
+        const int64_t pieces = (int64_t)layer->n * cpr;
+        hipLaunchKernelGGL(stage_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
+                           static_cast<const unsigned char *>(X) + (int64_t)c0 * esz, ldx, (int)layer->n, cols, esz, cpr,
+                           stage);
+        const int32_t rp = product(stage, (int64_t)cpr * per, cols, Y + c0, 1);
+        if (rp != XORENC_OK) return rp;
+      }
+      return XORENC_OK;
     }
   }
-  switch (layer->q) {
-    case 1: return xorenc_spmm_dispatch_q1(D, X, x_dtype, ldx, B, Y, ldy, x_fast, st);
-    case 2: return xorenc_spmm_dispatch_q2(D, X, x_dtype, ldx, B, Y, ldy, x_fast, st);
-    case 3: return xorenc_spmm_dispatch_q3(D, X, x_dtype, ldx, B, Y, ldy, x_fast, st);
-    default: return xorenc_spmm_dispatch_q4(D, X, x_dtype, ldx, B, Y, ldy, x_fast, st);
-  }
+  return product(X, ldx, B, Y, aligned ? 1 : 0);
 }

@@ -414,3 +414,12 @@ def test_many_columns_with_a_patch_list_at_an_odd_address_and_four_planes():
             got = Y.cpu().numpy()
             assert_every_output_close(got[:, :B], want, enc, exact)
             assert np.all(got[:, B:] == 3.0)
+
+
+@pytest.mark.parametrize("name,m,n,B,dtype,pad", [
+    ("large_q1", 100, 4096, 515, "bf16", 0), ("large_q2", 64, 5000, 1023, "bf16", 0), ("fig1", 70, 9000, 301, "bf16", 2),
+    ("tiny", 40, 4096, 300, "f32", 1), ("tiny", 33, 30000, 70, "bf16", 0)])
+def test_unaligned_rows_of_X_beyond_the_staging_area(name, m, n, B, dtype, pad):
+    """More than 4 MiB with padded rows: copied and multiplied a part of the columns at a time."""
+    got, want = _run(name, m, n, B, dtype, ldx_pad=pad, every_output=(dtype == "bf16"))
+    assert rel_fro(got, want) <= 4e-7
