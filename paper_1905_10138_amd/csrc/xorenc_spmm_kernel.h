@@ -120,7 +120,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   constexpr bool OFF_DMA = XDIR && PD == 1;
   constexpr int KO = OFF_DMA ? RB * Q : 0;
   constexpr int CSL = (KC + KO) * 256;                    // staging area of one slice (XDIR)
-  constexpr int XBUF = XDIR ? PD * (XSL + CSL) : XSL;     // one wave's LDS share (PD slice buffers)
+  constexpr int XBUF0 = XDIR ? PD * (XSL + CSL) : XSL;     // one wave's LDS share (PD slice buffers)
   constexpr int ROWS = 32 * RB;
   constexpr int NR = XF32 ? CW / 3 : CW;       // real X columns per workgroup
   constexpr int NCH = NARROW ? 1 : XF32 ? NR / 4 : CW / 8;  // 16-byte chunks per X row in global memory
@@ -138,7 +138,24 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
                                                          : 160 * 1024 - 2048 - JT * NIBMAX * 2048;
   constexpr int FIT = TILE_BUDGET / (TILE * 4);
   constexpr int NREG = largest_divisor_at_most(NW, FIT);
-  constexpr int LDSB = (NW * XBUF > NREG * TILE * 4) ? NW * XBUF : NREG * TILE * 4;
+  constexpr int LDSB0 = (NW * XBUF0 > NREG * TILE * 4) ? NW * XBUF0 : NREG * TILE * 4;
+  // Flip words of GS slices (long patch lists), [slice][row block and plane][lane], zero between groups: they lie behind
+  // the slice buffers, mostly where the reduction tiles will be.  Four slices if they fit without taking the room of the
+  // tables, else two or one; without any room (two slice buffers and the tables of wide slices) the patches of long
+  // lists are applied entry by entry, and so they are with six lists per wave, whose state spilled 50 registers.
+  constexpr int FLIP1 = RB * Q * 256;                          // one slice
+  constexpr int LDS_REST = JT * NIBMAX * 2048 + Q * ROWS * 4;  // shared tables, scales
+  constexpr int LDS_PRIV = NW * NIBMAX * 2048 + Q * ROWS * 4;  // tables per wave, scales
+  auto lds_with = [](int gs) { return LDSB0 > NW * (XBUF0 + gs * FLIP1) ? LDSB0 : NW * (XBUF0 + gs * FLIP1); };
+  auto fits = [lds_with](int gs) {
+    return XDIR && RB * Q <= 4 && lds_with(gs) + LDS_REST <= 160 * 1024 &&
+           (JT > 1 || LDSB0 + LDS_PRIV > 160 * 1024 || lds_with(gs) + LDS_PRIV <= 160 * 1024) &&
+           (NW != 4 || lds_with(gs) + (JT == 1 ? LDS_PRIV : LDS_REST) <= 80 * 1024);
+  };
+  constexpr int GS = fits(4) ? 4 : fits(2) ? 2 : fits(1) ? 1 : 0;
+  constexpr bool SCATTER = GS > 0;
+  constexpr int XBUF = XBUF0 + GS * FLIP1;
+  constexpr int LDSB = lds_with(GS);
   static_assert(!XF32 || NCB % 3 == 0, "fp32 X uses three bf16 terms per column");
   static_assert(FIT >= 1, "a reduction tile must fit in the X buffers");
   static_assert(NW % NREG == 0, "waves must split evenly over the reduction tiles");
@@ -558,6 +575,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
       tr_off[cb] = (uint32_t)(pos_lane * RSB + ((c ^ swz_of_pos(pos_lane)) * 16) + 8 * (c4 & 1));
     }
   }
+  uint32_t *const flip_area = reinterpret_cast<uint32_t *>(xbuf + (SCATTER ? XBUF0 : 0));
+  if constexpr (SCATTER) {
+#pragma unroll
+    for (int i = 0; i < GS * RB * Q; ++i) flip_area[i * 64 + lane] = 0u;
+  }
   const uint32_t *lut_g0 = lut + g;
   const uint32_t lane_id5 = (uint32_t)(rl * 2 + g);  // (row, half) as it appears in a patch entry
 
@@ -629,6 +651,72 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
       for (int p = 0; p < Q; ++p) pcur[rb][p] = 0u;
+    // Long lists (!PF): GS slices at a time, lane j holds entry j of the group's list, requested a group ahead (offsets
+    // two groups ahead), finds its slice by counting list ends and flips its bit in the slice's flip words.  (One entry
+    // after the other, read from memory: 4096 x 4096, two planes, S = 0.8, n_in = 13, B = 64: 30 us, now 14.)
+    constexpr bool GROUPS = !PF && SCATTER;
+    uint32_t goff[3][GROUPS ? RB : 1][GROUPS ? Q : 1], gent[2][GROUPS ? RB : 1][GROUPS ? Q : 1];
+    uint32_t glist[GROUPS ? RB : 1][GROUPS ? Q : 1];  // entries of the group
+    auto load_group_off = [&](int s, uint32_t(&o)[GROUPS ? RB : 1][GROUPS ? Q : 1]) {
+#pragma unroll
+      for (int rb = 0; rb < (GROUPS ? RB : 0); ++rb)
+#pragma unroll
+        for (int p = 0; p < Q; ++p) {
+          const int rbg = blockIdx.x * RB + rb;
+          o[rb][p] = 0u;
+          if (rbg < l_nrb && lane <= GS)  // (units behind the range: the end of the range's last list)
+            o[rb][p] = l_patch_off[(int64_t)p * l_n_units + (int64_t)rbg * l_spr + min(s + lane, w1)];
+        }
+    };
+    auto load_group_ent = [&](const uint32_t(&o)[GROUPS ? RB : 1][GROUPS ? Q : 1], uint32_t(&e)[GROUPS ? RB : 1][GROUPS ? Q : 1]) {
+#pragma unroll
+      for (int rb = 0; rb < (GROUPS ? RB : 0); ++rb)
+#pragma unroll
+        for (int p = 0; p < Q; ++p) {
+          const uint32_t a = __builtin_amdgcn_readlane(o[rb][p], 0);
+          e[rb][p] = 0u;
+          if ((uint32_t)lane < __builtin_amdgcn_readlane(o[rb][p], GS) - a) e[rb][p] = (l_patch + a)[lane];
+        }
+    };
+    auto group_patches = [&](int s) {
+      if (s > w0) {
+#pragma unroll
+        for (int rb = 0; rb < (GROUPS ? RB : 0); ++rb)
+#pragma unroll
+          for (int p = 0; p < Q; ++p) {
+            goff[0][rb][p] = goff[1][rb][p];
+            goff[1][rb][p] = goff[2][rb][p];
+            gent[0][rb][p] = gent[1][rb][p];
+          }
+      }
+      load_group_ent(goff[1], gent[1]);
+      load_group_off(s + 2 * GS, goff[2]);
+#pragma unroll
+      for (int rb = 0; rb < (GROUPS ? RB : 0); ++rb)
+#pragma unroll
+        for (int p = 0; p < Q; ++p) {
+          const uint32_t a = __builtin_amdgcn_readlane(goff[0][rb][p], 0);
+          const uint32_t total = __builtin_amdgcn_readlane(goff[0][rb][p], GS) - a;
+          glist[rb][p] = total;
+          for (uint32_t j0 = 0; j0 < total; j0 += 64u) {  // uniform
+            const uint32_t j = j0 + (uint32_t)lane;
+            if (j < total) {
+              uint32_t v = gent[0][rb][p];
+              if (j0) v = (l_patch + a)[j];
+              uint32_t t = 0;
+#pragma unroll
+              for (int k = 1; k < GS; ++k) t += j >= __builtin_amdgcn_readlane(goff[0][rb][p], k) - a ? 1u : 0u;
+              // entry = (row%32) << 6 | bit: the word half is bit 5
+              atomicXor(flip_area + (t * RB * Q + rb * Q + p) * 64 + ((v >> 6) | (v & 32u)), 1u << (v & 31u));
+            }
+          }
+        }
+    };
+    if constexpr (GROUPS) {
+      load_group_off(w0, goff[0]);
+      load_group_off(w0 + GS, goff[1]);
+      load_group_ent(goff[0], gent[0]);
+    }
     bf16x8 bfrag[4][NCB];
     uint32_t Snext[RB][Q];
     if constexpr (XDIR) {
@@ -672,6 +760,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
           __builtin_amdgcn_s_setprio(1);
         else
           __builtin_amdgcn_s_setprio(0);
+        if constexpr (!PF && SCATTER) {
+          if (((s - w0) & (GS - 1)) == 0) group_patches(s);
+        }
         uint32_t mw[RB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) mw[rb] = ring[d].mw[rb];
@@ -682,7 +773,13 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
 #pragma unroll
           for (int p = 0; p < Q; ++p) {
             uint32_t S = Snext[rb][p];
-            if constexpr (PF) {
+            if constexpr (!PF && SCATTER) {
+              if (glist[rb][p]) {  // uniform
+                uint32_t *const f = flip_area + (((s - w0) & (GS - 1)) * RB * Q + rb * Q + p) * 64 + lane;
+                S ^= *f;
+                *f = 0u;
+              }
+            } else if constexpr (PF) {
               const uint32_t pe = __builtin_amdgcn_readlane(offrel[rb][p], s - w0 + 1);
               for (uint32_t j = pcur[rb][p]; j < pe; ++j) {
                 const uint32_t v = __builtin_amdgcn_readlane(entv[rb][p], j);

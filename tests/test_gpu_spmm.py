@@ -423,3 +423,18 @@ def test_unaligned_rows_of_X_beyond_the_staging_area(name, m, n, B, dtype, pad):
     """More than 4 MiB with padded rows: copied and multiplied a part of the columns at a time."""
     got, want = _run(name, m, n, B, dtype, ldx_pad=pad, every_output=(dtype == "bf16"))
     assert rel_fro(got, want) <= 4e-7
+
+
+@pytest.mark.parametrize("name,m,n,n_out,n_in,B,S", [
+    # more than 64 entries in a wave's range: scattered into flip words four slices (two, one) at a time
+    ("large_q1", 320, 2048, 64, 8, 8, 0.8), ("large_q1", 320, 2048, 64, 8, 32, 0.75), ("large_q1", 300, 2010, 64, 8, 64, 0.75),
+    ("large_q1", 4100, 320, 64, 8, 512, 0.75), ("large_q1", 16384, 200, 64, 8, 256, 0.75), ("large_q2", 300, 1500, 64, 13, 64, 0.7),
+    ("large_q2", 8200, 330, 64, 8, 136, 0.75), ("lstm", 200, 2048, 64, 13, 32, 0.7), ("lstm", 200, 2048, 64, 32, 24, 0.3),
+    ("large_q1", 200, 2048, 192, 20, 64, 0.8), ("large_q2", 200, 1024, 128, 9, 24, 0.8), ("large_q1", 40000, 256, 64, 8, 8, 0.75),
+    # more than 64 entries in a group, more than 64 in a slice
+    ("large_q1", 100, 1024, 64, 4, 40, 0.5), ("large_q2", 100, 700, 64, 4, 16, 0.3),
+    # a range of more than 63 slices (reductions of 50000 columns), few and many patches
+    ("large_q1", 33, 50000, 64, 8, 16, 0.95), ("large_q1", 33, 50000, 64, 8, 64, 0.8)])
+def test_long_patch_lists(name, m, n, n_out, n_in, B, S):
+    got, want = _run(name, m, n, B, "bf16", S=S, n_out=n_out, n_in=n_in, every_output=True)
+    assert rel_fro(got, want) <= 4e-7
