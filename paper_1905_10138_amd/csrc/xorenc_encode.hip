@@ -17,6 +17,7 @@
 // every one of the 2^n_in inputs is tried on them as a matrix product on the matrix cores (exhaustive_search_kernel).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "xorenc_device.h"
@@ -229,7 +230,7 @@ struct ExhParams {
   uint64_t *pbits;
   Counts counts;
   int64_t n_slots, n_eslots;
-  int32_t n_in;
+  int32_t n_in, q;
   uint64_t Mcol[XORENC_MAX_J][XORENC_EXH_MAX_N_IN];  // [w][j]: bit i = M[64 w + i][j]
   uint64_t used[XORENC_MAX_J];                       // [w]: bit i = row 64 w + i of M is not zero
 };
@@ -254,7 +255,13 @@ __global__ void exhaustive_reset_kernel(uint32_t *list_len) { *list_len = 0; }
 // searched, one slice per lane, at 2J AND, 2J XOR and 2J population counts per input: 219 ms for the call, 0.35 ms now
 // (16384 x 4096 with half of the weights kept, n_out = 64, n_in = 16, where nearly every slice is searched: 14 and 5 ms).
 // The width of an item falls from 2^15 to 2^10 inputs when there are too few slices to give every wave eight items.
-template <int J>
+// ALL: every slice of the pass is searched, in one item each and without a list.  With few inputs that is cheaper than
+// the elimination that would sort out the slices that need no search (kAllMaxNIn; calls with n_in = 8, of which both
+// repeat with a larger patch buffer: 2000 x 1000, two planes, S = 0.8 83 us, 151 with the list; 4096 x 2048, S = 0.9 85,
+// 161; 500 x 9000, four planes, n_in = 10 115, 253).
+constexpr int kAllMaxNIn = 10;
+
+template <int J, bool ALL>
 __global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhParams P, int64_t first, int64_t n,
                                                                           const uint32_t *list_len) {
   constexpr int NS = 4;                                   // slice tiles of a wave
@@ -269,11 +276,11 @@ __global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhPa
     flip_s[c][w][h] = make_uint4(sign_bits(y, 0), sign_bits(y, 1), sign_bits(y, 2), sign_bits(y, 3));
   }
   __syncthreads();
-  const uint32_t n_list = *list_len;
+  const uint32_t n_list = ALL ? (uint32_t)P.q * (uint32_t)n : *list_len;
   const int64_t groups = ((int64_t)n_list + 32 * NS - 1) / (32 * NS);
   const int64_t waves = (int64_t)gridDim.x * (ENC_THREADS / 64);
   int c = P.n_in < 15 ? (P.n_in > 5 ? P.n_in : 5) : 15;
-  while (c > 10 && (groups << (P.n_in - c)) < 8 * waves) --c;
+  while (!ALL && c > 10 && (groups << (P.n_in - c)) < 8 * waves) --c;
   const int chunk_bits = P.n_in > c ? P.n_in - c : 0;
   const uint32_t tiles = 1u << (c - 5);
 
@@ -304,7 +311,8 @@ __global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhPa
     for (int t = 0; t < NS; ++t) {
       const int64_t li = group * (32 * NS) + 32 * t + rl;
       const bool valid = li < n_list;
-      const uint32_t entry = valid ? halves[2 * entry_word((uint32_t)li, first, (uint32_t)n, P.n_slots, J) + 1] : 0u;
+      uint32_t entry = 0u;
+      if (valid) entry = ALL ? (uint32_t)li : halves[2 * entry_word((uint32_t)li, first, (uint32_t)n, P.n_slots, J) + 1];
       word[t] = entry_word(entry, first, (uint32_t)n, P.n_slots, J);
       const int64_t mask_word = word[t] - entry / (uint32_t)n * P.n_slots;
       care_bits[t] = 0;
@@ -378,7 +386,11 @@ __global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhPa
       if (g == 0 && li < n_list) {
         const int32_t pair = (int32_t)v + (int32_t)(care_bits[t] << 14);  // mismatches << 15 | input inside the chunk
         const uint32_t x = (chunk << c) | (uint32_t)(pair & 0x7fff);
-        atomicMin(keys + 2 * word[t], ((uint32_t)(pair >> 15) + 1u) << 24 | x);
+        const uint32_t key = ((uint32_t)(pair >> 15) + 1u) << 24 | x;
+        if (ALL)
+          keys[2 * word[t]] = key;
+        else
+          atomicMin(keys + 2 * word[t], key);
       }
     }
   }
@@ -603,6 +615,16 @@ void launch_slices(const EncParams &P, int64_t first, int64_t n, uint32_t *list_
     hipLaunchKernelGGL((encode_slices_kernel<Q, false, SEARCH>), grid, dim3(ENC_THREADS), lds, st, P, first, n, list_len);
 }
 
+template <int J>
+void launch_search(bool all, dim3 search_grid, dim3 finish_grid, const ExhParams &E, int64_t first, int64_t n,
+                   const uint32_t *list_len, hipStream_t st) {
+  if (all)
+    hipLaunchKernelGGL((exhaustive_search_kernel<J, true>), search_grid, dim3(ENC_THREADS), 0, st, E, first, n, list_len);
+  else
+    hipLaunchKernelGGL((exhaustive_search_kernel<J, false>), search_grid, dim3(ENC_THREADS), 0, st, E, first, n, list_len);
+  hipLaunchKernelGGL(exhaustive_finish_kernel<J>, finish_grid, dim3(ENC_THREADS), 0, st, E, first, n);
+}
+
 template <bool SEARCH>
 void launch_slices_q(int q, const EncParams &P, int64_t first, int64_t n, uint32_t *list_len, hipStream_t st) {
   switch (q) {
@@ -678,6 +700,7 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
     E.n_slots = sz.n_slots;
     E.n_eslots = sz.n_eslots;
     E.n_in = n_in;
+    E.q = q;
     for (int w = 0; w < XORENC_MAX_J; ++w) {
       E.used[w] = 0;
       for (int i = 0; i < 64; ++i) E.used[w] |= (uint64_t)(P.M_rows[64 * w + i] != 0) << i;
@@ -692,31 +715,24 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
     const int64_t range = (int64_t)1 << 29;  // slices of a pass: list entries are 32-bit numbers
     for (int64_t first = 0; first < sz.n_eslots; first += range) {
       const int64_t n_pass = sz.n_eslots - first < range ? sz.n_eslots - first : range;
-      const dim3 eb(ENC_THREADS), fg((unsigned)((n_pass + ENC_THREADS - 1) / ENC_THREADS), (unsigned)q);
+      const dim3 fg((unsigned)((n_pass + ENC_THREADS - 1) / ENC_THREADS), (unsigned)q);
       const dim3 sg(J == 1 ? 1024 : J == 2 ? 768 : 512);  // search: the workgroups that are resident walk over the items
-      hipLaunchKernelGGL(exhaustive_reset_kernel, dim3(1), dim3(1), 0, st, list_len);
-      launch_slices_q<true>(q, P, first, n_pass, list_len, st);
+      const bool all = n_in <= kAllMaxNIn;
+      if (!all) {
+        hipLaunchKernelGGL(exhaustive_reset_kernel, dim3(1), dim3(1), 0, st, list_len);
+        launch_slices_q<true>(q, P, first, n_pass, list_len, st);
+      }
       switch (J) {
-        case 1:
-          hipLaunchKernelGGL(exhaustive_search_kernel<1>, sg, eb, 0, st, E, first, n_pass, list_len);
-          hipLaunchKernelGGL(exhaustive_finish_kernel<1>, fg, eb, 0, st, E, first, n_pass);
-          break;
-        case 2:
-          hipLaunchKernelGGL(exhaustive_search_kernel<2>, sg, eb, 0, st, E, first, n_pass, list_len);
-          hipLaunchKernelGGL(exhaustive_finish_kernel<2>, fg, eb, 0, st, E, first, n_pass);
-          break;
-        case 3:
-          hipLaunchKernelGGL(exhaustive_search_kernel<3>, sg, eb, 0, st, E, first, n_pass, list_len);
-          hipLaunchKernelGGL(exhaustive_finish_kernel<3>, fg, eb, 0, st, E, first, n_pass);
-          break;
-        default:
-          hipLaunchKernelGGL(exhaustive_search_kernel<4>, sg, eb, 0, st, E, first, n_pass, list_len);
-          hipLaunchKernelGGL(exhaustive_finish_kernel<4>, fg, eb, 0, st, E, first, n_pass);
-          break;
+        case 1: launch_search<1>(all, sg, fg, E, first, n_pass, list_len, st); break;
+        case 2: launch_search<2>(all, sg, fg, E, first, n_pass, list_len, st); break;
+        case 3: launch_search<3>(all, sg, fg, E, first, n_pass, list_len, st); break;
+        default: launch_search<4>(all, sg, fg, E, first, n_pass, list_len, st); break;
       }
     }
   }
-  const int units_per_block = ENC_UNITS * J, per = EMIT_UNITS / units_per_block;
+  // blocks of an emitting workgroup: as many as it has room for, fewer while there are not a thousand workgroups
+  const int units_per_block = ENC_UNITS * J;
+  const int per = std::max(1, std::min(EMIT_UNITS / units_per_block, n_blocks / 1024));
   const dim3 emit_grid((unsigned)((n_blocks + per - 1) / per));
   if (scan) {
     const int nscan = (n_blocks + SCAN_BLOCK - 1) / SCAN_BLOCK;
