@@ -23,6 +23,8 @@ constexpr int kSplitSlots = 4;
 constexpr size_t kSplitPartBytes = (size_t)kSplitMaxGroups * kSplitTileFloats * sizeof(float);  // 4 MiB
 constexpr size_t kSplitTicketBytes = (size_t)kSplitMaxGroups * sizeof(uint32_t);
 constexpr size_t kStageBytes = (size_t)4 << 20;  // 4 MiB: 8192 rows of 256 bf16 columns
+constexpr int64_t kXSplitMinWeights = 6000000;   // fp32 X: weights (of all planes), or weights times columns, from which
+constexpr int64_t kXSplitMinWork = 600000000;    // it is split by a kernel of its own
 constexpr int kStageMinB = 5;                    // (fewer columns are faster on the kernels that read X element by element)
 constexpr size_t kSplitSlotBytes = kSplitPartBytes + kSplitTicketBytes + kStageBytes;
 static_assert(kSplitSlotBytes % 256 == 0, "slots keep the array's alignment");
@@ -51,6 +53,47 @@ __global__ __launch_bounds__(256) void stage_x_kernel(const unsigned char *__res
     }
   }
   *reinterpret_cast<uint4 *>(dst + piece * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// fp32 X -> three bf16 matrices hi, mid, lo of `rows` x 8 cpr values whose sum is X exactly; one thread per 8 columns
+// of a row, rows from n on and columns from B on are zero
+__global__ __launch_bounds__(256) void split_x_kernel(const float *__restrict__ X, int64_t ldx, int n, int rows, int B,
+                                                      int cpr, unsigned char *__restrict__ dst) {
+  const int64_t piece = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (piece >= (int64_t)rows * cpr) return;
+  const int k = (int)(piece / cpr), c = 8 * (int)(piece - (int64_t)k * cpr);
+  const float *row = X + (int64_t)k * ldx + c;
+  const bool wide = (reinterpret_cast<uintptr_t>(row) & 15) == 0 && c + 8 <= B;
+  float v[8];
+  if (k >= n) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = 0.f;
+  } else if (wide) {
+    const float4 a = *reinterpret_cast<const float4 *>(row), b = *reinterpret_cast<const float4 *>(row + 4);
+    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = c + e < B ? row[e] : 0.f;
+  }
+  uint32_t w[3][4];
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[t][e] = 0u;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const uint32_t h0 = f32_to_bf16_rne(v[e]);
+    const float r1 = v[e] - __uint_as_float(h0 << 16);
+    const uint32_t h1 = f32_to_bf16_rne(r1);
+    const uint32_t h2 = f32_to_bf16_rne(r1 - __uint_as_float(h1 << 16));
+    w[0][e >> 1] |= h0 << (16 * (e & 1));
+    w[1][e >> 1] |= h1 << (16 * (e & 1));
+    w[2][e >> 1] |= h2 << (16 * (e & 1));
+  }
+  const int64_t term = (int64_t)rows * cpr;
+#pragma unroll
+  for (int t = 0; t < 3; ++t)
+    *reinterpret_cast<uint4 *>(dst + (t * term + piece) * 16) = make_uint4(w[t][0], w[t][1], w[t][2], w[t][3]);
 }
 }  // namespace
 static __device__ __align__(256) unsigned char split_scratch[kSplitSlots * kSplitSlotBytes];
@@ -108,7 +151,7 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
     D.split_part = reinterpret_cast<float *>(slot);
     D.split_ticket = reinterpret_cast<uint32_t *>(slot + kSplitPartBytes);
   }
-  auto product = [&](const void *Xp, int64_t ld, int32_t cols, float *Yp, int fast) -> int32_t {
+  auto product = [&](const void *Xp, int64_t ld, int32_t cols, float *Yp, int fast, int32_t x_dtype) -> int32_t {
     switch (layer->q) {
       case 1: return xorenc_spmm_dispatch_q1(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
       case 2: return xorenc_spmm_dispatch_q2(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
@@ -116,6 +159,30 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
       default: return xorenc_spmm_dispatch_q4(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
     }
   };
+  // fp32 X: split into three bf16 matrices in the staging area, as many columns at a time as fit (in whole 64s where
+  // there are more).  The product then runs on the direct-to-LDS kernels, which convert nothing; the launch and the pass
+  // over X cost 2 to 3 us, so small layers keep the kernels that split X on its way into LDS (us, B = 1 / 8 / 64 / 200:
+  // 1024 x 1024 9.8 8.3 8.5 12.6, here 9.4 9.3 9.8 12.2; 2048 x 2048 11.2 9.9 10.9 29.2, here 9.9 9.9 12.0 20.4;
+  // 4096 x 4096 17.6 15.2 22.6 83.7, here 12.1 12.1 16.9 47.6; 4096 x 9216 with two planes 34.6 29.3 51.5 465, here
+  // 18.8 18.8 32.0 120).
+  const int64_t weights = (int64_t)layer->m * layer->n * layer->q;
+  if (x_dtype == XORENC_X_F32 && (weights >= kXSplitMinWeights || weights * B >= kXSplitMinWork)) {
+    const int rows = D.spr * 64;
+    int64_t part = (int64_t)(kStageBytes / ((size_t)rows * 48)) * 8;  // columns that fit
+    if (part >= min(B, 64)) {
+      part = part >= B ? B : part / 64 * 64;
+      unsigned char *stage = slot + kSplitPartBytes + kSplitTicketBytes;
+      for (int c0 = 0; c0 < B; c0 += (int)part) {
+        const int cols = min((int)part, B - c0), cpr = (cols + 7) / 8;
+        const int64_t pieces = (int64_t)rows * cpr;
+        hipLaunchKernelGGL(split_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
+                           static_cast<const float *>(X) + c0, ldx, (int)layer->n, rows, cols, cpr, stage);
+        const int32_t rp = product(stage, (int64_t)cpr * 8, cols, Y + c0, 1, xorenc_spmm_detail::kXSplit);
+        if (rp != XORENC_OK) return rp;
+      }
+      return XORENC_OK;
+    }
+  }
   // rows of X that do not start on 16-byte boundaries: a padded copy, unless the few-column kernel (which reads X
   // element by element anyway) takes the call.  A copy that does not fit the staging area is made and multiplied a part
   // of the columns at a time (parts of nearly equal width, at least 64 columns of the area each: n <= 32768).
@@ -134,11 +201,11 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
         hipLaunchKernelGGL(stage_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
                            static_cast<const unsigned char *>(X) + (int64_t)c0 * esz, ldx, (int)layer->n, cols, esz, cpr,
                            stage);
-        const int32_t rp = product(stage, (int64_t)cpr * per, cols, Y + c0, 1);
+        const int32_t rp = product(stage, (int64_t)cpr * per, cols, Y + c0, 1, x_dtype);
         if (rp != XORENC_OK) return rp;
       }
       return XORENC_OK;
     }
   }
-  return product(X, ldx, B, Y, aligned ? 1 : 0);
+  return product(X, ldx, B, Y, aligned ? 1 : 0, x_dtype);
 }

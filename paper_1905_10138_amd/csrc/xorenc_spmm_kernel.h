@@ -89,6 +89,8 @@ constexpr int largest_divisor_at_most(int n, int cap) {
   return best;
 }
 
+constexpr int32_t kXSplit = 2;  // x_dtype of X that has been split into three bf16 matrices (inside the library only)
+
 template <bool V>
 struct BoolC {
   static constexpr bool value = V;
@@ -101,7 +103,10 @@ struct BoolC {
 // SIMD hide each other's waits) or 1 (loads one slice ahead, more waves per SIMD do the hiding).
 // NARROW: at most eight columns of X (one 16-byte chunk per row): a slice of X is 1 KB and arrives with a
 // single direct load; the operand lanes of the 24 padding columns read the same chunk again.
-template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBV, int JT, bool NARROW = false>
+// TERMS = 3: fp32 X that a kernel before this one has split into three bf16 matrices (hi, mid, lo, one after the other,
+// each of 64 rows per word of a row of W).  The wave walks over the three slices of X of every slice of W with the same
+// operands; hi has accumulators of its own, so that the sums of the large terms are rounded as they would be alone.
+template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBV, int JT, bool NARROW = false, int TERMS = 1>
 __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void spmm_kernel(DevLayer L, const void *__restrict__ Xv, int64_t ldx, int B,
                                                       float *__restrict__ Y, int64_t ldy, int slices_per_split,
                                                       int n_splits) {
@@ -210,8 +215,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   const int64_t row_bytes = ldx * ESZ;
   // (16-byte fetches are range-checked dword by dword: an odd number of bf16 columns ends in the middle of a dword,
   // which still has to count as inside; the two bytes behind it lie in the same aligned dword as the last element)
-  const uint32_t x_extent = ((uint32_t)((int64_t)(l_n - 1) * row_bytes + (int64_t)(B - col0) * ESZ) + (XFAST ? 3u : 0u)) &
-                            (XFAST ? ~3u : ~0u);
+  const uint32_t term_bytes = (uint32_t)((int64_t)l_spr * 64 * row_bytes);
+  const uint32_t x_extent =
+      TERMS > 1 ? TERMS * term_bytes - (uint32_t)(col0 * ESZ)
+                : ((uint32_t)((int64_t)(l_n - 1) * row_bytes + (int64_t)(B - col0) * ESZ) + (XFAST ? 3u : 0u)) &
+                      (XFAST ? ~3u : ~0u);
   const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t *>(static_cast<const uint8_t *>(Xv) + (int64_t)col0 * ESZ), 0, x_extent, kRsrcFlags);
   const __amdgpu_buffer_rsrc_t mrsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -250,8 +258,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   const u32x4 xdesc = {(uint32_t)x_base, (uint32_t)(x_base >> 32) & 0xffffu, x_extent, kRsrcFlags};
   const uint32_t xbuf_lds = __builtin_amdgcn_readfirstlane(
       (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)(xbuf));
-  auto dma_x = [&](int s, int which) {
-    const uint32_t sbase = (uint32_t)(s * 64 * row_bytes);  // uniform
+  auto dma_x = [&](int s, int which, int term = 0) {
+    const uint32_t sbase = (uint32_t)(s * 64 * row_bytes) + (TERMS > 1 ? (uint32_t)term * term_bytes : 0u);  // uniform
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const uint32_t so = __builtin_amdgcn_readfirstlane(sbase + (uint32_t)(row_of_pos(i << LB) * row_bytes));
@@ -561,6 +569,19 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[p][rb][cb][i] = 0.f;
 
+  static_assert(TERMS == 1 || (TERMS == 3 && XDIR && PD == 1 && !NARROW), "split X runs on the direct path with one buffer");
+  f32x16 acc_low[TERMS > 1 ? Q : 1][TERMS > 1 ? RB : 1][TERMS > 1 ? NCB : 1];  // mid and lo
+  if constexpr (TERMS > 1) {
+#pragma unroll
+    for (int p = 0; p < Q; ++p)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc_low[p][rb][cb][i] = 0.f;
+  }
+
   // per-lane address of the transposing reads inside the wave's buffer (see lds_read_tr16)
   const int jj = (lane >> 2) & 3, c4 = lane & 3;
   const uint8_t *tr_ptr =
@@ -743,8 +764,14 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
     if constexpr (XDIR && PD == 1) {
       if (cnt > 1) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the buffers have been read out
-        dma_x(w0 + 1, 0);
-        load_comp_hidden(w0 + 1, 0);
+        if constexpr (TERMS == 1) {
+          dma_x(w0 + 1, 0);
+          load_comp_hidden(w0 + 1, 0);
+        }
+      }
+      if constexpr (TERMS > 1) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        dma_x(w0, 0, 1);
       }
     }
 
@@ -817,6 +844,50 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
                 acc[p][rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag, bfrag[t][cb], acc[p][rb][cb], 0, 0, 0);
             }
         };
+        if constexpr (TERMS > 1) {
+          // the buffer holds one slice of one term: while it is multiplied, the next one lands
+#pragma unroll
+          for (int term = 0; term < TERMS; ++term) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+              for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int p = 0; p < Q; ++p) {
+                  const bf16x8 afrag = __builtin_bit_cast(bf16x8, expand_fp4_codes(Iw[rb][p][t]));
+#pragma unroll
+                  for (int cb = 0; cb < NCB; ++cb) {
+                    f32x16 &c = term == 0 ? acc[p][rb][cb] : acc_low[p][rb][cb];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(afrag, bfrag[t][cb], c, 0, 0, 0);
+                  }
+                }
+            if (term < TERMS - 1 || has_next) {  // uniform
+              __builtin_amdgcn_sched_barrier(0);
+              wait_loads(false);
+              __builtin_amdgcn_sched_barrier(0);
+              if (term == TERMS - 1) {
+                read_comp(0, ring[d ^ 1]);
+                lookup(ring[d ^ 1], Snext, s + 1);
+              }
+#pragma unroll
+              for (int t = 0; t < 4; ++t) read_bfrag(t, bfrag[t], 0);
+              __builtin_amdgcn_sched_barrier(0);
+              asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+              if (term == 0) {
+                dma_x(s, 0, 2);
+              } else if (term == 1) {
+                if (has_next) {
+                  dma_x(s + 1, 0, 0);
+                  load_comp_hidden(s + 1, 0);
+                }
+              } else {
+                dma_x(s + 1, 0, 1);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+          continue;
+        }
         mfma_step(0);
         if constexpr (XDIR && PD == 1) {
           // one buffer: slice s is entirely in operand registers, slice s+1 is landing; it is read
@@ -915,6 +986,10 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
       for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
+          if constexpr (TERMS > 1) {
+#pragma unroll
+            for (int p = 0; p < Q; ++p) acc[p][rb][cb][4 * j4 + k] += acc_low[p][rb][cb][4 * j4 + k];
+          }
           float v = a4[0][k] * acc[0][rb][cb][4 * j4 + k];
 #pragma unroll
           for (int p = 1; p < Q; ++p) v += a4[p][k] * acc[p][rb][cb][4 * j4 + k];
@@ -1020,16 +1095,16 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   }
 }
 
-template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBV, int JT, bool NARROW = false>
+template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBV, int JT, bool NARROW = false, int TERMS = 1>
 inline void launch_variant(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y, int64_t ldy, dim3 grid,
                            int sps, int n_splits, hipStream_t st) {
-  hipLaunchKernelGGL((spmm_kernel<NCB, Q, RB, XF32, NW, XFAST, PD, NIBV, JT, NARROW>), grid, dim3(NW * 64), 0, st, D, X,
+  hipLaunchKernelGGL((spmm_kernel<NCB, Q, RB, XF32, NW, XFAST, PD, NIBV, JT, NARROW, TERMS>), grid, dim3(NW * 64), 0, st, D, X,
                      ldx, B, Y, ldy, sps, n_splits);
 }
 
 // XMODE: 0 = the call site may see either layout, 1 = aligned X only, 2 = generic X only (keeps
 // variants that are never launched from being compiled)
-template <int NCB, int Q, int RB, bool XF32, int NW = 8, int PD = 2, int XMODE = 0, int JMODE = 0, bool NARROW = false>
+template <int NCB, int Q, int RB, bool XF32, int NW = 8, int PD = 2, int XMODE = 0, int JMODE = 0, bool NARROW = false, int TERMS = 1>
 int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y, int64_t ldy, int x_fast,
                     hipStream_t st) {
   constexpr int NR = XF32 ? (32 * NCB) / 3 : 32 * NCB;
@@ -1065,28 +1140,28 @@ int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float 
   } else {
     if constexpr (JMODE != 1)
       if (wide) switch (D.nib_variant) {
-          case 1: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 1, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          case 2: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 2, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          case 3: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 3, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          case 4: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 4, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          default: launch_variant<NCB, Q, RB, XF32, NW, true, PD, kFourTablesTwoDwords, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 1: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 1, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 2: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 2, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 3: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 3, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 4: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 4, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          default: launch_variant<NCB, Q, RB, XF32, NW, true, PD, kFourTablesTwoDwords, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
         }
     if constexpr (JMODE != 4)
       if (!wide) switch (D.nib_variant) {
-          case 1: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 1, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          case 2: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 2, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 1: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 1, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 2: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 2, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
           case 3:
             // (the four-wave workgroups that share a CU have LDS for one or two tables per wave only)
             if constexpr (NW == 4 && !XF32) return XORENC_EUNSUPPORTED;
-            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, 3, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
+            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, 3, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
             break;
           case 4:
             if constexpr (NW == 4 && !XF32) return XORENC_EUNSUPPORTED;
-            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, 4, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
+            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, 4, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
             break;
           default:
             if constexpr (NW == 4 && !XF32) return XORENC_EUNSUPPORTED;
-            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, kFourTablesTwoDwords, 1, NARROW>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
+            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, kFourTablesTwoDwords, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
             break;
         }
   }
@@ -1098,6 +1173,21 @@ int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float 
 template <int Q>
 int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64_t ldx, int B, float *Y, int64_t ldy,
                         int x_fast, hipStream_t st) {
+  if (x_dtype == kXSplit) {  // fp32 X as three bf16 matrices
+    if constexpr (Q <= 2) {
+      if (B > 32) {
+        if constexpr (Q == 1) {
+          // (64-row tiles once they give every CU one; X is re-read half as often)
+          if ((int64_t)((D.nrb + 1) / 2) * ((B + 63) / 64) >= 200)
+            return launch_spmm<2, Q, 2, false, 8, 1, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
+        }
+        return launch_spmm<2, Q, 1, false, 8, 1, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
+      }
+      return launch_spmm<1, Q, 1, false, 12, 1, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
+    } else {
+      return launch_spmm<1, Q, 1, false, 8, 1, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
+  }
   if (x_dtype == XORENC_X_F32) {
     if constexpr (Q <= 2)
       return launch_spmm<3, Q, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);

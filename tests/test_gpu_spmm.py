@@ -438,3 +438,37 @@ def test_unaligned_rows_of_X_beyond_the_staging_area(name, m, n, B, dtype, pad):
 def test_long_patch_lists(name, m, n, n_out, n_in, B, S):
     got, want = _run(name, m, n, B, "bf16", S=S, n_out=n_out, n_in=n_in, every_output=True)
     assert rel_fro(got, want) <= 4e-7
+
+
+@pytest.mark.parametrize("name,m,n,n_out,n_in,S,calls", [
+    # (columns, padding of the rows of X): one column block and two, ragged last pieces, parts of the staging area
+    ("large_q1", 4100, 1500, 64, 8, None, [(1, 0), (9, 0), (32, 0), (33, 3), (64, 0), (300, 1)]),
+    ("large_q1", 13000, 500, 192, 20, 0.9, [(8, 0), (65, 0), (130, 2)]),
+    ("large_q2", 2100, 1500, 64, 13, 0.75, [(5, 1), (31, 0), (64, 4), (100, 0)]),
+    ("large_q2", 400, 9100, 128, 16, 0.9, [(8, 0), (72, 0), (90, 0)]),
+    ("lstm", 1500, 1400, 64, 24, None, [(1, 1), (32, 0), (50, 0)]),
+    ("fig1", 200, 31000, 64, 16, None, [(8, 0), (20, 0)])])
+def test_fp32_X_split_by_a_kernel_of_its_own(name, m, n, n_out, n_in, S, calls):
+    """Layers from 6 million weights (and the last one, whose X does not fit the staging area with 20 columns): fp32 X
+    becomes three bf16 matrices first.  Every output within fp32's bound of the 64-bit result."""
+    for B, pad in calls:
+        got, want = _run(name, m, n, B, "f32", ldx_pad=pad, S=S, n_out=n_out, n_in=n_in, every_output=True)
+        assert rel_fro(got, want) <= 2e-7
+
+
+def test_fp32_X_of_many_magnitudes_and_four_planes():
+    """Values from 2^-60 to 2^60 next to each other, zeros and subnormals: hi + mid + lo is the value itself."""
+    import dataclasses
+    import torch
+    import paper_1905_10138_amd as xe
+    from oracle import encoder
+    from synth_inputs import CONFIGS, make_workload
+    wl = make_workload(dataclasses.replace(CONFIGS["lstm"], q=4, n_in=24, S=0.9), m=1300, n=1300)
+    enc = encoder.encode(wl.keep, wl.planes, wl.alpha, wl.M, wl.n)
+    L = pack_encoded(enc).to(torch.device("cuda:0"))
+    rng = np.random.default_rng(8)
+    X = (rng.standard_normal((wl.n, 40)) * np.exp2(rng.integers(-60, 61, size=(wl.n, 40)))).astype(np.float32)
+    X[::7] = 0.0
+    X[3::11] = np.float32(1e-42)
+    got = xe.spmm(L, torch.from_numpy(X).to("cuda:0")).cpu().numpy()
+    assert_every_output_close(got, decoder.spmm_f64(enc, X), enc, X)
