@@ -278,12 +278,14 @@ XORENC_API int32_t xorenc_decode(const xorenc_layer *layer, int32_t out_kind, vo
  * such a base address) and X has at least five columns: a first kernel then copies X into a 4 MiB staging area inside
  * the library with its rows padded to whole 16-byte pieces, and the product reads the copy; an X that needs more is
  * copied and multiplied in parts of its columns, two launches each (n <= 32768; larger n are read element by element)
- * (the fast kernels fetch X in 16-byte pieces).  For small layers the launch splits the reduction dimension over
- * several workgroups per output tile; their partial tiles meet in a scratch area, and the workgroup that finishes
- * last adds them in the order of their slice ranges.  Staging and scratch areas live in device memory that the
- * library keeps on every GPU (about 32 MiB, four slots taken in turn by successive calls).  At most four calls
- * that use a slot may therefore overlap on one GPU (on different streams; calls on one stream never overlap); a
- * fifth could read another call's partial sums or copy of X.
+ * (the fast kernels fetch X in 16-byte pieces).  fp32 X of larger layers (6 million weights of all planes, or 600
+ * million products) is split into its three bf16 terms in the same area first, in parts where they do not fit.  For
+ * small layers the launch splits the reduction dimension over several workgroups per output tile; their partial tiles
+ * meet in a scratch area, and the workgroup that finishes last adds them in a fixed order of their slice ranges.
+ * Staging and scratch areas live in device memory that the library keeps on every GPU (about 128 MiB, sixteen slots
+ * taken in turn by successive calls).  At most sixteen calls that use a slot may therefore overlap on one GPU (on
+ * different streams; calls on one stream never overlap); a seventeenth could read another call's partial sums or copy
+ * of X.
  * Nothing is allocated by the call.
  */
 XORENC_API int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t x_dtype, int64_t ldx, int32_t B, float *Y,

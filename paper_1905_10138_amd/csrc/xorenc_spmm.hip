@@ -19,7 +19,7 @@
 // against 170 us on a 16384 x 4096 layer); larger X are copied and multiplied in parts
 // (4096 x 9216, two planes, B = 1023: 2700 us on the element-wise kernels, 278 us).
 namespace {
-constexpr int kSplitSlots = 4;
+constexpr int kSplitSlots = 16;  // (128 MiB: most calls on fp32 or unaligned X use a slot's staging area)
 constexpr size_t kSplitPartBytes = (size_t)kSplitMaxGroups * kSplitTileFloats * sizeof(float);  // 4 MiB
 constexpr size_t kSplitTicketBytes = (size_t)kSplitMaxGroups * sizeof(uint32_t);
 constexpr size_t kStageBytes = (size_t)4 << 20;  // 4 MiB: 8192 rows of 256 bf16 columns

@@ -472,3 +472,31 @@ def test_fp32_X_of_many_magnitudes_and_four_planes():
     X[3::11] = np.float32(1e-42)
     got = xe.spmm(L, torch.from_numpy(X).to("cuda:0")).cpu().numpy()
     assert_every_output_close(got, decoder.spmm_f64(enc, X), enc, X)
+
+
+def test_calls_on_many_streams_keep_their_own_staging_and_scratch():
+    """Sixteen streams at a time, calls that split X, copy unaligned X or split the reduction over workgroups: every slot
+    is in use, and every result is the one a call alone gives, bit for bit."""
+    import torch
+    import paper_1905_10138_amd as xe
+    _, enc = encoded_workload("large_q1", 4100, 1500)
+    _, small = encoded_workload("fc6", 97, 640)
+    L, Ls = pack_encoded(enc).to(torch.device("cuda:0")), pack_encoded(small).to(torch.device("cuda:0"))
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(4)
+    jobs = []
+    for i in range(16):
+        layer = Ls if i % 4 == 3 else L
+        x = torch.randn((layer.n, 9 + 5 * i), device="cuda:0", generator=g)
+        x = x.to(torch.bfloat16) if i % 4 else x
+        jobs.append((layer, x, xe.spmm(layer, x).clone()))
+    streams = [torch.cuda.Stream() for _ in jobs]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        out = []
+        for (layer, x, _), st in zip(jobs, streams):
+            with torch.cuda.stream(st):
+                out.append(xe.spmm(layer, x))
+        torch.cuda.synchronize()
+        for (_, _, want), got in zip(jobs, out):
+            assert torch.equal(got, want)
