@@ -17,10 +17,10 @@
 // every one of the 2^n_in inputs is tried on them as a matrix product on the matrix cores (exhaustive_search_kernel).
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <mutex>
 
 #include "xorenc_device.h"
+#include "xorenc_encode_plan.h"
 
 // Scratch area of xorenc_encode_static: device memory that every GPU holds from the time the library is loaded.
 // In host code the array's name is only a handle for hipGetSymbolAddress; kernels get the looked-up address.
@@ -28,7 +28,6 @@ static __device__ __align__(256) unsigned char scratch[XORENC_STATIC_SCRATCH_BYT
 
 namespace {
 
-constexpr int ENC_THREADS = 256;
 constexpr int kMaxDevices = 64;
 
 // Address of `scratch` on the current device, looked up once per device (with that device current).
@@ -51,13 +50,11 @@ int32_t static_scratch_address(void **out) {
   return XORENC_OK;
 }
 
-constexpr int ENC_UNITS = ENC_THREADS / 32;  // 32-slice groups of a workgroup
-
-// The patch counts that the slices leave for the offsets live where the workspace has 4 bytes per unit and plane:
-// 2-byte counts (a unit has at most 2048 patches), and totals per counting block, the ENC_UNITS * J units that a
-// workgroup covers in one plane, in flattened (plane, block) order.
+// The patch counts that the slices leave for the offsets (encode_plan): 2-byte counts (a unit has at most 2048 patches),
+// and totals per counting block, the ENC_UNITS * J units that a workgroup covers in one plane, in flattened (plane,
+// block) order.
 struct Counts {
-  uint16_t *unit;     // [q*n_units]
+  uint16_t *unit;     // [q*n_units], null with one unit per plane: its count is the total of its block
   uint32_t *block;    // [q*n_blocks]
   uint32_t *scanned;  // [q*n_blocks + 1]: exclusive sums of `block` (only when there are many blocks)
   int32_t n_units, n_blocks;
@@ -96,7 +93,7 @@ __device__ inline void put_patches(uint64_t *pbits, const Counts &c, int p, int6
     if (valid && cnt) pbits[slot] = patches;
   }
   if (valid && (threadIdx.x & 31) == 0) {
-    c.unit[(int64_t)p * c.n_units + (slot - (int64_t)p * c.n_units * 32) / 32] = (uint16_t)cnt;
+    if (c.unit) c.unit[(int64_t)p * c.n_units + (slot - (int64_t)p * c.n_units * 32) / 32] = (uint16_t)cnt;  // uniform
     if (cnt) atomicAdd(block_total, cnt);
   }
 }
@@ -514,12 +511,9 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_add_kernel(uint32_t *off, i
 }
 
 // Offsets of the units' patch lists and the lists themselves.  A workgroup covers `per` counting blocks (at most
-// EMIT_UNITS units); where its lists start is the sum of the blocks before it, which it adds up itself (SCANNED: reads
-// from the scanned totals).  Adding them up reads 4 bytes per ENC_UNITS * J units and workgroup from the L2 (16384 x
-// 4096, two planes: 64 KB at most) and replaces three scan launches; beyond kDirectBlocks blocks the scan is cheaper.
-constexpr int EMIT_UNITS = 128;
-constexpr int kDirectBlocks = 32768;
-
+// EMIT_UNITS units); where its lists start is the sum of the blocks before it, which it adds up itself instead of three
+// scan launches (SCANNED: reads from the scanned totals).  Workgroups run in any order and `off` is written as they
+// go: nothing that another one still reads may lie there.
 template <bool SCANNED>
 __global__ __launch_bounds__(ENC_THREADS) void emit_patches_kernel(const uint64_t *pbits, Counts C, int q, int64_t n_slots,
                                                                   int units_per_block, int per, uint32_t *off,
@@ -534,7 +528,7 @@ __global__ __launch_bounds__(ENC_THREADS) void emit_patches_kernel(const uint64_
   const int p = min(blk, n_all - 1) / C.n_blocks;
   const int64_t u = (int64_t)(blk - p * C.n_blocks) * units_per_block + tid % units_per_block;
   const bool mine = tid < per * units_per_block && blk < n_all && u < C.n_units;
-  const uint32_t cnt = mine ? C.unit[(int64_t)p * C.n_units + u] : 0u;
+  const uint32_t cnt = !mine ? 0u : C.unit ? C.unit[(int64_t)p * C.n_units + u] : C.block[blk];
   uint32_t before = 0;  // patches of earlier workgroups
   if constexpr (SCANNED) {
     before = C.scanned[block0];
@@ -663,20 +657,15 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
   uint64_t *pbits = static_cast<uint64_t *>(workspace);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const int J = n_out / 64;
+  const EncodePlan plan = encode_plan(sz, q, n_out);
+  const int n_blocks = q * plan.n_blocks;
+  unsigned char *const area = reinterpret_cast<unsigned char *>(pbits + total);
   Counts C;
   C.n_units = (int32_t)sz.n_units;
-  C.n_blocks = (int32_t)((sz.n_eslots + ENC_THREADS - 1) / ENC_THREADS);
-  const int n_blocks = q * C.n_blocks;
-  const bool scan = n_blocks > kDirectBlocks;
-  // The workspace's 4 bytes per unit and plane hold 2 bytes per unit and 4 per block (8 where the totals are scanned,
-  // which takes thousands of blocks): a block has at least eight units or is the only one of its plane, so they fit
-  // from two units per plane on.  With one unit the counts lie in the offsets, which one workgroup writes after
-  // reading them.
-  unsigned char *const area = reinterpret_cast<unsigned char *>(pbits + total);
-  const int64_t unit_bytes = sz.n_units > 1 ? (2 * n_counts + 3) / 4 * 4 : 0;
-  C.unit = sz.n_units > 1 ? reinterpret_cast<uint16_t *>(area) : reinterpret_cast<uint16_t *>(patch_off_out);
-  C.block = reinterpret_cast<uint32_t *>(area + unit_bytes);
-  C.scanned = scan ? C.block + n_blocks : nullptr;
+  C.n_blocks = plan.n_blocks;
+  C.unit = plan.unit_at >= 0 ? reinterpret_cast<uint16_t *>(area + plan.unit_at) : nullptr;
+  C.block = reinterpret_cast<uint32_t *>(area + plan.block_at);
+  C.scanned = plan.scanned_at >= 0 ? reinterpret_cast<uint32_t *>(area + plan.scanned_at) : nullptr;
   EncParams P;
   P.mask = mask;
   P.planes = planes;
@@ -710,7 +699,7 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
         E.Mcol[w][j] = col;
       }
     }
-    // free until the last kernel overwrites every entry (behind the counts where those are in the offsets too)
+    // free until the last kernel overwrites every entry
     uint32_t *const list_len = patch_off_out + q * sz.n_units;
     const int64_t range = (int64_t)1 << 29;  // slices of a pass: list entries are 32-bit numbers
     for (int64_t first = 0; first < sz.n_eslots; first += range) {
@@ -730,20 +719,17 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
       }
     }
   }
-  // blocks of an emitting workgroup: as many as it has room for, fewer while there are not a thousand workgroups
-  const int units_per_block = ENC_UNITS * J;
-  const int per = std::max(1, std::min(EMIT_UNITS / units_per_block, n_blocks / 1024));
-  const dim3 emit_grid((unsigned)((n_blocks + per - 1) / per));
-  if (scan) {
+  const dim3 emit_grid(plan.emit_groups);
+  if (C.scanned) {
     const int nscan = (n_blocks + SCAN_BLOCK - 1) / SCAN_BLOCK;
     hipLaunchKernelGGL(scan_local_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, C.block, C.scanned, n_blocks);
     hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(1024), 0, st, C.scanned, n_blocks, nscan);
     hipLaunchKernelGGL(scan_add_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, C.scanned, n_blocks);
     hipLaunchKernelGGL(emit_patches_kernel<true>, emit_grid, dim3(ENC_THREADS), 0, st, pbits, C, q, sz.n_slots,
-                       units_per_block, per, patch_off_out, patch_out, patch_capacity);
+                       plan.units_per_block, plan.per, patch_off_out, patch_out, patch_capacity);
   } else {
     hipLaunchKernelGGL(emit_patches_kernel<false>, emit_grid, dim3(ENC_THREADS), 0, st, pbits, C, q, sz.n_slots,
-                       units_per_block, per, patch_off_out, patch_out, patch_capacity);
+                       plan.units_per_block, plan.per, patch_off_out, patch_out, patch_capacity);
   }
   return xorenc_internal_check_launch();
 }

@@ -240,3 +240,36 @@ def test_encoder_with_more_counting_blocks_than_one_workgroup_adds_up():
     got = xe.decode(L, xe.OUT_PLANES).view(q, m // 32, 32, n // 64)
     want = (planes & mask).view(q, m // 32, n // 64, 32).transpose(2, 3)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("q", [1, 2, 3, 4])
+@pytest.mark.parametrize("exhaustive", [False, True])
+def test_encoder_with_one_unit_per_plane_and_patches_in_every_plane(q, exhaustive):
+    """One counting block per plane with one unit: its total is the unit's count.  All three encoders against the
+    oracle."""
+    import torch
+    import paper_1905_10138_amd as xe
+    from oracle import encoder
+    rng = np.random.default_rng(60 + q)
+    m, n, n_in = 29, 61, 11
+    keep = np.zeros((m, 64), dtype=bool)
+    keep[:, :n] = rng.random((m, n)) < 0.5
+    planes = (rng.random((q, m, 64)) < 0.5) & keep
+    M = rng.integers(0, 2, size=(64, n_in), dtype=np.uint8)
+    alpha = np.ones((q, m), np.float32)
+    enc = encoder.encode(keep, planes, alpha, M, n, exhaustive=exhaustive)
+    assert np.all(enc.n_patch.reshape(q, -1).sum(axis=1) > 0)
+    dev = torch.device("cuda:0")
+    words = lambda a: torch.from_numpy(xe.pack_bits(a[:, :n]).view(np.int64))
+    M_rows = (M.astype(np.uint64) << np.arange(n_in, dtype=np.uint64)).sum(axis=1).astype(np.uint32)
+    mask, bits = words(keep).to(dev), torch.stack([words(p) for p in planes]).to(dev)
+    fn = xe.encode_exhaustive if exhaustive else xe.encode
+    L = fn(m, n, n_in, q, M_rows, mask, bits, torch.from_numpy(alpha).to(dev))
+    w_c, _, n_patch, d_patch = xe.unpack(L.to_host())
+    ow, _, onp, odp, _ = paper_format_arrays(enc)
+    assert np.array_equal(w_c, ow) and np.array_equal(n_patch, onp) and np.array_equal(d_patch, odp)
+    if not exhaustive:
+        off, patch = torch.full_like(L.patch_off, -1), torch.full_like(L.patch, -1)
+        e = torch.zeros_like(L.enc)
+        xe.encode_static(m, n, n_in, q, M_rows, mask, bits, e, off, patch)
+        assert torch.equal(off, L.patch_off) and torch.equal(patch, L.patch) and torch.equal(e, L.enc)

@@ -1,0 +1,78 @@
+"""Host-side plans of the library (headers without HIP), compiled with g++ together with the host sources and checked on
+the CPU for conditions that a run on the GPU would only break now and then."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1905_10138_amd", "csrc")
+
+
+def run_program(tmp_path, text, *sources, flags=()):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no g++ here")
+    src, exe = str(tmp_path / "main.cpp"), str(tmp_path / "main")
+    with open(src, "w") as f:
+        f.write(text)
+    subprocess.run([gxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, *flags, src,
+                    *[os.path.join(CSRC, s) for s in sources], "-o", exe], check=True, timeout=120)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout[-2000:]
+
+
+ENCODE_PLAN = r"""
+#include <cstdio>
+#include "xorenc_encode_plan.h"
+
+#define CHECK(c) do { if (!(c)) { std::printf("m=%d n=%d q=%d n_out=%d: %s\n", m, n, q, n_out, #c); return false; } } while (0)
+
+static bool check(int m, int n, int q, int n_out) {
+  xorenc_sizes sz;
+  CHECK(xorenc_get_sizes(m, n, 8, q, n_out, &sz) == XORENC_OK);
+  const EncodePlan P = encode_plan(sz, q, n_out);
+  // [0, end) of the workspace behind the bitmaps: units, blocks and scanned totals, one after the other
+  const int64_t end = 4 * (int64_t)q * sz.n_units, blocks = (int64_t)q * P.n_blocks;
+  int64_t at = 0;
+  if (P.unit_at >= 0) {
+    CHECK(P.unit_at >= at && P.unit_at % 2 == 0);
+    at = P.unit_at + 2 * q * sz.n_units;
+  } else {
+    CHECK(sz.n_units == 1 && P.n_blocks == 1);  // a block's total stands for its unit's count
+  }
+  CHECK(P.block_at >= at && P.block_at % 4 == 0);
+  at = P.block_at + 4 * blocks;
+  CHECK((P.scanned_at >= 0) == (blocks > kDirectBlocks));
+  if (P.scanned_at >= 0) {
+    CHECK(P.scanned_at >= at && P.scanned_at % 4 == 0);
+    at = P.scanned_at + 4 * (blocks + 1);
+  }
+  CHECK(at <= end);
+  CHECK((int64_t)P.n_blocks * P.units_per_block >= sz.n_units && (int64_t)(P.n_blocks - 1) * P.units_per_block < sz.n_units);
+  CHECK(P.per >= 1 && P.per * P.units_per_block <= EMIT_UNITS);
+  CHECK((int64_t)P.emit_groups * P.per >= blocks && (int64_t)(P.emit_groups - 1) * P.per < blocks);
+  return true;
+}
+
+int main() {
+  for (int q = 1; q <= 4; ++q)
+    for (int n_out = 64; n_out <= 256; n_out += 64) {
+      for (int m = 1; m <= 700; m += 31)
+        for (int n = 1; n <= 1400; n += 63)
+          if (!check(m, n, q, n_out)) return 1;
+      for (int m : {8191, 32768, 32800, 65536, 500000})
+        for (int n : {1, 64, 65, 4096, 9216, 30000})
+          if (!check(m, n, q, n_out)) return 1;
+    }
+  return 0;
+}
+"""
+
+
+def test_patch_counts_lie_in_the_workspace(tmp_path):
+    """The emission of the patch lists runs as many workgroups in any order, and each writes offsets as it goes: the
+    counts that the others still read have to lie in the workspace, apart from each other and inside its stated size.
+    (With one unit per plane they used to lie in the offsets: a late workgroup read what an early one had written.)"""
+    run_program(tmp_path, ENCODE_PLAN, "xorenc_host.cpp")
