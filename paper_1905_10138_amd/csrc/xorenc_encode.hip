@@ -245,8 +245,9 @@ __global__ void exhaustive_reset_kernel(uint32_t *list_len) { *list_len = 0; }
 // input) exactly (2 * 2^14 * 256 + 2^15 < 2^24; all terms are integers) and its minimum is the answer: half a v_min3_u32
 // on the bit patterns per input and slice.  Rows of M
 // that are zero mismatch or match whatever the input is and stay out, so that at most half of the care bits can
-// be mismatched at the minimum and a key (mismatches + 1) << 24 | input fits 32 bits.  Tiles are visited in Gray code
-// order: one column of M flips the signs of A (4 XORs per 64 bits, shared by the four slice tiles).
+// be mismatched at the minimum over all inputs and its key (mismatches + 1) << 24 | input fits 32 bits; the minimum over
+// one item's inputs can mismatch all 256, but not win, and its key is held at 255 << 24.  Tiles are visited in Gray
+// code order: one column of M flips the signs of A (4 XORs per 64 bits, shared by the four slice tiles).
 //
 // Bound: VALU issue beside the matrix instructions.  Every slice of 16384 x 4096, n_out = 192, n_in = 20 used to be
 // searched, one slice per lane, at 2J AND, 2J XOR and 2J population counts per input: 219 ms for the call, 0.35 ms now
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhPa
       if (g == 0 && li < n_list) {
         const int32_t pair = (int32_t)v + (int32_t)(care_bits[t] << 14);  // mismatches << 15 | input inside the chunk
         const uint32_t x = (chunk << c) | (uint32_t)(pair & 0x7fff);
-        const uint32_t key = ((uint32_t)(pair >> 15) + 1u) << 24 | x;
+        const uint32_t key = (uint32_t)(min(pair >> 15, 254) + 1) << 24 | x;  // (a chunk's minimum may be up to 256)
         if (ALL)
           keys[2 * word[t]] = key;
         else

@@ -273,3 +273,30 @@ def test_encoder_with_one_unit_per_plane_and_patches_in_every_plane(q, exhaustiv
         e = torch.zeros_like(L.enc)
         xe.encode_static(m, n, n_in, q, M_rows, mask, bits, e, off, patch)
         assert torch.equal(off, L.patch_off) and torch.equal(patch, L.patch) and torch.equal(e, L.enc)
+
+
+@pytest.mark.parametrize("n_in,low", [(12, 10), (14, 11)])
+def test_fewest_patches_when_a_part_of_the_inputs_mismatches_everywhere(n_in, low):
+    """Rows of M that are zero in their low columns, slices of 256 kept bits: whole runs of consecutive inputs mismatch 255
+    or 256 bits.  No such run may win over an input with few mismatches.  Compared with the oracle's search."""
+    import torch
+    import paper_1905_10138_amd as xe
+    from oracle import encoder
+    m = n = n_out = 256
+    keep = np.ones((m, n), dtype=bool)
+    planes = np.ones((1, m, n), dtype=bool)
+    planes[0, np.arange(m), np.arange(m)] = False    # one input gives all ones: one mismatch, the input 0 255 of them
+    planes[0, 7] = True                              # a solution without mismatches
+    M = np.zeros((n_out, n_in), dtype=np.uint8)
+    M[:, low] = 1
+    M[::3, low + 1] = 1
+    alpha = np.ones((1, m), np.float32)
+    enc = encoder.encode(keep, planes, alpha, M, n, exhaustive=True)
+    dev = torch.device("cuda:0")
+    words = lambda a: torch.from_numpy(xe.pack_bits(a, n_out).view(np.int64))
+    M_rows = (M.astype(np.uint64) << np.arange(n_in, dtype=np.uint64)).sum(axis=1).astype(np.uint32)
+    L = xe.encode_exhaustive(m, n, n_in, 1, M_rows, words(keep).to(dev), words(planes[0])[None].to(dev),
+                             torch.from_numpy(alpha).to(dev), n_out=n_out)
+    w_c, _, n_patch, d_patch = xe.unpack(L.to_host())
+    ow, _, onp, odp, _ = paper_format_arrays(enc)
+    assert np.array_equal(w_c, ow) and np.array_equal(n_patch, onp) and np.array_equal(d_patch, odp)
