@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "xorenc_internal.h"
+#include "xorenc_split_plan.h"
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -42,9 +43,6 @@ constexpr int nib_variant_of(int n_in) {
 }
 constexpr int tables_of_variant(int v) { return v == kFourTablesTwoDwords ? 4 : v; }
 constexpr bool two_dwords_of_variant(int v) { return v == 3 || v == kFourTablesTwoDwords; }
-
-constexpr int kSplitTileFloats = 4096;  // largest output tile of a split launch (64 x 64)
-constexpr int kSplitMaxGroups = 256;    // workgroups of a split launch (one per CU)
 
 // field `e` (n_in bits at bit e*n_in) of the encrypted bit stream, seen as aligned dwords
 static __device__ inline uint32_t load_enc(const uint8_t *enc, int64_t e, int n_in) {

@@ -22,9 +22,6 @@
 
 namespace xorenc_spmm_detail {
 
-constexpr int kSmallMaxB = 8;                // batch rows 0..7 are accumulator elements 0..3 of both halves
-constexpr int kSmallXBytes = 96 * 1024;      // LDS set aside for X^T (rows padded by 16 bytes)
-
 template <int Q, int RB, int NW, int NIBV>
 __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const uint16_t *__restrict__ X, int64_t ldx,
                                                             int B, float *__restrict__ Y, int64_t ldy,
@@ -346,7 +343,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
   // n_splits > 1: the tile (ROWS x 8 floats) is one of n_splits partial sums; it is parked in the library's
   // scratch area and the workgroup that arrives last adds the parts in the order of their slice ranges
   float *const my_part =
-      n_splits > 1 ? L.split_part + ((int64_t)blockIdx.x * n_splits + blockIdx.z) * kSplitTileFloats : nullptr;
+      n_splits > 1 ? L.split_part + ((int64_t)blockIdx.x * n_splits + blockIdx.z) * (ROWS * kSmallMaxB) : nullptr;
   for (int idx = tid; idx < ROWS * kSmallMaxB; idx += NW * 64) {
     const int r = idx >> 3, b = idx & 7;  // kSmallMaxB = 8 outputs per row
     const int gr = row0 + r;
@@ -367,7 +364,6 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
     }
   }
   if (n_splits > 1) {
-    static_assert(ROWS * kSmallMaxB <= kSplitTileFloats, "the tile must fit its slot of the scratch area");
     __shared__ uint32_t last_arrival;
     // the parts were written with device-coherent stores; once they are acknowledged the ticket may be taken
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -375,40 +371,19 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
     if (tid == 0) last_arrival = __hip_atomic_fetch_add(L.split_ticket + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(n_splits - 1) ? 1u : 0u;
     __syncthreads();
     if (last_arrival) {
-      const float *parts = L.split_part + (int64_t)blockIdx.x * n_splits * kSplitTileFloats;
+      const float *parts = L.split_part + (int64_t)blockIdx.x * n_splits * (ROWS * kSmallMaxB);
       for (int idx = tid; idx < ROWS * kSmallMaxB; idx += NW * 64) {
         const int r = idx >> 3, b = idx & 7;
         const int gr = row0 + r;
         if (b < B && gr < l_m) {
           float v = split_load(parts + idx);
-          for (int z = 1; z < n_splits; ++z) v += split_load(parts + (int64_t)z * kSplitTileFloats + idx);
+          for (int z = 1; z < n_splits; ++z) v += split_load(parts + (int64_t)z * (ROWS * kSmallMaxB) + idx);
           Y[(int64_t)gr * ldy + b] = v;
         }
       }
       if (tid == 0) L.split_ticket[blockIdx.x] = 0u;  // ready for the next launch
     }
   }
-}
-
-// true when the small-batch kernel applies to this call (bf16 X, few columns, X^T of one
-// workgroup's reduction range fits the LDS set aside for it); fills the grid shape
-template <int NW>
-inline bool small_plan(const DevLayer &D, int B, int RB, int *ks_out, int *sps_out) {
-  if (B > kSmallMaxB) return false;
-  const int row_groups = (D.nrb + RB - 1) / RB;
-  int ks = 1;
-  const int max_ks = (D.spr + NW - 1) / NW;
-  if (row_groups < kSplitMaxGroups && D.split_part && D.split_ticket)
-    ks = max(1, min(max_ks, kSplitMaxGroups / row_groups));  // at most one workgroup per CU
-  int sps = (D.spr + ks - 1) / ks;
-  sps = (sps + NW - 1) / NW * NW;
-  // shrink the range until X^T fits
-  while ((int64_t)B * ((int64_t)min(sps, D.spr) * 128 + 16) > kSmallXBytes && sps > NW) sps -= NW;
-  if ((int64_t)B * ((int64_t)min(sps, D.spr) * 128 + 16) > kSmallXBytes) return false;
-  ks = (D.spr + sps - 1) / sps;
-  *ks_out = ks;
-  *sps_out = sps;
-  return true;
 }
 
 template <int Q, int RB, int NW>
@@ -447,7 +422,8 @@ bool dispatch_small_q(const DevLayer &D, const void *X, int32_t x_dtype, int64_t
   constexpr int RB = (Q <= 3) ? 2 : 1;
   constexpr int NW = (Q == 1) ? 16 : (Q == 2 ? 12 : 8);
   int ks = 1, sps = 0;
-  if (!small_plan<NW>(D, B, RB, &ks, &sps)) return false;
+  const bool scratch = D.split_part && D.split_ticket;
+  if (!small_split((D.nrb + RB - 1) / RB, 32 * RB, D.spr, B, NW, scratch, &ks, &sps)) return false;
   *rc = launch_small<Q, RB, NW>(D, X, ldx, B, Y, ldy, ks, sps, st);
   return true;
 }

@@ -500,3 +500,34 @@ def test_calls_on_many_streams_keep_their_own_staging_and_scratch():
         torch.cuda.synchronize()
         for (_, _, want), got in zip(jobs, out):
             assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("m,n,q,n_in,B", [
+    # 130 and 258 row tiles of 32 rows, 129 of 64; X^T of the whole reduction does not fit LDS
+    (4160, 12800, 4, 13, 4), (8256, 12800, 4, 29, 4), (8250, 12800, 1, 13, 4), (8256, 16500, 2, 11, 3)])
+def test_few_unaligned_columns_of_long_rows(m, n, q, n_in, B):
+    """The few-column kernel's parts where more workgroups run than the chip has compute units, and the calls that it leaves
+    to the general kernel because they do not fit its scratch area.  Against the decoded matrix in 64 bits, twice (the
+    tickets are as they were)."""
+    import torch
+    import paper_1905_10138_amd as xe
+    dev = torch.device("cuda:0")
+    sz = xe.get_sizes(m, n, n_in, q)
+    g = torch.Generator(device=dev)
+    g.manual_seed(m + n_in)
+    words = lambda *shape: torch.randint(-2**63, 2**63 - 1, shape, dtype=torch.int64, device=dev, generator=g)
+    rows = torch.arange(sz["m_pad"], device=dev).view(-1, 1, 32) < m       # no kept bits on padding rows (n is whole words)
+    assert n % 64 == 0 or n == 16500
+    mask = (words(sz["n_slots"]) & words(sz["n_slots"]) & words(sz["n_slots"])).view(-1, sz["spr"], 32) * rows
+    if n % 64:
+        mask[:, -1] &= (1 << n % 64) - 1
+    M_rows = np.random.default_rng(n_in).integers(1, 1 << n_in, size=64).astype(np.uint32)
+    alpha = torch.rand((q, m), device=dev, generator=g) + 0.5
+    L = xe.encode(m, n, n_in, q, M_rows, mask.reshape(-1).contiguous(), words(q, sz["n_slots"]), alpha)
+    X = torch.randn((n, B), device=dev, generator=g).to(torch.bfloat16)
+    W = xe.decode(L, xe.OUT_F32)
+    want = torch.cat([W[i:i + 1024].double() @ X.double() for i in range(0, m, 1024)])
+    first = xe.spmm(L, X)
+    # fp32 decode rounds the sum of the planes' scales once per plane: 6e-8 of each weight
+    assert float((first.double() - want).norm() / want.norm()) <= 4e-7
+    assert torch.equal(xe.spmm(L, X), first)

@@ -76,3 +76,43 @@ def test_patch_counts_lie_in_the_workspace(tmp_path):
     counts that the others still read have to lie in the workspace, apart from each other and inside its stated size.
     (With one unit per plane they used to lie in the offsets: a late workgroup read what an early one had written.)"""
     run_program(tmp_path, ENCODE_PLAN, "xorenc_host.cpp")
+
+
+SMALL_SPLIT = r"""
+#include <cstdio>
+#include "xorenc_split_plan.h"
+
+#define CHECK(c) do { if (!(c)) { std::printf("groups=%d rows=%d spr=%d B=%d waves=%d scratch=%d ks=%d sps=%d: %s\n", \
+                                              groups, rows, spr, B, waves, scratch, ks, sps, #c); return false; } } while (0)
+
+static bool check(int groups, int rows, int spr, int B, int waves, bool scratch) {
+  int ks = 0, sps = 0;
+  if (!small_split(groups, rows, spr, B, waves, scratch, &ks, &sps)) return true;  // another kernel's
+  CHECK(ks >= 1 && sps >= 1 && (int64_t)ks * sps >= spr && (int64_t)(ks - 1) * sps < spr);
+  CHECK((int64_t)B * ((int64_t)(sps < spr ? sps : spr) * 128 + 16) <= kSmallXBytes);
+  if (ks > 1) {
+    CHECK(scratch);
+    CHECK(groups <= kSplitMaxGroups);  // tickets
+    CHECK((int64_t)groups * ks * rows * kSmallMaxB <= (int64_t)kSplitMaxGroups * kSplitTileFloats);
+  }
+  return true;
+}
+
+int main() {
+  for (int waves : {8, 12, 16})
+    for (int rows : {32, 64})
+      for (int B = 1; B <= 9; ++B)
+        for (int groups : {1, 2, 7, 64, 127, 128, 129, 200, 255, 256, 257, 300, 1024, 30000})
+          for (int spr = 1; spr <= 3000; spr += spr < 400 ? 1 : 37)
+            for (int scratch = 0; scratch < 2; ++scratch)
+              if (!check(groups, rows, spr, B, waves, scratch)) return 1;
+  return 0;
+}
+"""
+
+
+def test_parts_of_the_few_column_kernel_fit_the_scratch_area(tmp_path):
+    """The cut that makes X^T of a range fit LDS may take more workgroups than the chip has compute units: parts and tickets
+    have to lie inside the scratch area all the same.  (They used to run over its end: 12800 x 16384, four columns with a
+    leading dimension of four, 400 workgroups in the room of 256.)"""
+    run_program(tmp_path, SMALL_SPLIT)
