@@ -277,9 +277,10 @@ XORENC_API int32_t xorenc_decode(const xorenc_layer *layer, int32_t out_kind, vo
  * call, two when the rows of X do not start on 16-byte boundaries (ldx not a multiple of 8 bf16 / 4 fp32 values, or
  * such a base address) and X has at least five columns: a first kernel then copies X into a 4 MiB staging area inside
  * the library with its rows padded to whole 16-byte pieces, and the product reads the copy; an X that needs more is
- * copied and multiplied in parts of its columns, two launches each (n <= 32768; larger n are read element by element)
- * (the fast kernels fetch X in 16-byte pieces).  fp32 X of larger layers (6 million weights of all planes, or 600
- * million products) is split into its three bf16 terms in the same area first, in parts where they do not fit.  For
+ * copied and multiplied in parts of its columns, two launches each (n <= 32768 bf16, 16384 fp32; larger n are read
+ * element by element) (the fast kernels fetch X in 16-byte pieces).  fp32 X of larger layers (6 million weights of all planes, or
+ * 600 million products) is split into its three bf16 terms in the same area first, in parts of at least 64 columns
+ * where they do not fit (n up to about 10900; longer rows with more columns than fit are split on their way into LDS).  For
  * small layers the launch splits the reduction dimension over several workgroups per output tile; their partial tiles
  * meet in a scratch area, and the workgroup that finishes last adds them in a fixed order of their slice ranges.
  * Staging and scratch areas live in device memory that the library keeps on every GPU (about 128 MiB, sixteen slots

@@ -185,24 +185,27 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
   }
   // rows of X that do not start on 16-byte boundaries: a padded copy, unless the few-column kernel (which reads X
   // element by element anyway) takes the call.  A copy that does not fit the staging area is made and multiplied a part
-  // of the columns at a time (parts of nearly equal width, at least 64 columns of the area each: n <= 32768).
+  // of the columns at a time: at least 64 columns have to fit (n <= 32768 bf16, 16384 fp32), and the parts differ by one
+  // piece at most, so that none is so narrow (25 columns at least) that it would run, and round, as a call with few
+  // columns does.
   if (!aligned && B >= kStageMinB) {
     const int64_t fit = (int64_t)(kStageBytes / ((size_t)layer->n * 16)) * per / 64 * 64;  // columns, in whole 64s
     const bool whole = (int64_t)layer->n * ((B + per - 1) / per) * 16 <= (int64_t)kStageBytes;
     xorenc_spmm_detail::F4Plan unused;
     if ((whole || fit > 0) && !xorenc_spmm_detail::f4_applies(D, x_dtype, B, 0, &unused)) {
-      const int64_t parts = whole ? 1 : (B + fit - 1) / fit;
-      const int part = whole ? B : (int)((B + parts - 1) / parts + 7) / 8 * 8;
+      const int pieces_per_row = (B + per - 1) / per;
+      const int parts = whole ? 1 : (int)((B + fit - 1) / fit);
       unsigned char *stage = slot + kSplitPartBytes + kSplitTicketBytes;
-      for (int c0 = 0; c0 < B; c0 += part) {
-        const int cols = min(part, B - c0);
-        const int cpr = (cols + per - 1) / per;  // 16-byte pieces per row
+      for (int i = 0, c0 = 0; i < parts; ++i) {
+        const int cpr = pieces_per_row / parts + (i < pieces_per_row % parts ? 1 : 0);  // 16-byte pieces per row
+        const int cols = min(cpr * per, B - c0);
         const int64_t pieces = (int64_t)layer->n * cpr;
         hipLaunchKernelGGL(stage_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
                            static_cast<const unsigned char *>(X) + (int64_t)c0 * esz, ldx, (int)layer->n, cols, esz, cpr,
                            stage);
         const int32_t rp = product(stage, (int64_t)cpr * per, cols, Y + c0, 1, x_dtype);
         if (rp != XORENC_OK) return rp;
+        c0 += cols;
       }
       return XORENC_OK;
     }

@@ -531,3 +531,13 @@ def test_few_unaligned_columns_of_long_rows(m, n, q, n_in, B):
     # fp32 decode rounds the sum of the planes' scales once per plane: 6e-8 of each weight
     assert float((first.double() - want).norm() / want.norm()) <= 4e-7
     assert torch.equal(xe.spmm(L, X), first)
+
+
+@pytest.mark.parametrize("name,n,B", [("large_q1", 16000, 1921), ("large_q1", 15000, 2050), ("large_q2", 12000, 2049),
+                                      ("large_q1", 20000, 449)])
+def test_last_columns_of_an_X_in_parts_are_as_exact_as_the_others(name, n, B):
+    """One or two columns left over after whole parts would run as a call with few columns does, whose X is two 8-bit terms
+    (2e-6).  Every column keeps the bound of a call with many."""
+    got, want = _run(name, 40, n, B, "bf16")
+    err = np.linalg.norm(got - want, axis=0) / np.linalg.norm(want, axis=0)
+    assert err.max() <= 4e-7
