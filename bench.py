@@ -185,10 +185,11 @@ def spmm_runner(xe, torch, layer, x_dev, B, replica_bytes):
     ys = [torch.empty((layer.m, B), dtype=torch.float32, device=x_dev.device) for _ in range(R)]
     structs = [l.c_struct() for l in layers]
     xd = 0 if x_dev.dtype == torch.float32 else 1
-    calls = [(ctypes.byref(st), ctypes.c_void_p(x.data_ptr()), xd, x.stride(0), B, ctypes.c_void_p(y.data_ptr()), y.stride(0))
-             for st, x, y in zip(structs, xs, ys)]
-    runner = GraphRunner(torch, lib.xorenc_spmm, calls, "xorenc_spmm")
-    runner.keep = (layers, xs, ys, structs)  # the buffers live as long as the runner
+    ws = torch.empty(xe.SPMM_WORKSPACE_BYTES, dtype=torch.uint8, device=x_dev.device)  # all calls run on one stream
+    calls = [(ctypes.byref(st), ctypes.c_void_p(x.data_ptr()), xd, x.stride(0), B, ctypes.c_void_p(y.data_ptr()), y.stride(0),
+              ctypes.c_void_p(ws.data_ptr()), ws.numel()) for st, x, y in zip(structs, xs, ys)]
+    runner = GraphRunner(torch, lib.xorenc_spmm_ws, calls, "xorenc_spmm_ws")
+    runner.keep = (layers, xs, ys, structs, ws)  # the buffers live as long as the runner
     runner.ys, runner.comp_bytes, runner.step_bytes = ys, comp, step_bytes
     return runner
 

@@ -283,14 +283,28 @@ XORENC_API int32_t xorenc_decode(const xorenc_layer *layer, int32_t out_kind, vo
  * where they do not fit (n up to about 10900; longer rows with more columns than fit are split on their way into LDS).  For
  * small layers the launch splits the reduction dimension over several workgroups per output tile; their partial tiles
  * meet in a scratch area, and the workgroup that finishes last adds them in a fixed order of their slice ranges.
- * Staging and scratch areas live in device memory that the library keeps on every GPU (about 128 MiB, sixteen slots
- * taken in turn by successive calls).  At most sixteen calls that use a slot may therefore overlap on one GPU (on
- * different streams; calls on one stream never overlap); a seventeenth could read another call's partial sums or copy
- * of X.
+ * Staging and scratch areas live in device memory that the library keeps on every GPU (about 52 MiB).  They belong to a
+ * stream, or to a stream's part of a captured graph, from its first such call on and for good, so that calls and graphs
+ * may overlap in any way; a stream whose calls have not all run must not be destroyed (its handle may come back).  There
+ * is room for the first four such streams and captures.  A call on another one runs on kernels that need no such memory,
+ * which are slower, several times for many columns of unaligned X: programs with more streams, or that capture more than
+ * a few graphs, pass a workspace (xorenc_spmm_ws).
  * Nothing is allocated by the call.
  */
 XORENC_API int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t x_dtype, int64_t ldx, int32_t B, float *Y,
                     int64_t ldy, void *hip_stream);
+
+/*
+ * The same with a workspace of the caller's for the copies of X and the partial tiles: DEV, XORENC_SPMM_WORKSPACE_BYTES,
+ * 16-byte aligned, contents undefined before and after.  Calls whose kernels may run at the same time (a graph's: when it is
+ * replayed) need workspaces of their own; calls on one stream may share one.  workspace = NULL: the library's memory as
+ * above, and XORENC_ELIMIT, with nothing enqueued, where the call may need some and the stream has none or is being
+ * captured.  (What is left in the library's memory then are counters, 1 KB for each of the first 4096 streams and
+ * captures; the calls of later ones do not split the reduction.)
+ */
+#define XORENC_SPMM_WORKSPACE_BYTES (12u << 20)
+XORENC_API int32_t xorenc_spmm_ws(const xorenc_layer *layer, const void *X, int32_t x_dtype, int64_t ldx, int32_t B, float *Y,
+                                  int64_t ldy, void *workspace, int64_t workspace_bytes, void *hip_stream);
 
 #ifdef __cplusplus
 }

@@ -5,6 +5,7 @@ from .binding import (
     OUT_BF16,
     OUT_F32,
     OUT_PLANES,
+    SPMM_WORKSPACE_BYTES,
     STATIC_SCRATCH_BYTES,
     PackedLayer,
     XorencError,
@@ -28,7 +29,7 @@ from .binding import (
 )
 
 __all__ = [
-    "OUT_BF16", "OUT_F32", "OUT_PLANES", "PackedLayer", "XorencError", "check_packed", "decode", "encode", "encode_exhaustive", "encode_static", "STATIC_SCRATCH_BYTES",
+    "OUT_BF16", "OUT_F32", "OUT_PLANES", "PackedLayer", "XorencError", "check_packed", "decode", "encode", "encode_exhaustive", "encode_static", "STATIC_SCRATCH_BYTES", "SPMM_WORKSPACE_BYTES",
     "pack_bits",
     "paper_export", "paper_import", "paper_sizes", "get_sizes", "library_path", "load_library", "pack", "spmm", "strerror", "unpack", "version",
 ]

@@ -89,6 +89,8 @@ def load_library():
     lib.xorenc_decode.argtypes = [ctypes.POINTER(_Layer), i32, vp, i64, vp]
     lib.xorenc_spmm.restype = i32
     lib.xorenc_spmm.argtypes = [ctypes.POINTER(_Layer), vp, i32, i64, i32, vp, i64, vp]
+    lib.xorenc_spmm_ws.restype = i32
+    lib.xorenc_spmm_ws.argtypes = [ctypes.POINTER(_Layer), vp, i32, i64, i32, vp, i64, vp, i64, vp]
     _LIB = lib
     return lib
 
@@ -361,8 +363,13 @@ def decode(layer: PackedLayer, out_kind: int = OUT_PLANES, out=None):
     return out
 
 
+SPMM_WORKSPACE_BYTES = 12 << 20
+_ELIMIT = -6
+
+
 def spmm(layer: PackedLayer, X, Y=None):
-    """xorenc_spmm on the current stream: Y = W X with X (n, B) float32 or bfloat16, row-major."""
+    """xorenc_spmm on the current stream: Y = W X with X (n, B) float32 or bfloat16, row-major.  Calls on any streams and
+    replays of any graphs (captured with torch.cuda.graph) may overlap; graphs that share a memory pool may not."""
     import torch
     if not layer.on_device:
         raise ValueError("spmm needs a layer whose buffers are on the GPU")
@@ -378,6 +385,13 @@ def spmm(layer: PackedLayer, X, Y=None):
     if Y is None:
         Y = torch.empty((layer.m, B), dtype=torch.float32, device=X.device)
     st = layer.c_struct()
-    _check(load_library().xorenc_spmm(ctypes.byref(st), ctypes.c_void_p(X.data_ptr()), xd, X.stride(0), B,
-                                      ctypes.c_void_p(Y.data_ptr()), Y.stride(0), _stream_ptr()), "xorenc_spmm")
+    fn, stream = load_library().xorenc_spmm_ws, _stream_ptr()
+    xp, yp = ctypes.c_void_p(X.data_ptr()), ctypes.c_void_p(Y.data_ptr())
+    rc = fn(ctypes.byref(st), xp, xd, X.stride(0), B, yp, Y.stride(0), None, 0, stream)
+    if rc == _ELIMIT:
+        # the library has no memory for this stream, or the call is captured: torch's, in stream order or from the
+        # graph's pool, which keeps it as long as the graph
+        ws = torch.empty(SPMM_WORKSPACE_BYTES, dtype=torch.uint8, device=X.device)
+        rc = fn(ctypes.byref(st), xp, xd, X.stride(0), B, yp, Y.stride(0), ctypes.c_void_p(ws.data_ptr()), ws.numel(), stream)
+    _check(rc, "xorenc_spmm")
     return Y

@@ -24,7 +24,7 @@ struct DevLayer {
   int64_t n_slots, n_eslots;
   // Launches that split the reduction dimension over several workgroups per output tile: partial tiles
   // (kSplitTileFloats floats per workgroup, at most kSplitMaxGroups workgroups) and one arrival counter per
-  // output tile, zero between launches.  Filled by xorenc_spmm from the library's own scratch area.
+  // output tile, zero between launches; null: no launch splits the reduction.
   float *split_part;
   uint32_t *split_ticket;
   // column j of M restricted to word w of a slice (rows 64 w .. 64 w + 63): lower and upper 32 rows

@@ -1,33 +1,28 @@
 // xorenc_spmm entry point: argument validation and dispatch to the per-Q kernel instantiations.
-#include <atomic>
 #include <mutex>
 
+#include "xorenc_scratch.h"
 #include "xorenc_spmm_f4.h"
 
-// Scratch area of launches that split the reduction dimension over several workgroups per output tile
-// (small layers that would otherwise leave most of the chip idle): kSplitSlots slots, each with room for
-// the partial tiles of one launch and one arrival counter per output tile.  Counters are zero between
-// launches (the array starts zeroed and the last workgroup of a tile resets its counter).  Successive calls
-// take the slots in turn, so up to kSplitSlots split launches may be in flight on one GPU (on different
-// streams) without touching each other's parts.  In host code the array's name is only a handle for
-// hipGetSymbolAddress; kernels get the looked-up address.
+// Memory that products need beside their arguments, on every GPU from the time the library is loaded: sets of tickets and
+// slots (xorenc_scratch.h says whose they are).  A slot holds the partial tiles of one launch that splits the reduction
+// dimension over several workgroups per output tile (small layers that would otherwise leave most of the chip idle), and
+// a staging area for X.  Tickets are zero between launches: the array starts zeroed and the last workgroup of a tile
+// resets its counter.  In host code an array's name is only a handle for hipGetSymbolAddress; kernels get the
+// looked-up address.
 //
-// Each slot also holds a staging area for X: the fast kernels fetch X in 16-byte pieces and need rows that start
-// on 16-byte boundaries.  When the caller's X does not (a leading dimension that is not a multiple of eight bf16 or
-// four fp32 values, or an odd base address) and it fits, a small kernel copies it into the staging area with padded
-// rows first (one more launch, about 2 us) and the product runs on the copy (B = 33: 16 against 43 us, B = 65: 25
-// against 170 us on a 16384 x 4096 layer); larger X are copied and multiplied in parts
-// (4096 x 9216, two planes, B = 1023: 2700 us on the element-wise kernels, 278 us).
+// Staging: the fast kernels fetch X in 16-byte pieces and need rows that start on 16-byte boundaries.  When the caller's
+// X does not (a leading dimension that is not a multiple of eight bf16 or four fp32 values, or an odd base address) and
+// it fits, a small kernel copies it into the staging area with padded rows first (one more launch, about 2 us) and the
+// product runs on the copy (B = 33: 16 against 43 us, B = 65: 25 against 170 us on a 16384 x 4096 layer); larger X are
+// copied and multiplied in parts (4096 x 9216, two planes, B = 1023: 2700 us on the element-wise kernels, 278 us).
 namespace {
-constexpr int kSplitSlots = 16;  // (128 MiB: most calls on fp32 or unaligned X use a slot's staging area)
-constexpr size_t kSplitPartBytes = (size_t)kSplitMaxGroups * kSplitTileFloats * sizeof(float);  // 4 MiB
-constexpr size_t kSplitTicketBytes = (size_t)kSplitMaxGroups * sizeof(uint32_t);
-constexpr size_t kStageBytes = (size_t)4 << 20;  // 4 MiB: 8192 rows of 256 bf16 columns
 constexpr int64_t kXSplitMinWeights = 6000000;   // fp32 X: weights (of all planes), or weights times columns, from which
 constexpr int64_t kXSplitMinWork = 600000000;    // it is split by a kernel of its own
 constexpr int kStageMinB = 5;                    // (fewer columns are faster on the kernels that read X element by element)
-constexpr size_t kSplitSlotBytes = kSplitPartBytes + kSplitTicketBytes + kStageBytes;
-static_assert(kSplitSlotBytes % 256 == 0, "slots keep the array's alignment");
+constexpr int kSplitMinWords = 5;  // no kernel splits the reduction of rows with fewer words (the narrowest has four waves)
+static_assert(kTicketBytes % 256 == 0 && kPartBytes % 256 == 0 && kSlotBytes % 256 == 0, "all keep the arrays' alignment");
+static_assert(kSlotBytes == XORENC_SPMM_WORKSPACE_BYTES, "a workspace holds what a slot holds");
 
 // dst[k][0 .. cpr*16) = row k of X (B elements of esz bytes, leading dimension ldx), zero-filled to whole 16-byte
 // pieces; one thread per piece
@@ -96,14 +91,23 @@ __global__ __launch_bounds__(256) void split_x_kernel(const float *__restrict__ 
     *reinterpret_cast<uint4 *>(dst + (t * term + piece) * 16) = make_uint4(w[t][0], w[t][1], w[t][2], w[t][3]);
 }
 }  // namespace
-static __device__ __align__(256) unsigned char split_scratch[kSplitSlots * kSplitSlotBytes];
+static __device__ __align__(256) unsigned char scratch_area[kScratchOwners * kTicketBytes + kScratchSlots * kSlotBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
 
-int32_t split_scratch_address(unsigned char **out) {
+// Tickets and, unless the caller brings memory, a slot for a call on `st` of the current device; null where none are left.
+struct Scratch {
+  uint32_t *tickets;
+  unsigned char *slot;
+  uint32_t staged;
+};
+
+int32_t take_scratch(hipStream_t st, bool captured, uint64_t capture, bool want_slot, int stagings, Scratch *out) {
   static std::mutex lock;
   static unsigned char *address[kMaxDevices] = {};
+  static ScratchOwners owners[kMaxDevices];
+  static thread_local char this_thread;
   int dev = -1;
   const hipError_t ed = hipGetDevice(&dev);
   if (ed != hipSuccess) return xorenc_internal_hip_status((int32_t)ed);
@@ -111,18 +115,22 @@ int32_t split_scratch_address(unsigned char **out) {
   std::lock_guard<std::mutex> guard(lock);
   if (!address[dev]) {
     void *p = nullptr;
-    const hipError_t es = hipGetSymbolAddress(&p, HIP_SYMBOL(split_scratch));
+    const hipError_t es = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch_area));
     if (es != hipSuccess) return xorenc_internal_hip_status((int32_t)es);
     if (!p) return XORENC_EHIP;
     address[dev] = static_cast<unsigned char *>(p);
   }
-  *out = address[dev];
+  const ScratchOwner owner{st, st == hipStreamPerThread ? &this_thread : nullptr, captured ? capture : 0};
+  const ScratchShare share = owners[dev].share(owner, want_slot, stagings);
+  out->tickets = share.tickets < 0 ? nullptr : reinterpret_cast<uint32_t *>(address[dev] + share.tickets * kTicketBytes);
+  out->slot = share.slot < 0 ? nullptr : address[dev] + kScratchOwners * kTicketBytes + share.slot * kSlotBytes;
+  out->staged = share.staged;
   return XORENC_OK;
 }
-}  // namespace
 
-extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t x_dtype, int64_t ldx, int32_t B,
-                               float *Y, int64_t ldy, void *hip_stream) {
+// Without a workspace and a slot the call runs on the kernels that need neither, or is refused (limit_is_error).
+int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, int64_t ldx, int32_t B, float *Y, int64_t ldy,
+                    unsigned char *workspace, bool limit_is_error, void *hip_stream) {
   DevLayer D;
   const int32_t rc = xorenc_fill_dev_layer(layer, &D);
   if (rc != XORENC_OK) return rc;
@@ -140,17 +148,52 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
   // reaches output columns that are never stored)
   const bool aligned = (ldx % per == 0) && (((uintptr_t)X & 15) == 0);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  xorenc_internal_begin_call();
-  unsigned char *slot = nullptr;
-  {
-    static std::atomic<uint32_t> next_slot{0};
-    unsigned char *area = nullptr;
-    const int32_t rs = split_scratch_address(&area);
-    if (rs != XORENC_OK) return rs;
-    slot = area + (size_t)(next_slot.fetch_add(1u, std::memory_order_relaxed) % kSplitSlots) * kSplitSlotBytes;
-    D.split_part = reinterpret_cast<float *>(slot);
-    D.split_ticket = reinterpret_cast<uint32_t *>(slot + kSplitPartBytes);
+  // fp32 X: split into three bf16 matrices in the staging area, as many columns at a time as fit (in whole 64s where
+  // there are more).  The product then runs on the direct-to-LDS kernels, which convert nothing; the launch and the pass
+  // over X cost 2 to 3 us, so small layers keep the kernels that split X on its way into LDS (us, B = 1 / 8 / 64 / 200:
+  // 1024 x 1024 9.8 8.3 8.5 12.6, here 9.4 9.3 9.8 12.2; 2048 x 2048 11.2 9.9 10.9 29.2, here 9.9 9.9 12.0 20.4;
+  // 4096 x 4096 17.6 15.2 22.6 83.7, here 12.1 12.1 16.9 47.6; 4096 x 9216 with two planes 34.6 29.3 51.5 465, here
+  // 18.8 18.8 32.0 120).
+  int split_parts = 0, split_cols = 0;
+  const int64_t weights = (int64_t)layer->m * layer->n * layer->q;
+  if (x_dtype == XORENC_X_F32 && (weights >= kXSplitMinWeights || weights * B >= kXSplitMinWork)) {
+    const int64_t fit = (int64_t)(kStageBytes / ((size_t)D.spr * 64 * 48)) * 8;  // columns that fit
+    if (fit >= min(B, 64)) {
+      split_cols = fit >= B ? B : (int)(fit / 64 * 64);
+      split_parts = (B + split_cols - 1) / split_cols;
+    }
   }
+  // rows of X that do not start on 16-byte boundaries: a padded copy, unless the few-column kernel (which reads X
+  // element by element anyway) takes the call.  A copy that does not fit the staging area is made and multiplied a part
+  // of the columns at a time: at least 64 columns have to fit (n <= 32768 bf16, 16384 fp32), and the parts differ by one
+  // piece at most, so that none is so narrow (25 columns at least) that it would run, and round, as a call with few
+  // columns does.
+  int copy_parts = 0;
+  const int pieces_per_row = (int)(((int64_t)B + per - 1) / per);  // 16-byte pieces
+  if (!split_parts && !aligned && B >= kStageMinB) {
+    const int64_t fit = (int64_t)(kStageBytes / ((size_t)layer->n * 16)) * per / 64 * 64;  // columns, in whole 64s
+    const bool whole = (int64_t)layer->n * pieces_per_row * 16 <= (int64_t)kStageBytes;
+    xorenc_spmm_detail::F4Plan unused;
+    if ((whole || fit > 0) && !xorenc_spmm_detail::f4_applies(D, x_dtype, B, 0, &unused))
+      copy_parts = whole ? 1 : (int)((B + fit - 1) / fit);
+  }
+  Scratch scratch{};
+  if (split_parts || copy_parts || D.spr >= kSplitMinWords) {
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    unsigned long long capture = 0;
+    // (an error here, such as a capture elsewhere that bars the default stream, comes back from the launch)
+    if (hipStreamGetCaptureInfo(st, &capturing, &capture) != hipSuccess) capturing = hipStreamCaptureStatusNone;
+    const bool captured = capturing != hipStreamCaptureStatusNone;
+    if (captured && !workspace && limit_is_error) return XORENC_ELIMIT;
+    const int32_t rs = take_scratch(st, captured, capture, !workspace, split_parts + copy_parts, &scratch);
+    if (rs != XORENC_OK) return rs;
+    if (workspace) scratch.slot = workspace;
+    if (!scratch.slot && limit_is_error) return XORENC_ELIMIT;
+  }
+  xorenc_internal_begin_call();
+  D.split_part = scratch.tickets ? reinterpret_cast<float *>(scratch.slot) : nullptr;
+  D.split_ticket = scratch.tickets;
+  auto stage = [&](int i) { return scratch.slot + kPartBytes + (scratch.staged + i) % kStageAreas * kStageBytes; };
   auto product = [&](const void *Xp, int64_t ld, int32_t cols, float *Yp, int fast, int32_t x_dtype) -> int32_t {
     switch (layer->q) {
       case 1: return xorenc_spmm_dispatch_q1(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
@@ -159,56 +202,40 @@ extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t
       default: return xorenc_spmm_dispatch_q4(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
     }
   };
-  // fp32 X: split into three bf16 matrices in the staging area, as many columns at a time as fit (in whole 64s where
-  // there are more).  The product then runs on the direct-to-LDS kernels, which convert nothing; the launch and the pass
-  // over X cost 2 to 3 us, so small layers keep the kernels that split X on its way into LDS (us, B = 1 / 8 / 64 / 200:
-  // 1024 x 1024 9.8 8.3 8.5 12.6, here 9.4 9.3 9.8 12.2; 2048 x 2048 11.2 9.9 10.9 29.2, here 9.9 9.9 12.0 20.4;
-  // 4096 x 4096 17.6 15.2 22.6 83.7, here 12.1 12.1 16.9 47.6; 4096 x 9216 with two planes 34.6 29.3 51.5 465, here
-  // 18.8 18.8 32.0 120).
-  const int64_t weights = (int64_t)layer->m * layer->n * layer->q;
-  if (x_dtype == XORENC_X_F32 && (weights >= kXSplitMinWeights || weights * B >= kXSplitMinWork)) {
-    const int rows = D.spr * 64;
-    int64_t part = (int64_t)(kStageBytes / ((size_t)rows * 48)) * 8;  // columns that fit
-    if (part >= min(B, 64)) {
-      part = part >= B ? B : part / 64 * 64;
-      unsigned char *stage = slot + kSplitPartBytes + kSplitTicketBytes;
-      for (int c0 = 0; c0 < B; c0 += (int)part) {
-        const int cols = min((int)part, B - c0), cpr = (cols + 7) / 8;
-        const int64_t pieces = (int64_t)rows * cpr;
-        hipLaunchKernelGGL(split_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
-                           static_cast<const float *>(X) + c0, ldx, (int)layer->n, rows, cols, cpr, stage);
-        const int32_t rp = product(stage, (int64_t)cpr * 8, cols, Y + c0, 1, xorenc_spmm_detail::kXSplit);
-        if (rp != XORENC_OK) return rp;
-      }
-      return XORENC_OK;
+  if (scratch.slot) {
+    for (int i = 0, c0 = 0; i < split_parts; ++i, c0 += split_cols) {
+      const int rows = D.spr * 64, cols = min(split_cols, B - c0), cpr = (cols + 7) / 8;
+      const int64_t pieces = (int64_t)rows * cpr;
+      hipLaunchKernelGGL(split_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
+                         static_cast<const float *>(X) + c0, ldx, (int)layer->n, rows, cols, cpr, stage(i));
+      const int32_t rp = product(stage(i), (int64_t)cpr * 8, cols, Y + c0, 1, xorenc_spmm_detail::kXSplit);
+      if (rp != XORENC_OK) return rp;
     }
-  }
-  // rows of X that do not start on 16-byte boundaries: a padded copy, unless the few-column kernel (which reads X
-  // element by element anyway) takes the call.  A copy that does not fit the staging area is made and multiplied a part
-  // of the columns at a time: at least 64 columns have to fit (n <= 32768 bf16, 16384 fp32), and the parts differ by one
-  // piece at most, so that none is so narrow (25 columns at least) that it would run, and round, as a call with few
-  // columns does.
-  if (!aligned && B >= kStageMinB) {
-    const int64_t fit = (int64_t)(kStageBytes / ((size_t)layer->n * 16)) * per / 64 * 64;  // columns, in whole 64s
-    const bool whole = (int64_t)layer->n * ((B + per - 1) / per) * 16 <= (int64_t)kStageBytes;
-    xorenc_spmm_detail::F4Plan unused;
-    if ((whole || fit > 0) && !xorenc_spmm_detail::f4_applies(D, x_dtype, B, 0, &unused)) {
-      const int pieces_per_row = (B + per - 1) / per;
-      const int parts = whole ? 1 : (int)((B + fit - 1) / fit);
-      unsigned char *stage = slot + kSplitPartBytes + kSplitTicketBytes;
-      for (int i = 0, c0 = 0; i < parts; ++i) {
-        const int cpr = pieces_per_row / parts + (i < pieces_per_row % parts ? 1 : 0);  // 16-byte pieces per row
-        const int cols = min(cpr * per, B - c0);
-        const int64_t pieces = (int64_t)layer->n * cpr;
-        hipLaunchKernelGGL(stage_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
-                           static_cast<const unsigned char *>(X) + (int64_t)c0 * esz, ldx, (int)layer->n, cols, esz, cpr,
-                           stage);
-        const int32_t rp = product(stage, (int64_t)cpr * per, cols, Y + c0, 1, x_dtype);
-        if (rp != XORENC_OK) return rp;
-        c0 += cols;
-      }
-      return XORENC_OK;
+    for (int i = 0, c0 = 0; i < copy_parts; ++i) {
+      const int cpr = pieces_per_row / copy_parts + (i < pieces_per_row % copy_parts ? 1 : 0);
+      const int cols = min(cpr * per, B - c0);
+      const int64_t pieces = (int64_t)layer->n * cpr;
+      hipLaunchKernelGGL(stage_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
+                         static_cast<const unsigned char *>(X) + (int64_t)c0 * esz, ldx, (int)layer->n, cols, esz, cpr,
+                         stage(i));
+      const int32_t rp = product(stage(i), (int64_t)cpr * per, cols, Y + c0, 1, x_dtype);
+      if (rp != XORENC_OK) return rp;
+      c0 += cols;
     }
+    if (split_parts || copy_parts) return XORENC_OK;
   }
   return product(X, ldx, B, Y, aligned ? 1 : 0, x_dtype);
+}
+}  // namespace
+
+extern "C" int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t x_dtype, int64_t ldx, int32_t B,
+                               float *Y, int64_t ldy, void *hip_stream) {
+  return spmm_common(layer, X, x_dtype, ldx, B, Y, ldy, nullptr, false, hip_stream);
+}
+
+extern "C" int32_t xorenc_spmm_ws(const xorenc_layer *layer, const void *X, int32_t x_dtype, int64_t ldx, int32_t B,
+                                  float *Y, int64_t ldy, void *workspace, int64_t workspace_bytes, void *hip_stream) {
+  if (workspace && workspace_bytes < (int64_t)XORENC_SPMM_WORKSPACE_BYTES) return XORENC_EINVAL;
+  if ((uintptr_t)workspace & 15) return XORENC_EALIGN;
+  return spmm_common(layer, X, x_dtype, ldx, B, Y, ldy, static_cast<unsigned char *>(workspace), true, hip_stream);
 }

@@ -541,3 +541,151 @@ def test_last_columns_of_an_X_in_parts_are_as_exact_as_the_others(name, n, B):
     got, want = _run(name, 40, n, B, "bf16")
     err = np.linalg.norm(got - want, axis=0) / np.linalg.norm(want, axis=0)
     assert err.max() <= 4e-7
+
+
+def _scratch_layers(dev):
+    """Layers whose products use tickets, partial tiles and staged X: (layer, X) with a split reduction, X copied, fp32 X
+    split in one part and in several."""
+    import torch
+    _, enc = encoded_workload("large_q1", 4100, 1500)
+    _, small = encoded_workload("fc6", 97, 640)
+    L, Ls = pack_encoded(enc).to(dev), pack_encoded(small).to(dev)
+    g = torch.Generator(device=dev)
+    g.manual_seed(11)
+    x = lambda layer, B: torch.randn((layer.n, B), device=dev, generator=g)
+    bf = lambda t: t.to(torch.bfloat16)
+    return [(L, x(L, 700)), (Ls, bf(x(Ls, 8))), (L, bf(x(L, 33))), (Ls, bf(x(Ls, 5))), (L, x(L, 64)), (Ls, bf(x(Ls, 40)))]
+
+
+def test_a_long_call_beside_many_short_ones_on_another_stream():
+    """One stream holds a call in several parts while another one issues many: only two calls ever overlap."""
+    import torch
+    import paper_1905_10138_amd as xe
+    dev = torch.device("cuda:0")
+    jobs = _scratch_layers(dev)
+    want = [xe.spmm(L, x).clone() for L, x in jobs]
+    long_, short = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(5):
+        with torch.cuda.stream(long_):
+            a = [xe.spmm(*jobs[0]) for _ in range(4)]
+        with torch.cuda.stream(short):
+            b = [(i, xe.spmm(*jobs[i])) for _ in range(10) for i in (4, 2, 1, 3, 5)]
+        torch.cuda.synchronize()
+        assert all(torch.equal(y, want[0]) for y in a)
+        for i, y in b:
+            assert torch.equal(y, want[i]), i
+
+
+def test_graphs_replayed_beside_each_other_and_beside_calls():
+    """Three graphs captured on one stream, of more calls than the library has slots, replayed on streams of their own while
+    a fourth stream calls directly; each replay against the results of calls alone, bit for bit."""
+    import torch
+    import paper_1905_10138_amd as xe
+    dev = torch.device("cuda:0")
+    jobs = _scratch_layers(dev)
+    want = [xe.spmm(L, x).clone() for L, x in jobs]
+    capture, graphs = torch.cuda.Stream(), []
+    for k in range(3):
+        order = [(i + k) % len(jobs) for i in range(2 * len(jobs))]
+        ys = [torch.empty_like(want[i]) for i in order]
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=capture):
+            for i, y in zip(order, ys):
+                xe.spmm(*jobs[i], Y=y)
+        graphs.append((graph, order, ys))
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    for _ in range(6):
+        for _, _, ys in graphs:
+            for y in ys:
+                y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for (graph, _, _), st in zip(graphs, streams):
+            with torch.cuda.stream(st):
+                graph.replay()
+        with torch.cuda.stream(streams[3]):
+            direct = [xe.spmm(L, x) for L, x in jobs]
+        torch.cuda.synchronize()
+        for _, order, ys in graphs:
+            for i, y in zip(order, ys):
+                assert torch.equal(y, want[i]), i
+        for y, w in zip(direct, want):
+            assert torch.equal(y, w)
+
+
+def test_captures_are_told_apart():
+    """The library keeps what two captures on one stream use apart by the number HIP gives a capture."""
+    import ctypes
+    import torch
+    torch.zeros(1, device="cuda:0")
+    with open("/proc/self/maps") as f:               # the copy of the runtime that is in use
+        path = next(line.split()[-1] for line in f if "libamdhip64.so" in line)
+    hip = ctypes.CDLL(path)
+    hip.hipStreamGetCaptureInfo.argtypes = [ctypes.c_void_p, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_ulonglong)]
+    seen, stream = [], torch.cuda.Stream()
+    x = torch.zeros(16, device="cuda:0")
+    for _ in range(4):
+        with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=stream):
+            status, number = ctypes.c_int(-1), ctypes.c_ulonglong(0)
+            assert hip.hipStreamGetCaptureInfo(torch.cuda.current_stream().cuda_stream, ctypes.byref(status), ctypes.byref(number)) == 0
+            x.add_(1.0)
+        assert status.value == 1 and number.value != 0
+        seen.append(number.value)
+    assert len(set(seen)) == len(seen)
+
+
+def test_a_call_without_memory_for_its_stream_and_with_a_workspace():
+    """The C entry points: without a workspace a captured call, or one on a stream that finds all slots taken, is refused
+    by xorenc_spmm_ws with nothing enqueued and runs on other kernels in xorenc_spmm; with a workspace it is the same call
+    as any other, bit for bit."""
+    import ctypes
+    import torch
+    import paper_1905_10138_amd as xe
+    dev = torch.device("cuda:0")
+    lib = xe.load_library()
+    jobs = _scratch_layers(dev)
+    want = [xe.spmm(L, x).clone() for L, x in jobs]
+    ws = torch.empty(xe.SPMM_WORKSPACE_BYTES, dtype=torch.uint8, device=dev)
+    streams = [torch.cuda.Stream() for _ in range(8)]
+    torch.cuda.synchronize()
+
+    def call(i, y, stream, *workspace):
+        L, x = jobs[i]
+        st = L.c_struct()
+        fn = lib.xorenc_spmm_ws if workspace else lib.xorenc_spmm
+        return fn(ctypes.byref(st), x.data_ptr(), 0 if x.dtype == torch.float32 else 1, x.stride(0), x.shape[1], y.data_ptr(),
+                  y.stride(0), *workspace, stream.cuda_stream)
+
+    assert call(0, want[0], streams[0], ws.data_ptr(), xe.SPMM_WORKSPACE_BYTES - 1) == -1
+    assert call(0, want[0], streams[0], ws.data_ptr() + 8, xe.SPMM_WORKSPACE_BYTES) == -3
+    refused = 0
+    for i in range(len(jobs)):
+        for st in streams:
+            y = torch.full_like(want[i], 7.0)
+            torch.cuda.synchronize()
+            rc = call(i, y, st, None, 0)
+            torch.cuda.synchronize()
+            refused += rc == -6
+            assert rc in (0, -6) and torch.equal(y, want[i] if rc == 0 else torch.full_like(y, 7.0))
+            assert call(i, y, st) == 0
+            torch.cuda.synchronize()
+            assert float((y - want[i]).norm() / want[i].norm()) <= 4e-7
+            y.fill_(7.0)
+            torch.cuda.synchronize()
+            assert call(i, y, st, ws.data_ptr(), ws.numel()) == 0
+            torch.cuda.synchronize()
+            assert torch.equal(y, want[i])
+    assert refused >= 4 * len(jobs)
+    y = torch.full_like(want[2], 7.0)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        st = torch.cuda.current_stream()
+        rcs = [call(2, y, st, None, 0), call(2, y, st)]
+    assert rcs == [-6, 0]
+    for _ in range(3):
+        y.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float((y - want[2]).norm() / want[2].norm()) <= 4e-7

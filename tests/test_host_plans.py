@@ -116,3 +116,54 @@ def test_parts_of_the_few_column_kernel_fit_the_scratch_area(tmp_path):
     have to lie inside the scratch area all the same.  (They used to run over its end: 12800 x 16384, four columns with a
     leading dimension of four, 400 workgroups in the room of 256.)"""
     run_program(tmp_path, SMALL_SPLIT)
+
+
+SCRATCH_OWNERS = r"""
+#include <cstdio>
+#include <set>
+#include "xorenc_scratch.h"
+
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); return 1; } } while (0)
+
+static ScratchOwners owners, others;
+
+int main() {
+  auto at = [](uintptr_t p) { return reinterpret_cast<const void *>(p); };
+  // streams, threads behind the handle that stands for a thread's stream, and captures on the same stream
+  std::set<int> tickets, slots;
+  int first_tickets = -1, first_slot = -1;
+  for (int i = 0; i < 40; ++i) {
+    const ScratchOwner o = i < 10 ? ScratchOwner{at(i < 2 ? i : 0x7f0000000000 + 0x500 * i), nullptr, 0}
+                         : i < 20 ? ScratchOwner{at(2), at(0x600000 + 64 * i), 0} : ScratchOwner{at(0x7f0000000000), nullptr, (uint64_t)i};
+    const ScratchShare none = owners.share(o, false, 0), a = owners.share(o, true, 3);
+    CHECK(none.slot == -1 && none.tickets == a.tickets && a.tickets >= 0 && a.tickets < kScratchOwners);
+    CHECK(tickets.insert(a.tickets).second);                     // nobody else's
+    CHECK((a.slot >= 0) == (i < kScratchSlots) && a.slot < kScratchSlots);
+    if (a.slot >= 0) CHECK(slots.insert(a.slot).second);
+    if (i == 0) first_tickets = a.tickets, first_slot = a.slot;
+    for (int r = 0; r < 100; ++r) {                              // the calls of one owner keep their share
+      const ScratchShare b = owners.share(o, true, 1);
+      CHECK(b.tickets == a.tickets && b.slot == a.slot && b.staged == a.staged + 3 + r);
+    }
+  }
+  const ScratchShare again = owners.share(ScratchOwner{at(0), nullptr, 0}, true, 0);
+  CHECK(again.tickets == first_tickets && again.slot == first_slot);
+  // more captures than there are sets: the last ones get none, new streams still do, owners keep theirs
+  int served = 0;
+  for (uint64_t c = 1; c <= 3 * kScratchOwners; ++c) served += others.share(ScratchOwner{at(0x1000), nullptr, c}, false, 0).tickets >= 0;
+  CHECK(served == kScratchOwners - kScratchStreams);
+  CHECK(others.share(ScratchOwner{at(0x1000), nullptr, 5}, false, 0).tickets == 4);
+  std::set<int> streams;
+  for (int i = 0; i < kScratchStreams; ++i) streams.insert(others.share(ScratchOwner{at(0x2000 + 16 * i), nullptr, 0}, true, 0).tickets);
+  CHECK((int)streams.size() == kScratchStreams && *streams.begin() >= served && *streams.rbegin() < kScratchOwners);
+  CHECK(others.share(ScratchOwner{at(0x9000000), nullptr, 0}, true, 0).tickets == -1);
+  return 0;
+}
+"""
+
+
+def test_tickets_and_slots_have_one_owner(tmp_path):
+    """Two streams, or a stream and a captured graph, or two graphs, never share what a product keeps beside its arguments,
+    however many calls are made in between (slots used to be handed out in turn at the time of the call).  The addresses
+    that follow from a share are apart by construction."""
+    run_program(tmp_path, SCRATCH_OWNERS)
