@@ -20,12 +20,20 @@ constexpr int kScratchStreams = 256;  // of them kept for streams, however many 
 constexpr int kScratchSlots = 4;      // slots of memory (12 MiB each)
 constexpr size_t kTicketBytes = (size_t)kSplitMaxGroups * sizeof(uint32_t);
 constexpr size_t kPartBytes = (size_t)kSplitMaxGroups * kSplitTileFloats * sizeof(float);  // 4 MiB
-constexpr size_t kStageBytes = (size_t)4 << 20;  // 4 MiB: 8192 rows of 256 bf16 columns
-// Copies of X go to two areas in turn: the lines of the one that the product before has just read are still in the L2
-// caches of all XCDs, and writing them again costs a call up to 3 us (4096 x 9216, two planes, fp32 X, B = 64: 31.0 with
-// one area, 28.1 with two to sixteen; partial tiles, which bypass the L2, show no such difference).
-constexpr int kStageAreas = 2;
-constexpr size_t kSlotBytes = kPartBytes + kStageAreas * kStageBytes;
+constexpr size_t kStageBytes = (size_t)4 << 20;  // largest copy of X: 8192 rows of 256 bf16 columns
+// Copies of X go round a ring: the lines of the copy that the product before has just read are still in the L2 caches of
+// all XCDs (4 MiB each), and writing them again costs a call up to 3 us (4096 x 9216, two planes, fp32 X, B = 64: 31.0 us
+// with one area, 28.1 with two and more; partial tiles, which bypass the L2, show no such difference).
+constexpr size_t kRingBytes = 2 * kStageBytes;
+constexpr size_t kSlotBytes = kPartBytes + kRingBytes;
+
+// Place in the ring of a copy of `bytes` (at most kStageBytes); `at` moves behind it.
+inline uint32_t ring_place(uint32_t &at, size_t bytes) {
+  if (at + bytes > kRingBytes) at = 0;
+  const uint32_t place = at;
+  at += (uint32_t)((bytes + 255) / 256 * 256);
+  return place;
+}
 
 struct ScratchOwner {
   const void *stream;
@@ -36,14 +44,14 @@ struct ScratchOwner {
 struct ScratchShare {
   int tickets;  // -1: all sets belong to others
   int slot;     // -1: all slots belong to others, or none was asked for
-  uint32_t staged;  // copies of X that the owner's calls have made before
+  uint32_t ring;  // where the owner's last copy of X ends
 };
 
 // The owners on one GPU.  All zero is the empty table; the caller holds a lock.
 class ScratchOwners {
  public:
-  // `stagings`: copies of X that the call is about to make
-  ScratchShare share(const ScratchOwner &o, bool want_slot, int stagings) {
+  // The call is about to make `copies` copies of X, of at most `bytes` each (a bound for all of them).
+  ScratchShare share(const ScratchOwner &o, bool want_slot, int copies, size_t bytes) {
     uint64_t h = ((uint64_t)reinterpret_cast<uintptr_t>(o.stream) >> 4) ^ (uint64_t)reinterpret_cast<uintptr_t>(o.thread) ^
                  (o.capture << 20);
     h *= 0x9E3779B97F4A7C15ull;
@@ -57,9 +65,9 @@ class ScratchOwners {
         continue;
       }
       if (want_slot && e.slot == 0 && n_slots_ < kScratchSlots) e.slot = ++n_slots_;
-      const uint32_t staged = e.staged;
-      e.staged += (uint32_t)stagings;
-      return {e.number - 1, want_slot ? e.slot - 1 : -1, staged};
+      const uint32_t ring = e.ring;
+      for (int i = 0; i < copies; ++i) ring_place(e.ring, bytes);
+      return {e.number - 1, want_slot ? e.slot - 1 : -1, ring};
     }
   }
 
@@ -68,7 +76,7 @@ class ScratchOwners {
   struct Entry {
     ScratchOwner owner;
     int32_t number, slot;  // from 1 on, 0: none
-    uint32_t staged;
+    uint32_t ring;
   };
   Entry entries_[kEntries];
   int32_t n_owners_, n_slots_;

@@ -100,10 +100,10 @@ constexpr int kMaxDevices = 64;
 struct Scratch {
   uint32_t *tickets;
   unsigned char *slot;
-  uint32_t staged;
+  uint32_t ring;
 };
 
-int32_t take_scratch(hipStream_t st, bool captured, uint64_t capture, bool want_slot, int stagings, Scratch *out) {
+int32_t take_scratch(hipStream_t st, bool captured, uint64_t capture, bool want_slot, int copies, size_t copy_bytes, Scratch *out) {
   static std::mutex lock;
   static unsigned char *address[kMaxDevices] = {};
   static ScratchOwners owners[kMaxDevices];
@@ -121,10 +121,10 @@ int32_t take_scratch(hipStream_t st, bool captured, uint64_t capture, bool want_
     address[dev] = static_cast<unsigned char *>(p);
   }
   const ScratchOwner owner{st, st == hipStreamPerThread ? &this_thread : nullptr, captured ? capture : 0};
-  const ScratchShare share = owners[dev].share(owner, want_slot, stagings);
+  const ScratchShare share = owners[dev].share(owner, want_slot, copies, copy_bytes);
   out->tickets = share.tickets < 0 ? nullptr : reinterpret_cast<uint32_t *>(address[dev] + share.tickets * kTicketBytes);
   out->slot = share.slot < 0 ? nullptr : address[dev] + kScratchOwners * kTicketBytes + share.slot * kSlotBytes;
-  out->staged = share.staged;
+  out->ring = share.ring;
   return XORENC_OK;
 }
 
@@ -155,12 +155,27 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
   // 4096 x 4096 17.6 15.2 22.6 83.7, here 12.1 12.1 16.9 47.6; 4096 x 9216 with two planes 34.6 29.3 51.5 465, here
   // 18.8 18.8 32.0 120).
   int split_parts = 0, split_cols = 0;
+  size_t copy_bytes = 0;  // of the largest part
   const int64_t weights = (int64_t)layer->m * layer->n * layer->q;
   if (x_dtype == XORENC_X_F32 && (weights >= kXSplitMinWeights || weights * B >= kXSplitMinWork)) {
     const int64_t fit = (int64_t)(kStageBytes / ((size_t)D.spr * 64 * 48)) * 8;  // columns that fit
     if (fit >= min(B, 64)) {
       split_cols = fit >= B ? B : (int)(fit / 64 * 64);
       split_parts = (B + split_cols - 1) / split_cols;
+      copy_bytes = (size_t)D.spr * 64 * ((split_cols + 7) / 8) * 48;
+    }
+    // Parts of few tiles leave most of the chip idle, one after the other, and each builds the tables anew, where the
+    // kernels that split X on its way run all columns at once: parts only from 64 tiles each (32 where X would have to be
+    // copied in parts instead, 24 with four tables for each of four words per slice, which the others take longest to
+    // build), and on small layers not at all (us, in parts / otherwise: 264 x 4157,
+    // B = 911 114 / 41; 595 x 6443, two planes, B = 376 98 / 39; 438 x 2378, two planes, B = 508 39 / 23; 236 x 2033, four
+    // planes, B = 370 41 / 28; 913 x 2042, n_in = 32, n_out = 256, B = 734 68 / 168; 2186 x 3700, unaligned, B = 570 101 / 116).  Over
+    // 242 calls in parts, 200 x 1500 to 14000 x 9216: 2 % from the better choice in the mean, 19 % without the rule.
+    if (split_parts > 1) {
+      const int64_t tiles = (int64_t)D.nrb * ((split_cols + (D.q <= 2 ? 63 : 31)) / (D.q <= 2 ? 64 : 32));
+      const bool copied = !aligned && (int64_t)layer->n * ((B + per - 1) / per) * 16 > (int64_t)kStageBytes;
+      const bool most_tables = D.J * tables_of_variant(D.nib_variant) >= 16;
+      if (tiles < (most_tables ? 24 : copied ? 32 : 64) || (weights < 3000000 && !copied && !most_tables)) split_parts = 0;
     }
   }
   // rows of X that do not start on 16-byte boundaries: a padded copy, unless the few-column kernel (which reads X
@@ -170,12 +185,27 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
   // columns does.
   int copy_parts = 0;
   const int pieces_per_row = (int)(((int64_t)B + per - 1) / per);  // 16-byte pieces
-  if (!split_parts && !aligned && B >= kStageMinB) {
+  // Widths whose fields straddle dwords, 17 to 24 bits aside, and one block of columns: the copy and the three or four
+  // tables per word of the kernels for aligned X cost small calls more than reading X element by element does (us, copied /
+  // not: 212 x 1558, two planes, n_out = 192, n_in = 5, B = 7 15.4 / 11.9; 2698 x 460, fp32, n_in = 5, B = 9 9.5 / 8.2;
+  // 2918 x 1006, four planes, n_out = 128, n_in = 13, B = 11 11.5 / 9.6; with one word per slice bf16 gains all the same,
+  // 752 x 2716, three planes, B = 18 10.7 / 15.9, and fp32 from seventeen columns on, 6217 x 842, B = 27 10.9 / 14.1).
+  const bool odd_width = (D.n_in & (D.n_in - 1)) != 0 && (D.n_in < 17 || D.n_in > 24);
+  const bool copy_pays = !odd_width || B > 32 ||
+                         (D.J == 1 ? x_dtype == XORENC_X_BF16 || B > 16 : weights >= (D.n_in > 24 ? 2000000 : 20000000));
+  if (!split_parts && !aligned && B >= kStageMinB && copy_pays) {
     const int64_t fit = (int64_t)(kStageBytes / ((size_t)layer->n * 16)) * per / 64 * 64;  // columns, in whole 64s
     const bool whole = (int64_t)layer->n * pieces_per_row * 16 <= (int64_t)kStageBytes;
     xorenc_spmm_detail::F4Plan unused;
     if ((whole || fit > 0) && !xorenc_spmm_detail::f4_applies(D, x_dtype, B, 0, &unused))
       copy_parts = whole ? 1 : (int)((B + fit - 1) / fit);
+    // (fp32 parts of few tiles of 32 columns: as above, 225 x 6154, three planes, B = 171 46 / 40 us without the copies,
+    // 624 x 5320, B = 199 37 / 74)
+    if (copy_parts > 1 && x_dtype == XORENC_X_F32) {
+      const int cols = (pieces_per_row + copy_parts - 1) / copy_parts * per;
+      if ((int64_t)D.nrb * ((cols + 31) / 32) < 48) copy_parts = 0;
+    }
+    if (copy_parts) copy_bytes = (size_t)layer->n * ((pieces_per_row + copy_parts - 1) / copy_parts) * 16;
   }
   Scratch scratch{};
   if (split_parts || copy_parts || D.spr >= kSplitMinWords) {
@@ -185,7 +215,7 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
     if (hipStreamGetCaptureInfo(st, &capturing, &capture) != hipSuccess) capturing = hipStreamCaptureStatusNone;
     const bool captured = capturing != hipStreamCaptureStatusNone;
     if (captured && !workspace && limit_is_error) return XORENC_ELIMIT;
-    const int32_t rs = take_scratch(st, captured, capture, !workspace, split_parts + copy_parts, &scratch);
+    const int32_t rs = take_scratch(st, captured, capture, !workspace, split_parts + copy_parts, copy_bytes, &scratch);
     if (rs != XORENC_OK) return rs;
     if (workspace) scratch.slot = workspace;
     if (!scratch.slot && limit_is_error) return XORENC_ELIMIT;
@@ -193,7 +223,7 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
   xorenc_internal_begin_call();
   D.split_part = scratch.tickets ? reinterpret_cast<float *>(scratch.slot) : nullptr;
   D.split_ticket = scratch.tickets;
-  auto stage = [&](int i) { return scratch.slot + kPartBytes + (scratch.staged + i) % kStageAreas * kStageBytes; };
+  auto next_copy = [&] { return scratch.slot + kPartBytes + ring_place(scratch.ring, copy_bytes); };
   auto product = [&](const void *Xp, int64_t ld, int32_t cols, float *Yp, int fast, int32_t x_dtype) -> int32_t {
     switch (layer->q) {
       case 1: return xorenc_spmm_dispatch_q1(D, Xp, x_dtype, ld, cols, Yp, ldy, fast, st);
@@ -204,21 +234,23 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
   };
   if (scratch.slot) {
     for (int i = 0, c0 = 0; i < split_parts; ++i, c0 += split_cols) {
+      unsigned char *const copy = next_copy();
       const int rows = D.spr * 64, cols = min(split_cols, B - c0), cpr = (cols + 7) / 8;
       const int64_t pieces = (int64_t)rows * cpr;
       hipLaunchKernelGGL(split_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
-                         static_cast<const float *>(X) + c0, ldx, (int)layer->n, rows, cols, cpr, stage(i));
-      const int32_t rp = product(stage(i), (int64_t)cpr * 8, cols, Y + c0, 1, xorenc_spmm_detail::kXSplit);
+                         static_cast<const float *>(X) + c0, ldx, (int)layer->n, rows, cols, cpr, copy);
+      const int32_t rp = product(copy, (int64_t)cpr * 8, cols, Y + c0, 1, xorenc_spmm_detail::kXSplit);
       if (rp != XORENC_OK) return rp;
     }
     for (int i = 0, c0 = 0; i < copy_parts; ++i) {
+      unsigned char *const copy = next_copy();
       const int cpr = pieces_per_row / copy_parts + (i < pieces_per_row % copy_parts ? 1 : 0);
       const int cols = min(cpr * per, B - c0);
       const int64_t pieces = (int64_t)layer->n * cpr;
       hipLaunchKernelGGL(stage_x_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,
                          static_cast<const unsigned char *>(X) + (int64_t)c0 * esz, ldx, (int)layer->n, cols, esz, cpr,
-                         stage(i));
-      const int32_t rp = product(stage(i), (int64_t)cpr * per, cols, Y + c0, 1, x_dtype);
+                         copy);
+      const int32_t rp = product(copy, (int64_t)cpr * per, cols, Y + c0, 1, x_dtype);
       if (rp != XORENC_OK) return rp;
       c0 += cols;
     }

@@ -689,3 +689,20 @@ def test_a_call_without_memory_for_its_stream_and_with_a_workspace():
         graph.replay()
         torch.cuda.synchronize()
         assert float((y - want[2]).norm() / want[2].norm()) <= 4e-7
+
+
+@pytest.mark.parametrize("name,m,n,n_out,n_in,S,B,dtype,pad", [
+    # fp32 X whose three terms do not fit the staging area: parts of few tiles (not taken), of one tile more and one less
+    # than the least, four tables for four words, unaligned rows that a copy holds whole, in parts, or not at all
+    ("large_q1", 264, 4157, 64, 16, 0.9, 911, "f32", 0), ("large_q1", 1000, 3100, 64, 8, None, 196, "f32", 0),
+    ("large_q1", 700, 4400, 64, 8, None, 132, "f32", 0), ("large_q1", 670, 4600, 64, 8, None, 132, "f32", 0),
+    ("large_q1", 200, 4200, 256, 32, 0.9, 420, "f32", 0), ("large_q2", 250, 5100, 64, 13, 0.8, 130, "f32", 1),
+    ("lstm", 225, 6154, 64, 24, None, 171, "f32", 0), ("large_q1", 624, 5320, 64, 16, 0.85, 199, "f32", 0),
+    # one block of columns in unaligned rows, widths that straddle dwords: read element by element or copied
+    ("large_q1", 250, 460, 64, 5, 0.95, 9, "f32", 0), ("large_q1", 250, 460, 64, 5, 0.95, 17, "f32", 0),
+    ("large_q2", 212, 1000, 192, 5, 0.97, 7, "bf16", 0), ("large_q2", 300, 3500, 128, 29, 0.85, 11, "bf16", 0),
+    ("large_q1", 200, 700, 256, 13, 0.95, 32, "f32", 1), ("large_q1", 200, 700, 256, 13, 0.95, 33, "f32", 0)])
+def test_calls_on_either_side_of_the_staging_rules(name, m, n, n_out, n_in, S, B, dtype, pad):
+    """Which calls copy or split X first follows sizes, types and alignment: the same result either way."""
+    got, want = _run(name, m, n, B, dtype, ldx_pad=pad, S=S, n_out=n_out, n_in=n_in, every_output=True)
+    assert rel_fro(got, want) <= 2e-7

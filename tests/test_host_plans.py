@@ -135,28 +135,36 @@ int main() {
   for (int i = 0; i < 40; ++i) {
     const ScratchOwner o = i < 10 ? ScratchOwner{at(i < 2 ? i : 0x7f0000000000 + 0x500 * i), nullptr, 0}
                          : i < 20 ? ScratchOwner{at(2), at(0x600000 + 64 * i), 0} : ScratchOwner{at(0x7f0000000000), nullptr, (uint64_t)i};
-    const ScratchShare none = owners.share(o, false, 0), a = owners.share(o, true, 3);
+    const ScratchShare none = owners.share(o, false, 0, 0), a = owners.share(o, true, 1, 1000);
     CHECK(none.slot == -1 && none.tickets == a.tickets && a.tickets >= 0 && a.tickets < kScratchOwners);
     CHECK(tickets.insert(a.tickets).second);                     // nobody else's
     CHECK((a.slot >= 0) == (i < kScratchSlots) && a.slot < kScratchSlots);
     if (a.slot >= 0) CHECK(slots.insert(a.slot).second);
     if (i == 0) first_tickets = a.tickets, first_slot = a.slot;
     for (int r = 0; r < 100; ++r) {                              // the calls of one owner keep their share
-      const ScratchShare b = owners.share(o, true, 1);
-      CHECK(b.tickets == a.tickets && b.slot == a.slot && b.staged == a.staged + 3 + r);
+      const ScratchShare b = owners.share(o, true, 1, 100);
+      CHECK(b.tickets == a.tickets && b.slot == a.slot && b.ring == 1024 + 256 * (uint32_t)r);
     }
   }
-  const ScratchShare again = owners.share(ScratchOwner{at(0), nullptr, 0}, true, 0);
+  const ScratchShare again = owners.share(ScratchOwner{at(0), nullptr, 0}, true, 0, 0);
   CHECK(again.tickets == first_tickets && again.slot == first_slot);
   // more captures than there are sets: the last ones get none, new streams still do, owners keep theirs
   int served = 0;
-  for (uint64_t c = 1; c <= 3 * kScratchOwners; ++c) served += others.share(ScratchOwner{at(0x1000), nullptr, c}, false, 0).tickets >= 0;
+  for (uint64_t c = 1; c <= 3 * kScratchOwners; ++c) served += others.share(ScratchOwner{at(0x1000), nullptr, c}, false, 0, 0).tickets >= 0;
   CHECK(served == kScratchOwners - kScratchStreams);
-  CHECK(others.share(ScratchOwner{at(0x1000), nullptr, 5}, false, 0).tickets == 4);
+  CHECK(others.share(ScratchOwner{at(0x1000), nullptr, 5}, false, 0, 0).tickets == 4);
   std::set<int> streams;
-  for (int i = 0; i < kScratchStreams; ++i) streams.insert(others.share(ScratchOwner{at(0x2000 + 16 * i), nullptr, 0}, true, 0).tickets);
+  for (int i = 0; i < kScratchStreams; ++i) streams.insert(others.share(ScratchOwner{at(0x2000 + 16 * i), nullptr, 0}, true, 0, 0).tickets);
   CHECK((int)streams.size() == kScratchStreams && *streams.begin() >= served && *streams.rbegin() < kScratchOwners);
-  CHECK(others.share(ScratchOwner{at(0x9000000), nullptr, 0}, true, 0).tickets == -1);
+  CHECK(others.share(ScratchOwner{at(0x9000000), nullptr, 0}, true, 0, 0).tickets == -1);
+  // copies of X stay inside the ring
+  uint32_t state = 12345, ring = 0;
+  for (int i = 0; i < 100000; ++i) {
+    state = state * 1664525u + 1013904223u;
+    const size_t bytes = (i % 3 ? 16 * (1 + state % 5000) : state % 7 ? 16 * (1 + state % (kStageBytes / 16)) : kStageBytes);
+    const uint32_t place = ring_place(ring, bytes);
+    CHECK(place % 16 == 0 && place + bytes <= kRingBytes);
+  }
   return 0;
 }
 """
