@@ -37,7 +37,7 @@ extern "C" {
 #define XORENC_API
 #endif
 
-#define XORENC_VERSION 0x00020200u
+#define XORENC_VERSION 0x00020300u
 
 enum {
   XORENC_OK = 0,
@@ -225,9 +225,10 @@ XORENC_API int32_t xorenc_encode(int32_t m, int32_t n, int32_t n_in, int32_t q, 
  * Encoder on the GPU with the fewest patches (Section 5.2, minimising n_patch for small n_in): for
  * every slice the input of the XOR-gate network whose output differs from the quantised bits on the fewest care
  * positions; among equals the smallest input read as an integer (bit j = x_j).  Patches are the remaining
- * mismatches.  Arguments, outputs, workspace and stream behaviour exactly as xorenc_encode, three more kernels.  Slices
- * that can be encoded without patches cost what they cost in xorenc_encode; on the others all 2^n_in inputs are
- * tried (1.4 * 10^13 network evaluations per second on one MI355X at n_out = 64, 6 * 10^12 at 192 and 256).
+ * mismatches.  Arguments, outputs, workspace and stream behaviour exactly as xorenc_encode, one to three more kernels.
+ * From eleven input bits on, slices that can be encoded without patches cost what they cost in xorenc_encode; on the
+ * others, and on all slices with fewer input bits, all 2^n_in inputs are tried (1.4 * 10^13 network evaluations per
+ * second on one MI355X at n_out = 64, 6 * 10^12 at 192 and 256).
  * XORENC_EUNSUPPORTED for n_in > XORENC_EXH_MAX_N_IN.
  */
 #define XORENC_EXH_MAX_N_IN 24
@@ -273,22 +274,23 @@ XORENC_API int32_t xorenc_decode(const xorenc_layer *layer, int32_t out_kind, vo
  *   Y  DEV float, row-major m x B, leading dimension ldy >= B; overwritten.
  * Accumulation is fp32; alpha is applied in fp32 after the contraction of each plane.  fp32 X is
  * split exactly into three bf16 terms, so the fp32 path keeps fp32 accuracy on the matrix cores.
- * The same bits in Y for the same inputs on every call: sums are formed in a fixed order.  One kernel launch per
- * call, two when the rows of X do not start on 16-byte boundaries (ldx not a multiple of 8 bf16 / 4 fp32 values, or
- * such a base address) and X has at least five columns: a first kernel then copies X into a 4 MiB staging area inside
- * the library with its rows padded to whole 16-byte pieces, and the product reads the copy; an X that needs more is
- * copied and multiplied in parts of its columns, two launches each (n <= 32768 bf16, 16384 fp32; larger n are read
- * element by element) (the fast kernels fetch X in 16-byte pieces).  fp32 X of larger layers (6 million weights of all planes, or
- * 600 million products) is split into its three bf16 terms in the same area first, in parts of at least 64 columns
- * where they do not fit (n up to about 10900; longer rows with more columns than fit are split on their way into LDS).  For
- * small layers the launch splits the reduction dimension over several workgroups per output tile; their partial tiles
- * meet in a scratch area, and the workgroup that finishes last adds them in a fixed order of their slice ranges.
+ * The same bits in Y for the same inputs on every call that has the memory it may use (below): sums are formed in a fixed
+ * order.  One kernel launch per call, except where X is rewritten first, in a 4 MiB staging area (the fast kernels fetch
+ * X in 16-byte pieces of bf16):
+ *   - rows of X that do not start on 16-byte boundaries (ldx not a multiple of 8 bf16 / 4 fp32 values, or such a base
+ *     address), from five columns on: copied with padded rows;
+ *   - fp32 X of larger layers (6 million weights of all planes, or 600 million products): split into its bf16 terms.
+ * Two launches then, and two for every part of the columns where X does not fit and that is still the faster way (at least
+ * 64 columns have to fit: n <= 32768 bf16, 16384 fp32 copied, about 10900 fp32 split; otherwise the kernels that read X
+ * element by element, or split it on its way, take the call).  For small layers the launch splits the reduction dimension
+ * over several workgroups per output tile; their partial tiles meet in a scratch area, and the workgroup that finishes
+ * last adds them in a fixed order of their slice ranges.
  * Staging and scratch areas live in device memory that the library keeps on every GPU (about 52 MiB).  They belong to a
  * stream, or to a stream's part of a captured graph, from its first such call on and for good, so that calls and graphs
  * may overlap in any way; a stream whose calls have not all run must not be destroyed (its handle may come back).  There
  * is room for the first four such streams and captures.  A call on another one runs on kernels that need no such memory,
- * which are slower, several times for many columns of unaligned X: programs with more streams, or that capture more than
- * a few graphs, pass a workspace (xorenc_spmm_ws).
+ * which add in another order and are slower (4096 x 9216, two planes, B = 64 by a quarter, many columns of unaligned X
+ * several times): programs with more streams, or that capture more than a few graphs, pass a workspace (xorenc_spmm_ws).
  * Nothing is allocated by the call.
  */
 XORENC_API int32_t xorenc_spmm(const xorenc_layer *layer, const void *X, int32_t x_dtype, int64_t ldx, int32_t B, float *Y,

@@ -243,20 +243,19 @@ __global__ void exhaustive_reset_kernel(uint32_t *list_len) { *list_len = 0; }
 // slices x 64 bits per instruction.  A's block scale is 2^14 and the accumulator starts at the input's number in its
 // tile (and the shift that keeps it positive), so a result plus 32 * tile is a float that holds the pair (mismatches,
 // input) exactly (2 * 2^14 * 256 + 2^15 < 2^24; all terms are integers) and its minimum is the answer: half a v_min3_u32
-// on the bit patterns per input and slice.  Rows of M
-// that are zero mismatch or match whatever the input is and stay out, so that at most half of the care bits can
-// be mismatched at the minimum over all inputs and its key (mismatches + 1) << 24 | input fits 32 bits; the minimum over
-// one item's inputs can mismatch all 256, but not win, and its key is held at 255 << 24.  Tiles are visited in Gray
+// on the bit patterns per input and slice.  Rows of M that are zero mismatch or match whatever
+// the input is and stay out, so that at most half of the care bits can be mismatched at the minimum over all inputs and
+// its key (mismatches + 1) << 24 | input fits 32 bits; the minimum over one item's inputs can mismatch all 256, but not win, and its key is held at 255 << 24.  Tiles are visited in Gray
 // code order: one column of M flips the signs of A (4 XORs per 64 bits, shared by the four slice tiles).
 //
 // Bound: VALU issue beside the matrix instructions.  Every slice of 16384 x 4096, n_out = 192, n_in = 20 used to be
-// searched, one slice per lane, at 2J AND, 2J XOR and 2J population counts per input: 219 ms for the call, 0.35 ms now
+// searched, one slice per lane, at 2J AND, 2J XOR and 2J population counts per input: 219 ms for the call, 0.30 ms now
 // (16384 x 4096 with half of the weights kept, n_out = 64, n_in = 16, where nearly every slice is searched: 14 and 5 ms).
 // The width of an item falls from 2^15 to 2^10 inputs when there are too few slices to give every wave eight items.
 // ALL: every slice of the pass is searched, in one item each and without a list.  With few inputs that is cheaper than
-// the elimination that would sort out the slices that need no search (kAllMaxNIn; calls with n_in = 8, of which both
-// repeat with a larger patch buffer: 2000 x 1000, two planes, S = 0.8 83 us, 151 with the list; 4096 x 2048, S = 0.9 85,
-// 161; 500 x 9000, four planes, n_in = 10 115, 253).
+// the elimination that would sort out the slices that need no search, however few these are, and than joining the list
+// (kAllMaxNIn; us for the kernels of a call, all slices / with the list: 16384 x 4096, S = 0.95, n_in = 8 34 / 199, n_in =
+// 10 55 / 124, with n_out = 192 47 / 117; S = 0.8, n_in = 10 60 / 254; 1024 x 1024, S = 0.9, n_in = 8 13 / 26).
 constexpr int kAllMaxNIn = 10;
 
 template <int J, bool ALL>

@@ -1034,7 +1034,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
     return v[0];
   };
   // n_splits > 1: this workgroup holds one of n_splits partial sums of its tile.  It parks the tile in the
-  // library's scratch area and takes a ticket; the workgroup that arrives last adds the parts in the order
+  // scratch area and takes a ticket; the workgroup that arrives last adds the parts in the order
   // of their slice ranges (so the result does not depend on who was last) and writes Y.  No zero-fill, no
   // atomics on Y, nobody waits for anybody.
   float *const my_part =

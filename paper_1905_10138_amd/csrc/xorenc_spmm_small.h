@@ -340,7 +340,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
     }
   }
   __syncthreads();
-  // n_splits > 1: the tile (ROWS x 8 floats) is one of n_splits partial sums; it is parked in the library's
+  // n_splits > 1: the tile (ROWS x 8 floats) is one of n_splits partial sums; it is parked in the
   // scratch area and the workgroup that arrives last adds the parts in the order of their slice ranges
   float *const my_part =
       n_splits > 1 ? L.split_part + ((int64_t)blockIdx.x * n_splits + blockIdx.z) * (ROWS * kSmallMaxB) : nullptr;

@@ -332,9 +332,9 @@ def test_spmm_random_shapes(name, m, n, n_out, n_in, B, dtype, pad):
     ("lstm", 6000, 3000, 32, "bf16"), ("tiny", 256, 256, 8, "f32"), ("fc6", 97, 640, 3, "bf16")])
 def test_split_reduction_is_deterministic_and_one_launch(name, m, n, B, dtype):
     """Layers with fewer output tiles than CUs split the reduction dimension over several workgroups per tile.
-    Their partial sums meet in the library's scratch area and are added in a fixed order: the same bits on
-    every call, also when calls on other layers come in between (the scratch slots are taken in turn and the
-    arrival counters must be back at zero after every launch), and Y needs no clearing beforehand."""
+    Their partial sums meet in scratch memory and are added in a fixed order: the same bits on every call, also when
+    calls on other layers come in between (they use the same memory, and the arrival counters must be back at zero
+    after every launch), and Y needs no clearing beforehand."""
     import torch
     import paper_1905_10138_amd as xe
     wl, enc = encoded_workload(name, m, n)
@@ -351,7 +351,7 @@ def test_split_reduction_is_deterministic_and_one_launch(name, m, n, B, dtype):
     assert_every_output_close(first.cpu().numpy(), decoder.spmm_f64(enc, exact), enc, exact) if dtype == "bf16" else None
     for i in range(12):
         if i % 3 == 1:
-            xe.spmm(other, xo)                  # another split launch in between: takes the next slot
+            xe.spmm(other, xo)                  # another split launch in between: the same scratch memory
         Y.fill_(float(i))
         xe.spmm(L, xg, Y=Y)
         assert torch.equal(Y, first), f"call {i} differs"
@@ -475,8 +475,8 @@ def test_fp32_X_of_many_magnitudes_and_four_planes():
 
 
 def test_calls_on_many_streams_keep_their_own_staging_and_scratch():
-    """Sixteen streams at a time, calls that split X, copy unaligned X or split the reduction over workgroups: every slot
-    is in use, and every result is the one a call alone gives, bit for bit."""
+    """Sixteen streams at a time, calls that split X, copy unaligned X or split the reduction over workgroups: more streams
+    than the library has slots, and every result is the one a call alone gives, bit for bit."""
     import torch
     import paper_1905_10138_amd as xe
     _, enc = encoded_workload("large_q1", 4100, 1500)
