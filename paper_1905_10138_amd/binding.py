@@ -386,12 +386,12 @@ def spmm(layer: PackedLayer, X, Y=None):
         Y = torch.empty((layer.m, B), dtype=torch.float32, device=X.device)
     st = layer.c_struct()
     fn, stream = load_library().xorenc_spmm_ws, _stream_ptr()
-    xp, yp = ctypes.c_void_p(X.data_ptr()), ctypes.c_void_p(Y.data_ptr())
+    xp, yp = X.data_ptr(), Y.data_ptr()
     rc = fn(ctypes.byref(st), xp, xd, X.stride(0), B, yp, Y.stride(0), None, 0, stream)
     if rc == _ELIMIT:
         # the library has no memory for this stream, or the call is captured: torch's, in stream order or from the
         # graph's pool, which keeps it as long as the graph
         ws = torch.empty(SPMM_WORKSPACE_BYTES, dtype=torch.uint8, device=X.device)
-        rc = fn(ctypes.byref(st), xp, xd, X.stride(0), B, yp, Y.stride(0), ctypes.c_void_p(ws.data_ptr()), ws.numel(), stream)
+        rc = fn(ctypes.byref(st), xp, xd, X.stride(0), B, yp, Y.stride(0), ws.data_ptr(), ws.numel(), stream)
     _check(rc, "xorenc_spmm")
     return Y

@@ -208,6 +208,12 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
     if (copy_parts) copy_bytes = (size_t)layer->n * ((pieces_per_row + copy_parts - 1) / copy_parts) * 16;
   }
   Scratch scratch{};
+  // A copy and the product that reads it are enqueued together: another thread's call on the same stream must not get its
+  // copy, which may go to the same place, in between.
+  static std::mutex enqueue[64];
+  std::unique_lock<std::mutex> together;
+  if (split_parts || copy_parts)
+    together = std::unique_lock<std::mutex>(enqueue[(reinterpret_cast<uintptr_t>(st) >> 4) % 64]);
   if (split_parts || copy_parts || D.spr >= kSplitMinWords) {
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     unsigned long long capture = 0;

@@ -706,3 +706,34 @@ def test_calls_on_either_side_of_the_staging_rules(name, m, n, n_out, n_in, S, B
     """Which calls copy or split X first follows sizes, types and alignment: the same result either way."""
     got, want = _run(name, m, n, B, dtype, ldx_pad=pad, S=S, n_out=n_out, n_in=n_in, every_output=True)
     assert rel_fro(got, want) <= 2e-7
+
+
+def test_threads_that_call_on_one_stream():
+    """Copies of X as large as a staging area from several threads at once, on one stream: each product reads its own."""
+    import threading
+    import torch
+    import paper_1905_10138_amd as xe
+    dev = torch.device("cuda:0")
+    _, enc = encoded_workload("large_q1", 4100, 1500)
+    L = pack_encoded(enc).to(dev)
+    g = torch.Generator(device=dev)
+    g.manual_seed(21)
+    xs = [torch.randn((L.n, 448 if i % 2 else 700), device=dev, generator=g) for i in range(8)]
+    want = [xe.spmm(L, x).clone() for x in xs]
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    got = [[] for _ in xs]
+
+    def work(i):
+        with torch.cuda.stream(stream):
+            for _ in range(12):
+                got[i].append(xe.spmm(L, xs[i]))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(xs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for i, w in enumerate(want):
+        assert len(got[i]) == 12 and all(torch.equal(y, w) for y in got[i]), i
