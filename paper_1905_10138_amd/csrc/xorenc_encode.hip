@@ -13,8 +13,10 @@
 // the smallest one read as an integer among equals.  A slice on which Algorithm 1 drops nothing has a solution
 // without mismatches, and back-substitution gives the smallest such input: its pivots are the columns that are not
 // sums of lower columns, so a free variable (a sum of lower columns) can be 0 whatever the higher variables are and
-// a pivot variable is determined by the higher ones.  Only the other slices are searched: they are listed, and
-// every one of the 2^n_in inputs is tried on them as a matrix product on the matrix cores (exhaustive_search_kernel).
+// a pivot variable is determined by the higher ones.  Only the other slices are searched.  Those with at most 32 care
+// bits are tried by syndrome first (fewest_patches): sets of one, two, three care bits whose flips make the equations
+// solvable.  The rest are listed, and every one of the 2^n_in inputs is tried on them as a matrix product on the matrix
+// cores (exhaustive_search_kernel).
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -98,6 +100,76 @@ __device__ inline void put_patches(uint64_t *pbits, const Counts &c, int p, int6
   }
 }
 
+// Fewest patches of one slice by syndrome: a wave, a care bit per lane, at most 32 of them (the equation of a lane's care
+// bit in `row`, the wanted bit on top; 0 beyond the last).  The rows are brought to reduced echelon form, pivots in ascending
+// columns; `sums` are the equations a reduced row is the sum of.  Where the coefficients of a reduced row vanish, its right-hand
+// side has to be 0: the flips of a set of care bits must change exactly those that are 1 (the syndrome), and change the
+// solution with free variables 0, the smallest one for this set, by the sum of the bits' columns.  The sets of one care bit
+// are tried, then of two and of three; the first size with a match is the minimum and its smallest solution the answer.
+// Returns false, for the whole wave, when no set of three or fewer matches.
+//
+// Bound: the chain of cross-lane reads, about 2 us a slice.  A search takes 2^n_in inputs: the 1500 of 360000 slices of
+// 16384 x 4096, S = 0.95, n_out = 192, n_in = 20 that need patches took 220 us of matrix instructions, now the pass over all
+// slices, which hides these waves behind its others, is 0.5 us longer and the search kernel returns after 4.5 us.
+__device__ bool fewest_patches(uint32_t row, int n_care, int n_in, uint32_t *x_out) {
+  const int lane = threadIdx.x & 63;
+  uint32_t sums = lane < n_care ? 1u << lane : 0u;
+  uint64_t pivots = 0;  // lanes whose row is a pivot row
+  uint32_t pivot_bit = 0;
+  for (int j = 0; j < n_in; ++j) {  // uniform
+    const bool set = (row >> j) & 1u;
+    const uint64_t from = __ballot(set) & ~pivots;
+    if (!from) continue;
+    const int k = __builtin_ctzll(from);
+    pivots |= 1ull << k;
+    const uint32_t pivot_row = __builtin_amdgcn_readlane(row, k), pivot_sums = __builtin_amdgcn_readlane(sums, k);
+    if (lane == k) {
+      pivot_bit = 1u << j;
+    } else if (set) {
+      row ^= pivot_row;
+      sums ^= pivot_sums;
+    }
+  }
+  // columns: what flipping this lane's care bit changes, in the vanished rows (numbered) and in the solution
+  uint32_t change = 0, change_x = 0, syndrome = 0, x0 = 0, number = 1;
+  for (int k = 0; k < n_care; ++k) {  // uniform
+    const uint32_t in = ((uint32_t)__builtin_amdgcn_readlane(sums, k) >> (lane & 31)) & 1u;
+    const uint32_t rhs = (uint32_t)__builtin_amdgcn_readlane(row, k) >> 31;
+    const uint32_t bit = __builtin_amdgcn_readlane(pivot_bit, k);
+    if (bit) {
+      change_x |= in * bit;
+      x0 |= rhs * bit;
+    } else {
+      change |= in * number;
+      syndrome |= rhs * number;
+      number <<= 1;
+    }
+  }
+  uint32_t best = 0xffffffffu;
+  if (lane < n_care && change == syndrome) best = x0 ^ change_x;
+  if (!__ballot(best != 0xffffffffu)) {
+    for (int i = 0; i < n_care; ++i) {
+      const uint32_t want = syndrome ^ __builtin_amdgcn_readlane(change, i);
+      if (lane < n_care && change == want) best = min(best, x0 ^ change_x ^ __builtin_amdgcn_readlane(change_x, i));
+    }
+  }
+  if (!__ballot(best != 0xffffffffu)) {
+    for (int i = 0; i < n_care; ++i) {
+      const uint32_t want_i = syndrome ^ __builtin_amdgcn_readlane(change, i);
+      const uint32_t x_i = x0 ^ __builtin_amdgcn_readlane(change_x, i);
+      for (int k = i + 1; k < n_care; ++k) {
+        const uint32_t want = want_i ^ __builtin_amdgcn_readlane(change, k);
+        if (lane < n_care && change == want) best = min(best, x_i ^ change_x ^ __builtin_amdgcn_readlane(change_x, k));
+      }
+    }
+  }
+  if (!__ballot(best != 0xffffffffu)) return false;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, o, 64));
+  *x_out = best;
+  return true;
+}
+
 // Algorithm 1.  The planes share the mask, so the coefficients of a slice's equations, which of them join the basis
 // and the pivots are the same for all planes: one elimination with Q right-hand sides, which travel in the bits above
 // the n_in coefficients of a row (PACKED: n_in + Q <= 32) or as bits per pivot in a register per plane.
@@ -108,12 +180,13 @@ __device__ inline void put_patches(uint64_t *pbits, const Counts &c, int p, int6
 // one elimination per plane and rows from the arguments.
 //
 // SEARCH: first pass of the encoder with the fewest patches, over the slices [first, first + n).  The low half of a
-// slice's first patch word becomes its key: the solution x (below 2^24) when nothing was dropped, otherwise all ones,
-// and the slice joins the list, whose entry i is the high half of the first patch word of slice i of the pass's
-// numbering; *list_len counts them.
+// slice's first patch word becomes its key: the solution x (below 2^24) when nothing was dropped, x with the lowest bit of
+// the mismatch count set when syndromes gave the fewest patches, otherwise all ones, and the slice joins the list, whose
+// entry i is the high half of the first patch word of slice i of the pass's numbering; *list_len counts them.  The
+// workgroup's waves take turns at the slices that are tried by syndrome (syndrome_care says which).
 template <int Q, bool PACKED, bool SEARCH>
 __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P, int64_t first, int64_t n,
-                                                                   uint32_t *list_len) {
+                                                                   uint32_t *list_len, SyndromeCare care) {
   extern __shared__ uint32_t enc_lds[];  // [n_in][ENC_THREADS] basis, then the 64 J rows of the network
   __shared__ uint32_t block_total[Q];
   uint32_t *const rows = enc_lds + P.n_in * ENC_THREADS;
@@ -132,18 +205,20 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P,
   uint32_t have = 0;         // bit j: a basis row with pivot j exists
   uint32_t rhsbits[Q] = {};  // !PACKED: bit j = right-hand side of that row
   bool dropped[Q] = {};
+  int n_care = 0;
   for (int w = 0; w < P.J; ++w) {  // uniform; care bits in ascending position over the whole slice
     const int64_t slot = slot0 + 32 * w;
-    uint64_t care = valid ? P.mask[slot] : 0ull;
+    uint64_t kept = valid ? P.mask[slot] : 0ull;  // care bits
+    if constexpr (SEARCH) n_care += __builtin_popcountll(kept);
     uint64_t bits[Q], patches[Q];
 #pragma unroll
     for (int p = 0; p < Q; ++p) {
       bits[p] = valid ? P.planes[p * P.n_slots + slot] : 0ull;
       patches[p] = 0;
     }
-    while (care) {
-      const int i = __builtin_ctzll(care);
-      care &= care - 1;
+    while (kept) {
+      const int i = __builtin_ctzll(kept);
+      kept &= kept - 1;
       uint32_t row = rows[64 * w + i];
       uint32_t rhs = 0;  // bit p: plane p
 #pragma unroll
@@ -198,20 +273,66 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P,
   for (int p = 0; p < Q; ++p) store_enc_unit(P.enc, p * P.n_eslots + eslot, n_in, x[p], valid);
   if constexpr (SEARCH) {
     uint32_t *const halves = reinterpret_cast<uint32_t *>(P.pbits);
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // The basis is not needed any more: its place takes the slices to be tried by syndrome (tid << 8 | care bits << 2 |
+    // plane) and a slice's equations per wave.  (n_in KB; the queue takes 1 KB per plane at most, and n_in is above ten.)
+    uint32_t *const queue = enc_lds + 32 * (ENC_THREADS / 64);
+    uint32_t *const queued = &block_total[0];  // (no counts are made in this pass)
+    auto put_on_list = [&](bool put, int p, int64_t entry_rel) {
+      const uint64_t listed = __ballot(put);
+      if (!listed) return;  // uniform
+      const int leader = __builtin_ctzll(listed);
+      uint32_t base = 0;
+      if (lane == leader) base = atomicAdd(list_len, (uint32_t)__builtin_popcountll(listed));
+      base = (uint32_t)__shfl((int)base, leader, 64);
+      if (put) {
+        const uint32_t at = base + (uint32_t)__builtin_popcountll(listed & ((1ull << lane) - 1ull));
+        halves[2 * entry_word(at, first, (uint32_t)n, P.n_slots, P.J) + 1] = (uint32_t)(p * n + entry_rel);
+      }
+    };
+    __syncthreads();
 #pragma unroll
     for (int p = 0; p < Q; ++p) {
       const bool search = valid && dropped[p];
       if (valid) halves[2 * (p * P.n_slots + slot0)] = search ? 0xffffffffu : x[p];
-      const uint64_t listed = __ballot(search);
-      if (listed) {
-        const int lane = tid & 63, leader = __builtin_ctzll(listed);
-        uint32_t base = 0;
-        if (lane == leader) base = atomicAdd(list_len, (uint32_t)__builtin_popcountll(listed));
-        base = (uint32_t)__shfl((int)base, leader, 64);
-        if (search) {
-          const uint32_t at = base + (uint32_t)__builtin_popcountll(listed & ((1ull << lane) - 1ull));
-          halves[2 * entry_word(at, first, (uint32_t)n, P.n_slots, P.J) + 1] = (uint32_t)(p * n + rel);
-        }
+      const bool by_syndrome = search && n_care <= care.few;
+      if (by_syndrome) queue[atomicAdd(queued, 1u)] = (uint32_t)tid << 8 | (uint32_t)n_care << 2 | (uint32_t)p;
+      put_on_list(search && !by_syndrome, p, rel);
+    }
+    __syncthreads();
+    const uint32_t n_queued = __builtin_amdgcn_readfirstlane(*queued);
+    const int most_care = n_queued <= (uint32_t)kSyndromeFew ? care.few : care.many;  // uniform for the workgroup
+    if (most_care < care.few) {
+      for (uint32_t i0 = 0; i0 < n_queued; i0 += ENC_THREADS) {  // uniform
+        const uint32_t e = i0 + tid < n_queued ? queue[i0 + tid] : 0u;
+        put_on_list((int)((e >> 2) & 63u) > most_care, (int)(e & 3u), (int64_t)blockIdx.x * ENC_THREADS + (e >> 8));
+      }
+    }
+    uint32_t *const eqs = enc_lds + 32 * wave;
+    for (uint32_t i = wave; i < n_queued; i += ENC_THREADS / 64) {  // uniform per wave
+      const uint32_t e = __builtin_amdgcn_readfirstlane(queue[i]);
+      if ((int)((e >> 2) & 63u) > most_care) continue;
+      const int p = (int)(e & 3u);
+      const int64_t r = (int64_t)blockIdx.x * ENC_THREADS + (e >> 8);
+      const int64_t word = first_word(first + r, P.J);
+      // lane = bit position; the care bits' equations move to lanes 0, 1, ...
+      int n_eqs = 0;
+      for (int w = 0; w < P.J; ++w) {  // uniform
+        const uint64_t kept = P.mask[word + 32 * w], bits = P.planes[p * P.n_slots + word + 32 * w];
+        if ((kept >> lane) & 1)
+          eqs[n_eqs + __builtin_popcountll(kept & ((1ull << lane) - 1ull))] =
+              rows[64 * w + lane] | (uint32_t)((bits >> lane) & 1) << 31;
+        n_eqs += __builtin_popcountll(kept);
+      }
+      n_eqs = __builtin_amdgcn_readfirstlane(n_eqs);
+      __builtin_amdgcn_wave_barrier();  // (LDS operations of a wave execute in order)
+      uint32_t xs = 0;
+      const bool found = fewest_patches(lane < n_eqs ? eqs[lane] : 0u, n_eqs, n_in, &xs);
+      __builtin_amdgcn_wave_barrier();
+      if (found) {  // uniform
+        if (lane == 0) halves[2 * (p * P.n_slots + word)] = 1u << 24 | xs;
+      } else {
+        put_on_list(lane == 0, p, r);
       }
     }
   } else {
@@ -249,8 +370,9 @@ __global__ void exhaustive_reset_kernel(uint32_t *list_len) { *list_len = 0; }
 // code order: one column of M flips the signs of A (4 XORs per 64 bits, shared by the four slice tiles).
 //
 // Bound: VALU issue beside the matrix instructions.  Every slice of 16384 x 4096, n_out = 192, n_in = 20 used to be
-// searched, one slice per lane, at 2J AND, 2J XOR and 2J population counts per input: 219 ms for the call, 0.30 ms now
-// (16384 x 4096 with half of the weights kept, n_out = 64, n_in = 16, where nearly every slice is searched: 14 and 5 ms).
+// searched, one slice per lane, at 2J AND, 2J XOR and 2J population counts per input: 219 ms for the call, 0.30 ms with the
+// slices that need patches in this kernel, 0.09 ms since syndromes leave it those they do not solve (16384 x 4096 with half
+// of the weights kept, n_out = 64, n_in = 16, where nearly every slice is searched here: 14 and 5 ms).
 // The width of an item falls from 2^15 to 2^10 inputs when there are too few slices to give every wave eight items.
 // ALL: every slice of the pass is searched, in one item each and without a list.  With few inputs that is cheaper than
 // the elimination that would sort out the slices that need no search, however few these are, and than joining the list
@@ -600,13 +722,15 @@ __global__ __launch_bounds__(ENC_THREADS) void emit_patches_kernel(const uint64_
 }
 
 template <int Q, bool SEARCH>
-void launch_slices(const EncParams &P, int64_t first, int64_t n, uint32_t *list_len, hipStream_t st) {
+void launch_slices(const EncParams &P, int64_t first, int64_t n, uint32_t *list_len, SyndromeCare care, hipStream_t st) {
   const dim3 grid((unsigned)((n + ENC_THREADS - 1) / ENC_THREADS));
   const size_t lds = ((size_t)P.n_in * ENC_THREADS + 64 * P.J) * sizeof(uint32_t);
   if (P.n_in + Q <= 32)
-    hipLaunchKernelGGL((encode_slices_kernel<Q, true, SEARCH>), grid, dim3(ENC_THREADS), lds, st, P, first, n, list_len);
+    hipLaunchKernelGGL((encode_slices_kernel<Q, true, SEARCH>), grid, dim3(ENC_THREADS), lds, st, P, first, n, list_len,
+                       care);
   else
-    hipLaunchKernelGGL((encode_slices_kernel<Q, false, SEARCH>), grid, dim3(ENC_THREADS), lds, st, P, first, n, list_len);
+    hipLaunchKernelGGL((encode_slices_kernel<Q, false, SEARCH>), grid, dim3(ENC_THREADS), lds, st, P, first, n, list_len,
+                       care);
 }
 
 template <int J>
@@ -620,12 +744,12 @@ void launch_search(bool all, dim3 search_grid, dim3 finish_grid, const ExhParams
 }
 
 template <bool SEARCH>
-void launch_slices_q(int q, const EncParams &P, int64_t first, int64_t n, uint32_t *list_len, hipStream_t st) {
+void launch_slices_q(int q, const EncParams &P, int64_t first, int64_t n, uint32_t *list_len, SyndromeCare care, hipStream_t st) {
   switch (q) {
-    case 1: launch_slices<1, SEARCH>(P, first, n, list_len, st); break;
-    case 2: launch_slices<2, SEARCH>(P, first, n, list_len, st); break;
-    case 3: launch_slices<3, SEARCH>(P, first, n, list_len, st); break;
-    default: launch_slices<4, SEARCH>(P, first, n, list_len, st); break;
+    case 1: launch_slices<1, SEARCH>(P, first, n, list_len, care, st); break;
+    case 2: launch_slices<2, SEARCH>(P, first, n, list_len, care, st); break;
+    case 3: launch_slices<3, SEARCH>(P, first, n, list_len, care, st); break;
+    default: launch_slices<4, SEARCH>(P, first, n, list_len, care, st); break;
   }
 }
 
@@ -678,7 +802,7 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
   P.J = J;
   for (int i = 0; i < XORENC_MAX_N_OUT; ++i) P.M_rows[i] = i < n_out ? M_rows[i] : 0u;
   if (!exhaustive) {
-    launch_slices_q<false>(q, P, 0, sz.n_eslots, nullptr, st);
+    launch_slices_q<false>(q, P, 0, sz.n_eslots, nullptr, SyndromeCare{}, st);
   } else {
     ExhParams E;
     E.mask = mask;
@@ -709,7 +833,7 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
       const bool all = n_in <= kAllMaxNIn;
       if (!all) {
         hipLaunchKernelGGL(exhaustive_reset_kernel, dim3(1), dim3(1), 0, st, list_len);
-        launch_slices_q<true>(q, P, first, n_pass, list_len, st);
+        launch_slices_q<true>(q, P, first, n_pass, list_len, syndrome_care(n_in, J, (n_pass + ENC_THREADS - 1) / ENC_THREADS), st);
       }
       switch (J) {
         case 1: launch_search<1>(all, sg, fg, E, first, n_pass, list_len, st); break;

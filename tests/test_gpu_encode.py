@@ -300,3 +300,43 @@ def test_fewest_patches_when_a_part_of_the_inputs_mismatches_everywhere(n_in, lo
     w_c, _, n_patch, d_patch = xe.unpack(L.to_host())
     ow, _, onp, odp, _ = paper_format_arrays(enc)
     assert np.array_equal(w_c, ow) and np.array_equal(n_patch, onp) and np.array_equal(d_patch, odp)
+
+
+@pytest.mark.parametrize("n_out,n_in,q,busy,copies", [
+    # the widths where the search over a list begins and the widest that the oracle lists whole; workgroups with few
+    # slices to search, with many, and (205 workgroups of slices of four words) with many that are worth their syndromes
+    (64, 11, 1, 12, 1), (64, 11, 2, 200, 1), (128, 13, 3, 5, 1), (192, 16, 1, 14, 1), (64, 16, 4, 4, 3),
+    (256, 16, 1, 220, 205)])
+def test_fewest_patches_by_syndrome(n_out, n_in, q, busy, copies):
+    """Slices with 1 to 40 kept bits (32 and n_in + 12 are the most that are tried by syndrome), some without a solution for
+    one to many bits; zero and equal rows in the network, so that short slices need patches as well.  256 slices, the
+    others of the workgroup solvable, against the oracle's search, bit for bit; every copy of them gives the same."""
+    import torch
+    import paper_1905_10138_amd as xe
+    from oracle import encoder
+    rng = np.random.default_rng(100 * n_in + n_out + busy)
+    m = 256
+    keep = np.zeros((m, n_out), dtype=bool)
+    for i, r in enumerate(rng.permutation(m)[:busy]):
+        keep[r, rng.permutation(n_out)[:1 + (i * 7 + 24) % 40]] = True
+    planes = (rng.random((q, m, n_out)) < 0.5) & keep
+    M = rng.integers(0, 2, size=(n_out, n_in), dtype=np.uint8)
+    M[::11] = 0
+    M[1::5] = M[2]
+    M[3::7] = M[4]
+    enc = encoder.encode(keep, planes, np.ones((q, m), np.float32), M, n_out, exhaustive=True)
+    ow, _, onp, odp, _ = paper_format_arrays(enc)
+    assert onp.max() > 3
+    keep, planes = np.tile(keep, (copies, 1)), np.tile(planes, (1, copies, 1))
+    dev = torch.device("cuda:0")
+    words = lambda a: torch.from_numpy(xe.pack_bits(a, n_out).view(np.int64))
+    M_rows = (M.astype(np.uint64) << np.arange(n_in, dtype=np.uint64)).sum(axis=1).astype(np.uint32)
+    L = xe.encode_exhaustive(m * copies, n_out, n_in, q, M_rows, words(keep).to(dev),
+                             torch.stack([words(p) for p in planes]).to(dev),
+                             torch.ones((q, m * copies), dtype=torch.float32, device=dev), n_out=n_out)
+    w_c, _, n_patch, d_patch = xe.unpack(L.to_host())
+    shape = (q, copies, m)
+    assert np.array_equal(np.asarray(w_c).reshape(shape), np.broadcast_to(np.asarray(ow).reshape(q, 1, m), shape))
+    assert np.array_equal(np.asarray(n_patch).reshape(shape), np.broadcast_to(np.asarray(onp).reshape(q, 1, m), shape))
+    per_plane = np.split(np.asarray(odp), np.cumsum(np.asarray(onp).reshape(q, -1).sum(axis=1))[:-1])
+    assert np.array_equal(np.asarray(d_patch), np.concatenate([np.tile(d, copies) for d in per_plane]))
