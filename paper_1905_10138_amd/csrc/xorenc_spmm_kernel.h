@@ -82,6 +82,37 @@ __device__ inline u32x4 split_load4(__amdgpu_buffer_rsrc_t r, uint32_t byte_off)
   return __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, kCoherentAux);
 }
 
+// One XOR table by one wave: entry v = XOR of the eight columns selected by the bits of v, lower and upper 32 rows next to
+// each other.  A lane builds the entries lane, lane + 64, lane + 128 and lane + 192.
+__device__ inline void build_xor_table(int lane, const uint32_t *col_lo, const uint32_t *col_hi, uint32_t *table) {
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int t = 0; t < 6; ++t)
+    if ((lane >> t) & 1) {
+      lo ^= col_lo[t];
+      hi ^= col_hi[t];
+    }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t klo = ((k & 1) ? col_lo[6] : 0u) ^ ((k & 2) ? col_lo[7] : 0u);
+    const uint32_t khi = ((k & 1) ? col_hi[6] : 0u) ^ ((k & 2) ? col_hi[7] : 0u);
+    *reinterpret_cast<uint2 *>(table + 2 * (64 * k + lane)) = make_uint2(lo ^ klo, hi ^ khi);
+  }
+}
+
+// The tables of every word of a slice, shared by a workgroup of `waves` waves.  Bound: the scalar loads of the columns, which
+// have to travel before anything is built.  A wave takes a table at a time, so that the waves' loads travel together; one
+// table after the other by all waves, each behind its own loads, took 1.5 us of every product with six tables (192-bit
+// slices, n_in = 16: 4096 x 4096, B = 32 8.2 -> 6.7 us) and 1.1 us with nine in spmm_tile_kernel.
+__device__ inline void build_shared_tables(const DevLayer &L, int wave, int waves, int lane, int J, int nib, uint32_t *lut,
+                                           int word_stride) {
+  for (int i = wave; i < J * nib; i += waves) {  // uniform
+    const int w = i / nib, b = i - w * nib;
+    build_xor_table(lane, L.Mcol_lo + w * XORENC_MAX_N_IN + 8 * b, L.Mcol_hi + w * XORENC_MAX_N_IN + 8 * b,
+                    lut + w * word_stride + 512 * b);
+  }
+}
+
 constexpr int largest_divisor_at_most(int n, int cap) {
   int best = 1;
   for (int d = 1; d <= n && d <= cap; ++d)
@@ -487,36 +518,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
 
   // ---- XOR tables T_b[v] = XOR of the columns 8b..8b+7 of M selected by the bits of v, and alpha
   if constexpr (PRIV_LUT) {
-    // each lane builds entries lane, lane+64, lane+128, lane+192 of its wave's copy
-    for (int b = 0; b < NIBT; ++b) {
-      uint32_t lo = 0, hi = 0;
-#pragma unroll
-      for (int t = 0; t < 6; ++t)
-        if ((lane >> t) & 1) {
-          lo ^= L.Mcol_lo[8 * b + t];
-          hi ^= L.Mcol_hi[8 * b + t];
-        }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t klo = ((k & 1) ? L.Mcol_lo[8 * b + 6] : 0u) ^ ((k & 2) ? L.Mcol_lo[8 * b + 7] : 0u);
-        const uint32_t khi = ((k & 1) ? L.Mcol_hi[8 * b + 6] : 0u) ^ ((k & 2) ? L.Mcol_hi[8 * b + 7] : 0u);
-        *reinterpret_cast<uint2 *>(lut + 2 * (b * 256 + 64 * k + lane)) = make_uint2(lo ^ klo, hi ^ khi);
-      }
-    }
+    for (int b = 0; b < NIBT; ++b) build_xor_table(lane, L.Mcol_lo + 8 * b, L.Mcol_hi + 8 * b, lut + 512 * b);
   } else {
-    for (int w = 0; w < l_J; ++w)      // uniform
-      for (int b = 0; b < nib; ++b)    // uniform
-        for (int v = tid; v < 256; v += NW * 64) {
-          uint32_t lo = 0, hi = 0;
-#pragma unroll
-          for (int t = 0; t < 8; ++t)
-            if ((v >> t) & 1) {
-              lo ^= L.Mcol_lo[w * XORENC_MAX_N_IN + 8 * b + t];
-              hi ^= L.Mcol_hi[w * XORENC_MAX_N_IN + 8 * b + t];
-            }
-          lut[w * LUT_WORD + 2 * (b * 256 + v)] = lo;
-          lut[w * LUT_WORD + 2 * (b * 256 + v) + 1] = hi;
-        }
+    build_shared_tables(L, wave, NW, lane, l_J, nib, lut, LUT_WORD);
   }
   for (int i = tid; i < Q * ROWS; i += NW * 64) {  // read only after the barrier that follows the loop
     const int p = i / ROWS, r = row0 + i % ROWS;

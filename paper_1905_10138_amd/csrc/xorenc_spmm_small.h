@@ -157,34 +157,9 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
 
   // ---- XOR tables and alpha
   if constexpr (PRIV_LUT) {
-    for (int b = 0; b < NIBT; ++b) {
-      uint32_t lo = 0, hi = 0;
-#pragma unroll
-      for (int t = 0; t < 6; ++t)
-        if ((lane >> t) & 1) {
-          lo ^= L.Mcol_lo[8 * b + t];
-          hi ^= L.Mcol_hi[8 * b + t];
-        }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t klo = ((k & 1) ? L.Mcol_lo[8 * b + 6] : 0u) ^ ((k & 2) ? L.Mcol_lo[8 * b + 7] : 0u);
-        const uint32_t khi = ((k & 1) ? L.Mcol_hi[8 * b + 6] : 0u) ^ ((k & 2) ? L.Mcol_hi[8 * b + 7] : 0u);
-        *reinterpret_cast<uint2 *>(lut + 2 * (b * 256 + 64 * k + lane)) = make_uint2(lo ^ klo, hi ^ khi);
-      }
-    }
+    for (int b = 0; b < NIBT; ++b) build_xor_table(lane, L.Mcol_lo + 8 * b, L.Mcol_hi + 8 * b, lut + 512 * b);
   } else {
-    for (int b = 0; b < NIBT; ++b)
-      for (int v = tid; v < 256; v += NW * 64) {
-        uint32_t lo = 0, hi = 0;
-#pragma unroll
-        for (int t = 0; t < 8; ++t)
-          if ((v >> t) & 1) {
-            lo ^= L.Mcol_lo[8 * b + t];
-            hi ^= L.Mcol_hi[8 * b + t];
-          }
-        lut[2 * (b * 256 + v)] = lo;
-        lut[2 * (b * 256 + v) + 1] = hi;
-      }
+    build_shared_tables(L, wave, NW, lane, 1, NIBT, lut, 0);
   }
   for (int i = tid; i < Q * ROWS; i += NW * 64) {
     const int p = i / ROWS, r = row0 + i % ROWS;

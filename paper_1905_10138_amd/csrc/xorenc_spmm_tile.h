@@ -246,19 +246,7 @@ __global__ __launch_bounds__(WR *KG * 64, 2) void spmm_tile_kernel(DevLayer L, c
   load_off(1);
 
   // ---- XOR tables and scales, shared by the workgroup
-  for (int w = 0; w < l_J; ++w)
-#pragma unroll
-    for (int b = 0; b < NIBT; ++b)
-      for (int v = tid; v < 256; v += NW * 64) {
-        uint32_t lo = 0, hi = 0;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const uint32_t on = 0u - ((uint32_t)(v >> t) & 1u);
-          lo ^= L.Mcol_lo[w * XORENC_MAX_N_IN + 8 * b + t] & on;
-          hi ^= L.Mcol_hi[w * XORENC_MAX_N_IN + 8 * b + t] & on;
-        }
-        *reinterpret_cast<uint2 *>(lut + 2 * ((w * NIBT + b) * 256 + v)) = make_uint2(lo, hi);
-      }
+  build_shared_tables(L, wave, NW, lane, l_J, NIBT, lut, NIBT * 512);
   for (int i = tid; i < Q * ROWS; i += NW * 64) {
     const int p = i / ROWS, r = row0 + i % ROWS;
     alpha_s[i] = (r < l_m) ? -0.5f * L.alpha[(int64_t)p * l_m + r] : 0.f;
