@@ -440,6 +440,19 @@ def test_long_patch_lists(name, m, n, n_out, n_in, B, S):
     assert rel_fro(got, want) <= 4e-7
 
 
+@pytest.mark.parametrize("name,n_out,n_in,S,B", [
+    # about two, four and eight entries per list, at most 64 in a wave's range (two slices for waves of eight and twelve):
+    # below and above the line from which a slice's entries are scattered together; one to three planes, one and two
+    # blocks of columns, few columns, wide slices
+    ("large_q1", 64, 12, 0.85, 8), ("large_q1", 64, 12, 0.8, 32), ("large_q1", 64, 12, 0.78, 64), ("large_q2", 64, 16, 0.8, 8),
+    ("large_q2", 64, 13, 0.8, 33), ("lstm", 64, 16, 0.8, 24), ("lstm", 64, 13, 0.85, 40), ("large_q1", 192, 28, 0.82, 24),
+    ("large_q2", 128, 22, 0.8, 64)])
+@pytest.mark.parametrize("m,n", [(70, 500), (257, 1030), (1000, 2040)])
+def test_lists_with_several_entries_per_slice(name, n_out, n_in, S, B, m, n):
+    got, want = _run(name, m, n, B, "bf16", S=S, n_out=n_out, n_in=n_in, every_output=True)
+    assert rel_fro(got, want) <= 4e-7
+
+
 @pytest.mark.parametrize("name,m,n,n_out,n_in,S,calls", [
     # (columns, padding of the rows of X): one column block and two, ragged last pieces, parts of the staging area
     ("large_q1", 4100, 1500, 64, 8, None, [(1, 0), (9, 0), (32, 0), (33, 3), (64, 0), (300, 1)]),
