@@ -1136,19 +1136,11 @@ int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float 
   constexpr int NR = XF32 ? (32 * NCB) / 3 : 32 * NCB;
   const int row_groups = (D.nrb + RB - 1) / RB;
   const int col_groups = (B + NR - 1) / NR;
-  // split the reduction dimension across workgroups only when the tile grid alone cannot fill
-  // the chip; every wave should still own at least one slice
-  int ks = 1;
-  const int base = row_groups * col_groups;
-  const int max_ks = (D.spr + NW - 1) / NW;
-  // at most 256 workgroups: these variants run one per CU, and a second round would pay prologue and epilogue again
-  if (base < kSplitMaxGroups && 32 * RB * NR <= kSplitTileFloats && D.split_part && D.split_ticket)
-    ks = max(1, min(min(max_ks, kSplitMaxGroups / base), 4));  // (the last workgroup of a tile reads every part)
-  int sps = (D.spr + ks - 1) / ks;
-  sps = (sps + NW - 1) / NW * NW;
-  ks = (D.spr + sps - 1) / sps;
-  const dim3 grid(row_groups, col_groups, ks);
-  const int atomic = ks;  // number of splits: the kernel reduces them through the scratch area when > 1
+  const ReductionCut cut = cut_reduction(CutVariant{Q, NCB, RB, NW, D.J == 1, TERMS > 1, XF32}, D.spr, row_groups, col_groups,
+                                         D.split_part && D.split_ticket);
+  const int sps = cut.sps;
+  const dim3 grid(row_groups, col_groups, cut.ks);
+  const int atomic = cut.ks;  // number of splits: the kernel reduces them through the scratch area when > 1
   // JMODE: 1 = slices of one 64-bit word only, 4 = up to four words (more table space), 0 = both
   if (D.J > 1 && JMODE == 1) return XORENC_EUNSUPPORTED;
   const bool wide = (JMODE == 4) || (JMODE == 0 && D.J > 1);
@@ -1224,31 +1216,49 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
   // Small layers take 32-row tiles: twice the workgroups (still one round), half the accumulators and half the tile
   // exchange per wave.  It pays while a wave's share of the reduction stays short (measured: up to eight slices
   // per wave it wins, 2048 x 16384 at B = 64 14.4 against 16.8 us; at sixteen it loses, 8192 x 8192 19.7 against
-  // 16.6 us): slices per wave with 32-row tiles, nw waves and the split launch_spmm would choose.
+  // 16.6 us): slices per wave with 32-row tiles, nw waves and the most workgroups per tile.
   auto rb1_slices_per_wave = [&](int nw, int col_groups) {
     const int64_t tiles = (int64_t)D.nrb * col_groups;
     if (tiles > kSplitMaxGroups) return 1 << 30;
     int ks = 1;
-    if (tiles < kSplitMaxGroups) ks = max(1, min(min((D.spr + nw - 1) / nw, (int)(kSplitMaxGroups / tiles)), 4));
+    if (tiles < kSplitMaxGroups) ks = max(1, min(min((D.spr + nw - 1) / nw, (int)(kSplitMaxGroups / tiles)), kSplitMaxParts));
     const int sps = (D.spr + ks - 1) / ks;
     return (sps + nw - 1) / nw;
   };
   const bool small_wide = rb1_slices_per_wave(8, (B + 63) / 64) <= 8;    // 33 and more columns, eight waves
   const bool small_block = rb1_slices_per_wave(12, blocks) <= 8;         // one column block, twelve waves
   const bool small_narrow = rb1_slices_per_wave(12, 1) <= 12;            // at most eight columns
+  // Among 32-row tiles: eight or twelve waves, one or two blocks of columns, by the estimate of cut_reduction.  Twelve
+  // waves have shorter shares and more partial tiles to add (2048 x 4096, B = 8 6.4 against 6.7 us; 1024 x 1024, three
+  // planes 6.4 against 6.2); one block of columns spares the meeting of workgroups while its tiles fit one round
+  // (2048 x 2048, B = 64 5.9 against 7.8 us; 2048 x 8192 10.6 against 10.0).
+  auto estimate = [&](int ncb, int nw) {
+    const int groups = (blocks + ncb - 1) / ncb;
+    if ((int64_t)D.nrb * groups > kSplitMaxGroups) return 1e9;
+    return cut_reduction(CutVariant{Q, ncb, 1, nw, D.J == 1, false, false}, D.spr, D.nrb, groups,
+                         D.split_part && D.split_ticket).us;
+  };
+  const bool eight_waves = estimate(1, 8) <= estimate(1, 12);
+  const bool one_block = estimate(1, 8) < estimate(2, 8);
   if constexpr (Q == 1) {
     if (!x_fast) {
       if (blocks == 1) return launch_spmm<1, Q, 2, false, 16, 1, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
       return launch_spmm<2, Q, 2, false, 8, 2, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
-    if (B <= 8 && D.J == 1 && small_narrow) return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (B <= 8 && D.J == 1 && small_narrow) {
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
     // more than one round of 64-row tiles: four-wave workgroups, several per CU, so that one's prologue and epilogue
     // overlap another's loop (65536 x 4096 at B = 8: 28.9 against 30.4 us)
     if (B <= 8 && D.J == 1 && D.nib_variant <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
       return launch_spmm<1, Q, 2, false, 4, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (B <= 8 && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
-    // (small layers: 32-row tiles while they fit one round, see below; 4096 x 4096 at B = 32: 7.5 against 8.6 us)
-    if (blocks == 1 && D.J == 1 && small_block) return launch_spmm<1, Q, 1, false, 12, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    // (small layers: 32-row tiles while they fit one round, see above)
+    if (blocks == 1 && D.J == 1 && small_block) {
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
     // (several rounds: four-wave workgroups as above; 65536 x 4096 at B = 32: 32.5 against 34.8 us)
     if (blocks == 1 && D.J == 1 && D.nib_variant <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
       return launch_spmm<1, Q, 2, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
@@ -1261,16 +1271,23 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
     if (D.J == 1 && D.nib_variant <= 2 && tiles128 > 256)
       return launch_spmm<2, Q, 4, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (D.J == 1 && tiles128 >= 200) return launch_spmm<2, Q, 4, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-    // (small layers, see above; 2048 x 2048 at B = 64: 7.6 against 9.3 us, 4096 x 4096: 9.4 against 11.5 us)
-    if (D.J == 1 && small_wide) return launch_spmm<2, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (D.J == 1 && small_wide) {
+      if (one_block) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<2, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
     return launch_spmm<2, Q, 2, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
   } else if constexpr (Q == 2) {
-    if (B <= 8 && x_fast && D.J == 1 && small_narrow) return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (B <= 8 && x_fast && D.J == 1 && small_narrow) {
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
     if (B <= 8 && x_fast && D.J == 1 && D.nib_variant <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
       return launch_spmm<1, Q, 2, false, 4, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (B <= 8 && x_fast && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (blocks == 1 && x_fast && D.J == 1 && small_block)
+    if (blocks == 1 && x_fast && D.J == 1 && small_block) {
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
       return launch_spmm<1, Q, 1, false, 12, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
     if (blocks == 1 && x_fast) return launch_spmm<1, Q, 2, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (blocks == 1) return launch_spmm<1, Q, 2, false>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (!x_fast) return launch_spmm<2, Q, 1, false, 8, 2, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
@@ -1281,14 +1298,19 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
     const int64_t tiles64 = (int64_t)((D.nrb + 1) / 2) * ((B + 63) / 64);
     if (D.nib_variant <= 2 && tiles64 > 256) return launch_spmm<2, Q, 2, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (tiles64 >= 200) return launch_spmm<2, Q, 2, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (one_block) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     return launch_spmm<2, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
   } else if constexpr (Q == 3) {
-    // (12 waves with one slice buffer: measured 13.2 against 18.9 us with 8 waves and two buffers, 6000 x 3000, B = 32)
-    if (B <= 8 && x_fast && D.J == 1 && small_narrow) return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (B <= 8 && x_fast && D.J == 1 && small_narrow) {
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
     if (B <= 8 && x_fast && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     // (32-row tiles on small layers: 6000 x 3000 at B = 32 9.8 against 12.3 us)
-    if (x_fast && D.J == 1 && small_block)
+    if (x_fast && D.J == 1 && small_block) {
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
       return launch_spmm<1, Q, 1, false, 12, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
     if (x_fast) return launch_spmm<1, Q, 2, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     return launch_spmm<1, Q, 2, false>(D, X, ldx, B, Y, ldy, x_fast, st);
   } else {

@@ -440,6 +440,16 @@ def test_long_patch_lists(name, m, n, n_out, n_in, B, S):
     assert rel_fro(got, want) <= 4e-7
 
 
+@pytest.mark.parametrize("name,n_out,n_in", [("large_q1", 64, 8), ("large_q2", 64, 16), ("lstm", 64, 24), ("large_q1", 64, 27)])
+@pytest.mark.parametrize("B", [8, 9, 32, 33, 64, 65, 128])
+@pytest.mark.parametrize("m,n", [(31, 64), (257, 520), (1000, 1100), (2049, 2100), (500, 8200)])
+def test_small_layers_over_all_cuts_of_the_reduction(name, n_out, n_in, B, m, n):
+    """Layers of one round of 32-row tiles: eight and twelve waves, one and two blocks of columns, one to four workgroups per
+    tile, with waves and parts that get no word of a row."""
+    got, want = _run(name, m, n, B, "bf16", n_out=n_out, n_in=n_in, every_output=True)
+    assert rel_fro(got, want) <= 4e-7
+
+
 @pytest.mark.parametrize("name,n_out,n_in,S,B", [
     # about two, four and eight entries per list, at most 64 in a wave's range (two slices for waves of eight and twelve):
     # below and above the line from which a slice's entries are scattered together; one to three planes, one and two

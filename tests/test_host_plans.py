@@ -118,6 +118,45 @@ def test_parts_of_the_few_column_kernel_fit_the_scratch_area(tmp_path):
     run_program(tmp_path, SMALL_SPLIT)
 
 
+CUT = r"""
+#include <cstdio>
+#include "xorenc_split_plan.h"
+
+#define CHECK(e) do { if (!(e)) { std::printf("q=%d cols=%d rows=%d waves=%d spr=%d groups=%d x %d scratch=%d ks=%d sps=%d: %s\n", \
+    v.q, v.col_blocks, v.row_blocks, v.waves, spr, rg, cg, scratch, c.ks, c.sps, #e); return false; } } while (0)
+
+static bool check(const CutVariant &v, int spr, int rg, int cg, bool scratch) {
+  const ReductionCut c = cut_reduction(v, spr, rg, cg, scratch);
+  CHECK(c.sps >= 1 && c.sps % v.waves == 0);  // whole words per wave
+  CHECK((int64_t)c.ks * c.sps >= spr && (int64_t)(c.ks - 1) * c.sps < spr);  // every word once, no empty part
+  CHECK(c.ks >= 1 && c.ks <= kSplitMaxParts && c.us > 0.0);
+  if (c.ks > 1) {
+    CHECK(scratch && (int64_t)rg * cg * c.ks <= kSplitMaxGroups);  // tickets and parts
+    CHECK(32 * v.row_blocks * (v.convert_x ? 32 : 32 * v.col_blocks) <= kSplitTileFloats);
+  }
+  return true;
+}
+
+int main() {
+  for (int q = 1; q <= 4; ++q)
+    for (int cols : {1, 2, 3})
+      for (int rows : {1, 2, 4})
+        for (int waves : {4, 8, 12, 16})
+          for (int kind = 0; kind < 6; ++kind)
+            for (int rg : {1, 2, 7, 63, 64, 65, 127, 128, 129, 255, 256, 257, 512, 30000})
+              for (int cg : {1, 2, 4, 5, 33})
+                for (int spr = 1; spr <= 2000; spr += spr < 100 ? 1 : 131)
+                  for (int scratch = 0; scratch < 2; ++scratch)
+                    if (!check(CutVariant{q, cols, rows, waves, kind % 2 == 0, kind / 2 == 1, kind / 2 == 2}, spr, rg, cg, scratch)) return 1;
+  return 0;
+}
+"""
+
+
+def test_cuts_of_the_reduction_cover_it_and_fit_the_scratch_area(tmp_path):
+    run_program(tmp_path, CUT)
+
+
 SCRATCH_OWNERS = r"""
 #include <cstdio>
 #include <set>
