@@ -15,7 +15,7 @@
 // fully independent until the final reduction: each wave streams the 64 rows of X that belong to
 // its current slice through private LDS buffers and gathers its B operands from them with the
 // transposing LDS read, so the main loop has no workgroup barrier.  Aligned bf16 X goes from global
-// memory straight into LDS (two slice buffers per wave, requested a slice and a half ahead); any
+// memory straight into LDS (one slice buffer per wave, requested a slice ahead); any
 // other X passes through registers (one buffer).  Lane (rl = lane%32, g = lane/32) holds the
 // 32-bit half g of the slice of row rl of each row block.
 //
@@ -130,20 +130,18 @@ struct BoolC {
 // NIBV: the layer's nib_variant (number of byte-indexed tables, one or two dwords per field; nib_variant_of), or 0:
 // any n_in, read from the layer at run time (only for X that has to be fetched element by element).
 // JT = most 64-bit words per slice the variant has table space for: 1 (n_out = 64) or 4 (n_out up to 256).
-// PD = slice buffers per wave on the direct path: 2 (loads a slice and a half ahead, two waves per
-// SIMD hide each other's waits) or 1 (loads one slice ahead, more waves per SIMD do the hiding).
 // NARROW: at most eight columns of X (one 16-byte chunk per row): a slice of X is 1 KB and arrives with a
 // single direct load; the operand lanes of the 24 padding columns read the same chunk again.
 // TERMS = 3: fp32 X that a kernel before this one has split into three bf16 matrices (hi, mid, lo, one after the other,
 // each of 64 rows per word of a row of W).  The wave walks over the three slices of X of every slice of W with the same
 // operands; hi has accumulators of its own, so that the sums of the large terms are rounded as they would be alone.
-template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBV, int JT, bool NARROW = false, int TERMS = 1>
+template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int NIBV, int JT, bool NARROW = false, int TERMS = 1>
 __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void spmm_kernel(DevLayer L, const void *__restrict__ Xv, int64_t ldx, int B,
                                                       float *__restrict__ Y, int64_t ldy, int slices_per_split,
                                                       int n_splits) {
   constexpr int CW = 32 * NCB;                 // bf16 columns held in LDS per X row
   // XDIR: bf16 X with 16-byte aligned rows goes from global memory straight into LDS (no register
-  // staging); the wave then owns two unpadded, swizzled slice buffers.  Otherwise X passes through
+  // staging); the wave then owns one unpadded, swizzled slice buffer.  Otherwise X passes through
   // registers into one padded buffer.
   constexpr bool XDIR = XFAST && !XF32;
   static_assert(!NARROW || (XDIR && NCB == 1), "narrow rows of X exist on the direct path with one column block");
@@ -151,12 +149,12 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   constexpr int XSL = 64 * RSB;                     // the 64 X rows of one slice
   constexpr int NIBT = tables_of_variant(NIBV);
   constexpr int KC = RB * (1 + Q * (two_dwords_of_variant(NIBV) ? 2 : 1));  // compressed dwords per lane and slice (XDIR)
-  // With one slice buffer the staging area also takes the patch offsets of the wave's range (one dword
+  // The staging area also takes the patch offsets of the wave's range (one dword
   // per lane, row block and plane), fetched ahead of everything else.
-  constexpr bool OFF_DMA = XDIR && PD == 1;
+  constexpr bool OFF_DMA = XDIR;
   constexpr int KO = OFF_DMA ? RB * Q : 0;
   constexpr int CSL = (KC + KO) * 256;                    // staging area of one slice (XDIR)
-  constexpr int XBUF0 = XDIR ? PD * (XSL + CSL) : XSL;     // one wave's LDS share (PD slice buffers)
+  constexpr int XBUF0 = XDIR ? XSL + CSL : XSL;  // one wave's LDS share
   constexpr int ROWS = 32 * RB;
   constexpr int NR = XF32 ? CW / 3 : CW;       // real X columns per workgroup
   constexpr int NCH = NARROW ? 1 : XF32 ? NR / 4 : CW / 8;  // 16-byte chunks per X row in global memory
@@ -177,7 +175,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   constexpr int LDSB0 = (NW * XBUF0 > NREG * TILE * 4) ? NW * XBUF0 : NREG * TILE * 4;
   // Flip words of GS slices (long patch lists), [slice][row block and plane][lane], zero between groups: they lie behind
   // the slice buffers, mostly where the reduction tiles will be.  Four slices if they fit without taking the room of the
-  // tables, else two or one; without any room (two slice buffers and the tables of wide slices) the patches of long
+  // tables, else two or one; without any room the patches of long
   // lists are applied entry by entry, and so they are with six lists per wave, whose state spilled 50 registers.
   constexpr int FLIP1 = RB * Q * 256;                          // one slice
   constexpr int LDS_REST = JT * NIBMAX * 2048 + Q * ROWS * 4;  // shared tables, scales
@@ -284,17 +282,17 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   const int xch = XDIR ? ((lane % NCH) ^ swz_of_pos(lane / NCH)) : (XFAST ? lane % NCH : 0);
   const uint32_t x_lane_off = (uint32_t)(xrow * row_bytes) + ((col0 + xch * EPC < B) ? xch * 16 : 0);
   const uint32_t x_lds_off = XFAST ? (uint32_t)(xrow * RSB + xch * 16) : (uint32_t)(lane * RSB);
-  // direct global -> LDS copy of slice s into slice buffer `which` of this wave (XDIR)
+  // direct global -> LDS copy of slice s into this wave's slice buffer (XDIR)
   const uint64_t x_base = reinterpret_cast<uint64_t>(static_cast<const uint8_t *>(Xv) + (int64_t)col0 * ESZ);
   const u32x4 xdesc = {(uint32_t)x_base, (uint32_t)(x_base >> 32) & 0xffffu, x_extent, kRsrcFlags};
   const uint32_t xbuf_lds = __builtin_amdgcn_readfirstlane(
       (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)(xbuf));
-  auto dma_x = [&](int s, int which, int term = 0) {
+  auto dma_x = [&](int s, int term = 0) {
     const uint32_t sbase = (uint32_t)(s * 64 * row_bytes) + (TERMS > 1 ? (uint32_t)term * term_bytes : 0u);  // uniform
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const uint32_t so = __builtin_amdgcn_readfirstlane(sbase + (uint32_t)(row_of_pos(i << LB) * row_bytes));
-      const uint32_t dst = __builtin_amdgcn_readfirstlane(xbuf_lds + (uint32_t)(which * XSL + i * 1024));
+      const uint32_t dst = __builtin_amdgcn_readfirstlane(xbuf_lds + (uint32_t)(i * 1024));
       asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(dst), "v"(x_lane_off),
                    "s"(xdesc), "s"(so)
                    : "memory");
@@ -412,7 +410,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
                        (uint32_t)(reinterpret_cast<uint64_t>(l_enc) >> 32) & 0xffffu,
                        enc_bytes, kRsrcFlags};
   constexpr int NGRP = NCH + KC;  // loads per slice
-  uint32_t *const cbuf = reinterpret_cast<uint32_t *>(xbuf + (XDIR ? PD * XSL : 0));  // after the X slices
+  uint32_t *const cbuf = reinterpret_cast<uint32_t *>(xbuf + (XDIR ? XSL : 0));  // after the X slice
   const uint32_t cbuf_lds = __builtin_amdgcn_readfirstlane(
       (uint32_t)(size_t)(__attribute__((address_space(3))) uint32_t *)(cbuf));
   auto dma_dword = [&](uint32_t lds_addr, uint32_t lane_off, const u32x4 &desc, uint32_t so) {
@@ -421,8 +419,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
                  "v"(lane_off), "s"(desc), "s"(__builtin_amdgcn_readfirstlane(so))
                  : "memory");
   };
-  auto load_comp_hidden = [&](int s, int which) {
-    int k = which * KC;
+  auto load_comp_hidden = [&](int s) {
+    int k = 0;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       const uint32_t u = (uint32_t)((blockIdx.x * RB + rb) * l_spr + s);  // uniform
@@ -436,8 +434,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
       }
     }
   };
-  auto read_comp = [&](int which, Comp &c) {
-    int k = which * KC;
+  auto read_comp = [&](Comp &c) {
+    int k = 0;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
       c.mw[rb] = cbuf[(k++) * 64 + lane];
@@ -448,13 +446,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
       }
     }
   };
-  // loads return in order: all of them, or all but the newest slice's, have landed
-  auto wait_loads = [&](bool newer_group_in_flight) {
-    if (newer_group_in_flight)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NGRP) : "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  };
+  auto wait_loads = [&] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
 
   // ---- first loads go out before anything else so that they overlap the table build
   Comp ring[2];
@@ -477,12 +469,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   }
   if constexpr (XDIR) {
     if (cnt > 0) {
-      load_comp_hidden(w0, 0);
-      dma_x(w0, 0);
-    }
-    if (PD == 2 && cnt > 1) {
-      load_comp_hidden(w0 + 1, 1);
-      dma_x(w0 + 1, 1);
+      load_comp_hidden(w0);
+      dma_x(w0);
     }
   } else {
     if (cnt > 0) {
@@ -575,7 +563,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[p][rb][cb][i] = 0.f;
 
-  static_assert(TERMS == 1 || (TERMS == 3 && XDIR && PD == 1 && !NARROW), "split X runs on the direct path with one buffer");
+  static_assert(TERMS == 1 || (TERMS == 3 && XDIR && !NARROW), "split X runs on the direct path");
   f32x16 acc_low[TERMS > 1 ? Q : 1][TERMS > 1 ? RB : 1][TERMS > 1 ? NCB : 1];  // mid and lo
   if constexpr (TERMS > 1) {
 #pragma unroll
@@ -644,14 +632,14 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
       }
   };
   // B operands of MFMA step t of the slice currently in LDS
-  auto read_bfrag = [&](int t, bf16x8(&bf)[NCB], int which) {
+  auto read_bfrag = [&](int t, bf16x8(&bf)[NCB]) {
     const int par = t >> 1, e = t & 1;
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
       s16x4 lo, hi;
       if constexpr (XDIR) {
         // X rows +par, +2e, +16 are row positions +4, +8, +16
-        const uint8_t *src = xbuf + which * XSL + tr_off[cb] + (4 * par + 8 * e) * RSB;
+        const uint8_t *src = xbuf + tr_off[cb] + (4 * par + 8 * e) * RSB;
         lo = lds_read_tr16(src);
         hi = lds_read_tr16(src + 16 * RSB);
       } else {
@@ -755,9 +743,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
     bf16x8 bfrag[4][NCB];
     uint32_t Snext[RB][Q];
     if constexpr (XDIR) {
-      // both prologue slices have landed in LDS, their compressed words in registers
-      wait_loads(false);
-      read_comp(0, ring[0]);
+      // the first slice has landed in LDS
+      wait_loads();
+      read_comp(ring[0]);
       // the compiler places its own wait for the patch words here, not at their first use in the loop
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
@@ -773,19 +761,19 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
       if (cnt > 1) load_x(w0 + 1, xr);
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) read_bfrag(t, bfrag[t], 0);
+    for (int t = 0; t < 4; ++t) read_bfrag(t, bfrag[t]);
     lookup(ring[0], Snext, w0);
-    if constexpr (XDIR && PD == 1) {
+    if constexpr (XDIR) {
       if (cnt > 1) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the buffers have been read out
         if constexpr (TERMS == 1) {
-          dma_x(w0 + 1, 0);
-          load_comp_hidden(w0 + 1, 0);
+          dma_x(w0 + 1);
+          load_comp_hidden(w0 + 1);
         }
       }
       if constexpr (TERMS > 1) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        dma_x(w0, 0, 1);
+        dma_x(w0, 1);
       }
     }
 
@@ -886,25 +874,25 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
                 }
             if (term < TERMS - 1 || has_next) {  // uniform
               __builtin_amdgcn_sched_barrier(0);
-              wait_loads(false);
+              wait_loads();
               __builtin_amdgcn_sched_barrier(0);
               if (term == TERMS - 1) {
-                read_comp(0, ring[d ^ 1]);
+                read_comp(ring[d ^ 1]);
                 lookup(ring[d ^ 1], Snext, s + 1);
               }
 #pragma unroll
-              for (int t = 0; t < 4; ++t) read_bfrag(t, bfrag[t], 0);
+              for (int t = 0; t < 4; ++t) read_bfrag(t, bfrag[t]);
               __builtin_amdgcn_sched_barrier(0);
               asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
               if (term == 0) {
-                dma_x(s, 0, 2);
+                dma_x(s, 2);
               } else if (term == 1) {
                 if (has_next) {
-                  dma_x(s + 1, 0, 0);
-                  load_comp_hidden(s + 1, 0);
+                  dma_x(s + 1, 0);
+                  load_comp_hidden(s + 1);
                 }
               } else {
-                dma_x(s + 1, 0, 1);
+                dma_x(s + 1, 1);
               }
               __builtin_amdgcn_sched_barrier(0);
             }
@@ -912,55 +900,28 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
           continue;
         }
         mfma_step(0);
-        if constexpr (XDIR && PD == 1) {
-          // one buffer: slice s is entirely in operand registers, slice s+1 is landing; it is read
+        if constexpr (XDIR) {
+          // slice s is entirely in operand registers, slice s+1 is landing; it is read
           // out at the end of the iteration and the buffer handed to slice s+2
           mfma_step(1);
           mfma_step(2);
           mfma_step(3);
           if (has_next) {
             __builtin_amdgcn_sched_barrier(0);
-            wait_loads(false);
+            wait_loads();
             __builtin_amdgcn_sched_barrier(0);
-            read_comp(0, ring[d ^ 1]);
+            read_comp(ring[d ^ 1]);
             lookup(ring[d ^ 1], Snext, s + 1);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) read_bfrag(t, bfrag[t], 0);
+            for (int t = 0; t < 4; ++t) read_bfrag(t, bfrag[t]);
             if (s + 2 < w1) {
               __builtin_amdgcn_sched_barrier(0);
               asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-              dma_x(s + 2, 0);
-              load_comp_hidden(s + 2, 0);
+              dma_x(s + 2);
+              load_comp_hidden(s + 2);
               __builtin_amdgcn_sched_barrier(0);
             }
           }
-        } else if constexpr (XDIR) {
-          // Slice buffer d (slice s) has no reader left once the operand reads issued during the
-          // previous iteration have returned, so slice s+2 starts to land in it now; its compressed
-          // words replace those of slice s, which the interleave above was the last to use.
-          const bool more = s + 2 < w1;
-          __builtin_amdgcn_sched_barrier(0);
-          if (more) {
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            dma_x(s + 2, d);
-            load_comp_hidden(s + 2, d);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          mfma_step(1);
-          // slice s+1 was requested one iteration ago: wait for it (not for slice s+2)
-          __builtin_amdgcn_sched_barrier(0);
-          wait_loads(more);
-          __builtin_amdgcn_sched_barrier(0);
-          if (has_next) {
-            read_comp(d ^ 1, ring[d ^ 1]);
-            lookup(ring[d ^ 1], Snext, s + 1);
-            read_bfrag(0, bfrag[0], d ^ 1);
-            read_bfrag(1, bfrag[1], d ^ 1);
-          }
-          mfma_step(2);
-          if (has_next) read_bfrag(2, bfrag[2], d ^ 1);
-          mfma_step(3);
-          if (has_next) read_bfrag(3, bfrag[3], d ^ 1);
         } else {
           mfma_step(1);
           // all operands of slice s are in registers: the LDS buffer takes slice s+1, whose operand
@@ -971,14 +932,14 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
             load_x(s + 2, xr);
           }
           if (has_next) {
-            read_bfrag(0, bfrag[0], d ^ 1);
-            read_bfrag(1, bfrag[1], d ^ 1);
+            read_bfrag(0, bfrag[0]);
+            read_bfrag(1, bfrag[1]);
           }
           mfma_step(2);
-          if (has_next) read_bfrag(2, bfrag[2], d ^ 1);
+          if (has_next) read_bfrag(2, bfrag[2]);
           mfma_step(3);
           if (has_next) {
-            read_bfrag(3, bfrag[3], d ^ 1);
+            read_bfrag(3, bfrag[3]);
             lookup(ring[d ^ 1], Snext, s + 1);
           }
         }
@@ -1121,16 +1082,16 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   }
 }
 
-template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int PD, int NIBV, int JT, bool NARROW = false, int TERMS = 1>
+template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int NIBV, int JT, bool NARROW = false, int TERMS = 1>
 inline void launch_variant(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y, int64_t ldy, dim3 grid,
                            int sps, int n_splits, hipStream_t st) {
-  hipLaunchKernelGGL((spmm_kernel<NCB, Q, RB, XF32, NW, XFAST, PD, NIBV, JT, NARROW, TERMS>), grid, dim3(NW * 64), 0, st, D, X,
+  hipLaunchKernelGGL((spmm_kernel<NCB, Q, RB, XF32, NW, XFAST, NIBV, JT, NARROW, TERMS>), grid, dim3(NW * 64), 0, st, D, X,
                      ldx, B, Y, ldy, sps, n_splits);
 }
 
 // XMODE: 0 = the call site may see either layout, 1 = aligned X only, 2 = generic X only (keeps
 // variants that are never launched from being compiled)
-template <int NCB, int Q, int RB, bool XF32, int NW = 8, int PD = 2, int XMODE = 0, int JMODE = 0, bool NARROW = false, int TERMS = 1>
+template <int NCB, int Q, int RB, bool XF32, int NW = 8, int XMODE = 0, int JMODE = 0, bool NARROW = false, int TERMS = 1>
 int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y, int64_t ldy, int x_fast,
                     hipStream_t st) {
   constexpr int NR = XF32 ? (32 * NCB) / 3 : 32 * NCB;
@@ -1147,9 +1108,9 @@ int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float 
   if (!x_fast) {
     if constexpr (XMODE != 1) {
       if constexpr (JMODE != 1)
-        if (wide) launch_variant<NCB, Q, RB, XF32, NW, false, 1, 0, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
+        if (wide) launch_variant<NCB, Q, RB, XF32, NW, false, 0, 4>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
       if constexpr (JMODE != 4)
-        if (!wide) launch_variant<NCB, Q, RB, XF32, NW, false, 1, 0, 1>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
+        if (!wide) launch_variant<NCB, Q, RB, XF32, NW, false, 0, 1>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
     } else {
       return XORENC_EUNSUPPORTED;
     }
@@ -1158,28 +1119,28 @@ int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float 
   } else {
     if constexpr (JMODE != 1)
       if (wide) switch (D.nib_variant) {
-          case 1: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 1, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          case 2: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 2, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          case 3: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 3, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          case 4: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 4, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          default: launch_variant<NCB, Q, RB, XF32, NW, true, PD, kFourTablesTwoDwords, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 1: launch_variant<NCB, Q, RB, XF32, NW, true, 1, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 2: launch_variant<NCB, Q, RB, XF32, NW, true, 2, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 3: launch_variant<NCB, Q, RB, XF32, NW, true, 3, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 4: launch_variant<NCB, Q, RB, XF32, NW, true, 4, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          default: launch_variant<NCB, Q, RB, XF32, NW, true, kFourTablesTwoDwords, 4, false, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
         }
     if constexpr (JMODE != 4)
       if (!wide) switch (D.nib_variant) {
-          case 1: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 1, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
-          case 2: launch_variant<NCB, Q, RB, XF32, NW, true, PD, 2, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 1: launch_variant<NCB, Q, RB, XF32, NW, true, 1, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
+          case 2: launch_variant<NCB, Q, RB, XF32, NW, true, 2, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st); break;
           case 3:
             // (the four-wave workgroups that share a CU have LDS for one or two tables per wave only)
             if constexpr (NW == 4 && !XF32) return XORENC_EUNSUPPORTED;
-            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, 3, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
+            else launch_variant<NCB, Q, RB, XF32, NW, true, 3, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
             break;
           case 4:
             if constexpr (NW == 4 && !XF32) return XORENC_EUNSUPPORTED;
-            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, 4, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
+            else launch_variant<NCB, Q, RB, XF32, NW, true, 4, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
             break;
           default:
             if constexpr (NW == 4 && !XF32) return XORENC_EUNSUPPORTED;
-            else launch_variant<NCB, Q, RB, XF32, NW, true, PD, kFourTablesTwoDwords, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
+            else launch_variant<NCB, Q, RB, XF32, NW, true, kFourTablesTwoDwords, 1, NARROW, TERMS>(D, X, ldx, B, Y, ldy, grid, sps, atomic, st);
             break;
         }
   }
@@ -1197,13 +1158,13 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
         if constexpr (Q == 1) {
           // (64-row tiles once they give every CU one; X is re-read half as often)
           if ((int64_t)((D.nrb + 1) / 2) * ((B + 63) / 64) >= 200)
-            return launch_spmm<2, Q, 2, false, 8, 1, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
+            return launch_spmm<2, Q, 2, false, 8, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
         }
-        return launch_spmm<2, Q, 1, false, 8, 1, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
+        return launch_spmm<2, Q, 1, false, 8, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
       }
-      return launch_spmm<1, Q, 1, false, 12, 1, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
     } else {
-      return launch_spmm<1, Q, 1, false, 8, 1, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 8, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
   }
   if (x_dtype == XORENC_X_F32) {
@@ -1240,81 +1201,105 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
   };
   const bool eight_waves = estimate(1, 8) <= estimate(1, 12);
   const bool one_block = estimate(1, 8) < estimate(2, 8);
+  // Slices of several words: 32-row tiles, twelve waves, while they fit one round, also with one plane (us, 64-row tiles /
+  // here: n_out = 192, n_in = 20, 2048 x 2048, B = 64 11.9 / 7.5, 1024 x 8192 16.8 / 10.7; three planes 16.4 / 12.1;
+  // n_out = 128, n_in = 16, 2500 x 1500, three planes, B = 32 11.5 / 8.7; 6000 x 3000, two blocks of columns 13.1 / 10.9).
+  if constexpr (Q <= 3) {
+    if (x_fast && D.J > 1) {
+      if constexpr (Q <= 2)
+        if (blocks > 1 && estimate(2, 8) < estimate(1, 12)) return launch_spmm<2, Q, 1, false, 8, 1, 4>(D, X, ldx, B, Y, ldy, x_fast, st);
+      if ((int64_t)D.nrb * blocks <= kSplitMaxGroups) return launch_spmm<1, Q, 1, false, 12, 1, 4>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
+  }
   if constexpr (Q == 1) {
     if (!x_fast) {
-      if (blocks == 1) return launch_spmm<1, Q, 2, false, 16, 1, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
-      return launch_spmm<2, Q, 2, false, 8, 2, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
+      if (blocks == 1) return launch_spmm<1, Q, 2, false, 16, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<2, Q, 2, false, 8, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
     if (B <= 8 && D.J == 1 && small_narrow) {
-      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
-      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
     // more than one round of 64-row tiles: four-wave workgroups, several per CU, so that one's prologue and epilogue
     // overlap another's loop (65536 x 4096 at B = 8: 28.9 against 30.4 us)
     if (B <= 8 && D.J == 1 && D.nib_variant <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
-      return launch_spmm<1, Q, 2, false, 4, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (B <= 8 && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 2, false, 4, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (B <= 8 && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     // (small layers: 32-row tiles while they fit one round, see above)
     if (blocks == 1 && D.J == 1 && small_block) {
-      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
     // (several rounds: four-wave workgroups as above; 65536 x 4096 at B = 32: 32.5 against 34.8 us)
     if (blocks == 1 && D.J == 1 && D.nib_variant <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
-      return launch_spmm<1, Q, 2, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (blocks == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 2, false, 4, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (blocks == 1) return launch_spmm<1, Q, 2, false, 12, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     // 128-row tiles halve the number of times X is re-read; used once they still fill most of the chip.
     // Up to 256 of them run as eight-wave workgroups, one per CU, in a single round; more run as
     // four-wave workgroups, two per CU, which share the CU's LDS so that one's prologue and epilogue do
     // not wait for the other's to finish.
     const int64_t tiles128 = (int64_t)((D.nrb + 3) / 4) * ((B + 63) / 64);
     if (D.J == 1 && D.nib_variant <= 2 && tiles128 > 256)
-      return launch_spmm<2, Q, 4, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (D.J == 1 && tiles128 >= 200) return launch_spmm<2, Q, 4, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<2, Q, 4, false, 4, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (D.J == 1 && tiles128 >= 200) return launch_spmm<2, Q, 4, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (D.J == 1 && small_wide) {
-      if (one_block) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-      return launch_spmm<2, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      if (one_block) return launch_spmm<1, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<2, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
-    return launch_spmm<2, Q, 2, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    return launch_spmm<2, Q, 2, false, 8, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
   } else if constexpr (Q == 2) {
     if (B <= 8 && x_fast && D.J == 1 && small_narrow) {
-      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
-      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
     if (B <= 8 && x_fast && D.J == 1 && D.nib_variant <= 2 && (D.nrb + 1) / 2 > kSplitMaxGroups)
-      return launch_spmm<1, Q, 2, false, 4, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (B <= 8 && x_fast && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 2, false, 4, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (B <= 8 && x_fast && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     if (blocks == 1 && x_fast && D.J == 1 && small_block) {
-      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
-    if (blocks == 1 && x_fast) return launch_spmm<1, Q, 2, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (blocks == 1) return launch_spmm<1, Q, 2, false>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (!x_fast) return launch_spmm<2, Q, 1, false, 8, 2, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
-    // two slice buffers per wave leave no room for the tables of multi-word slices
-    if (D.J > 1) return launch_spmm<2, Q, 1, false, 8, 1, 1, 4>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (blocks == 1 && x_fast) return launch_spmm<1, Q, 2, false, 12, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (blocks == 1) return launch_spmm<1, Q, 2, false, 8, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (!x_fast) return launch_spmm<2, Q, 1, false, 8, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (D.J > 1) return launch_spmm<2, Q, 1, false, 8, 1, 4>(D, X, ldx, B, Y, ldy, x_fast, st);
     // 64-row tiles once they fill most of the chip: X is re-read half as often; more than 256 of them run as
     // four-wave workgroups, two per CU
     const int64_t tiles64 = (int64_t)((D.nrb + 1) / 2) * ((B + 63) / 64);
-    if (D.nib_variant <= 2 && tiles64 > 256) return launch_spmm<2, Q, 2, false, 4, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (tiles64 >= 200) return launch_spmm<2, Q, 2, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (one_block) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-    return launch_spmm<2, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (D.nib_variant <= 2 && tiles64 > 256) return launch_spmm<2, Q, 2, false, 4, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (tiles64 >= 200) return launch_spmm<2, Q, 2, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (one_block) return launch_spmm<1, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    return launch_spmm<2, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
   } else if constexpr (Q == 3) {
     if (B <= 8 && x_fast && D.J == 1 && small_narrow) {
-      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
-      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
-    if (B <= 8 && x_fast && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (B <= 8 && x_fast && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     // (32-row tiles on small layers: 6000 x 3000 at B = 32 9.8 against 12.3 us)
     if (x_fast && D.J == 1 && small_block) {
-      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-      return launch_spmm<1, Q, 1, false, 12, 1, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
-    if (x_fast) return launch_spmm<1, Q, 2, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-    return launch_spmm<1, Q, 2, false>(D, X, ldx, B, Y, ldy, x_fast, st);
+    // (more than one round of them: two blocks of columns, 6000 x 3000 at B = 64 12.6 against 14.8 us, 8192 x 1024 at
+    // B = 128 13.7 against 16.5)
+    if (x_fast && D.J == 1 && blocks > 1 && (int64_t)D.nrb * blocks > kSplitMaxGroups)
+      return launch_spmm<2, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (x_fast) return launch_spmm<1, Q, 2, false, 12, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    return launch_spmm<1, Q, 2, false, 8, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
   } else {
-    return launch_spmm<1, Q, 1, false>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (!x_fast) return launch_spmm<1, Q, 1, false, 8, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (D.J > 1) {
+      if ((int64_t)D.nrb * blocks <= kSplitMaxGroups) return launch_spmm<1, Q, 1, false, 12, 1, 4>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 8, 1, 4>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
+    // (one slice buffer per wave instead of two: 1024 x 8192, B = 64 11.4 against 12.1 us)
+    if (B <= 8) {
+      if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 1, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
+    if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    return launch_spmm<1, Q, 1, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
   }
 }
 

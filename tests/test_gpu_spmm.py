@@ -450,6 +450,36 @@ def test_small_layers_over_all_cuts_of_the_reduction(name, n_out, n_in, B, m, n)
     assert rel_fro(got, want) <= 4e-7
 
 
+@pytest.mark.parametrize("name,n_out,n_in", [("large_q1", 192, 20), ("large_q1", 128, 8), ("large_q2", 128, 16),
+                                             ("large_q2", 256, 31), ("lstm", 192, 24), ("lstm", 64, 24)])
+@pytest.mark.parametrize("m,n,B", [(40, 130, 8), (257, 520, 32), (1000, 1100, 65), (2049, 2100, 33), (500, 6100, 64),
+                                   (4200, 300, 64), (4200, 900, 33), (8230, 200, 40), (8230, 200, 24)])
+def test_wide_slices_and_three_planes_in_32_row_tiles(name, n_out, n_in, m, n, B):
+    """One round of 32-row tiles with one and two blocks of columns, and layers just beyond it."""
+    got, want = _run(name, m, n, B, "bf16", n_out=n_out, n_in=n_in, every_output=True)
+    assert rel_fro(got, want) <= 4e-7
+
+
+@pytest.mark.parametrize("n_out,n_in,m,n", [(64, 8, 257, 520), (64, 16, 2049, 1100), (64, 24, 500, 6100), (64, 27, 8230, 200),
+                                            (192, 20, 1000, 1100), (256, 28, 8230, 300)])
+def test_four_planes(n_out, n_in, m, n):
+    """Aligned X of one to three blocks of columns, eight and twelve waves, more than one round of tiles."""
+    import dataclasses
+    import torch
+    import paper_1905_10138_amd as xe
+    from oracle import encoder
+    from synth_inputs import CONFIGS, make_workload
+    wl = make_workload(dataclasses.replace(CONFIGS["lstm"], q=4, n_in=n_in, n_out=n_out, S=0.9), m=m, n=n)
+    enc = encoder.encode(wl.keep, wl.planes, wl.alpha, wl.M, wl.n)
+    L = pack_encoded(enc).to(torch.device("cuda:0"))
+    for B in (8, 24, 72):
+        stored, exact = draw_X(wl.n, B, "bf16", 7)
+        Y = xe.spmm(L, torch.from_numpy(stored.view(np.int16)).view(torch.bfloat16).to("cuda:0"))
+        want = decoder.spmm_f64(enc, exact)
+        assert_every_output_close(Y.cpu().numpy(), want, enc, exact)
+        assert rel_fro(Y.cpu().numpy(), want) <= 4e-7
+
+
 @pytest.mark.parametrize("name,n_out,n_in,S,B", [
     # about two, four and eight entries per list, at most 64 in a wave's range (two slices for waves of eight and twelve):
     # below and above the line from which a slice's entries are scattered together; one to three planes, one and two
