@@ -176,13 +176,14 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   // Flip words of GS slices (long patch lists), [slice][row block and plane][lane], zero between groups: they lie behind
   // the slice buffers, mostly where the reduction tiles will be.  Four slices if they fit without taking the room of the
   // tables, else two or one; without any room the patches of long
-  // lists are applied entry by entry, and so they are with six lists per wave, whose state spilled 50 registers.
+  // lists are applied entry by entry, and so they are with more than four lists per wave of twelve waves, whose state spilled
+  // 50 registers.
   constexpr int FLIP1 = RB * Q * 256;                          // one slice
   constexpr int LDS_REST = JT * NIBMAX * 2048 + Q * ROWS * 4;  // shared tables, scales
   constexpr int LDS_PRIV = NW * NIBMAX * 2048 + Q * ROWS * 4;  // tables per wave, scales
   auto lds_with = [](int gs) { return LDSB0 > NW * (XBUF0 + gs * FLIP1) ? LDSB0 : NW * (XBUF0 + gs * FLIP1); };
   auto fits = [lds_with](int gs) {
-    return XDIR && RB * Q <= 4 && lds_with(gs) + LDS_REST <= 160 * 1024 &&
+    return XDIR && (RB * Q <= 4 || NW <= 8) && lds_with(gs) + LDS_REST <= 160 * 1024 &&
            (JT > 1 || LDSB0 + LDS_PRIV > 160 * 1024 || lds_with(gs) + LDS_PRIV <= 160 * 1024) &&
            (NW != 4 || lds_with(gs) + (JT == 1 ? LDS_PRIV : LDS_REST) <= 80 * 1024);
   };
@@ -1275,7 +1276,14 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
       if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
       return launch_spmm<1, Q, 1, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
-    if (B <= 8 && x_fast && D.J == 1) return launch_spmm<1, Q, 2, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    // (64-row tiles: eight waves, which have registers for lists of many patches (16384 x 1024, S = 0.8, n_in = 16, B = 32
+    // 14.8 -> 9.9 us, n_out = 192, n_in = 30 82.9 -> 16.2); twelve on longer rows of one-word slices, 16384 x 3000, B = 24
+    // 16.2 against 16.8)
+    const bool twelve = D.J == 1 && D.spr > 40;
+    if (B <= 8 && x_fast && D.J == 1) {
+      if (twelve) return launch_spmm<1, Q, 2, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+      return launch_spmm<1, Q, 2, false, 8, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
+    }
     // (32-row tiles on small layers: 6000 x 3000 at B = 32 9.8 against 12.3 us)
     if (x_fast && D.J == 1 && small_block) {
       if (eight_waves) return launch_spmm<1, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
@@ -1285,7 +1293,8 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
     // B = 128 13.7 against 16.5)
     if (x_fast && D.J == 1 && blocks > 1 && (int64_t)D.nrb * blocks > kSplitMaxGroups)
       return launch_spmm<2, Q, 1, false, 8, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
-    if (x_fast) return launch_spmm<1, Q, 2, false, 12, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (x_fast && twelve) return launch_spmm<1, Q, 2, false, 12, 1, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
+    if (x_fast) return launch_spmm<1, Q, 2, false, 8, 1>(D, X, ldx, B, Y, ldy, x_fast, st);
     return launch_spmm<1, Q, 2, false, 8, 2>(D, X, ldx, B, Y, ldy, x_fast, st);
   } else {
     if (!x_fast) return launch_spmm<1, Q, 1, false, 8, 2>(D, X, ldx, B, Y, ldy, x_fast, st);

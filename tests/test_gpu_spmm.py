@@ -460,6 +460,17 @@ def test_wide_slices_and_three_planes_in_32_row_tiles(name, n_out, n_in, m, n, B
     assert rel_fro(got, want) <= 4e-7
 
 
+@pytest.mark.parametrize("name,n_out,n_in,S", [("large_q1", 128, 16, None), ("large_q2", 192, 24, None), ("lstm", 256, 31, 0.9),
+                                               ("large_q1", 256, 30, 0.8), ("lstm", 192, 30, 0.8)])
+@pytest.mark.parametrize("m,n,B,dtype,pad", [(33, 130, 1, "bf16", 0), (257, 520, 2, "bf16", 1), (1000, 1100, 4, "bf16", 0),
+                                             (4200, 300, 3, "bf16", 2), (40, 130, 1, "f32", 0), (257, 520, 33, "f32", 0),
+                                             (600, 1100, 8, "f32", 1), (10300, 130, 24, "bf16", 0)])
+def test_wide_slices_copy_or_split_X_at_any_size(name, n_out, n_in, S, m, n, B, dtype, pad):
+    """Few columns of bf16 and any fp32 with slices of several words, with few and with many patches per slice."""
+    got, want = _run(name, m, n, B, dtype, ldx_pad=pad, S=S, n_out=n_out, n_in=n_in, every_output=(dtype == "bf16"))
+    assert rel_fro(got, want) <= 4e-7
+
+
 @pytest.mark.parametrize("n_out,n_in,m,n", [(64, 8, 257, 520), (64, 16, 2049, 1100), (64, 24, 500, 6100), (64, 27, 8230, 200),
                                             (192, 20, 1000, 1100), (256, 28, 8230, 300)])
 def test_four_planes(n_out, n_in, m, n):
