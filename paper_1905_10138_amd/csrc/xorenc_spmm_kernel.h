@@ -175,19 +175,24 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   constexpr int LDSB0 = (NW * XBUF0 > NREG * TILE * 4) ? NW * XBUF0 : NREG * TILE * 4;
   // Flip words of GS slices (long patch lists), [slice][row block and plane][lane], zero between groups: they lie behind
   // the slice buffers, mostly where the reduction tiles will be.  Four slices if they fit without taking the room of the
-  // tables, else two or one; without any room the patches of long
-  // lists are applied entry by entry, and so they are with more than four lists per wave of twelve waves, whose state spilled
-  // 50 registers.
+  // tables per wave, else two or one.  Where these tables leave no room at all, four lists per wave share one set of tables
+  // (four planes, twelve waves, odd n_in up to 24: 1280 x 6144, S = 0.9, n_in = 5, B = 88 63.9 us entry by entry, 16.4 so;
+  // S = 0.91, n_in = 24, lists of few entries: 13.1 and 13.2), and fewer lists are applied entry by entry (n_in = 32 in
+  // slices of one word, which hardly need patches).  So they are with more than four lists per wave of twelve waves, whose
+  // state spilled 50 registers.
   constexpr int FLIP1 = RB * Q * 256;                          // one slice
   constexpr int LDS_REST = JT * NIBMAX * 2048 + Q * ROWS * 4;  // shared tables, scales
   constexpr int LDS_PRIV = NW * NIBMAX * 2048 + Q * ROWS * 4;  // tables per wave, scales
   auto lds_with = [](int gs) { return LDSB0 > NW * (XBUF0 + gs * FLIP1) ? LDSB0 : NW * (XBUF0 + gs * FLIP1); };
-  auto fits = [lds_with](int gs) {
+  auto fits = [lds_with](int gs, bool keep_priv) {
     return XDIR && (RB * Q <= 4 || NW <= 8) && lds_with(gs) + LDS_REST <= 160 * 1024 &&
-           (JT > 1 || LDSB0 + LDS_PRIV > 160 * 1024 || lds_with(gs) + LDS_PRIV <= 160 * 1024) &&
+           (!keep_priv || JT > 1 || LDSB0 + LDS_PRIV > 160 * 1024 || lds_with(gs) + LDS_PRIV <= 160 * 1024) &&
            (NW != 4 || lds_with(gs) + (JT == 1 ? LDS_PRIV : LDS_REST) <= 80 * 1024);
   };
-  constexpr int GS = fits(4) ? 4 : fits(2) ? 2 : fits(1) ? 1 : 0;
+  constexpr bool PRIV_FIRST = RB * Q < 4 || fits(1, true);
+  constexpr int GS = fits(4, PRIV_FIRST) ? 4 : fits(2, PRIV_FIRST) ? 2 : fits(1, PRIV_FIRST) ? 1 : 0;
+  static_assert(GS > 0 || !XDIR || (RB * Q > 4 && NW > 8) || (Q == 2 && NIBV == 4),
+                "kernels for aligned X scatter long patch lists, but for the two stated above");
   constexpr bool SCATTER = GS > 0;
   constexpr int XBUF = XBUF0 + GS * FLIP1;
   constexpr int LDSB = lds_with(GS);

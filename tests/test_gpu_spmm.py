@@ -472,9 +472,10 @@ def test_wide_slices_copy_or_split_X_at_any_size(name, n_out, n_in, S, m, n, B, 
 
 
 @pytest.mark.parametrize("n_out,n_in,m,n", [(64, 8, 257, 520), (64, 16, 2049, 1100), (64, 24, 500, 6100), (64, 27, 8230, 200),
-                                            (192, 20, 1000, 1100), (256, 28, 8230, 300)])
+                                            (192, 20, 1000, 1100), (256, 28, 8230, 300), (64, 5, 100, 12000)])
 def test_four_planes(n_out, n_in, m, n):
-    """Aligned X of one to three blocks of columns, eight and twelve waves, more than one round of tiles."""
+    """Aligned X of one to three blocks of columns, eight and twelve waves, more than one round of tiles; n_in = 5: lists of
+    more than 64 entries in every wave's range, scattered by twelve waves that share their tables."""
     import dataclasses
     import torch
     import paper_1905_10138_amd as xe
