@@ -46,38 +46,41 @@ constexpr int kSplitMaxParts = 4;  // the workgroup that arrives last at a tile 
 // Variant of the kernel for `col_blocks` blocks of 32 columns and `row_blocks` of 32 rows per workgroup of `waves` waves.
 struct CutVariant {
   int q, col_blocks, row_blocks, waves;
-  bool one_word, split_x, convert_x;  // slices of one word; three terms per column in memory, made on the way into LDS
+  bool one_word, split_x;  // slices of one word; X in memory as three terms per column
+  bool by_entry;           // long patch lists are taken entry by entry
 };
 
 // Splitting a tile's reduction over workgroups shortens every wave's share and costs a meeting: parts stored to the
 // coherent level, a ticket, the parts read back by the last, one after the other.  Filling the chip's CUs at any price, as
 // was done before, paid 1.3 to 2.5 us for it to save a few slices of 0.3 to 0.7 us each (us, most workgroups / this rule:
 // 2048 x 2048, B = 8 7.0 / 5.5; 4096 x 1024, B = 64 7.1 / 5.5; 2500 x 1500, two planes, B = 64 8.0 / 6.3).  The time of a
-// word per wave and of a meeting were fitted to 500 products of 512 x 512 to 4096 x 9216, one to three planes, all cuts
-// timed on each; over these the rule is 0.5 % from the best cut in the mean.
+// word per wave and of a meeting were fitted to 500 products of 512 x 512 to 4096 x 9216, one to three planes, with few
+// patches, n_in = 16 and 24 (one word per slice) or 16 and 20, all cuts timed on each: 0.5 % from the best cut in the mean
+// over these very products.  Other widths, four planes and longer lists have the same estimate.
+// Kernels that take lists entry by entry (X read element by element, or split on its way) have no such estimate: a word
+// takes 0.3 us or, with the hundreds of entries of a narrow encrypted vector, 10, and the host does not know the lists.
+// They fill the chip (us, so / by the estimate: 3877 x 1051, two planes, n_out = 128, n_in = 5, B = 9 33 / 64; fp32 X,
+// 3094 x 316, four planes, S = 0.8, n_in = 7, B = 12 41 / 69; 2043 x 303, three planes, n_in = 11, B = 64 9.2 / 9.9; the
+// other way 969 x 539, n_in = 14, B = 100 8.8 / 8.2).
 inline ReductionCut cut_reduction(const CutVariant &v, int spr, int row_groups, int col_groups, bool scratch) {
   const int64_t tiles = (int64_t)row_groups * col_groups;
   double word = 0.1 + 0.2 * v.q;
-  if (v.convert_x) {
-    word = 1.9;
-  } else {
-    if (v.col_blocks > 1) word *= 1.4;
-    if (v.row_blocks > 1) word *= 1.7;
-    if (v.waves > 8) word *= 1.25;
-    if (v.split_x) word *= 3.0;
-    if (!v.one_word) word *= 1.75;
-    // narrow tiles read W once per block of columns, and rows of X in halves of a cache line
-    if (v.col_blocks == 1 && col_groups > 1) word = (word + 0.06 * (col_groups - 1)) * (spr > 64 ? 1.3 : 1.0);
-  }
-  const bool large_tile = !v.convert_x && v.col_blocks * v.row_blocks > 1;
+  if (v.col_blocks > 1) word *= 1.4;
+  if (v.row_blocks > 1) word *= 1.7;
+  if (v.waves > 8) word *= 1.25;
+  if (v.split_x) word *= 3.0;
+  if (!v.one_word) word *= 1.75;
+  // narrow tiles read W once per block of columns, and rows of X in halves of a cache line
+  if (v.col_blocks == 1 && col_groups > 1) word = (word + 0.06 * (col_groups - 1)) * (spr > 64 ? 1.3 : 1.0);
+  const bool large_tile = v.col_blocks * v.row_blocks > 1;
   double fixed = 0.0;
   if (v.waves > 8 && v.one_word) fixed += 0.1 + 0.15 * v.q;
   if (v.col_blocks == 2) fixed += 0.35 + 0.05 * v.q;
   int most = 1;
-  if (scratch && tiles < kSplitMaxGroups && 1024 * v.row_blocks * (v.convert_x ? 1 : v.col_blocks) <= kSplitTileFloats)
+  if (scratch && tiles < kSplitMaxGroups && 1024 * v.row_blocks * v.col_blocks <= kSplitTileFloats)
     most = (int)std::max<int64_t>(1, std::min<int64_t>({(spr + v.waves - 1) / v.waves, kSplitMaxGroups / tiles, kSplitMaxParts}));
   ReductionCut best{1, 0, 0.0};
-  for (int want = 1; want <= most; ++want) {
+  for (int want = v.by_entry ? most : 1; want <= most; ++want) {
     int sps = (spr + want - 1) / want;
     sps = (sps + v.waves - 1) / v.waves * v.waves;
     const int ks = (spr + sps - 1) / sps;

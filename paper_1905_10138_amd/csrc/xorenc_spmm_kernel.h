@@ -1103,8 +1103,8 @@ int32_t launch_spmm(const DevLayer &D, const void *X, int64_t ldx, int B, float 
   constexpr int NR = XF32 ? (32 * NCB) / 3 : 32 * NCB;
   const int row_groups = (D.nrb + RB - 1) / RB;
   const int col_groups = (B + NR - 1) / NR;
-  const ReductionCut cut = cut_reduction(CutVariant{Q, NCB, RB, NW, D.J == 1, TERMS > 1, XF32}, D.spr, row_groups, col_groups,
-                                         D.split_part && D.split_ticket);
+  const ReductionCut cut = cut_reduction(CutVariant{Q, NR / 32, RB, NW, D.J == 1, TERMS > 1, !x_fast || XF32}, D.spr, row_groups,
+                                         col_groups, D.split_part && D.split_ticket);
   const int sps = cut.sps;
   const dim3 grid(row_groups, col_groups, cut.ks);
   const int atomic = cut.ks;  // number of splits: the kernel reduces them through the scratch area when > 1

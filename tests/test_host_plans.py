@@ -132,7 +132,15 @@ static bool check(const CutVariant &v, int spr, int rg, int cg, bool scratch) {
   CHECK(c.ks >= 1 && c.ks <= kSplitMaxParts && c.us > 0.0);
   if (c.ks > 1) {
     CHECK(scratch && (int64_t)rg * cg * c.ks <= kSplitMaxGroups);  // tickets and parts
-    CHECK(32 * v.row_blocks * (v.convert_x ? 32 : 32 * v.col_blocks) <= kSplitTileFloats);
+    CHECK(32 * v.row_blocks * 32 * v.col_blocks <= kSplitTileFloats);
+  }
+  if (v.by_entry) {  // as many parts as there are CUs and whole words per wave for
+    int most = 1;
+    while (scratch && most < kSplitMaxParts && (int64_t)rg * cg * (most + 1) <= kSplitMaxGroups && most * v.waves < spr &&
+           1024 * v.row_blocks * v.col_blocks <= kSplitTileFloats)
+      ++most;
+    const int sps = ((spr + most - 1) / most + v.waves - 1) / v.waves * v.waves;
+    CHECK(c.sps == sps && c.ks == (spr + sps - 1) / sps);
   }
   return true;
 }
