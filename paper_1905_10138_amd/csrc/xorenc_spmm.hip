@@ -161,7 +161,8 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
   // n_out = 192, n_in = 24, two planes, 512 x 512, B = 1 14.4 / 9.9; three planes, n_out = 256, 768 x 2400, B = 33 23.3 /
   // 14.5; S = 0.8, n_in = 30, 2048 x 2048, B = 64 40.7 / 14.1; one plane, n_out = 128, n_in = 16, 1024 x 1024, B = 8 and 64
   // 11.6 / 10.1 and 10.2 / 11.5: one plane with few tables and two blocks of columns stays with the sizes above).
-  const bool wide_split = D.J > 1 && (D.q > 1 || B <= 32 || D.nib_variant > 2);
+  // Rows of fewer than kSplitMinWords words, for which no call needed memory before, stay as they were: accepted without any.
+  const bool wide_split = D.J > 1 && D.spr >= kSplitMinWords && (D.q > 1 || B <= 32 || D.nib_variant > 2);
   if (x_dtype == XORENC_X_F32 && (weights >= kXSplitMinWeights || weights * B >= kXSplitMinWork || wide_split)) {
     const int64_t fit = (int64_t)(kStageBytes / ((size_t)D.spr * 64 * 48)) * 8;  // columns that fit
     if (fit >= min(B, 64)) {
@@ -202,7 +203,8 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
   // (us, element by element / copied: n_out = 192, n_in = 24, two planes, 256 x 512, B = 1 13.7 / 9.0, 4096 x 4096 19.5 /
   // 12.6; three planes, n_out = 256, 1024 x 1024, B = 2 19.2 / 10.8; S = 0.85, n_in = 30, 9968 x 6732, two planes 240 / 33;
   // four planes 1024 x 1024 11.2 / 11.7, 768 x 7424 18.4 / 15.8).
-  const bool few_wide = D.J > 1 && x_dtype == XORENC_X_BF16 && (layer->q < 4 || weights >= 20000000);
+  // (Rows of few words as for fp32 X.)
+  const bool few_wide = D.J > 1 && D.spr >= kSplitMinWords && x_dtype == XORENC_X_BF16 && (layer->q < 4 || weights >= 20000000);
   if (!split_parts && !aligned && (B >= kStageMinB || few_wide) && copy_pays) {
     const int64_t fit = (int64_t)(kStageBytes / ((size_t)layer->n * 16)) * per / 64 * 64;  // columns, in whole 64s
     const bool whole = (int64_t)layer->n * pieces_per_row * 16 <= (int64_t)kStageBytes;

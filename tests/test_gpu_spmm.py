@@ -756,6 +756,48 @@ def test_a_call_without_memory_for_its_stream_and_with_a_workspace():
         assert float((y - want[2]).norm() / want[2].norm()) <= 4e-7
 
 
+@pytest.mark.parametrize("name,n,n_out,n_in", [("large_q1", 128, 128, 16), ("large_q2", 130, 192, 20), ("lstm", 250, 256, 31)])
+def test_rows_of_few_words_need_no_memory(name, n, n_out, n_in):
+    """xorenc_spmm_ws without a workspace accepts captured calls, and calls on more streams than the library has slots, where
+    a row has at most four words: few columns of unaligned bf16 X, aligned or few columns of fp32 X, slices of several words."""
+    import ctypes
+    import torch
+    import paper_1905_10138_amd as xe
+    wl, enc = encoded_workload(name, 300, n, None, n_out, n_in)
+    L = pack_encoded(enc).to(torch.device("cuda:0"))
+    st = L.c_struct()
+    fn = xe.load_library().xorenc_spmm_ws
+    jobs = []
+    for dtype, B in [("bf16", 1), ("bf16", 3), ("f32", 1), ("f32", 8), ("f32", 36)]:
+        stored, exact = draw_X(n, B, dtype, 11 + B)
+        x = torch.from_numpy(stored.view(np.int16)).view(torch.bfloat16) if dtype == "bf16" else torch.from_numpy(stored)
+        jobs.append((x.to("cuda:0"), torch.empty((300, B), dtype=torch.float32, device="cuda:0"), decoder.spmm_f64(enc, exact)))
+
+    def call(x, y, stream):
+        return fn(ctypes.byref(st), x.data_ptr(), 0 if x.dtype == torch.float32 else 1, x.stride(0), x.shape[1], y.data_ptr(),
+                  y.stride(0), None, 0, stream.cuda_stream)
+
+    def check():
+        torch.cuda.synchronize()
+        for _, y, want in jobs:
+            assert rel_fro(y.cpu().numpy(), want) <= 4e-7
+            y.fill_(7.0)
+        torch.cuda.synchronize()
+
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    torch.cuda.synchronize()
+    for stream in streams:
+        assert [call(x, y, stream) for x, y, _ in jobs] == [0] * len(jobs)
+        check()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rcs = [call(x, y, torch.cuda.current_stream()) for x, y, _ in jobs]
+    assert rcs == [0] * len(jobs)
+    for _ in range(3):
+        graph.replay()
+        check()
+
+
 @pytest.mark.parametrize("name,m,n,n_out,n_in,S,B,dtype,pad", [
     # fp32 X whose three terms do not fit the staging area: parts of few tiles (not taken), of one tile more and one less
     # than the least, four tables for four words, unaligned rows that a copy holds whole, in parts, or not at all
