@@ -278,9 +278,12 @@ XORENC_API int32_t xorenc_decode(const xorenc_layer *layer, int32_t out_kind, vo
  * order.  One kernel launch per call, except where X is rewritten first, in a 4 MiB staging area (the fast kernels fetch
  * X in 16-byte pieces of bf16):
  *   - rows of X that do not start on 16-byte boundaries (ldx not a multiple of 8 bf16 / 4 fp32 values, or such a base
- *     address), from five columns on, bf16 with slices of several words at any number of columns: copied with padded rows;
- *   - fp32 X of larger layers (6 million weights of all planes, or 600 million products) and of most layers with slices of
- *     several words: split into its bf16 terms.
+ *     address): copied with padded rows, from five columns on.  With slices of several words bf16 X of fewer columns is
+ *     copied too where rows have at least five words and the tables are many, the rows long or the layer large.  Up to 32
+ *     columns of widths that straddle dwords (neither a power of two nor 17..24) are copied only with one word per slice
+ *     (fp32: from 17 columns on) or on large layers;
+ *   - fp32 X of larger layers (6 million weights of all planes, or 600 million products), and with slices of several words
+ *     under the conditions above: split into its bf16 terms.
  * Two launches then, and two for every part of the columns where X does not fit and that is still the faster way (at least
  * 64 columns have to fit: n <= 32768 bf16, 16384 fp32 copied, about 10900 fp32 split; otherwise the kernels that read X
  * element by element, or split it on its way, take the call).  For small layers the launch splits the reduction dimension

@@ -157,12 +157,22 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
   int split_parts = 0, split_cols = 0;
   size_t copy_bytes = 0;  // of the largest part
   const int64_t weights = (int64_t)layer->m * layer->n * layer->q;
-  // Slices of several words: at any size, the kernels for split X scatter long patch lists (us, split on the way / before:
-  // n_out = 192, n_in = 24, two planes, 512 x 512, B = 1 14.4 / 9.9; three planes, n_out = 256, 768 x 2400, B = 33 23.3 /
-  // 14.5; S = 0.8, n_in = 30, 2048 x 2048, B = 64 40.7 / 14.1; one plane, n_out = 128, n_in = 16, 1024 x 1024, B = 8 and 64
-  // 11.6 / 10.1 and 10.2 / 11.5: one plane with few tables and two blocks of columns stays with the sizes above).
+  // Slices of several words: smaller layers, and few columns of bf16 (below), gain from a split or a copy too, because the
+  // kernels behind it have 32-row tiles and scatter long patch lists.  In a graph nearly always (1.7x in the mean of 141
+  // random layers, few patches 1.0 to 1.7, long lists up to 8).  But a second launch costs a program that calls directly 3 us
+  // of host time: 11 us a call become 14 where the kernels are shorter than that.  So it is made where the kernels that do
+  // without take longest: many tables to build, or many words of all planes per row to walk through, or large layers.  Over
+  // the 141 layers direct calls are 1.29 times as fast so, 1.27 with two launches at any size; 34 of the 49 that lost more
+  // than 5 % no longer do (us, direct calls, one launch / two: n_out = 128, 1024 x 1024, n_in = 8, B = 1 11.1 / 14.0; fp32,
+  // 2223 x 1002, two planes, n_in = 24, B = 8 11.6 / 14.0), the others have tables for 12 and more (n_out = 192, n_in = 32,
+  // S = 0.9, 1000 x 1000, B = 2 13.3 / 15.0, in a graph 14.3 / 8.8; S = 0.8, 768 x 2400, B = 1 29.8 / 14.9).
   // Rows of fewer than kSplitMinWords words, for which no call needed memory before, stay as they were: accepted without any.
-  const bool wide_split = D.J > 1 && D.spr >= kSplitMinWords && (D.q > 1 || B <= 32 || D.nib_variant > 2);
+  const bool two_launches = D.J > 1 && D.spr >= kSplitMinWords &&
+                            (D.J * tables_of_variant(D.nib_variant) >= 12 || D.q * D.spr >= 40 || weights >= 20000000);
+  // (us, split on the way / before: n_out = 192, n_in = 24, three planes, 1024 x 1024, B = 33 18.6 / 13.7; n_out = 256,
+  // 768 x 2400, B = 33 23.3 / 14.5; S = 0.8, n_in = 30, 2048 x 2048, B = 64 40.7 / 14.1.  One plane with few tables and two
+  // blocks of columns stays with the sizes above: n_out = 128, n_in = 16, 1024 x 1024, B = 64 10.2 / 11.5.)
+  const bool wide_split = two_launches && (D.q > 1 || B <= 32 || D.nib_variant > 2);
   if (x_dtype == XORENC_X_F32 && (weights >= kXSplitMinWeights || weights * B >= kXSplitMinWork || wide_split)) {
     const int64_t fit = (int64_t)(kStageBytes / ((size_t)D.spr * 64 * 48)) * 8;  // columns that fit
     if (fit >= min(B, 64)) {
@@ -199,12 +209,10 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
   const bool odd_width = (D.n_in & (D.n_in - 1)) != 0 && (D.n_in < 17 || D.n_in > 24);
   const bool copy_pays = !odd_width || B > 32 ||
                          (D.J == 1 ? x_dtype == XORENC_X_BF16 || B > 16 : weights >= (D.n_in > 24 ? 2000000 : 20000000));
-  // Few columns of bf16 and slices of several words: the kernels for aligned X have 32-row tiles and scatter long patch lists
-  // (us, element by element / copied: n_out = 192, n_in = 24, two planes, 256 x 512, B = 1 13.7 / 9.0, 4096 x 4096 19.5 /
-  // 12.6; three planes, n_out = 256, 1024 x 1024, B = 2 19.2 / 10.8; S = 0.85, n_in = 30, 9968 x 6732, two planes 240 / 33;
-  // four planes 1024 x 1024 11.2 / 11.7, 768 x 7424 18.4 / 15.8).
-  // (Rows of few words as for fp32 X.)
-  const bool few_wide = D.J > 1 && D.spr >= kSplitMinWords && x_dtype == XORENC_X_BF16 && (layer->q < 4 || weights >= 20000000);
+  // Few columns of bf16 and slices of several words, as above (us, element by element / copied: n_out = 192, n_in = 24, two
+  // planes, 4096 x 4096, B = 1 19.5 / 12.6; three planes, n_out = 256, 1024 x 1024, B = 2 19.2 / 10.8; S = 0.85, n_in = 30,
+  // 9968 x 6732, two planes 240 / 33; four planes 1024 x 1024 11.2 / 11.7, 768 x 7424 18.4 / 15.8).
+  const bool few_wide = two_launches && x_dtype == XORENC_X_BF16 && (layer->q < 4 || weights >= 20000000);
   if (!split_parts && !aligned && (B >= kStageMinB || few_wide) && copy_pays) {
     const int64_t fit = (int64_t)(kStageBytes / ((size_t)layer->n * 16)) * per / 64 * 64;  // columns, in whole 64s
     const bool whole = (int64_t)layer->n * pieces_per_row * 16 <= (int64_t)kStageBytes;

@@ -464,9 +464,12 @@ def test_wide_slices_and_three_planes_in_32_row_tiles(name, n_out, n_in, m, n, B
                                                ("large_q1", 256, 30, 0.8), ("lstm", 192, 30, 0.8)])
 @pytest.mark.parametrize("m,n,B,dtype,pad", [(33, 130, 1, "bf16", 0), (257, 520, 2, "bf16", 1), (1000, 1100, 4, "bf16", 0),
                                              (4200, 300, 3, "bf16", 2), (40, 130, 1, "f32", 0), (257, 520, 33, "f32", 0),
-                                             (600, 1100, 8, "f32", 1), (10300, 130, 24, "bf16", 0)])
+                                             (600, 1100, 8, "f32", 1), (10300, 130, 24, "bf16", 0),
+                                             (40, 2700, 3, "bf16", 0), (70, 2500, 8, "f32", 0)])
 def test_wide_slices_copy_or_split_X_at_any_size(name, n_out, n_in, S, m, n, B, dtype, pad):
-    """Few columns of bf16 and any fp32 with slices of several words, with few and with many patches per slice."""
+    """Few columns of bf16 and any fp32 with slices of several words, with few and with many patches per slice: rows of few
+    words and layers with few tables that the kernels without a copy take, and long rows and many tables that are copied (a
+    power of two or 24 as the width) or split first."""
     got, want = _run(name, m, n, B, dtype, ldx_pad=pad, S=S, n_out=n_out, n_in=n_in, every_output=(dtype == "bf16"))
     assert rel_fro(got, want) <= 4e-7
 
