@@ -204,7 +204,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   // ones are shared by the workgroup.
   constexpr bool PRIV_LUT = JT == 1 && NIBT >= 1 && LDSB + NW * NIBT * 2048 + Q * ROWS * 4 <= 160 * 1024;
   constexpr int LUT_WORD = NIBMAX * 512;  // dwords of the tables of one 64-bit word of a slice
-  __shared__ uint32_t lut_all[(PRIV_LUT ? NW : 1) * JT * LUT_WORD];
+  __shared__ __attribute__((aligned(16))) uint32_t lut_all[(PRIV_LUT ? NW : 1) * JT * LUT_WORD];
   uint32_t *const lut = lut_all + (PRIV_LUT ? (threadIdx.x >> 6) * LUT_WORD : 0);
   static_assert(LDSB + (PRIV_LUT ? NW : 1) * JT * LUT_WORD * 4 + Q * ROWS * 4 <= 160 * 1024, "LDS budget");
   __shared__ __attribute__((aligned(16))) float alpha_s[Q * ROWS];

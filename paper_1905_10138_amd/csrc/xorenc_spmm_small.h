@@ -32,7 +32,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const u
   static_assert(RED_FLOATS * 4 <= kSmallXBytes, "the reduction area must fit where X^T was");
   constexpr bool PRIV_LUT = NW * NIBT * 2048 <= 32 * 1024;
   __shared__ __attribute__((aligned(16))) uint8_t xt_all[kSmallXBytes];
-  __shared__ uint32_t lut_all[(PRIV_LUT ? NW : 1) * NIBT * 512];
+  __shared__ __attribute__((aligned(16))) uint32_t lut_all[(PRIV_LUT ? NW : 1) * NIBT * 512];
   __shared__ float alpha_s[Q * ROWS];
   uint32_t *const lut = lut_all + (PRIV_LUT ? (threadIdx.x >> 6) * NIBT * 512 : 0);
 
