@@ -379,6 +379,8 @@ __global__ void exhaustive_reset_kernel(uint32_t *list_len) { *list_len = 0; }
 // (kAllMaxNIn; us for the kernels of a call, all slices / with the list: 16384 x 4096, S = 0.95, n_in = 8 34 / 199, n_in =
 // 10 55 / 124, with n_out = 192 47 / 117; S = 0.8, n_in = 10 60 / 254; 1024 x 1024, S = 0.9, n_in = 8 13 / 26).
 constexpr int kAllMaxNIn = 10;
+static_assert(32 * (ENC_THREADS / 64) + XORENC_MAX_Q * ENC_THREADS <= (kAllMaxNIn + 1) * ENC_THREADS,
+              "equations and queue of the slices tried by syndrome take the place of the basis");
 
 template <int J, bool ALL>
 __global__ __launch_bounds__(ENC_THREADS, 2) void exhaustive_search_kernel(ExhParams P, int64_t first, int64_t n,

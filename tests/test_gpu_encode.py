@@ -304,9 +304,10 @@ def test_fewest_patches_when_a_part_of_the_inputs_mismatches_everywhere(n_in, lo
 
 @pytest.mark.parametrize("n_out,n_in,q,busy,copies", [
     # the widths where the search over a list begins and the widest that the oracle lists whole; workgroups with few
-    # slices to search, with many, and (205 workgroups of slices of four words) with many that are worth their syndromes
+    # slices to search, with many, of which none or those of up to three kept bits are worth their syndromes, and (1024
+    # workgroups) those of up to 28 and 19: test_host_plans.py states these limits
     (64, 11, 1, 12, 1), (64, 11, 2, 200, 1), (128, 13, 3, 5, 1), (192, 16, 1, 14, 1), (64, 16, 4, 4, 3),
-    (256, 16, 1, 220, 205)])
+    (256, 16, 1, 220, 205), (256, 16, 1, 220, 1024), (64, 16, 1, 256, 1024)])
 def test_fewest_patches_by_syndrome(n_out, n_in, q, busy, copies):
     """Slices with 1 to 40 kept bits (32 and n_in + 12 are the most that are tried by syndrome), some without a solution for
     one to many bits; zero and equal rows in the network, so that short slices need patches as well.  256 slices, the

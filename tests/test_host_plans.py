@@ -78,6 +78,42 @@ def test_patch_counts_lie_in_the_workspace(tmp_path):
     run_program(tmp_path, ENCODE_PLAN, "xorenc_host.cpp")
 
 
+SYNDROME = r"""
+#include <cstdio>
+#include "xorenc_encode_plan.h"
+
+#define CHECK(c) do { if (!(c)) { std::printf("n_in=%d J=%d workgroups=%lld: %s\n", n_in, J, (long long)groups, #c); return 1; } } while (0)
+
+int main() {
+  for (int n_in = 11; n_in <= 24; ++n_in)
+    for (int J = 1; J <= 4; ++J) {
+      int before = 0;
+      for (int64_t groups : {(int64_t)1, (int64_t)2, (int64_t)63, (int64_t)205, (int64_t)1024, (int64_t)100000, (int64_t)1 << 21}) {
+        const SyndromeCare care = syndrome_care(n_in, J, groups);
+        CHECK(care.few >= 1 && care.few <= 32);                // a lane and a bit of a dword per kept bit
+        CHECK(care.many >= before && care.many <= care.few);   // the more workgroups, the more are worth it
+        before = care.many;
+      }
+    }
+  // the workgroups of test_gpu_encode.py's test_fewest_patches_by_syndrome
+  struct { int n_in, J, groups, few, many; } const cases[] = {{11, 1, 1, 23, 0}, {13, 2, 1, 25, 0}, {16, 3, 1, 28, 0},
+                                                              {16, 1, 3, 28, 0}, {16, 4, 205, 28, 3}, {16, 4, 1024, 28, 28},
+                                                              {16, 1, 1024, 28, 19}};
+  for (const auto &c : cases) {
+    const int n_in = c.n_in, J = c.J;
+    const int64_t groups = c.groups;
+    const SyndromeCare care = syndrome_care(n_in, J, groups);
+    CHECK(care.few == c.few && care.many == c.many);
+  }
+  return 0;
+}
+"""
+
+
+def test_slices_tried_by_syndrome(tmp_path):
+    run_program(tmp_path, SYNDROME)
+
+
 SMALL_SPLIT = r"""
 #include <cstdio>
 #include "xorenc_split_plan.h"
