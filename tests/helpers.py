@@ -9,6 +9,16 @@ from oracle import gf2
 from synth_inputs import CONFIGS, make_workload
 
 
+# (planes, m, n, columns, blocks of columns and waves of a workgroup, workgroups per tile): layers on 32-row tiles whose
+# reduction is cut into two or three parts
+CUTS_IN_PARTS = [
+    (1, 3000, 7000, 32, 1, 12, 2), (1, 1500, 4100, 64, 1, 8, 2), (1, 3000, 4100, 64, 2, 8, 2), (1, 257, 4100, 8, 1, 8, 3),
+    (1, 257, 3600, 64, 1, 8, 3), (1, 2049, 4100, 64, 2, 8, 3), (2, 3000, 3600, 8, 1, 8, 2), (2, 3000, 4100, 32, 1, 12, 2),
+    (2, 1500, 3000, 64, 1, 8, 2), (2, 3000, 4100, 64, 2, 8, 2), (2, 257, 2500, 32, 1, 8, 3), (2, 2049, 4100, 64, 2, 8, 3),
+    (3, 1500, 1800, 8, 1, 8, 2), (3, 3000, 2500, 32, 1, 8, 2), (3, 257, 2100, 32, 1, 8, 3),
+]
+
+
 def paper_format_arrays(enc: "oenc.Encoded"):
     """Oracle `Encoded` -> (w_c uint32[q,l], keep uint64[m*spr] row-major 64-bit words, n_patch uint16[q,l],
     d_patch uint8[], M_rows uint32[n_out])."""

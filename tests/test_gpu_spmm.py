@@ -6,7 +6,7 @@ observed error is far below both; the bounds are the contract, not the expectati
 import numpy as np
 import pytest
 
-from helpers import encoded_workload, pack_encoded, rel_fro
+from helpers import CUTS_IN_PARTS, encoded_workload, pack_encoded, rel_fro
 from oracle import decoder
 from synth_inputs import draw_X
 
@@ -444,9 +444,22 @@ def test_long_patch_lists(name, m, n, n_out, n_in, B, S):
 @pytest.mark.parametrize("B", [8, 9, 32, 33, 64, 65, 128])
 @pytest.mark.parametrize("m,n", [(31, 64), (257, 520), (1000, 1100), (2049, 2100), (500, 8200)])
 def test_small_layers_over_all_cuts_of_the_reduction(name, n_out, n_in, B, m, n):
-    """Layers of one round of 32-row tiles: eight and twelve waves, one and two blocks of columns, one to four workgroups per
-    tile, with waves and parts that get no word of a row."""
+    """Layers of one round of 32-row tiles: eight and twelve waves, one and two blocks of columns, one and four workgroups per
+    tile (two and three below), with waves and parts that get no word of a row."""
     got, want = _run(name, m, n, B, "bf16", n_out=n_out, n_in=n_in, every_output=True)
+    assert rel_fro(got, want) <= 4e-7
+
+
+@pytest.mark.parametrize("q,m,n,B,col_blocks,waves,parts", CUTS_IN_PARTS)
+def test_two_and_three_workgroups_per_tile(q, m, n, B, col_blocks, waves, parts):
+    got, want = _run(["large_q1", "large_q2", "lstm"][q - 1], m, n, B, "bf16", every_output=True)
+    assert rel_fro(got, want) <= 4e-7
+
+
+@pytest.mark.parametrize("m,n,B", [(8200, 2600, 8), (8200, 2600, 24), (2100, 6200, 64)])
+def test_long_patch_lists_of_three_planes_on_long_rows(m, n, B):
+    """64-row tiles with twelve waves, which read lists of more than 64 entries one after the other from memory."""
+    got, want = _run("lstm", m, n, B, "bf16", S=0.8, n_out=64, n_in=13, every_output=True)
     assert rel_fro(got, want) <= 4e-7
 
 

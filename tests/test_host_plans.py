@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from helpers import CUTS_IN_PARTS
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1905_10138_amd", "csrc")
 
@@ -199,6 +201,40 @@ int main() {
 
 def test_cuts_of_the_reduction_cover_it_and_fit_the_scratch_area(tmp_path):
     run_program(tmp_path, CUT)
+
+
+CUT_IN_PARTS = r"""
+#include <cstdio>
+#include "xorenc_split_plan.h"
+
+int main() {
+  struct { int q, m, n, B, col_blocks, waves, ks; } const cases[] = {CASES};
+  for (const auto &c : cases) {
+    const int rg = (c.m + 31) / 32, spr = (c.n + 63) / 64, blocks = (c.B + 31) / 32;
+    // 32-row tiles: eight or twelve waves and one block of columns, or eight and two
+    ReductionCut best{0, 0, 1e9};
+    int cols = 0, waves = 0;
+    for (const auto &v : {CutVariant{c.q, 1, 1, 8, true, false, false}, CutVariant{c.q, 1, 1, 12, true, false, false},
+                          CutVariant{c.q, 2, 1, 8, true, false, false}}) {
+      if (blocks > 1 ? v.waves > 8 : v.col_blocks > 1) continue;
+      const int cg = (blocks + v.col_blocks - 1) / v.col_blocks;
+      if (rg * cg > kSplitMaxGroups) continue;
+      const ReductionCut cut = cut_reduction(v, spr, rg, cg, true);
+      if (cut.us < best.us) best = cut, cols = v.col_blocks, waves = v.waves;
+    }
+    if (best.ks != c.ks || cols != c.col_blocks || waves != c.waves) {
+      std::printf("q=%d %d x %d B=%d: %d parts, %d blocks of columns, %d waves\n", c.q, c.m, c.n, c.B, best.ks, cols, waves);
+      return 1;
+    }
+  }
+  return 0;
+}
+"""
+
+
+def test_layers_in_two_and_three_parts(tmp_path):
+    """The layers of test_gpu_spmm.py's test_two_and_three_workgroups_per_tile have as many parts as it says."""
+    run_program(tmp_path, CUT_IN_PARTS.replace("CASES", ", ".join("{%d, %d, %d, %d, %d, %d, %d}" % c for c in CUTS_IN_PARTS)))
 
 
 SCRATCH_OWNERS = r"""
