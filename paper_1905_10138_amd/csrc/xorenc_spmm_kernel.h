@@ -1170,6 +1170,9 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
       }
       return launch_spmm<1, Q, 1, false, 12, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
     } else {
+      // (four planes keep 8 to 10 registers in scratch memory, 5 without the loop for short lists of several entries: 4096 x
+      // 4096, S = 0.91, n_in = 16, B = 64 24.3 us with and without that loop, 2048 x 2048, S = 0.8, n_in = 14, B = 32 12.5
+      // against 13.7)
       return launch_spmm<1, Q, 1, false, 8, 1, 0, false, 3>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
   }
@@ -1282,8 +1285,10 @@ int32_t dispatch_spmm_q(const DevLayer &D, const void *X, int32_t x_dtype, int64
       return launch_spmm<1, Q, 1, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
     }
     // (64-row tiles: eight waves, which have registers for lists of many patches (16384 x 1024, S = 0.8, n_in = 16, B = 32
-    // 14.8 -> 9.9 us, n_out = 192, n_in = 30 82.9 -> 16.2); twelve on longer rows of one-word slices, 16384 x 3000, B = 24
-    // 16.2 against 16.8)
+    // 14.8 -> 9.9 us, n_out = 192, n_in = 30 82.9 -> 16.2); twelve on longer rows of one-word slices with few patches,
+    // 16384 x 4096, S = 0.95, n_in = 8, B = 8 16.3 against 17.3, 16384 x 3000, S = 0.91, n_in = 16 12.6 against 12.7, 4096 x
+    // 9216, B = 64 19.0 against 18.8.  Twelve take lists of more than 64 entries one after the other from memory: S = 0.8,
+    // n_in = 13, 8200 x 2600, B = 8 66 against 20, 4096 x 9216, B = 64 109 against 31.  The host does not know the lists.)
     const bool twelve = D.J == 1 && D.spr > 40;
     if (B <= 8 && x_fast && D.J == 1) {
       if (twelve) return launch_spmm<1, Q, 2, false, 12, 1, 1, true>(D, X, ldx, B, Y, ldy, x_fast, st);
