@@ -84,20 +84,23 @@ __device__ inline int64_t entry_word(uint32_t entry, int64_t first, uint32_t n, 
 }
 
 // Patches of the 32 slices of a unit (one per lane of a half wave): count for the unit and its block, bitmaps if there
-// are any.  Every lane of the wave calls this with the same w; `block_total` is LDS.
+// are any.  Every lane of the wave calls this with the same w; `block_total` is LDS.  The slices' counts are added up bit by
+// bit with scalar instructions (most are 0 or 1).
 __device__ inline void put_patches(uint64_t *pbits, const Counts &c, int p, int64_t slot, uint64_t patches, bool valid,
                                    uint32_t *block_total) {
-  uint32_t cnt = 0;
-  if (__ballot(patches != 0)) {  // uniform
-    cnt = (uint32_t)__builtin_popcountll(patches);
-#pragma unroll
-    for (int o = 16; o >= 1; o >>= 1) cnt += (uint32_t)__shfl_xor((int)cnt, o, 32);
-    if (valid && cnt) pbits[slot] = patches;
+  const uint32_t mine = (uint32_t)__builtin_popcountll(patches);
+  uint32_t low = 0, high = 0;  // uniform: of the wave's two units
+  for (int k = 0; k < 7; ++k) {
+    const uint64_t have = __ballot((mine >> k) & 1u);
+    low += (uint32_t)__builtin_popcount((uint32_t)have) << k;
+    high += (uint32_t)__builtin_popcount((uint32_t)(have >> 32)) << k;
+    if (!__ballot(mine >> (k + 1))) break;  // uniform
   }
-  if (valid && (threadIdx.x & 31) == 0) {
-    if (c.unit) c.unit[(int64_t)p * c.n_units + (slot - (int64_t)p * c.n_units * 32) / 32] = (uint16_t)cnt;  // uniform
-    if (cnt) atomicAdd(block_total, cnt);
-  }
+  const uint32_t cnt = threadIdx.x & 32 ? high : low;
+  if (valid && cnt) pbits[slot] = patches;
+  if (valid && c.unit && (threadIdx.x & 31) == 0)
+    c.unit[(int64_t)p * c.n_units + (slot - (int64_t)p * c.n_units * 32) / 32] = (uint16_t)cnt;
+  if (low + high && (threadIdx.x & 63) == 0) atomicAdd(block_total, low + high);
 }
 
 // Fewest patches of one slice by syndrome: a wave, a care bit per lane, at most 32 of them (the equation of a lane's care
@@ -170,103 +173,251 @@ __device__ bool fewest_patches(uint32_t row, int n_care, int n_in, uint32_t *x_o
   return true;
 }
 
+// Algorithm 1 on slices with at most kFewCare care bits, a lane each (n_in + Q <= 27).  Slot t holds what the t-th equation
+// of the lane's slice became, or 0 if it was dropped or redundant: from bit 5 on its coefficients and above them the planes'
+// right-hand sides, in the lowest five bits the place of its pivot, the lowest coefficient.  An equation is reduced against
+// the slots before it in their order: a slot has no bit at the pivots of those before it, so a cleared pivot stays cleared,
+// and what remains is the one equation of its kind without bits at pivots, as in the other order.  All slots are registers
+// and a reduction step is two instructions (the bit at the pivot spread over a word, of whose shift the instruction takes
+// the lowest five bits, and and-xor), where a chain of LDS reads took about 300 cycles.
+//
+// Bound: instructions, about 34 and two per slot before it for an equation, of the slice with the most care bits in the
+// wave; with few waves the latency of the words' and the network's loads, which travel together.  us for the kernels of a call,
+// all in LDS / so: 2048 x 2048, S = 0.91, n_in = 16 15.4 / 11.8; 4096 x 4096, three planes, S = 0.8, n_in = 24 34.6 / 26.4;
+// 16384 x 4096, two planes, S = 0.95, n_in = 8 34.0 / 32.4; search, n_out = 192, n_in = 20 48.3 / 43.9.  Slices with more than
+// 32 care bits would need more registers than eight waves have (24 slots: 38 us for the second, a few slices had more).
+constexpr int kFewCare = 32;
+constexpr int kPivotBits = 5;
+constexpr bool has_few_care(int Q, int J) { return J * (1 + 2 * Q) <= 10; }  // (the words of wider ones fill the registers)
+
+template <int Q, int J>
+struct FewCare {
+  uint64_t kept[J], bits[J][Q];     // in: care bits, wanted bits
+  uint64_t patches[J][Q];           // out
+  uint32_t x[Q];                    // out: the solution with free variables 0
+
+  // rows: the network's, in LDS; n_care: of the lane's slice; steps: most care bits of a slice of the wave (uniform)
+  __device__ inline void solve(const uint32_t *rows, int n_in, uint32_t coefs, int n_care, int steps) {
+    uint32_t slot[kFewCare];
+    coefs <<= kPivotBits;
+    n_in += kPivotBits;
+    int word = 0;          // the lane's word of the slice (J > 1)
+    uint64_t left = kept[0], now[Q];
+#pragma unroll
+    for (int p = 0; p < Q; ++p) now[p] = bits[0][p];
+#pragma unroll
+    for (int w = 0; w < J; ++w)
+#pragma unroll
+      for (int p = 0; p < Q; ++p) patches[w][p] = 0;
+    auto next_word = [&] {
+      if constexpr (J > 1) {
+#pragma unroll
+        for (int k = 1; k < J; ++k) {  // (an empty word may follow)
+          if (!__ballot(left == 0 && word < J - 1)) break;  // uniform
+          const bool go = left == 0 && word < J - 1;
+          word += go ? 1 : 0;
+#pragma unroll
+          for (int w = 1; w < J; ++w)
+            if (go && word == w) {
+              left = kept[w];
+#pragma unroll
+              for (int p = 0; p < Q; ++p) now[p] = bits[w][p];
+            }
+        }
+      }
+    };
+    // the next equation: its row of the network and right-hand sides (whatever it is behind the lane's last one)
+    int at = 0, at_word = 0;
+    uint32_t row = 0;
+    auto fetch = [&] {
+      next_word();
+      at = (int)__builtin_ctzll(left | 1ull << 63);
+      asm volatile("" : "+v"(at));  // (compared as 32 bits)
+      at_word = word;
+      left &= left - 1;
+      row = rows[(J > 1 ? 64 * word : 0) + at] << kPivotBits;
+#pragma unroll
+      for (int p = 0; p < Q; ++p) {
+        const uint32_t half = at < 32 ? (uint32_t)now[p] : (uint32_t)(now[p] >> 32);
+        row |= __builtin_amdgcn_ubfe(half, (uint32_t)at, 1u) << (n_in + p);
+      }
+    };
+    fetch();
+#pragma unroll
+    for (int t = 0; t < kFewCare; ++t) {
+      if (t < steps) {  // uniform
+        uint32_t r = t < n_care ? row : 0u;
+        const int i = at, w_i = at_word;
+        if (t + 1 < kFewCare) fetch();
+#pragma unroll
+        for (int k = 0; k < t; ++k) r ^= (uint32_t)__builtin_amdgcn_sbfe((int)r, slot[k], 1u) & slot[k];
+        const bool gone = (r & coefs) == 0;
+        if (__ballot(gone && r >> kPivotBits)) {  // uniform: the equation is dropped where its right-hand side is 1
+          const uint32_t rhs = gone ? r >> n_in : 0u;
+#pragma unroll
+          for (int w = 0; w < J; ++w)
+#pragma unroll
+            for (int p = 0; p < Q; ++p)
+              if (J == 1 || w == w_i) patches[w][p] |= (uint64_t)((rhs >> p) & 1u) << i;
+        }
+        const uint32_t pivots = 0xffffffffu >> (32 - kPivotBits);
+        slot[t] = gone ? 0u : (r & ~pivots) | (uint32_t)__builtin_ctz((r & ~pivots) | 1u << 31);
+      }
+    }
+    // back-substitution, last slot first: a slot's other bits are free columns and pivots of later slots
+#pragma unroll
+    for (int p = 0; p < Q; ++p) x[p] = 0;
+#pragma unroll
+    for (int t = kFewCare - 1; t >= 0; --t) {
+      if (t < steps) {  // uniform
+#pragma unroll
+        for (int p = 0; p < Q; ++p) {
+          const uint32_t sum = (uint32_t)__builtin_popcount(slot[t] & coefs & x[p]) + (slot[t] >> (n_in + p));
+          x[p] |= (sum & 1u) << (slot[t] & 31u);
+        }
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < Q; ++p) x[p] >>= kPivotBits;
+  }
+};
+
 // Algorithm 1.  The planes share the mask, so the coefficients of a slice's equations, which of them join the basis
 // and the pivots are the same for all planes: one elimination with Q right-hand sides, which travel in the bits above
 // the n_in coefficients of a row (PACKED: n_in + Q <= 32) or as bits per pivot in a register per plane.
 //
-// Bound: the chain of dependent LDS reads of a reduction (one per set pivot) and the longest of 64 slices in a wave.
-// The network's rows are read from LDS (they used to be fetched from the kernel arguments with a vector load per
-// equation), and the basis takes n_in KB of LDS instead of 32.  16384 x 4096, two planes, n_in = 8: 24 us; 45 us with
-// one elimination per plane and rows from the arguments.
+// Waves whose slices have few care bits keep everything in registers (FewCare).  The others' bound is the chain of dependent
+// LDS reads of a reduction (one per set pivot) and the longest of 64 slices in a wave.  The network's rows are read from LDS
+// (they used to be fetched from the kernel arguments with a vector load per equation), and the basis takes n_in KB of
+// LDS instead of 32.  Slices of 64 bits have a kernel of their own (JT = 1), all others share one (JT = 4).
 //
 // SEARCH: first pass of the encoder with the fewest patches, over the slices [first, first + n).  The low half of a
 // slice's first patch word becomes its key: the solution x (below 2^24) when nothing was dropped, x with the lowest bit of
 // the mismatch count set when syndromes gave the fewest patches, otherwise all ones, and the slice joins the list, whose
 // entry i is the high half of the first patch word of slice i of the pass's numbering; *list_len counts them.  The
 // workgroup's waves take turns at the slices that are tried by syndrome (syndrome_care says which).
-template <int Q, bool PACKED, bool SEARCH>
+template <int Q, bool PACKED, bool SEARCH, int JT>
 __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P, int64_t first, int64_t n,
                                                                    uint32_t *list_len, SyndromeCare care) {
   extern __shared__ uint32_t enc_lds[];  // [n_in][ENC_THREADS] basis, then the 64 J rows of the network
   __shared__ uint32_t block_total[Q];
   uint32_t *const rows = enc_lds + P.n_in * ENC_THREADS;
   const int tid = threadIdx.x;
-  for (int i = tid; i < 64 * P.J; i += ENC_THREADS) rows[i] = P.M_rows[i];
   if (tid < Q) block_total[tid] = 0;
   const int64_t rel = (int64_t)blockIdx.x * ENC_THREADS + tid;
   const bool valid = rel < n;
   const int64_t eslot = first + (valid ? rel : 0);
-  const int64_t slot0 = first_word(eslot, P.J);
+  const int l_J = JT ? JT : P.J;
+  const int64_t slot0 = first_word(eslot, l_J);
   const int n_in = P.n_in;
   const uint32_t coefs = n_in < 32 ? (1u << n_in) - 1u : 0xffffffffu;
   uint32_t *const basis = enc_lds + tid;  // row with pivot j at basis[j * ENC_THREADS]
+  // the slice's words are requested before the network's rows are staged: they travel together
+  uint64_t kept_all[JT ? JT : 1], bits_all[JT ? JT : 1][Q];
+  int n_care = 0;
+#pragma unroll
+  for (int w = 0; w < JT; ++w) {
+    kept_all[w] = valid ? P.mask[slot0 + 32 * w] : 0ull;
+#pragma unroll
+    for (int p = 0; p < Q; ++p) bits_all[w][p] = valid ? P.planes[p * P.n_slots + slot0 + 32 * w] : 0ull;
+  }
+  for (int i = tid; i < 64 * l_J; i += ENC_THREADS) rows[i] = P.M_rows[i];
   __syncthreads();
 
-  uint32_t have = 0;         // bit j: a basis row with pivot j exists
-  uint32_t rhsbits[Q] = {};  // !PACKED: bit j = right-hand side of that row
   bool dropped[Q] = {};
-  int n_care = 0;
-  for (int w = 0; w < P.J; ++w) {  // uniform; care bits in ascending position over the whole slice
-    const int64_t slot = slot0 + 32 * w;
-    uint64_t kept = valid ? P.mask[slot] : 0ull;  // care bits
-    if constexpr (SEARCH) n_care += __builtin_popcountll(kept);
-    uint64_t bits[Q], patches[Q];
+  uint32_t x[Q] = {};
 #pragma unroll
-    for (int p = 0; p < Q; ++p) {
-      bits[p] = valid ? P.planes[p * P.n_slots + slot] : 0ull;
-      patches[p] = 0;
+  for (int w = 0; w < JT; ++w) n_care += __builtin_popcountll(kept_all[w]);
+  if (SEARCH && JT == 0)
+    for (int w = 0; w < l_J; ++w) n_care += valid ? __builtin_popcountll(P.mask[slot0 + 32 * w]) : 0;
+  asm volatile("" : "+v"(n_care));  // (compared as 32 bits)
+  if (JT && !__ballot(n_care > kFewCare)) {  // uniform
+    if constexpr (JT != 0) {
+      FewCare<Q, JT> few;
+#pragma unroll
+      for (int w = 0; w < JT; ++w) {
+        few.kept[w] = kept_all[w];
+#pragma unroll
+        for (int p = 0; p < Q; ++p) few.bits[w][p] = bits_all[w][p];
+      }
+      int steps = 0;  // the largest n_care
+      for (int s = 32; s > 0; s >>= 1) steps += __ballot(n_care >= steps + s) ? s : 0;
+      few.solve(rows, n_in, coefs, n_care, steps);
+#pragma unroll
+      for (int p = 0; p < Q; ++p) x[p] = few.x[p];
+#pragma unroll
+      for (int w = 0; w < JT; ++w) {
+#pragma unroll
+        for (int p = 0; p < Q; ++p) {
+          dropped[p] = dropped[p] || few.patches[w][p] != 0;
+          if constexpr (!SEARCH)
+            put_patches(P.pbits, P.counts, p, p * P.n_slots + slot0 + 32 * w, few.patches[w][p], valid, block_total + p);
+        }
+      }
     }
-    while (kept) {
-      const int i = __builtin_ctzll(kept);
-      kept &= kept - 1;
-      uint32_t row = rows[64 * w + i];
-      uint32_t rhs = 0;  // bit p: plane p
+  } else {
+    uint32_t have = 0;         // bit j: a basis row with pivot j exists
+    uint32_t rhsbits[Q] = {};  // !PACKED: bit j = right-hand side of that row
+    for (int w = 0; w < l_J; ++w) {  // uniform; care bits in ascending position over the whole slice
+      const int64_t slot = slot0 + 32 * w;
+      uint64_t kept = valid ? P.mask[slot] : 0ull;  // care bits
+      uint64_t bits[Q], patches[Q];
 #pragma unroll
-      for (int p = 0; p < Q; ++p) rhs |= (uint32_t)((bits[p] >> i) & 1) << p;
-      if constexpr (PACKED) row |= rhs << n_in;
-      uint32_t t = row & have;
-      while (t) {  // reduce, ascending pivots (a basis row has no bit below its pivot)
-        const int j = __builtin_ctz(t);
-        row ^= basis[j * ENC_THREADS];
+      for (int p = 0; p < Q; ++p) {
+        bits[p] = valid ? P.planes[p * P.n_slots + slot] : 0ull;
+        patches[p] = 0;
+      }
+      while (kept) {
+        const int i = __builtin_ctzll(kept);
+        kept &= kept - 1;
+        uint32_t row = rows[64 * w + i];
+        uint32_t rhs = 0;  // bit p: plane p
+#pragma unroll
+        for (int p = 0; p < Q; ++p) rhs |= (uint32_t)((bits[p] >> i) & 1) << p;
+        if constexpr (PACKED) row |= rhs << n_in;
+        uint32_t t = row & have;
+        while (t) {  // reduce, ascending pivots (a basis row has no bit below its pivot)
+          const int j = __builtin_ctz(t);
+          row ^= basis[j * ENC_THREADS];
+          if constexpr (!PACKED) {
+#pragma unroll
+            for (int p = 0; p < Q; ++p) rhs ^= ((rhsbits[p] >> j) & 1u) << p;
+          }
+          t = row & have;
+        }
+        if ((row & coefs) == 0) {  // 0 ... 0 | rhs: the equation is dropped where that is 1
+          if constexpr (PACKED) rhs = row >> n_in;
+#pragma unroll
+          for (int p = 0; p < Q; ++p) patches[p] |= (uint64_t)((rhs >> p) & 1u) << i;
+          continue;
+        }
+        const int piv = __builtin_ctz(row);
+        basis[piv * ENC_THREADS] = row;
+        have |= 1u << piv;
         if constexpr (!PACKED) {
 #pragma unroll
-          for (int p = 0; p < Q; ++p) rhs ^= ((rhsbits[p] >> j) & 1u) << p;
+          for (int p = 0; p < Q; ++p) rhsbits[p] |= ((rhs >> p) & 1u) << piv;
         }
-        t = row & have;
       }
-      if ((row & coefs) == 0) {  // 0 ... 0 | rhs: the equation is dropped where that is 1
-        if constexpr (PACKED) rhs = row >> n_in;
 #pragma unroll
-        for (int p = 0; p < Q; ++p) patches[p] |= (uint64_t)((rhs >> p) & 1u) << i;
-        continue;
-      }
-      const int piv = __builtin_ctz(row);
-      basis[piv * ENC_THREADS] = row;
-      have |= 1u << piv;
-      if constexpr (!PACKED) {
-#pragma unroll
-        for (int p = 0; p < Q; ++p) rhsbits[p] |= ((rhs >> p) & 1u) << piv;
+      for (int p = 0; p < Q; ++p) {
+        dropped[p] = dropped[p] || patches[p] != 0;
+        if constexpr (!SEARCH)
+          put_patches(P.pbits, P.counts, p, p * P.n_slots + slot, patches[p], valid, block_total + p);
       }
     }
+    // back-substitution, free variables = 0, highest pivot first
+    uint32_t t = have;
+    while (t) {
+      const int j = 31 - __builtin_clz(t);
+      t &= ~(1u << j);
+      const uint32_t row = basis[j * ENC_THREADS];
 #pragma unroll
-    for (int p = 0; p < Q; ++p) {
-      dropped[p] = dropped[p] || patches[p] != 0;
-      if constexpr (!SEARCH)
-        put_patches(P.pbits, P.counts, p, p * P.n_slots + slot, patches[p], valid, block_total + p);
-    }
-  }
-  // back-substitution, free variables = 0, highest pivot first
-  uint32_t x[Q] = {};
-  uint32_t t = have;
-  while (t) {
-    const int j = 31 - __builtin_clz(t);
-    t &= ~(1u << j);
-    const uint32_t row = basis[j * ENC_THREADS];
-#pragma unroll
-    for (int p = 0; p < Q; ++p) {
-      const uint32_t others = row & coefs & x[p];  // pivots above j already solved; free ones are 0
-      const uint32_t rhs = PACKED ? row >> (n_in + p) : rhsbits[p] >> j;
-      x[p] |= ((rhs ^ (uint32_t)__builtin_popcount(others)) & 1u) << j;
+      for (int p = 0; p < Q; ++p) {
+        const uint32_t others = row & coefs & x[p];  // pivots above j already solved; free ones are 0
+        const uint32_t rhs = PACKED ? row >> (n_in + p) : rhsbits[p] >> j;
+        x[p] |= ((rhs ^ (uint32_t)__builtin_popcount(others)) & 1u) << j;
+      }
     }
   }
 #pragma unroll
@@ -725,14 +876,19 @@ __global__ __launch_bounds__(ENC_THREADS) void emit_patches_kernel(const uint64_
 
 template <int Q, bool SEARCH>
 void launch_slices(const EncParams &P, int64_t first, int64_t n, uint32_t *list_len, SyndromeCare care, hipStream_t st) {
-  const dim3 grid((unsigned)((n + ENC_THREADS - 1) / ENC_THREADS));
+  const dim3 grid((unsigned)((n + ENC_THREADS - 1) / ENC_THREADS)), block(ENC_THREADS);
   const size_t lds = ((size_t)P.n_in * ENC_THREADS + 64 * P.J) * sizeof(uint32_t);
-  if (P.n_in + Q <= 32)
-    hipLaunchKernelGGL((encode_slices_kernel<Q, true, SEARCH>), grid, dim3(ENC_THREADS), lds, st, P, first, n, list_len,
-                       care);
+  const bool packed = P.n_in + Q <= 32, in_slots = P.n_in + Q + kPivotBits <= 32;
+  if (in_slots && P.J == 1)
+    hipLaunchKernelGGL((encode_slices_kernel<Q, true, SEARCH, 1>), grid, block, lds, st, P, first, n, list_len, care);
+  else if (in_slots && P.J == 2 && has_few_care(Q, 2))
+    hipLaunchKernelGGL((encode_slices_kernel<Q, true, SEARCH, has_few_care(Q, 2) ? 2 : 0>), grid, block, lds, st, P, first, n, list_len, care);
+  else if (in_slots && P.J == 3 && has_few_care(Q, 3))
+    hipLaunchKernelGGL((encode_slices_kernel<Q, true, SEARCH, has_few_care(Q, 3) ? 3 : 0>), grid, block, lds, st, P, first, n, list_len, care);
+  else if (packed)
+    hipLaunchKernelGGL((encode_slices_kernel<Q, true, SEARCH, 0>), grid, block, lds, st, P, first, n, list_len, care);
   else
-    hipLaunchKernelGGL((encode_slices_kernel<Q, false, SEARCH>), grid, dim3(ENC_THREADS), lds, st, P, first, n, list_len,
-                       care);
+    hipLaunchKernelGGL((encode_slices_kernel<Q, false, SEARCH, 0>), grid, block, lds, st, P, first, n, list_len, care);
 }
 
 template <int J>

@@ -87,6 +87,19 @@ def test_gpu_encoder_random_geometries(name, m, n, n_out, n_in, S):
     _check_against_oracle(wl, enc)
 
 
+# Slices of at most 32 care bits are solved in registers where coefficients, right-hand sides and five bits fit a word (n_in +
+# planes <= 27), wave by wave: both sides of either limit, waves that mix them, and slices with dozens of patches.
+@pytest.mark.parametrize("name,m,n,n_out,n_in,S", [("fig1", 150, 300, 64, 26, 0.5), ("fig1", 150, 300, 64, 27, 0.6),
+                                                   ("lstm", 70, 300, 64, 24, 0.6), ("lstm", 70, 300, 64, 25, 0.6),
+                                                   ("fc6", 70, 600, 128, 25, 0.78), ("fc6", 70, 600, 128, 26, 0.78),
+                                                   ("fig1", 100, 700, 192, 26, 0.85), ("fig1", 100, 700, 256, 20, 0.9),
+                                                   ("lstm", 64, 400, 128, 20, 0.8), ("large_q2", 40, 500, 64, 4, 0.5),
+                                                   ("large_q1", 40, 500, 64, 8, 0.05)])
+def test_gpu_encoder_edges_of_the_elimination_in_registers(name, m, n, n_out, n_in, S):
+    wl, enc = encoded_workload(name, m, n, S=S, n_out=n_out, n_in=n_in)
+    _check_against_oracle(wl, enc)
+
+
 @pytest.mark.parametrize("name,m,n,n_out,n_in,S", _random_encoder_cases(10, 6, 12))
 def test_gpu_exhaustive_encoder_random_geometries(name, m, n, n_out, n_in, S):
     wl, enc = encoded_workload(name, m, n, S=S, n_out=n_out, n_in=n_in, exhaustive=True)
