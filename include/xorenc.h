@@ -239,6 +239,18 @@ XORENC_API int32_t xorenc_encode_exhaustive(int32_t m, int32_t n, int32_t n_in, 
                                             void *hip_stream);
 
 /*
+ * xorenc_encode, or with fewest_patches != 0 xorenc_encode_exhaustive, for callers that need the patch total at once: waits
+ * for hip_stream and leaves the total in *total_out, HOST memory that the GPU can write (hipHostMalloc), 4-byte aligned.
+ * The last kernel writes it there, which spares the caller a copy of patch_off_out[q*n_units] behind the kernels
+ * (about 9 us).  The only call that waits; not for streams that are being captured.
+ */
+XORENC_API int32_t xorenc_encode_total(int32_t fewest_patches, int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,
+                                       const uint32_t *M_rows, const uint64_t *mask, const uint64_t *planes,
+                                       uint8_t *enc_out, uint32_t *patch_off_out, uint16_t *patch_out,
+                                       int64_t patch_capacity, void *workspace, int64_t workspace_bytes,
+                                       uint32_t *total_out, void *hip_stream);
+
+/*
  * xorenc_encode for callers that cannot allocate device memory and have no workspace to pass: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs, kernels and
  * stream behaviour as xorenc_encode, without the workspace: the patch bitmaps and the per-unit counts go to an

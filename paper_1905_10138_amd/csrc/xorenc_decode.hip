@@ -23,6 +23,18 @@ int32_t xorenc_internal_check_launch(void) { return xorenc_internal_hip_status((
 
 void xorenc_internal_begin_call(void) { (void)hipGetLastError(); }
 
+// bit i of out[j] = bit j of in[i]: halves of the square change places, then halves of the halves
+static void transpose_bits(const uint32_t *in, uint32_t *out) {
+  std::copy(in, in + 32, out);
+  uint32_t low = 0x0000ffffu;
+  for (int d = 16; d; d >>= 1, low ^= low << d)
+    for (int i = 0; i < 32; i = (i + d + 1) & ~d) {
+      const uint32_t t = ((out[i] >> d) ^ out[i + d]) & low;
+      out[i] ^= t << d;
+      out[i + d] ^= t;
+    }
+}
+
 int32_t xorenc_fill_dev_layer(const xorenc_layer *layer, DevLayer *D) {
   if (!layer || layer->struct_size != sizeof(xorenc_layer)) return XORENC_EINVAL;
   xorenc_sizes sz;
@@ -54,19 +66,19 @@ int32_t xorenc_fill_dev_layer(const xorenc_layer *layer, DevLayer *D) {
   D->q = layer->q;
   D->n_slots = sz.n_slots;
   D->n_eslots = sz.n_eslots;
-  for (int j = 0; j < XORENC_MAX_J * XORENC_MAX_N_IN; ++j) D->Mcol_lo[j] = D->Mcol_hi[j] = 0;
-  for (int i = 0; i < layer->n_out; ++i) {
-    const uint32_t row = layer->M_rows[i];
-    if (layer->n_in < 32 && (row >> layer->n_in)) return XORENC_EINVAL;
-    const int w = i / 64, ii = i % 64;
-    for (int j = 0; j < layer->n_in; ++j)
-      if ((row >> j) & 1) {
-        if (ii < 32)
-          D->Mcol_lo[w * XORENC_MAX_N_IN + j] |= 1u << ii;
-        else
-          D->Mcol_hi[w * XORENC_MAX_N_IN + j] |= 1u << (ii - 32);
-      }
-  }
+  const uint32_t beyond = layer->n_in < 32 ? ~0u << layer->n_in : 0u;
+  uint32_t any = 0;
+  for (int i = 0; i < layer->n_out; ++i) any |= layer->M_rows[i];
+  if (any & beyond) return XORENC_EINVAL;
+  static_assert(XORENC_MAX_N_IN == 32, "the columns of 32 rows are a square of bits");
+  for (int w = 0; w < XORENC_MAX_J; ++w)
+    for (int h = 0; h < 2; ++h) {
+      uint32_t *const columns = (h ? D->Mcol_hi : D->Mcol_lo) + w * 32;
+      if (w < D->J)
+        transpose_bits(layer->M_rows + 64 * w + 32 * h, columns);
+      else
+        std::fill(columns, columns + 32, 0u);
+    }
   return XORENC_OK;
 }
 
@@ -97,7 +109,7 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 // product is exact: the same fp32 sums in the same order as ((+-a_1) + (+-a_2)) + ..., and +0.0 where pruned.
 // MW: slices of more than one word (the word's place in its slice picks the tables and the encrypted vector).
 template <int Q, int KIND, bool MW>
-__global__ __launch_bounds__(256) void decode_run_kernel(DevLayer L, void *__restrict__ outv, int64_t ld,
+__global__ __launch_bounds__(256) void decode_run_kernel(DevLayerFor<MW ? XORENC_MAX_J : 1> L, void *__restrict__ outv, int64_t ld,
                                                          int runs_per_rb) {
   constexpr bool DENSE = KIND != 0;
   constexpr int RS = 80;  // bytes between staged rows: the 64 of the run and padding (spreads the staging writes over the banks)
@@ -384,7 +396,7 @@ void launch_decode_run(const DevLayer &D, void *out, int64_t ld, hipStream_t st)
   const size_t lut_bytes = (size_t)D.J * D.nib * (256 + 32) * sizeof(uint2);
   const dim3 grid((unsigned)((runs + 3) / 4)), block(256);
   if (D.J == 1)
-    hipLaunchKernelGGL((decode_run_kernel<Q, KIND, false>), grid, block, lut_bytes, st, D, out, ld, runs_per_rb);
+    hipLaunchKernelGGL((decode_run_kernel<Q, KIND, false>), grid, block, lut_bytes, st, layer_argument<1>(D), out, ld, runs_per_rb);
   else
     hipLaunchKernelGGL((decode_run_kernel<Q, KIND, true>), grid, block, lut_bytes, st, D, out, ld, runs_per_rb);
 }

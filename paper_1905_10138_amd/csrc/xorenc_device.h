@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "xorenc_internal.h"
 #include "xorenc_split_plan.h"
 
@@ -11,7 +13,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-struct DevLayer {
+struct DevLayerCore {
   const uint8_t *enc;
   const uint32_t *mask32;  // the uint64 mask words seen as pairs of 32-bit halves
   const uint32_t *patch_off;
@@ -27,10 +29,27 @@ struct DevLayer {
   // output tile, zero between launches; null: no launch splits the reduction.
   float *split_part;
   uint32_t *split_ticket;
-  // column j of M restricted to word w of a slice (rows 64 w .. 64 w + 63): lower and upper 32 rows
-  uint32_t Mcol_lo[XORENC_MAX_J * XORENC_MAX_N_IN];
-  uint32_t Mcol_hi[XORENC_MAX_J * XORENC_MAX_N_IN];
 };
+
+// The form of a kernel's argument, with M for slices of up to JT words.  A launch copies its arguments to memory that the
+// GPU reads: 1.2 KB of them cost 0.8 us of host time more than a few words do, so kernels for slices of one word take a
+// quarter of M.
+template <int JT>
+struct DevLayerFor : DevLayerCore {
+  // column j of M restricted to word w of a slice (rows 64 w .. 64 w + 63): lower and upper 32 rows
+  uint32_t Mcol_lo[JT * XORENC_MAX_N_IN];
+  uint32_t Mcol_hi[JT * XORENC_MAX_N_IN];
+};
+typedef DevLayerFor<XORENC_MAX_J> DevLayer;
+
+template <int JT>
+inline DevLayerFor<JT> layer_argument(const DevLayer &D) {
+  DevLayerFor<JT> A;
+  static_cast<DevLayerCore &>(A) = D;
+  std::copy(D.Mcol_lo, D.Mcol_lo + JT * XORENC_MAX_N_IN, A.Mcol_lo);
+  std::copy(D.Mcol_hi, D.Mcol_hi + JT * XORENC_MAX_N_IN, A.Mcol_hi);
+  return A;
+}
 
 
 // The product kernels' variants: tables per word, and whether a lane fetches one or two dwords for a field.  Widths that

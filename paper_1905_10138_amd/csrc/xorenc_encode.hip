@@ -792,7 +792,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_add_kernel(uint32_t *off, i
 template <bool SCANNED>
 __global__ __launch_bounds__(ENC_THREADS) void emit_patches_kernel(const uint64_t *pbits, Counts C, int q, int64_t n_slots,
                                                                   int units_per_block, int per, uint32_t *off,
-                                                                  uint16_t *patch, int64_t capacity) {
+                                                                  uint16_t *patch, int64_t capacity, uint32_t *total) {
   __shared__ uint32_t wsum[ENC_THREADS / 64], start_s[EMIT_UNITS];
   __shared__ int64_t slot_s[EMIT_UNITS];  // first bitmap of a unit with patches, -1 for the others
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -842,7 +842,10 @@ __global__ __launch_bounds__(ENC_THREADS) void emit_patches_kernel(const uint64_
   }
   if (mine) {
     off[(int64_t)p * C.n_units + u] = start;
-    if (p == q - 1 && u == C.n_units - 1) off[(int64_t)q * C.n_units] = start + cnt;
+    if (p == q - 1 && u == C.n_units - 1) {
+      off[(int64_t)q * C.n_units] = start + cnt;
+      if (total) __hip_atomic_store(total, start + cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
   __syncthreads();
   // a half wave per unit; the bitmaps of its units are requested together
@@ -918,7 +921,7 @@ namespace {
 int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,
                       const uint32_t *M_rows, const uint64_t *mask, const uint64_t *planes, uint8_t *enc_out,
                       uint32_t *patch_off_out, uint16_t *patch_out, int64_t patch_capacity, void *workspace,
-                      int64_t workspace_bytes, void *hip_stream) {
+                      int64_t workspace_bytes, uint32_t *total_out, void *hip_stream) {
   xorenc_sizes sz;
   const int32_t rc = xorenc_get_sizes(m, n, n_in, q, n_out, &sz);
   if (rc != XORENC_OK) return rc;
@@ -1008,10 +1011,10 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
     hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(1024), 0, st, C.scanned, n_blocks, nscan);
     hipLaunchKernelGGL(scan_add_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, C.scanned, n_blocks);
     hipLaunchKernelGGL(emit_patches_kernel<true>, emit_grid, dim3(ENC_THREADS), 0, st, pbits, C, q, sz.n_slots,
-                       plan.units_per_block, plan.per, patch_off_out, patch_out, patch_capacity);
+                       plan.units_per_block, plan.per, patch_off_out, patch_out, patch_capacity, total_out);
   } else {
     hipLaunchKernelGGL(emit_patches_kernel<false>, emit_grid, dim3(ENC_THREADS), 0, st, pbits, C, q, sz.n_slots,
-                       plan.units_per_block, plan.per, patch_off_out, patch_out, patch_capacity);
+                       plan.units_per_block, plan.per, patch_off_out, patch_out, patch_capacity, total_out);
   }
   return xorenc_internal_check_launch();
 }
@@ -1023,7 +1026,7 @@ extern "C" int32_t xorenc_encode(int32_t m, int32_t n, int32_t n_in, int32_t q, 
                                  uint32_t *patch_off_out, uint16_t *patch_out, int64_t patch_capacity,
                                  void *workspace, int64_t workspace_bytes, void *hip_stream) {
   return encode_common(false, m, n, n_in, q, n_out, M_rows, mask, planes, enc_out, patch_off_out, patch_out,
-                       patch_capacity, workspace, workspace_bytes, hip_stream);
+                       patch_capacity, workspace, workspace_bytes, nullptr, hip_stream);
 }
 
 extern "C" int32_t xorenc_encode_static(int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,
@@ -1039,7 +1042,7 @@ extern "C" int32_t xorenc_encode_static(int32_t m, int32_t n, int32_t n_in, int3
   const int32_t rs = static_scratch_address(&area);
   if (rs != XORENC_OK) return rs;
   return encode_common(false, m, n, n_in, q, n_out, M_rows, mask, planes, enc_out, patch_off_out, patch_out,
-                       patch_capacity, area, XORENC_STATIC_SCRATCH_BYTES, hip_stream);
+                       patch_capacity, area, XORENC_STATIC_SCRATCH_BYTES, nullptr, hip_stream);
 }
 
 extern "C" int32_t xorenc_encode_exhaustive(int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,
@@ -1048,5 +1051,18 @@ extern "C" int32_t xorenc_encode_exhaustive(int32_t m, int32_t n, int32_t n_in, 
                                             int64_t patch_capacity, void *workspace, int64_t workspace_bytes,
                                             void *hip_stream) {
   return encode_common(true, m, n, n_in, q, n_out, M_rows, mask, planes, enc_out, patch_off_out, patch_out,
-                       patch_capacity, workspace, workspace_bytes, hip_stream);
+                       patch_capacity, workspace, workspace_bytes, nullptr, hip_stream);
+}
+
+extern "C" int32_t xorenc_encode_total(int32_t fewest_patches, int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,
+                                       const uint32_t *M_rows, const uint64_t *mask, const uint64_t *planes,
+                                       uint8_t *enc_out, uint32_t *patch_off_out, uint16_t *patch_out,
+                                       int64_t patch_capacity, void *workspace, int64_t workspace_bytes,
+                                       uint32_t *total_out, void *hip_stream) {
+  if (!total_out) return XORENC_EINVAL;
+  if ((uintptr_t)total_out & 3) return XORENC_EALIGN;
+  const int32_t rc = encode_common(fewest_patches != 0, m, n, n_in, q, n_out, M_rows, mask, planes, enc_out, patch_off_out,
+                                   patch_out, patch_capacity, workspace, workspace_bytes, total_out, hip_stream);
+  if (rc != XORENC_OK) return rc;
+  return xorenc_internal_hip_status((int32_t)hipStreamSynchronize(static_cast<hipStream_t>(hip_stream)));
 }

@@ -64,7 +64,7 @@ struct F4Plan {
 // round are requested before the current round's work (always the same number of requests, so that the waits
 // can count them: the last round asks for its own granule again), its patch entries after it.
 template <int Q, int NIBT, int PMAX, bool MR>
-__global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayer L, const uint16_t *__restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L, const uint16_t *__restrict__ X, int64_t ldx,
                                                                int B, float *__restrict__ Y, int64_t ldy, int PW, int KS,
                                                                int RG, int rounds, uint64_t kq_tab,
                                                                uint64_t rg_tab) {
@@ -588,6 +588,7 @@ template <int Q>
 int32_t launch_f4(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y, int64_t ldy, const F4Plan &P,
                   hipStream_t st) {
   const uint16_t *Xh = static_cast<const uint16_t *>(X);
+  const DevLayerFor<1> A = layer_argument<1>(D);
   const dim3 grid(P.grid), block(kF4Waves * 64);
   uint64_t kq_tab = 0, rg_tab = 0;  // wave w: K range w % KS of granule w / KS of the round
   for (int w = 0; w < kF4Waves; ++w) {
@@ -596,17 +597,17 @@ int32_t launch_f4(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y
   }
   if (P.rounds == 1 && B <= kF4MaxBOneRound) {
     switch (D.nib) {
-      case 1: hipLaunchKernelGGL((spmm_f4_kernel<Q, 1, f4_pmax(Q), false>), grid, block, 0, st, D, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
-      case 2: hipLaunchKernelGGL((spmm_f4_kernel<Q, 2, f4_pmax(Q), false>), grid, block, 0, st, D, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
-      case 3: hipLaunchKernelGGL((spmm_f4_kernel<Q, 3, f4_pmax(Q), false>), grid, block, 0, st, D, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
-      default: hipLaunchKernelGGL((spmm_f4_kernel<Q, 4, f4_pmax(Q), false>), grid, block, 0, st, D, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
+      case 1: hipLaunchKernelGGL((spmm_f4_kernel<Q, 1, f4_pmax(Q), false>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
+      case 2: hipLaunchKernelGGL((spmm_f4_kernel<Q, 2, f4_pmax(Q), false>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
+      case 3: hipLaunchKernelGGL((spmm_f4_kernel<Q, 3, f4_pmax(Q), false>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
+      default: hipLaunchKernelGGL((spmm_f4_kernel<Q, 4, f4_pmax(Q), false>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
     }
   } else {
     switch (D.nib) {
-      case 1: hipLaunchKernelGGL((spmm_f4_kernel<Q, 1, f4_pmax_mr(Q, 1), true>), grid, block, 0, st, D, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
-      case 2: hipLaunchKernelGGL((spmm_f4_kernel<Q, 2, f4_pmax_mr(Q, 2), true>), grid, block, 0, st, D, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
-      case 3: hipLaunchKernelGGL((spmm_f4_kernel<Q, 3, f4_pmax_mr(Q, 3), true>), grid, block, 0, st, D, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
-      default: hipLaunchKernelGGL((spmm_f4_kernel<Q, 4, f4_pmax_mr(Q, 4), true>), grid, block, 0, st, D, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
+      case 1: hipLaunchKernelGGL((spmm_f4_kernel<Q, 1, f4_pmax_mr(Q, 1), true>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
+      case 2: hipLaunchKernelGGL((spmm_f4_kernel<Q, 2, f4_pmax_mr(Q, 2), true>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
+      case 3: hipLaunchKernelGGL((spmm_f4_kernel<Q, 3, f4_pmax_mr(Q, 3), true>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
+      default: hipLaunchKernelGGL((spmm_f4_kernel<Q, 4, f4_pmax_mr(Q, 4), true>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
     }
   }
   return xorenc_internal_check_launch();

@@ -104,7 +104,8 @@ __device__ inline void build_xor_table(int lane, const uint32_t *col_lo, const u
 // have to travel before anything is built.  A wave takes a table at a time, so that the waves' loads travel together; one
 // table after the other by all waves, each behind its own loads, took 1.5 us of every product with six tables (192-bit
 // slices, n_in = 16: 4096 x 4096, B = 32 8.2 -> 6.7 us) and 1.1 us with nine in spmm_tile_kernel.
-__device__ inline void build_shared_tables(const DevLayer &L, int wave, int waves, int lane, int J, int nib, uint32_t *lut,
+template <int JT>
+__device__ inline void build_shared_tables(const DevLayerFor<JT> &L, int wave, int waves, int lane, int J, int nib, uint32_t *lut,
                                            int word_stride) {
   for (int i = wave; i < J * nib; i += waves) {  // uniform
     const int w = i / nib, b = i - w * nib;
@@ -136,7 +137,7 @@ struct BoolC {
 // each of 64 rows per word of a row of W).  The wave walks over the three slices of X of every slice of W with the same
 // operands; hi has accumulators of its own, so that the sums of the large terms are rounded as they would be alone.
 template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int NIBV, int JT, bool NARROW = false, int TERMS = 1>
-__global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void spmm_kernel(DevLayer L, const void *__restrict__ Xv, int64_t ldx, int B,
+__global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void spmm_kernel(DevLayerFor<JT> L, const void *__restrict__ Xv, int64_t ldx, int B,
                                                       float *__restrict__ Y, int64_t ldy, int slices_per_split,
                                                       int n_splits) {
   constexpr int CW = 32 * NCB;                 // bf16 columns held in LDS per X row
@@ -1091,7 +1092,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
 template <int NCB, int Q, int RB, bool XF32, int NW, bool XFAST, int NIBV, int JT, bool NARROW = false, int TERMS = 1>
 inline void launch_variant(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y, int64_t ldy, dim3 grid,
                            int sps, int n_splits, hipStream_t st) {
-  hipLaunchKernelGGL((spmm_kernel<NCB, Q, RB, XF32, NW, XFAST, NIBV, JT, NARROW, TERMS>), grid, dim3(NW * 64), 0, st, D, X,
+  hipLaunchKernelGGL((spmm_kernel<NCB, Q, RB, XF32, NW, XFAST, NIBV, JT, NARROW, TERMS>), grid, dim3(NW * 64), 0, st,
+                     layer_argument<JT>(D), X,
                      ldx, B, Y, ldy, sps, n_splits);
 }
 

@@ -23,7 +23,7 @@
 namespace xorenc_spmm_detail {
 
 template <int Q, int RB, int NW, int NIBV>
-__global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayer L, const uint16_t *__restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(NW * 64) void spmm_small_kernel(DevLayerFor<1> L, const uint16_t *__restrict__ X, int64_t ldx,
                                                             int B, float *__restrict__ Y, int64_t ldy,
                                                             int slices_per_split, int n_splits) {
   constexpr int NIBT = tables_of_variant(NIBV);
@@ -367,21 +367,22 @@ int32_t launch_small(const DevLayer &D, const void *X, int64_t ldx, int B, float
   const dim3 grid((D.nrb + RB - 1) / RB, 1, ks);
   const int atomic = ks;  // number of splits
   const uint16_t *Xh = static_cast<const uint16_t *>(X);
+  const DevLayerFor<1> A = layer_argument<1>(D);
   switch (D.nib_variant) {
     case 1:
-      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 1>), grid, dim3(NW * 64), 0, st, D, Xh, ldx, B, Y, ldy, sps, atomic);
+      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 1>), grid, dim3(NW * 64), 0, st, A, Xh, ldx, B, Y, ldy, sps, atomic);
       break;
     case 2:
-      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 2>), grid, dim3(NW * 64), 0, st, D, Xh, ldx, B, Y, ldy, sps, atomic);
+      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 2>), grid, dim3(NW * 64), 0, st, A, Xh, ldx, B, Y, ldy, sps, atomic);
       break;
     case 3:
-      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 3>), grid, dim3(NW * 64), 0, st, D, Xh, ldx, B, Y, ldy, sps, atomic);
+      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 3>), grid, dim3(NW * 64), 0, st, A, Xh, ldx, B, Y, ldy, sps, atomic);
       break;
     case 4:
-      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 4>), grid, dim3(NW * 64), 0, st, D, Xh, ldx, B, Y, ldy, sps, atomic);
+      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, 4>), grid, dim3(NW * 64), 0, st, A, Xh, ldx, B, Y, ldy, sps, atomic);
       break;
     default:
-      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, kFourTablesTwoDwords>), grid, dim3(NW * 64), 0, st, D, Xh, ldx, B, Y, ldy, sps, atomic);
+      hipLaunchKernelGGL((spmm_small_kernel<Q, RB, NW, kFourTablesTwoDwords>), grid, dim3(NW * 64), 0, st, A, Xh, ldx, B, Y, ldy, sps, atomic);
       break;
   }
   return xorenc_internal_check_launch();

@@ -354,3 +354,34 @@ def test_fewest_patches_by_syndrome(n_out, n_in, q, busy, copies):
     assert np.array_equal(np.asarray(n_patch).reshape(shape), np.broadcast_to(np.asarray(onp).reshape(q, 1, m), shape))
     per_plane = np.split(np.asarray(odp), np.cumsum(np.asarray(onp).reshape(q, -1).sum(axis=1))[:-1])
     assert np.array_equal(np.asarray(d_patch), np.concatenate([np.tile(d, copies) for d in per_plane]))
+
+
+def test_patch_totals_of_calls_in_several_threads_and_retries():
+    """The total comes back in a word of host memory per thread: calls of several threads on their own streams, and calls
+    whose first patch buffer was too small, get their own."""
+    import threading
+    import torch
+    cases = [("tiny", 256, 256, 0.5), ("fig1", 200, 448, 0.6), ("large_q1", 320, 1024, 0.9)]
+    works = [encoded_workload(name, m, n, S=S, n_out=64, n_in=8) for name, m, n, S in cases]
+    want = [sum(int(p.sum()) for p in enc.n_patch) for _, enc in works]
+    got = {}
+
+    def run(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            got[i] = [gpu_encode(works[i][0]).patch.numel() for _ in range(20)]
+
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(len(works))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert got == {i: [w] * 20 for i, w in enumerate(want)}
+    import paper_1905_10138_amd as xe
+    wl = works[0][0]
+    mask = torch.from_numpy(xe.pack_bits(wl.keep[:, :wl.n], 64).view(np.int64)).cuda()
+    planes = torch.from_numpy(xe.pack_bits(wl.planes[0][:, :wl.n], 64).view(np.int64)[None].copy()).cuda()
+    M_rows = (wl.M.astype(np.uint64) << np.arange(8, dtype=np.uint64)).sum(axis=1).astype(np.uint32)
+    for cap in (0, 1, want[0] - 1, want[0]):
+        L = xe.encode(wl.m, wl.n, 8, 1, M_rows, mask, planes, torch.from_numpy(wl.alpha).cuda(), patch_capacity=cap)
+        assert L.patch.numel() == want[0]
+        assert np.array_equal(L.patch.cpu().numpy(), gpu_encode(wl).patch.cpu().numpy())
