@@ -103,19 +103,45 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   const int spr64 = l_spr * 64;
   const uint32_t CS = (uint32_t)(spr64 * 2 + 16);     // bytes between the columns of the raw copy of X
 
-  // ---- X first: it is needed first.  Thread t takes rows t, t + NT, ... of every column (rows beyond n read as
-  // zero); the first XR rows per column are requested now, the rest (long reductions) when those are parked.
+  // ---- X first: it is needed first.  One item = the 32 values of one half-word (blk) of one column (c), converted by one
+  // thread.  Columns that follow each other without gaps (ldx == B, at most two) are requested by that thread in 16-byte
+  // pieces and never pass through LDS unconverted: one trip to memory and two barriers fewer (us a launch, 4096 x 9216, two
+  // planes, B = 1 10.1 -> 8.8, B = 2 11.8 -> 9.8; 16384 x 4096, one plane, B = 1 8.2 -> 7.6).
+  // Otherwise thread t takes rows t, t + NT, ... of every column (rows beyond n read as zero); the first XR rows per
+  // column are requested now, the rest (long reductions of more columns) when those are parked.
+  const bool direct = B <= 2 && ldx == B && (reinterpret_cast<uintptr_t>(X) & 15) == 0;  // uniform
+  const int nb = 2 * l_spr, nb_pad = 4 * ((l_spr + 1) >> 1);
+  int cv_c, cv_blk;
+  if (MR && B >= 5) {
+    cv_c = tid & 7;
+    cv_blk = tid >> 3;
+  } else if (B >= 3) {  // lanes c fastest, then blk%4: the 16-byte reads of 16 lanes fall into 16 different bank groups
+    cv_c = tid & 3;
+    cv_blk = tid >> 2;
+  } else {
+    cv_c = B == 2 ? tid & 1 : 0;
+    cv_blk = B == 2 ? tid >> 1 : tid;
+  }
+  const bool cv_valid = cv_c < B && cv_blk < nb_pad;
   const uint32_t x_extent = (uint32_t)(((int64_t)(l_n - 1) * ldx + B) * 2);
   const __amdgpu_buffer_rsrc_t xrsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(X), 0, x_extent, kRsrcFlags);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(X), 0, direct ? (x_extent + 3u) & ~3u : x_extent, kRsrcFlags);
   const uint32_t row_bytes = (uint32_t)(ldx * 2);
-  uint16_t xv[MAXB][XR];
+  u32x4 xd[8];            // direct: the item's pieces (of both columns)
+  uint16_t xv[MAXB][XR];  // otherwise
+  if (direct) {
 #pragma unroll
-  for (int c = 0; c < MAXB; ++c)
-    if (c < B)  // uniform
+    for (int i = 0; i < 8; ++i)
+      if (i < 4 || B == 2)  // uniform
+        xd[i] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, cv_valid ? (uint32_t)cv_blk * (uint32_t)(64 * B) + 16u * i : 1u << 30, 0, 0);
+  } else {
 #pragma unroll
-      for (int i = 0; i < XR; ++i)
-        xv[c][i] = __builtin_amdgcn_raw_buffer_load_b16(xrsrc, (uint32_t)(tid + i * NT) * row_bytes + (uint32_t)(2 * c), 0, 0);
+    for (int c = 0; c < MAXB; ++c)
+      if (c < B)  // uniform
+#pragma unroll
+        for (int i = 0; i < XR; ++i)
+          xv[c][i] = __builtin_amdgcn_raw_buffer_load_b16(xrsrc, (uint32_t)(tid + i * NT) * row_bytes + (uint32_t)(2 * c), 0, 0);
+  }
 
   // ---- compressed words of one granule: per pair the lane's mask half and its dword(s) of encrypted bits
   struct Ring {
@@ -217,52 +243,55 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   for (int s = 0; s < FG; ++s) *reinterpret_cast<u32x4 *>(myflips + s * 256 + lane * 4) = u32x4{0u, 0u, 0u, 0u};
 
   // ---- raw X into LDS, column-major: element (k, c) at c*CS + 2k
-#pragma unroll
-  for (int c = 0; c < MAXB; ++c)
-    if (c < B)  // uniform
-#pragma unroll
-      for (int i = 0; i < XR; ++i)
-        if (tid + i * NT < spr64) *reinterpret_cast<uint16_t *>(xs + c * CS + (tid + i * NT) * 2) = xv[c][i];
-  for (int c = 0; c < B; ++c)                          // uniform
-    for (int k0 = XR * NT; k0 < spr64; k0 += XR * NT) {  // uniform
-      uint16_t v[XR];
-#pragma unroll
-      for (int i = 0; i < XR; ++i)
-        v[i] = __builtin_amdgcn_raw_buffer_load_b16(xrsrc, (uint32_t)(k0 + tid + i * NT) * row_bytes + (uint32_t)(2 * c), 0, 0);
-#pragma unroll
-      for (int i = 0; i < XR; ++i)
-        if (k0 + tid + i * NT < spr64) *reinterpret_cast<uint16_t *>(xs + c * CS + (k0 + tid + i * NT) * 2) = v[i];
-    }
-  __syncthreads();  // raw X complete
-
-  // ---- X -> two e4m3 terms per value.  One item = the 32 values of one half-word (blk) of one column (c); the
-  // half-words of the word that pads an odd number of words to whole pairs are written as zeros.
-  const int nb = 2 * l_spr, nb_pad = 4 * ((l_spr + 1) >> 1);
-  int cv_c, cv_blk;
-  if (MR && B >= 5) {
-    cv_c = tid & 7;
-    cv_blk = tid >> 3;
-  } else if (B >= 3) {  // lanes c fastest, then blk%4: the 16-byte reads of 16 lanes fall into 16 different bank groups
-    cv_c = tid & 3;
-    cv_blk = tid >> 2;
-  } else {
-    cv_c = B == 2 ? tid & 1 : 0;
-    cv_blk = B == 2 ? tid >> 1 : tid;
-  }
-  const bool cv_valid = cv_c < B && cv_blk < nb_pad;
   u32x4 V4[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) V4[i] = u32x4{0u, 0u, 0u, 0u};
-  if (cv_valid && cv_blk < nb) {
-    const uint8_t *src = xs + cv_c * CS + cv_blk * 64;
+  if (!direct) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) V4[i] = *reinterpret_cast<const u32x4 *>(src + 16 * i);
+    for (int c = 0; c < MAXB; ++c)
+      if (c < B)  // uniform
+#pragma unroll
+        for (int i = 0; i < XR; ++i)
+          if (tid + i * NT < spr64) *reinterpret_cast<uint16_t *>(xs + c * CS + (tid + i * NT) * 2) = xv[c][i];
+    for (int c = 0; c < B; ++c)                          // uniform
+      for (int k0 = XR * NT; k0 < spr64; k0 += XR * NT) {  // uniform
+        uint16_t v[XR];
+#pragma unroll
+        for (int i = 0; i < XR; ++i)
+          v[i] = __builtin_amdgcn_raw_buffer_load_b16(xrsrc, (uint32_t)(k0 + tid + i * NT) * row_bytes + (uint32_t)(2 * c), 0, 0);
+#pragma unroll
+        for (int i = 0; i < XR; ++i)
+          if (k0 + tid + i * NT < spr64) *reinterpret_cast<uint16_t *>(xs + c * CS + (k0 + tid + i * NT) * 2) = v[i];
+      }
+    __syncthreads();  // raw X complete
+    // (the half-words of the word that pads an odd number of words to whole pairs are written as zeros)
+    if (cv_valid && cv_blk < nb) {
+      const uint8_t *src = xs + cv_c * CS + cv_blk * 64;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) V4[i] = *reinterpret_cast<const u32x4 *>(src + 16 * i);
+    }
+    __syncthreads();  // every raw value is in a register: the area becomes the operand area
   }
-  __syncthreads();  // every raw value is in a register: the area becomes the operand area
+
+  // ---- X -> two e4m3 terms per value
   if (cv_valid) {
     uint32_t V[16];
+    if (direct) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) V[i] = V4[i >> 2][i & 3];
+      for (int i = 0; i < 16; ++i) {
+        V[i] = xd[i >> 2][i & 3];
+        if (B == 2)  // uniform: rows 2 i and 2 i + 1, each with its two columns in a dword
+          V[i] = __builtin_amdgcn_perm(xd[i >> 1][2 * (i & 1) + 1], xd[i >> 1][2 * (i & 1)], cv_c ? 0x07060302u : 0x05040100u);
+      }
+      const int left = l_n - 32 * cv_blk;  // rows of the item; the dword that the last one ends in may hold another value
+      if (left < 32) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) V[i] &= 2 * i + 1 < left ? ~0u : 2 * i < left ? 0xFFFFu : 0u;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) V[i] = V4[i >> 2][i & 3];
+    }
     uint32_t mx = 0u;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -361,12 +390,16 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
       }
     }
   }
-  __syncthreads();  // the operand area is free: it now takes the partial sums
+  // the partial sums lie behind the operands, or in their place once every wave has its own
+  constexpr int RED_BYTES = (MR ? 2 : 1) * kF4Waves * Q * 512;
+  const int x_bytes = nb_pad * 64 * B;
+  const int red_at = x_bytes + RED_BYTES <= kF4XBytes ? x_bytes : 0;
+  if (red_at == 0) __syncthreads();  // uniform
 
   const uint8_t *const lut_lane = reinterpret_cast<const uint8_t *>(lut) + (kg & 1) * 16;
   const uint32_t last_bits = (uint32_t)(n_in - 8 * (NIBT - 1));
   const uint32_t flip_lane = (uint32_t)(lane * 16);
-  float *const red = reinterpret_cast<float *>(xs);
+  float *const red = reinterpret_cast<float *>(xs + red_at);
   __builtin_amdgcn_s_setprio(0);
 
   // one round: the granules gran0 + r RG .. of the workgroup
@@ -395,39 +428,49 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
       // where an entry v = (row%32) << 6 | bit goes inside the flip area of its unit, and the bit it flips
       auto flip_addr = [](uint32_t v) { return ((((v >> 6) & 15u) + ((v >> 1) & 16u)) << 4) + ((v & 3u) << 2); };
       auto flip_val = [](uint32_t v) { return 8u << (((v >> 2) & 7u) << 2); };
+      // A group is G pairs of QI planes, as many as the flip area has room for: the mask's four arrangements are formed once
+      // for the planes of a pair (4096 x 9216, two planes, B = 1 8.8 -> 8.6 us).
+      constexpr int QI = Q <= FG ? Q : 1;
+      constexpr int G = FG / QI;
+#pragma unroll
+      for (int p0 = 0; p0 < Q; p0 += QI) {
 #pragma clang loop unroll(full)
-      for (int g0 = 0; g0 < PMAX; g0 += FG) {
-        if (g0 < npw) {  // uniform; a break here would make the trip count a run-time value and keep the loop rolled
+        for (int g0 = 0; g0 < PMAX; g0 += G) {
+          if (g0 < npw) {  // uniform; a break here would make the trip count a run-time value and keep the loop rolled
+            // ---- patch flips of the group's 2 G units (words w_lo + 2 g0 ..): list ends ub[k] relative to the first entry of
+            // the wave's range; entry j belongs to unit t = number of ends <= j, whose 512 bytes of the plane's flip area
+            // start at 512 t
+            uint32_t ub[QI][2 * G + 1];
 #pragma unroll
-          for (int p = 0; p < Q; ++p) {
-            // ---- patch flips of the group's 2 FG units (words w_lo + 2 g0 ..): list ends ub[k] relative to the
-            // first entry of the wave's range; entry j belongs to unit t = number of ends <= j, whose 512 bytes of
-            // the flip area start at 512 t
-            const uint32_t base = __builtin_amdgcn_readlane(offv[p], 0);
-            uint32_t ub[2 * FG + 1];
+            for (int pi = 0; pi < QI; ++pi) {
+              const int p = p0 + pi;
+              uint32_t(&ends)[2 * G + 1] = ub[pi];
+              uint8_t *const area = fl + pi * (G * 1024);
+              const uint32_t base = __builtin_amdgcn_readlane(offv[p], 0);
 #pragma unroll
-            for (int k = 0; k <= 2 * FG; ++k)
-              ub[k] = __builtin_amdgcn_readlane(offv[p], (2 * g0 + k) < 2 * PMAX ? (2 * g0 + k) : 2 * PMAX) - base;
-            if (ub[2 * FG] > ub[0]) {  // uniform
-              if (fast) {
-                if (f_mine[p] && (uint32_t)lane >= ub[0] && (uint32_t)lane < ub[2 * FG]) {
-                  uint32_t t = 0;
+              for (int k = 0; k <= 2 * G; ++k)
+                ends[k] = __builtin_amdgcn_readlane(offv[p], (2 * g0 + k) < 2 * PMAX ? (2 * g0 + k) : 2 * PMAX) - base;
+              if (ends[2 * G] > ends[0]) {  // uniform
+                if (fast) {
+                  if (f_mine[p] && (uint32_t)lane >= ends[0] && (uint32_t)lane < ends[2 * G]) {
+                    uint32_t t = 0;
 #pragma unroll
-                  for (int k = 1; k < 2 * FG; ++k) t += (uint32_t)lane >= ub[k] ? 1u : 0u;
-                  __hip_atomic_fetch_xor(reinterpret_cast<uint32_t *>(fl + f_addr[p] + t * 512u), f_val[p],
-                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                }
-              } else {
-                for (uint32_t j0 = ub[0]; j0 < ub[2 * FG]; j0 += 64u) {  // uniform
-                  const uint32_t j = j0 + (uint32_t)lane;
-                  if (j < ub[2 * FG]) {
-                    const uint32_t v = (l_patch + base)[j];
-                    if ((int)(v >> 10) == h) {
-                      uint32_t t = 0;
+                    for (int k = 1; k < 2 * G; ++k) t += (uint32_t)lane >= ends[k] ? 1u : 0u;
+                    __hip_atomic_fetch_xor(reinterpret_cast<uint32_t *>(area + f_addr[p] + t * 512u), f_val[p],
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                  }
+                } else {
+                  for (uint32_t j0 = ends[0]; j0 < ends[2 * G]; j0 += 64u) {  // uniform
+                    const uint32_t j = j0 + (uint32_t)lane;
+                    if (j < ends[2 * G]) {
+                      const uint32_t v = (l_patch + base)[j];
+                      if ((int)(v >> 10) == h) {
+                        uint32_t t = 0;
 #pragma unroll
-                      for (int k = 1; k < 2 * FG; ++k) t += j >= ub[k] ? 1u : 0u;
-                      __hip_atomic_fetch_xor(reinterpret_cast<uint32_t *>(fl + flip_addr(v) + t * 512u), flip_val(v),
-                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                        for (int k = 1; k < 2 * G; ++k) t += j >= ends[k] ? 1u : 0u;
+                        __hip_atomic_fetch_xor(reinterpret_cast<uint32_t *>(area + flip_addr(v) + t * 512u), flip_val(v),
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                      }
                     }
                   }
                 }
@@ -435,50 +478,53 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
             }
             // ---- the group's pairs
 #pragma unroll
-            for (int s = 0; s < FG; ++s) {
+            for (int s = 0; s < G; ++s) {
               const int pp = g0 + s;
               if (pp < PMAX && pp < npw) {  // uniform
                 const uint32_t mw = ring.mw[pp < PMAX ? pp : 0];
-                uint32_t x;
-                if (two_dw)
-                  x = __builtin_amdgcn_alignbit(ring.e1[pp < PMAX ? pp : 0][p], ring.e0[pp < PMAX ? pp : 0][p], sh);
-                else
-                  x = ring.e0[pp < PMAX ? pp : 0][p] >> sh;
-                u32x4 sg;
-                {
-                  const uint32_t i0 = NIBT == 1 ? __builtin_amdgcn_ubfe(x, 0, last_bits) : (x & 255u);
-                  sg = *reinterpret_cast<const u32x4 *>(lut_lane + i0 * 32u);
-                }
-                if constexpr (NIBT >= 2) {
-                  const uint32_t i1 = NIBT == 2 ? __builtin_amdgcn_ubfe(x, 8, last_bits) : ((x >> 8) & 255u);
-                  sg ^= *reinterpret_cast<const u32x4 *>(lut_lane + 8192u + i1 * 32u);
-                }
-                if constexpr (NIBT >= 3) {
-                  const uint32_t i2 = NIBT == 3 ? __builtin_amdgcn_ubfe(x, 16, last_bits) : ((x >> 16) & 255u);
-                  sg ^= *reinterpret_cast<const u32x4 *>(lut_lane + 16384u + i2 * 32u);
-                }
-                if constexpr (NIBT >= 4) {
-                  const uint32_t i3 = __builtin_amdgcn_ubfe(x, 24, last_bits);
-                  sg ^= *reinterpret_cast<const u32x4 *>(lut_lane + 24576u + i3 * 32u);
-                }
-                if (ub[2 * s + 2] > ub[2 * s]) {  // uniform: the pair has entries; the area is left zeroed
-                  u32x4 *fp = reinterpret_cast<u32x4 *>(fl + s * 1024 + flip_lane);
-                  sg ^= *fp;
-                  *fp = u32x4{0u, 0u, 0u, 0u};
-                }
-                i32x8 bw;
-                bw[0] = (int)((mw & 0x11111111u) | sg[0]);
-                bw[1] = (int)((mw & 0x22222222u) | sg[1]);
-                bw[2] = (int)((mw & 0x44444444u) | sg[2]);
-                bw[3] = (int)(((mw >> 3) & 0x11111111u) | sg[3]);
-                bw[4] = bw[5] = bw[6] = bw[7] = 0;
+                const u32x4 kept = {mw & 0x11111111u, mw & 0x22222222u, mw & 0x44444444u, (mw >> 3) & 0x11111111u};
                 const int sa = (int)xsc[(pp < PMAX ? pp : 0) >> 2];
                 const i32x8 xo = xop[pp < PMAX ? pp : 0];
-                switch (pp & 3) {  // the byte of the scale register is part of the instruction
-                  case 0: acc[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xo, bw, acc[p], 0, 4, 0, sa, 0, 127); break;
-                  case 1: acc[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xo, bw, acc[p], 0, 4, 1, sa, 0, 127); break;
-                  case 2: acc[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xo, bw, acc[p], 0, 4, 2, sa, 0, 127); break;
-                  default: acc[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xo, bw, acc[p], 0, 4, 3, sa, 0, 127); break;
+#pragma unroll
+                for (int pi = 0; pi < QI; ++pi) {
+                  const int p = p0 + pi;
+                  uint32_t x;
+                  if (two_dw)
+                    x = __builtin_amdgcn_alignbit(ring.e1[pp < PMAX ? pp : 0][p], ring.e0[pp < PMAX ? pp : 0][p], sh);
+                  else
+                    x = ring.e0[pp < PMAX ? pp : 0][p] >> sh;
+                  u32x4 sg;
+                  {
+                    const uint32_t i0 = NIBT == 1 ? __builtin_amdgcn_ubfe(x, 0, last_bits) : (x & 255u);
+                    sg = *reinterpret_cast<const u32x4 *>(lut_lane + i0 * 32u);
+                  }
+                  if (ub[pi][2 * s + 2] > ub[pi][2 * s]) {  // uniform: the pair has entries; the area is left zeroed
+                    u32x4 *fp = reinterpret_cast<u32x4 *>(fl + pi * (G * 1024) + s * 1024 + flip_lane);
+                    sg ^= *fp;
+                    *fp = u32x4{0u, 0u, 0u, 0u};
+                  }
+                  if constexpr (NIBT >= 2) {
+                    const uint32_t i1 = NIBT == 2 ? __builtin_amdgcn_ubfe(x, 8, last_bits) : ((x >> 8) & 255u);
+                    sg ^= *reinterpret_cast<const u32x4 *>(lut_lane + 8192u + i1 * 32u);
+                  }
+                  if constexpr (NIBT >= 3) {
+                    const uint32_t i2 = NIBT == 3 ? __builtin_amdgcn_ubfe(x, 16, last_bits) : ((x >> 16) & 255u);
+                    sg ^= *reinterpret_cast<const u32x4 *>(lut_lane + 16384u + i2 * 32u);
+                  }
+                  if constexpr (NIBT >= 4) {
+                    const uint32_t i3 = __builtin_amdgcn_ubfe(x, 24, last_bits);
+                    sg ^= *reinterpret_cast<const u32x4 *>(lut_lane + 24576u + i3 * 32u);
+                  }
+                  i32x8 bw;
+#pragma unroll
+                  for (int d = 0; d < 4; ++d) bw[d] = (int)(sg[d] | kept[d]);
+                  bw[4] = bw[5] = bw[6] = bw[7] = 0;
+                  switch (pp & 3) {  // the byte of the scale register is part of the instruction
+                    case 0: acc[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xo, bw, acc[p], 0, 4, 0, sa, 0, 127); break;
+                    case 1: acc[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xo, bw, acc[p], 0, 4, 1, sa, 0, 127); break;
+                    case 2: acc[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xo, bw, acc[p], 0, 4, 2, sa, 0, 127); break;
+                    default: acc[p] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(xo, bw, acc[p], 0, 4, 3, sa, 0, 127); break;
+                  }
                 }
               }
             }
@@ -505,8 +551,16 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
         float y = 0.f;
 #pragma unroll
         for (int p = 0; p < Q; ++p) {
-          float sum = src[p * 128];
-          for (int k = 1; k < KS; ++k) sum += src[(k * Q + p) * 128];
+          // (four reads travel together)
+          float sum = 0.f;
+          for (int k0 = 0; k0 < KS; k0 += 4) {  // uniform
+            float v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = src[(min(k0 + k, KS - 1) * Q + p) * 128];
+            sum = k0 ? sum + v[0] : v[0];
+#pragma unroll
+            for (int k = 1; k < 4; ++k) sum = k0 + k < KS ? sum + v[k] : sum;
+          }
           const float a = -2.0f * al[p];
           y = p == 0 ? a * sum : y + a * sum;
         }

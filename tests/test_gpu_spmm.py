@@ -860,3 +860,40 @@ def test_threads_that_call_on_one_stream():
     torch.cuda.synchronize()
     for i, w in enumerate(want):
         assert len(got[i]) == 12 and all(torch.equal(y, w) for y in got[i]), i
+
+
+@pytest.mark.parametrize("m,n,q,n_in", [(40, 1, 1, 8), (70, 33, 1, 16), (64, 95, 2, 16), (33, 130, 3, 20), (64, 2047, 4, 8),
+                                        (48, 4097, 2, 24), (80, 9001, 1, 16), (4500, 4001, 2, 8), (64, 16383, 1, 8)])
+def test_columns_without_gaps_are_the_columns_with_gaps(m, n, q, n_in):
+    """One or two columns that follow each other without gaps go to the converting threads in 16-byte pieces, others element
+    by element through LDS: the same conversion, so the same bits in Y, also where the last piece ends inside a dword and
+    what lies behind X is not a number.  (16 383 rows: the sums take the operands' place; 4500 rows of W: several rounds.)"""
+    import torch
+    import paper_1905_10138_amd as xe
+    dev = torch.device("cuda:0")
+    sz = xe.get_sizes(m, n, n_in, q)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    words = lambda *shape: torch.randint(-2**63, 2**63 - 1, shape, dtype=torch.int64, device=dev, generator=g)
+    mask = (words(sz["n_slots"]) & words(sz["n_slots"]) & words(sz["n_slots"])).view(-1, sz["spr"], 32)
+    mask = mask * (torch.arange(sz["m_pad"], device=dev).view(-1, 1, 32) < m)
+    if n % 64:
+        mask[:, -1] &= (1 << n % 64) - 1
+    M_rows = np.random.default_rng(n_in).integers(1, 1 << n_in, size=64).astype(np.uint32)
+    alpha = torch.rand((q, m), device=dev, generator=g) + 0.5
+    L = xe.encode(m, n, n_in, q, M_rows, mask.reshape(-1).contiguous(), words(q, sz["n_slots"]), alpha)
+    W = xe.decode(L, xe.OUT_F32).double()
+    for B in (1, 2):
+        whole = torch.full((n * B + 24,), float("nan"), dtype=torch.bfloat16, device=dev)
+        X = whole[:n * B].view(n, B)
+        X.copy_(torch.randn((n, B), device=dev, generator=g))
+        gaps = torch.full((n, B + 3), float("nan"), dtype=torch.bfloat16, device=dev)[:, :B]
+        gaps.copy_(X)
+        shifted = torch.full((n * B + 24,), float("nan"), dtype=torch.bfloat16, device=dev)[1:1 + n * B].view(n, B)
+        shifted.copy_(X)
+        Y = xe.spmm(L, X)
+        assert torch.equal(Y, xe.spmm(L, gaps))
+        assert torch.equal(Y, xe.spmm(L, shifted))
+        want = W @ X.double()
+        # two FP8 terms per value, see few_column_allowance: 1.5e-6 to 5e-6 of the result's norm observed
+        assert float((Y.double() - want).norm() / want.norm()) <= 2e-5
