@@ -251,6 +251,15 @@ XORENC_API int32_t xorenc_encode_total(int32_t fewest_patches, int32_t m, int32_
                                        uint32_t *total_out, void *hip_stream);
 
 /*
+ * Behind xorenc_encode_total with the same sizes, whose total exceeds its patch_capacity: writes the offsets and the patch
+ * lists again, into a larger buffer, from what that call left in its workspace (one kernel instead of all of them), and
+ * waits.  The workspace must not have been used in between.
+ */
+XORENC_API int32_t xorenc_encode_patches(int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,
+                                         uint32_t *patch_off_out, uint16_t *patch_out, int64_t patch_capacity,
+                                         void *workspace, int64_t workspace_bytes, uint32_t *total_out, void *hip_stream);
+
+/*
  * xorenc_encode for callers that cannot allocate device memory and have no workspace to pass: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, outputs, kernels and
  * stream behaviour as xorenc_encode, without the workspace: the patch bitmaps and the per-unit counts go to an

@@ -92,6 +92,8 @@ def load_library():
     lib.xorenc_encode_exhaustive.argtypes = lib.xorenc_encode.argtypes
     lib.xorenc_encode_total.restype = i32
     lib.xorenc_encode_total.argtypes = [i32] + lib.xorenc_encode.argtypes[:-1] + [vp, vp]
+    lib.xorenc_encode_patches.restype = i32
+    lib.xorenc_encode_patches.argtypes = [i32, i32, i32, i32, i32, vp, vp, i64, vp, i64, vp, vp]
     lib.xorenc_encode_static.restype = i32
     lib.xorenc_encode_static.argtypes = [i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, i64, vp]
     lib.xorenc_decode.restype = i32
@@ -314,8 +316,8 @@ def encode(m, n, n_in, q, M_rows, mask, planes, alpha, patch_capacity: Optional[
            n_out: int = 64, _entry: str = "xorenc_encode") -> PackedLayer:
     """xorenc_encode on the current stream.  mask: int64 GPU tensor [n_slots] (unit-major words),
     planes: int64 GPU tensor [q, n_slots], alpha: float32 GPU tensor [q, m].  Returns a device
-    PackedLayer that shares `mask` and `alpha`.  Synchronises once to read the patch total (the
-    C call itself does not) and retries with a larger patch buffer if the first was too small."""
+    PackedLayer that shares `mask` and `alpha`.  Waits for the patch total, and writes the patch lists
+    again if the first buffer was too small for them."""
     import torch
     lib = load_library()
     sz = _sizes(m, n, n_in, q, n_out)
@@ -331,18 +333,18 @@ def encode(m, n, n_in, q, M_rows, mask, planes, alpha, patch_capacity: Optional[
     cap = int(patch_capacity) if patch_capacity is not None else max(1024, q * n_slots // 8)
     fewest = 1 if _entry == "xorenc_encode_exhaustive" else 0
     total = _patch_total()
-    while True:
-        patch = torch.empty(cap, dtype=torch.int16, device=dev)
-        rc = lib.xorenc_encode_total(fewest, m, n, n_in, q, n_out, M_rows.__array_interface__["data"][0], mask.data_ptr(),
-                                     planes.data_ptr(), enc.data_ptr(), patch_off.data_ptr(), patch.data_ptr(), cap,
-                                     ws.data_ptr(), ws_bytes, total.data_ptr(), _stream_ptr())
-        if rc != 0:
-            _PINNED.total = None  # (a kernel that is still in flight may write it)
-            _check(rc, _entry)
-        found = total.item()
-        if found <= cap:
-            break
-        cap = found
+    patch = torch.empty(cap, dtype=torch.int16, device=dev)
+    rc = lib.xorenc_encode_total(fewest, m, n, n_in, q, n_out, M_rows.__array_interface__["data"][0], mask.data_ptr(),
+                                 planes.data_ptr(), enc.data_ptr(), patch_off.data_ptr(), patch.data_ptr(), cap,
+                                 ws.data_ptr(), ws_bytes, total.data_ptr(), _stream_ptr())
+    found = total.item() if rc == 0 else 0
+    if found > cap:  # the lists once more, into a buffer that holds them
+        patch = torch.empty(found, dtype=torch.int16, device=dev)
+        rc = lib.xorenc_encode_patches(m, n, n_in, q, n_out, patch_off.data_ptr(), patch.data_ptr(), found, ws.data_ptr(),
+                                       ws_bytes, total.data_ptr(), _stream_ptr())
+    if rc != 0:
+        _PINNED.total = None  # (a kernel that is still in flight may write it)
+        _check(rc, _entry)
     return PackedLayer(m, n, n_in, q, M_rows, enc, mask, patch_off, patch[:found], alpha, n_out)
 
 

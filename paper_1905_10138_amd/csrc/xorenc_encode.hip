@@ -932,6 +932,28 @@ void launch_slices_q(int q, const EncParams &P, int64_t first, int64_t n, uint32
 
 namespace {
 
+Counts counts_in(const EncodePlan &plan, const xorenc_sizes &sz, int32_t q, uint64_t *pbits) {
+  unsigned char *const area = reinterpret_cast<unsigned char *>(pbits + (int64_t)q * sz.n_slots);
+  Counts C;
+  C.n_units = (int32_t)sz.n_units;
+  C.n_blocks = plan.n_blocks;
+  C.unit = plan.unit_at >= 0 ? reinterpret_cast<uint16_t *>(area + plan.unit_at) : nullptr;
+  C.block = reinterpret_cast<uint32_t *>(area + plan.block_at);
+  C.scanned = plan.scanned_at >= 0 ? reinterpret_cast<uint32_t *>(area + plan.scanned_at) : nullptr;
+  return C;
+}
+
+void launch_emit(const EncodePlan &plan, const uint64_t *pbits, const Counts &C, int32_t q, const xorenc_sizes &sz,
+                 uint32_t *patch_off_out, uint16_t *patch_out, int64_t patch_capacity, uint32_t *total_out, hipStream_t st) {
+  const dim3 grid(plan.emit_groups), block(ENC_THREADS);
+  if (C.scanned)
+    hipLaunchKernelGGL(emit_patches_kernel<true>, grid, block, 0, st, pbits, C, q, sz.n_slots, plan.units_per_block,
+                       plan.per, patch_off_out, patch_out, patch_capacity, total_out);
+  else
+    hipLaunchKernelGGL(emit_patches_kernel<false>, grid, block, 0, st, pbits, C, q, sz.n_slots, plan.units_per_block,
+                       plan.per, patch_off_out, patch_out, patch_capacity, total_out);
+}
+
 int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,
                       const uint32_t *M_rows, const uint64_t *mask, const uint64_t *planes, uint8_t *enc_out,
                       uint32_t *patch_off_out, uint16_t *patch_out, int64_t patch_capacity, void *workspace,
@@ -958,13 +980,7 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
   const int J = n_out / 64;
   const EncodePlan plan = encode_plan(sz, q, n_out);
   const int n_blocks = q * plan.n_blocks;
-  unsigned char *const area = reinterpret_cast<unsigned char *>(pbits + total);
-  Counts C;
-  C.n_units = (int32_t)sz.n_units;
-  C.n_blocks = plan.n_blocks;
-  C.unit = plan.unit_at >= 0 ? reinterpret_cast<uint16_t *>(area + plan.unit_at) : nullptr;
-  C.block = reinterpret_cast<uint32_t *>(area + plan.block_at);
-  C.scanned = plan.scanned_at >= 0 ? reinterpret_cast<uint32_t *>(area + plan.scanned_at) : nullptr;
+  const Counts C = counts_in(plan, sz, q, pbits);
   EncParams P;
   P.mask = mask;
   P.planes = planes;
@@ -1018,18 +1034,13 @@ int32_t encode_common(bool exhaustive, int32_t m, int32_t n, int32_t n_in, int32
       }
     }
   }
-  const dim3 emit_grid(plan.emit_groups);
   if (C.scanned) {
     const int nscan = (n_blocks + SCAN_BLOCK - 1) / SCAN_BLOCK;
     hipLaunchKernelGGL(scan_local_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, C.block, C.scanned, n_blocks);
     hipLaunchKernelGGL(scan_blocks_kernel, dim3(1), dim3(1024), 0, st, C.scanned, n_blocks, nscan);
     hipLaunchKernelGGL(scan_add_kernel, dim3(nscan), dim3(SCAN_THREADS), 0, st, C.scanned, n_blocks);
-    hipLaunchKernelGGL(emit_patches_kernel<true>, emit_grid, dim3(ENC_THREADS), 0, st, pbits, C, q, sz.n_slots,
-                       plan.units_per_block, plan.per, patch_off_out, patch_out, patch_capacity, total_out);
-  } else {
-    hipLaunchKernelGGL(emit_patches_kernel<false>, emit_grid, dim3(ENC_THREADS), 0, st, pbits, C, q, sz.n_slots,
-                       plan.units_per_block, plan.per, patch_off_out, patch_out, patch_capacity, total_out);
   }
+  launch_emit(plan, pbits, C, q, sz, patch_off_out, patch_out, patch_capacity, total_out, st);
   return xorenc_internal_check_launch();
 }
 
@@ -1079,4 +1090,27 @@ extern "C" int32_t xorenc_encode_total(int32_t fewest_patches, int32_t m, int32_
                                    patch_out, patch_capacity, workspace, workspace_bytes, total_out, hip_stream);
   if (rc != XORENC_OK) return rc;
   return xorenc_internal_hip_status((int32_t)hipStreamSynchronize(static_cast<hipStream_t>(hip_stream)));
+}
+
+extern "C" int32_t xorenc_encode_patches(int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,
+                                         uint32_t *patch_off_out, uint16_t *patch_out, int64_t patch_capacity,
+                                         void *workspace, int64_t workspace_bytes, uint32_t *total_out, void *hip_stream) {
+  xorenc_sizes sz;
+  const int32_t rc = xorenc_get_sizes(m, n, n_in, q, n_out, &sz);
+  if (rc != XORENC_OK) return rc;
+  if (!patch_off_out || !workspace || !total_out || patch_capacity < 0 || (patch_capacity > 0 && !patch_out))
+    return XORENC_EINVAL;
+  const int64_t n_counts = (int64_t)q * sz.n_units;
+  if (workspace_bytes < (int64_t)q * sz.n_slots * 8 + n_counts * 4) return XORENC_EINVAL;
+  if (n_counts > (int64_t)1 << 30) return XORENC_EUNSUPPORTED;
+  if (((uintptr_t)workspace & 7) || ((uintptr_t)patch_off_out & 3) || ((uintptr_t)patch_out & 1) || ((uintptr_t)total_out & 3))
+    return XORENC_EALIGN;
+  xorenc_internal_begin_call();
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  uint64_t *const pbits = static_cast<uint64_t *>(workspace);
+  const EncodePlan plan = encode_plan(sz, q, n_out);
+  launch_emit(plan, pbits, counts_in(plan, sz, q, pbits), q, sz, patch_off_out, patch_out, patch_capacity, total_out, st);
+  const int32_t rl = xorenc_internal_check_launch();
+  if (rl != XORENC_OK) return rl;
+  return xorenc_internal_hip_status((int32_t)hipStreamSynchronize(st));
 }
