@@ -216,7 +216,7 @@ int32_t spmm_common(const xorenc_layer *layer, const void *X, int32_t x_dtype, i
   if (!split_parts && !aligned && (B >= kStageMinB || few_wide) && copy_pays) {
     const int64_t fit = (int64_t)(kStageBytes / ((size_t)layer->n * 16)) * per / 64 * 64;  // columns, in whole 64s
     const bool whole = (int64_t)layer->n * pieces_per_row * 16 <= (int64_t)kStageBytes;
-    xorenc_spmm_detail::F4Plan unused;
+    F4Plan unused;
     if ((whole || fit > 0) && !xorenc_spmm_detail::f4_applies(D, x_dtype, B, 0, &unused))
       copy_parts = whole ? 1 : (int)((B + fit - 1) / fit);
     // (fp32 parts of few tiles of 32 columns: as above, 225 x 6154, three planes, B = 171 46 / 40 us without the copies,

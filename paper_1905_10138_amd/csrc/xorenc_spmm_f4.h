@@ -38,6 +38,7 @@
 #ifndef XORENC_SPMM_F4_H
 #define XORENC_SPMM_F4_H
 
+#include "xorenc_f4_plan.h"
 #include "xorenc_spmm_kernel.h"
 
 namespace xorenc_spmm_detail {
@@ -45,18 +46,6 @@ namespace xorenc_spmm_detail {
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 typedef __attribute__((ext_vector_type(2))) short s16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
-
-constexpr int kF4MaxB = 8;                  // the 16 rows of the X operand: two terms of eight columns
-constexpr int kF4MaxBOneRound = 2;          // beyond that the other kernels are faster on one round (measured) ...
-constexpr int kF4MinRoundsWide = 4;         // ... and pays from this many rounds on (measured, 4096 columns of W)
-constexpr int kF4Waves = 16;
-constexpr int kF4XBytes = 64 * 1024 + 256;  // raw X, then the X operands, then the partial sums
-constexpr int kF4MaxSpr = 256;              // 16 waves x 8 pairs x 2 words
-constexpr int kF4SclBytes = 2304;           // two scale bytes per (half-word, column)
-
-struct F4Plan {
-  int PW, KS, RG, grid, rounds;
-};
 
 // kq_tab / rg_tab: four bits per wave, the wave's K range and its place among the RG granules of a round.
 // MR: a workgroup walks over `rounds` sets of RG granules (layers with more granules than one round of workgroups
@@ -460,9 +449,11 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                   }
                 } else {
-                  for (uint32_t j0 = ends[0]; j0 < ends[2 * G]; j0 += 64u) {  // uniform
+                  // (entries of words behind the range would stay in the area of a pair that nobody reads)
+                  const uint32_t last = min(ends[2 * G], (uint32_t)__builtin_amdgcn_readlane(offv[p], 2 * PW) - base);
+                  for (uint32_t j0 = ends[0]; j0 < last; j0 += 64u) {  // uniform
                     const uint32_t j = j0 + (uint32_t)lane;
-                    if (j < ends[2 * G]) {
+                    if (j < last) {
                       const uint32_t v = (l_patch + base)[j];
                       if ((int)(v >> 10) == h) {
                         uint32_t t = 0;
@@ -593,51 +584,6 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   }
 }
 
-// Picks the decomposition: PW word pairs per wave (at most PMAX), KS K ranges, RG granules per workgroup and
-// round, and the number of rounds (at most one workgroup per CU); false when the kernel does not apply to the call.
-inline bool f4_plan(const DevLayer &D, int B, int PMAX, int PMAX_MR, F4Plan *out) {
-  if (B < 1 || B > kF4MaxB || D.J != 1 || D.spr > kF4MaxSpr) return false;
-  const int spr_pad = 2 * ((D.spr + 1) / 2);  // whole word pairs
-  // raw X (with its column padding) and the operands of the whole K range share one area; scales next to it
-  if ((int64_t)spr_pad * 128 * B + 256 > kF4XBytes || 4 * spr_pad * B + 16 > kF4SclBytes) return false;
-  // one conversion item (half-word, column) per thread
-  const int items = 2 * spr_pad * (B >= 5 ? 8 : (B >= 3 ? 4 : B));
-  if (items > kF4Waves * 64) return false;
-  const int pairs = (D.spr + 1) / 2;
-  const int n_gran = 2 * D.nrb;
-  int best_cost = 1 << 30;
-  F4Plan best{};
-  for (int pw = PMAX; pw >= 1; --pw) {
-    const int ks = (pairs + pw - 1) / pw;
-    if (ks > kF4Waves) break;
-    const int rg = min(kF4Waves / ks, 8);  // at most 8 x 128 outputs per workgroup and round: one per thread
-    const int wgs = (n_gran + rg - 1) / rg;
-    const int grid = min(wgs, kSplitMaxGroups);
-    const int rounds = (wgs + grid - 1) / grid;
-    // the kernel variant that walks over rounds also serves more than two columns; its requests of the next round
-    // need registers too
-    if ((rounds > 1 || B > kF4MaxBOneRound) && pw > PMAX_MR) continue;
-    // time of a wave: a fixed part, then per round its pairs and the exchange of the partial sums; among equals,
-    // more workgroups
-    const int cost = (4 + rounds * (pw + 2)) * 1024 - grid;
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = F4Plan{pw, ks, rg, grid, rounds};
-    }
-  }
-  if (best_cost == (1 << 30)) return false;
-  if (B > kF4MaxBOneRound && best.rounds < kF4MinRoundsWide) return false;
-  *out = best;
-  return true;
-}
-
-// pairs per wave: what fits 128 registers, without and with the words of a round requested ahead (more tables
-// need more temporaries, a field that straddles two dwords a larger set of words per pair)
-constexpr int f4_pmax(int Q) { return Q == 1 ? 8 : (Q == 2 ? 6 : (Q == 3 ? 4 : 2)); }
-constexpr int f4_pmax_mr(int Q, int nibt) {
-  return Q == 1 ? (nibt == 1 ? 6 : 4) : Q == 2 ? (nibt == 3 ? 3 : 4) : Q == 3 ? (nibt == 3 ? 2 : 3) : 2;
-}
-
 template <int Q>
 int32_t launch_f4(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y, int64_t ldy, const F4Plan &P,
                   hipStream_t st) {
@@ -677,7 +623,7 @@ inline bool f4_applies(const DevLayer &D, int32_t x_dtype, int B, int x_fast, F4
   // (widths whose fields straddle dwords outside 17..24 bits stay with the kernels that multiply exact bf16 terms, as
   // they always did: their results are thirty times closer to the 64-bit ones)
   if ((D.n_in & (D.n_in - 1)) != 0 && D.nib != 3) return false;
-  return f4_plan(D, B, f4_pmax(D.q), f4_pmax_mr(D.q, D.nib), plan);
+  return f4_plan(D.spr, D.nrb, D.q, D.nib, B, plan);
 }
 
 // bf16 X with at most two columns (eight on tall layers), slices of one 64-bit word, one dword of encrypted bits

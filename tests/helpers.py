@@ -18,6 +18,14 @@ CUTS_IN_PARTS = [
     (3, 1500, 1800, 8, 1, 8, 2), (3, 3000, 2500, 32, 1, 8, 2), (3, 257, 2100, 32, 1, 8, 3),
 ]
 
+# (planes, m, n, n_in, word pairs per wave, rounds): layers on which waves of the few-column kernel end inside a group of word
+# pairs whose patch flips are scattered together
+FEW_COLUMNS_IN_ROUNDS = [
+    (1, 4352, 8448, 8, 5, 2), (1, 8500, 5300, 32, 3, 3), (1, 9216, 5632, 24, 3, 3), (2, 8448, 4352, 8, 3, 3),
+    (2, 8500, 4300, 16, 3, 3), (2, 9216, 4608, 24, 3, 3), (3, 6000, 3000, 17, 3, 1), (3, 6000, 3000, 24, 3, 1),
+    (3, 9216, 4608, 32, 3, 3), (4, 6000, 3000, 8, 2, 2), (2, 4096, 9216, 16, 5, 1),
+]
+
 
 def paper_format_arrays(enc: "oenc.Encoded"):
     """Oracle `Encoded` -> (w_c uint32[q,l], keep uint64[m*spr] row-major 64-bit words, n_patch uint16[q,l],

@@ -6,7 +6,7 @@ observed error is far below both; the bounds are the contract, not the expectati
 import numpy as np
 import pytest
 
-from helpers import CUTS_IN_PARTS, encoded_workload, pack_encoded, rel_fro
+from helpers import CUTS_IN_PARTS, FEW_COLUMNS_IN_ROUNDS, encoded_workload, pack_encoded, rel_fro
 from oracle import decoder
 from synth_inputs import draw_X
 
@@ -897,3 +897,40 @@ def test_columns_without_gaps_are_the_columns_with_gaps(m, n, q, n_in):
         want = W @ X.double()
         # two FP8 terms per value, see few_column_allowance: 1.5e-6 to 5e-6 of the result's norm observed
         assert float((Y.double() - want).norm() / want.norm()) <= 2e-5
+
+
+@pytest.mark.parametrize("q,m,n,n_in,pairs,rounds", FEW_COLUMNS_IN_ROUNDS)
+def test_long_patch_lists_of_few_columns(q, m, n, n_in, pairs, rounds):
+    """Lists of more than 64 entries in every wave's range, in groups of word pairs that reach beyond the range: nothing of the
+    next range may stay behind in the flip area.  (Entries of the next range used to be scattered too, and the next plane or
+    round took them for its own.)  Against the decoded weights in 64 bits; one wrong weight of all is 1e-4 of the result."""
+    import torch
+    import paper_1905_10138_amd as xe
+    dev = torch.device("cuda:0")
+    sz = xe.get_sizes(m, n, n_in, q)
+    g = torch.Generator(device=dev)
+    g.manual_seed(m + n_in)
+    words = lambda *shape: torch.randint(-2**63, 2**63 - 1, shape, dtype=torch.int64, device=dev, generator=g)
+    kept = words(sz["n_slots"])  # about 16, 32 or 48 care bits in a slice: at least four patches
+    if n_in <= 8:
+        kept &= words(sz["n_slots"])
+    elif n_in > 24:
+        kept |= words(sz["n_slots"])
+    mask = kept.view(-1, sz["spr"], 32)
+    mask = mask * (torch.arange(sz["m_pad"], device=dev).view(-1, 1, 32) < m)
+    if n % 64:
+        mask[:, -1] &= (1 << n % 64) - 1
+    M_rows = np.random.default_rng(n_in).integers(1, 1 << n_in, size=64).astype(np.uint32)
+    alpha = torch.rand((q, m), device=dev, generator=g) + 0.5
+    L = xe.encode(m, n, n_in, q, M_rows, mask.reshape(-1).contiguous(), words(q, sz["n_slots"]), alpha)
+    assert L.patch.numel() > 3 * q * m * sz["spr"]
+    W = xe.decode(L, xe.OUT_F32).double()
+    for B in (1, 2):
+        X = torch.randn((n, B), device=dev, generator=g).to(torch.bfloat16)
+        gaps = torch.zeros((n, B + 1), dtype=torch.bfloat16, device=dev)[:, :B]
+        gaps.copy_(X)
+        want = W @ X.double()
+        for x in (X, gaps):
+            Y = xe.spmm(L, x).double()
+            # two FP8 terms per value, see few_column_allowance: 1.5e-6 to 5e-6 of the result's norm observed
+            assert float((Y - want).norm() / want.norm()) <= 2e-5

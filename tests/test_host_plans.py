@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from helpers import CUTS_IN_PARTS
+from helpers import CUTS_IN_PARTS, FEW_COLUMNS_IN_ROUNDS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1905_10138_amd", "csrc")
@@ -235,6 +235,32 @@ int main() {
 def test_layers_in_two_and_three_parts(tmp_path):
     """The layers of test_gpu_spmm.py's test_two_and_three_workgroups_per_tile have as many parts as it says."""
     run_program(tmp_path, CUT_IN_PARTS.replace("CASES", ", ".join("{%d, %d, %d, %d, %d, %d, %d}" % c for c in CUTS_IN_PARTS)))
+
+
+FEW_COLUMNS = r"""
+#include <cstdio>
+#include "xorenc_f4_plan.h"
+
+int main() {
+  struct { int q, m, n, n_in, pw, rounds; } const cases[] = {CASES};
+  for (const auto &c : cases)
+    for (int B = 1; B <= 2; ++B) {
+      F4Plan P{};
+      const bool taken = f4_plan((c.n + 63) / 64, (c.m + 31) / 32, c.q, (c.n_in + 7) / 8, B, &P);
+      if (!taken || P.PW != c.pw || P.rounds != c.rounds) {
+        std::printf("q=%d %d x %d n_in=%d B=%d: taken %d, %d pairs, %d rounds\n", c.q, c.m, c.n, c.n_in, B, taken, P.PW, P.rounds);
+        return 1;
+      }
+    }
+  return 0;
+}
+"""
+
+
+def test_layers_whose_waves_end_inside_a_group(tmp_path):
+    """The layers of test_gpu_spmm.py's test_long_patch_lists_of_few_columns have the word pairs per wave and the rounds
+    that it says."""
+    run_program(tmp_path, FEW_COLUMNS.replace("CASES", ", ".join("{%d, %d, %d, %d, %d, %d}" % c for c in FEW_COLUMNS_IN_ROUNDS)))
 
 
 SCRATCH_OWNERS = r"""
