@@ -200,3 +200,21 @@ def test_random_geometries_pack_unpack_export_import(name, m, n, n_out, n_in, S)
     assert stream.size == (want.total_bits + 7) // 8
     w3, np3, dp3 = xe.paper_import(enc.m, enc.n, enc.n_in, enc.q, stream, blk, enc.n_out)
     assert np.array_equal(w3, w_c) and np.array_equal(np3, n_patch) and np.array_equal(dp3, d_patch)
+
+
+def test_calls_refuse_what_is_not_a_layer():
+    """A layer goes to the library as its structure or as the structure's bytes; a number, a shorter buffer or another
+    structure is refused before the call."""
+    lib = binding.load_library()
+    layer = xe.PackedLayer(70, 200, 16, 1, np.zeros(64, np.uint32), *[np.zeros(1, np.uint8)] * 5)
+    structure = layer.c_struct()
+    as_bytes = bytes(structure)
+    assert len(as_bytes) == ctypes.sizeof(binding._Layer) == 72
+    for fn, rest in ((lib.xorenc_decode, (0, None, 0, None)), (lib.xorenc_spmm, (None, 0, 1, 1, None, 1, None)),
+                     (lib.xorenc_spmm_ws, (None, 0, 1, 1, None, 1, None, 0, None))):
+        for wrong in (ctypes.addressof(structure), as_bytes[:-1], as_bytes + b"0", ctypes.byref(binding._Sizes()),
+                      ctypes.c_void_p(ctypes.addressof(structure)), "layer", layer):
+            with pytest.raises(ctypes.ArgumentError):
+                fn(wrong, *rest)
+        for right in (as_bytes, structure, ctypes.byref(structure), ctypes.pointer(structure), None):
+            assert fn(right, *rest) == -1  # (no output)
