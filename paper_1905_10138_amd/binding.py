@@ -16,6 +16,8 @@ import numpy as np
 OUT_PLANES, OUT_F32, OUT_BF16 = 0, 1, 2
 X_F32, X_BF16 = 0, 1
 
+_EHIP = -4
+
 _LIB = None
 
 
@@ -24,7 +26,7 @@ class XorencError(RuntimeError):
         self.code = code
         msg = strerror(code) if _LIB is not None else str(code)
         extra = ""
-        if code == -4 and _LIB is not None:
+        if code == _EHIP and _LIB is not None:
             extra = f" (hipError_t {_LIB.xorenc_last_hip_error()})"
         super().__init__(f"{where}: xorenc status {code}: {msg}{extra}")
 
@@ -310,6 +312,7 @@ def pack_bits(a: np.ndarray, n_out: int = 64) -> np.ndarray:
 
 
 _PINNED = threading.local()
+_WRITTEN_LATE = []  # words of calls that failed on the GPU: a kernel may still write them, so they are never given back
 
 
 def _patch_total():
@@ -351,8 +354,10 @@ def encode(m, n, n_in, q, M_rows, mask, planes, alpha, patch_capacity: Optional[
         patch = torch.empty(found, dtype=torch.int16, device=dev)
         rc = lib.xorenc_encode_patches(m, n, n_in, q, n_out, patch_off.data_ptr(), patch.data_ptr(), found, ws.data_ptr(),
                                        ws_bytes, total.data_ptr(), _stream_ptr())
+    if rc == _EHIP:  # (other refusals come before the first kernel)
+        _WRITTEN_LATE.append(total)
+        _PINNED.total = None
     if rc != 0:
-        _PINNED.total = None  # (a kernel that is still in flight may write it)
         _check(rc, _entry)
     return PackedLayer(m, n, n_in, q, M_rows, enc, mask, patch_off, patch[:found], alpha, n_out)
 

@@ -218,3 +218,35 @@ def test_calls_refuse_what_is_not_a_layer():
                 fn(wrong, *rest)
         for right in (as_bytes, structure, ctypes.byref(structure), ctypes.pointer(structure), None):
             assert fn(right, *rest) == -1  # (no output)
+
+
+def test_the_word_of_a_failed_call_is_kept(monkeypatch):
+    """After an error of the GPU a kernel may still write the word in host memory that takes the patch total: the word is
+    neither used again nor given back to the allocator.  A call that was refused before its first kernel leaves it in use."""
+    import torch
+    real = binding.load_library()
+
+    class Failing:
+        xorenc_get_sizes, xorenc_strerror = real.xorenc_get_sizes, real.xorenc_strerror
+        code = 0
+
+        def xorenc_encode_total(self, *args):
+            return self.code
+
+    lib = Failing()
+    word = torch.zeros(1, dtype=torch.int32)
+    monkeypatch.setattr(binding, "load_library", lambda: lib)
+    monkeypatch.setattr(binding, "_stream_ptr", lambda: 0)
+    monkeypatch.setattr(binding._PINNED, "total", word, raising=False)
+    monkeypatch.setattr(binding, "_WRITTEN_LATE", [])
+    mask, planes = torch.zeros(32, dtype=torch.int64), torch.zeros((1, 32), dtype=torch.int64)
+    call = lambda: xe.encode(32, 64, 8, 1, np.zeros(64, np.uint32), mask, planes, torch.ones((1, 32)))
+    assert call().patch.numel() == 0
+    for lib.code in (-1, -2, -3):
+        with pytest.raises(xe.XorencError):
+            call()
+        assert binding._PINNED.total is word and not binding._WRITTEN_LATE
+    lib.code = -4
+    with pytest.raises(xe.XorencError):
+        call()
+    assert binding._PINNED.total is None and len(binding._WRITTEN_LATE) == 1 and binding._WRITTEN_LATE[0] is word
