@@ -969,10 +969,14 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   // without a barrier of its own) is complete
   __syncthreads();
   // One plane: its scales wait until the waves' sums have been added, 4 multiplications a thread there instead of 16 per 32 x 32
-  // block in every wave here, where all of them issue at once (16384 x 4096, B = 8 8.6 -> 8.4 us, B = 256 36.3 -> 35.7; 2048 x
-  // 2048, B = 64 5.9 -> 5.9 (47.6 -> 46.9 for eight); and one rounding a sum less: 5.4e-8 -> 2.6e-8 from the exact result).
+  // block in every wave here, where all of them issue at once, and one rounding a sum less: 2.6e-8 instead of 5.4e-8 from the
+  // exact result.  (Time: 0 to 1 %, no more than two placements of the same buffers differ.)
+  // A sum that leaves the range of fp32 (or is not a number) is taken again from scaled parts, which may stay inside it: by its
+  // thread where every wave has a tile of its own, by the workgroup where two waves share one, behind a barrier that costs
+  // what the multiplications did (16384 x 4096, B = 128 22.0 -> 22.4 us, B = 256 35.0 -> 35.7).
   constexpr bool SCALE_LAST = Q == 1 && !XF32 && TERMS == 1;
-  if constexpr (!SCALE_LAST) {
+  constexpr bool REDO = SCALE_LAST && NREG < NW;
+  auto scale_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -995,44 +999,62 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
             acc[0][rb][cb][4 * j4 + k] = v;  // plane 0's accumulator now holds the scaled sum
           }
       }
-  }
+  };
+  if constexpr (!SCALE_LAST) scale_sums();
   float *red = reinterpret_cast<float *>(xbuf_all);
-  for (int round = 0; round < NW / NREG; ++round) {
-    if (wave / NREG == round) {
-      float *tile = red + (wave % NREG) * TILE;
+  auto add_up_waves = [&]() __attribute__((always_inline)) {
+    for (int round = 0; round < NW / NREG; ++round) {
+      if (wave / NREG == round) {
+        float *tile = red + (wave % NREG) * TILE;
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
+          for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-          for (int j4 = 0; j4 < 4; ++j4) {
-            // four consecutive rows of one column: one 16-byte LDS access; columns beyond B are never
-            // stored, so their lanes stay out (with few columns most of the tile is such padding)
-            if (XF32 || col0 + cb * 32 + rl < B) {
-              f32x4 *dst = reinterpret_cast<f32x4 *>(tile + (cb * 32 + rl) * TS + rb * 32 + 8 * j4 + 4 * g);
-              f32x4 v = {acc[0][rb][cb][4 * j4], acc[0][rb][cb][4 * j4 + 1], acc[0][rb][cb][4 * j4 + 2],
-                         acc[0][rb][cb][4 * j4 + 3]};
-              if (round != 0) v += *dst;
-              *dst = v;
+            for (int j4 = 0; j4 < 4; ++j4) {
+              // four consecutive rows of one column: one 16-byte LDS access; columns beyond B are never
+              // stored, so their lanes stay out (with few columns most of the tile is such padding)
+              if (XF32 || col0 + cb * 32 + rl < B) {
+                f32x4 *dst = reinterpret_cast<f32x4 *>(tile + (cb * 32 + rl) * TS + rb * 32 + 8 * j4 + 4 * g);
+                f32x4 v = {acc[0][rb][cb][4 * j4], acc[0][rb][cb][4 * j4 + 1], acc[0][rb][cb][4 * j4 + 2],
+                           acc[0][rb][cb][4 * j4 + 3]};
+                if (round != 0) v += *dst;
+                *dst = v;
+              }
             }
-          }
+      }
+      __syncthreads();
     }
-    __syncthreads();
-  }
+  };
+  add_up_waves();
   // final pass: a thread owns four consecutive rows of one column; lanes run over columns, so each
   // of its four stores is contiguous across the wave
-  auto reduced4 = [&](int col, int rq) {
+  bool out_of_range = false;
+  auto reduced4 = [&](int col, int rq, auto scaled) __attribute__((always_inline)) {
     // (added in pairs, pairs of pairs, ...: fewer roundings on the way of each part than one after the other)
     const float *src = red + col * TS + 4 * rq;
-    f32x4 v[NREG];
+    auto sum = [&](auto &&read) __attribute__((always_inline)) {
+      f32x4 v[NREG];
 #pragma unroll
-    for (int r = 0; r < NREG; ++r) v[r] = *reinterpret_cast<const f32x4 *>(src + r * TILE);
+      for (int r = 0; r < NREG; ++r) v[r] = read(r);
 #pragma unroll
-    for (int s = 1; s < NREG; s *= 2)
+      for (int s = 1; s < NREG; s *= 2)
 #pragma unroll
-      for (int r = 0; r + s < NREG; r += 2 * s) v[r] += v[r + s];
-    if constexpr (SCALE_LAST) v[0] *= *reinterpret_cast<const f32x4 *>(alpha_s + 4 * rq);
-    return v[0];
+        for (int r = 0; r + s < NREG; r += 2 * s) v[r] += v[r + s];
+      return v[0];
+    };
+    auto part = [&](int r) { return *reinterpret_cast<const f32x4 *>(src + r * TILE); };
+    f32x4 v = sum(part);
+    if constexpr (!decltype(scaled)::value) {
+      const f32x4 a = *reinterpret_cast<const f32x4 *>(alpha_s + 4 * rq);
+      const bool in_range = fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]) < __builtin_huge_valf();
+      if constexpr (!REDO) {
+        if (!in_range) return sum([&](int r) { return part(r) * a; });
+      }
+      out_of_range = out_of_range || !in_range;
+      v *= a;
+    }
+    return v;
   };
   // n_splits > 1: this workgroup holds one of n_splits partial sums of its tile.  It parks the tile in the
   // scratch area and takes a ticket; the workgroup that arrives last adds the parts in the order
@@ -1041,26 +1063,36 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   float *const my_part =
       n_splits > 1 ? L.split_part + ((int64_t)(blockIdx.y * gridDim.x + blockIdx.x) * n_splits + blockIdx.z) * kSplitTileFloats
                    : nullptr;
-  for (int idx = tid; idx < (ROWS / 4) * NR; idx += NW * 64) {
-    const int rq = idx / NR, nn = idx % NR;
-    const int gc = col0 + nn;
-    if (gc < B) {
-      f32x4 v;
-      if (XF32) {
-        const int c = 96 * (nn >> 5) + (nn & 31);
-        v = (reduced4(c, rq) + reduced4(c + 32, rq)) + reduced4(c + 64, rq);
-      } else {
-        v = reduced4(nn, rq);
-      }
-      if (n_splits > 1) {
-        split_store4(split_rsrc(my_part), 16u * idx, __builtin_bit_cast(u32x4, v));
-      } else {
+  auto store_sums = [&](auto scaled) __attribute__((always_inline)) {
+    for (int idx = tid; idx < (ROWS / 4) * NR; idx += NW * 64) {
+      const int rq = idx / NR, nn = idx % NR;
+      const int gc = col0 + nn;
+      if (gc < B) {
+        f32x4 v;
+        if (XF32) {
+          const int c = 96 * (nn >> 5) + (nn & 31);
+          v = (reduced4(c, rq, scaled) + reduced4(c + 32, rq, scaled)) + reduced4(c + 64, rq, scaled);
+        } else {
+          v = reduced4(nn, rq, scaled);
+        }
+        if (n_splits > 1) {
+          split_store4(split_rsrc(my_part), 16u * idx, __builtin_bit_cast(u32x4, v));
+        } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int gr = row0 + 4 * rq + k;
-          if (gr < l_m) Y[(int64_t)gr * ldy + gc] = v[k];
+          for (int k = 0; k < 4; ++k) {
+            const int gr = row0 + 4 * rq + k;
+            if (gr < l_m) Y[(int64_t)gr * ldy + gc] = v[k];
+          }
         }
       }
+    }
+  };
+  store_sums(BoolC<!SCALE_LAST>{});
+  if constexpr (REDO) {
+    if (__syncthreads_or(out_of_range)) {  // uniform
+      scale_sums();
+      add_up_waves();
+      store_sums(BoolC<true>{});
     }
   }
   if (n_splits > 1) {

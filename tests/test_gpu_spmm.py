@@ -3,6 +3,8 @@
 Tolerances (relative Frobenius error against fp64): 2e-3 for bf16 X, 1e-5 for fp32 X.  The
 kernel multiplies exact +-2/0 operands with exact bf16 terms and accumulates in fp32, so the
 observed error is far below both; the bounds are the contract, not the expectation."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -934,3 +936,29 @@ def test_long_patch_lists_of_few_columns(q, m, n, n_in, pairs, rounds):
             Y = xe.spmm(L, x).double()
             # two FP8 terms per value, see few_column_allowance: 1.5e-6 to 5e-6 of the result's norm observed
             assert float((Y - want).norm() / want.norm()) <= 2e-5
+
+
+@pytest.mark.parametrize("m,n,n_out,n_in,B,pad", [
+    (256, 1024, 64, 8, 8, 0), (2048, 3072, 64, 16, 8, 0), (40000, 512, 64, 8, 8, 0), (2048, 2048, 64, 16, 64, 0),
+    (256, 1500, 64, 24, 32, 0), (4096, 1024, 64, 8, 32, 0), (40000, 512, 64, 8, 32, 0), (16384, 1024, 64, 8, 128, 0),
+    (33000, 1024, 64, 8, 128, 0), (4096, 1024, 64, 27, 96, 0), (1000, 1200, 64, 16, 40, 3), (1000, 1200, 64, 13, 20, 3),
+    (2048, 2304, 192, 20, 24, 0), (9000, 1536, 192, 20, 64, 0), (9000, 2048, 256, 28, 64, 0), (600, 1536, 192, 13, 9, 1),
+    (600, 1600, 128, 29, 20, 1)])
+def test_sums_beyond_the_range_of_fp32_before_they_are_scaled(m, n, n_out, n_in, B, pad):
+    """One plane with small scales: the sum over a row is beyond 3.4e38, the scaled sums of the waves and their sum are not.
+    Column b of X has the signs of row b."""
+    import torch
+    import paper_1905_10138_amd as xe
+    wl, enc = encoded_workload("large_q1", m, n, 0.9, n_out, n_in)
+    enc = dataclasses.replace(enc, alpha=(enc.alpha * np.float32(1e-6)).astype(np.float32))
+    W = decoder.dequantize_f64(enc)
+    sign = np.sign(W[:B].T)
+    stored = (sign * (2.0e38 / np.maximum(1, (sign != 0).sum(axis=0)))[None, :]).astype(np.float32)
+    buf = torch.zeros((n, B + pad), dtype=torch.bfloat16)
+    buf[:, :B] = torch.from_numpy(stored).to(torch.bfloat16)
+    exact = buf[:, :B].to(torch.float64).numpy()
+    L = pack_encoded(enc).to(torch.device("cuda:0"))
+    Y = xe.spmm(L, buf.to("cuda:0")[:, :B]).cpu().numpy()
+    want = W @ exact
+    assert np.abs(want / enc.alpha.astype(np.float64)[0][:, None]).max() > 1.9e38  # (the kernels multiply by twice the signs)
+    assert_every_output_close(Y, want, enc, exact)
