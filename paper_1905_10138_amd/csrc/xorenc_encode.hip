@@ -356,16 +356,31 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P,
       }
     }
   } else {
+    // These waves take the longest and mostly wait: beside waves that solve in registers they issue first (us for the kernels
+    // of a call, without / with the registers, the last with the words read twice and no priority: 16384 x 4096, n_out = 192,
+    // S = 0.91, n_in = 20 47.6 / 40.8 / 56.3; 4096 x 4096, S = 0.7, n_in = 24 36.8 / 34.0 / 45.1; 8192 x 4096, two planes,
+    // n_out = 128, S = 0.85, n_in = 24 48.3 / 44.8 / 54.2; where no wave is such, S = 0.9 and n_in = 16, nothing changes).
+    if constexpr (JT != 0) __builtin_amdgcn_s_setprio(3);
     uint32_t have = 0;         // bit j: a basis row with pivot j exists
     uint32_t rhsbits[Q] = {};  // !PACKED: bit j = right-hand side of that row
     for (int w = 0; w < l_J; ++w) {  // uniform; care bits in ascending position over the whole slice
       const int64_t slot = slot0 + 32 * w;
-      uint64_t kept = valid ? P.mask[slot] : 0ull;  // care bits
-      uint64_t bits[Q], patches[Q];
+      uint64_t kept, bits[Q], patches[Q] = {};  // kept: care bits
+      if constexpr (JT == 0) {
+        kept = valid ? P.mask[slot] : 0ull;
 #pragma unroll
-      for (int p = 0; p < Q; ++p) {
-        bits[p] = valid ? P.planes[p * P.n_slots + slot] : 0ull;
-        patches[p] = 0;
+        for (int p = 0; p < Q; ++p) bits[p] = valid ? P.planes[p * P.n_slots + slot] : 0ull;
+      } else {
+        kept = kept_all[0];
+#pragma unroll
+        for (int p = 0; p < Q; ++p) bits[p] = bits_all[0][p];
+#pragma unroll
+        for (int k = 1; k < JT; ++k)
+          if (w == k) {  // uniform
+            kept = kept_all[k];
+#pragma unroll
+            for (int p = 0; p < Q; ++p) bits[p] = bits_all[k][p];
+          }
       }
       while (kept) {
         const int i = __builtin_ctzll(kept);
@@ -419,6 +434,7 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P,
         x[p] |= ((rhs ^ (uint32_t)__builtin_popcount(others)) & 1u) << j;
       }
     }
+    if constexpr (JT != 0) __builtin_amdgcn_s_setprio(0);
   }
 #pragma unroll
   for (int p = 0; p < Q; ++p) store_enc_unit(P.enc, p * P.n_eslots + eslot, n_in, x[p], valid);

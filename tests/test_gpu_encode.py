@@ -106,6 +106,16 @@ def test_gpu_exhaustive_encoder_random_geometries(name, m, n, n_out, n_in, S):
     _check_against_oracle(wl, enc, exhaustive=True)
 
 
+# The search's first pass: waves whose slices are all solved in registers, none, and both, one to four words, one to four planes
+@pytest.mark.parametrize("name,m,n,n_out,n_in,S", [("fc6", 70, 600, 128, 12, 0.78), ("fc6", 70, 600, 128, 12, 0.92),
+                                                   ("fig1", 100, 700, 192, 12, 0.85), ("fig1", 100, 700, 128, 11, 0.8),
+                                                   ("lstm", 70, 300, 64, 12, 0.6), ("lstm", 64, 400, 128, 12, 0.9),
+                                                   ("large_q2", 40, 700, 192, 12, 0.92), ("fig1", 40, 500, 256, 12, 0.9)])
+def test_gpu_exhaustive_encoder_edges_of_the_elimination_in_registers(name, m, n, n_out, n_in, S):
+    wl, enc = encoded_workload(name, m, n, S=S, n_out=n_out, n_in=n_in, exhaustive=True)
+    _check_against_oracle(wl, enc, exhaustive=True)
+
+
 def test_exhaustive_encoder_rejects_large_n_in():
     import torch
     import paper_1905_10138_amd as xe
