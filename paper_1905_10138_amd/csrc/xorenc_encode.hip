@@ -328,8 +328,6 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P,
   uint32_t x[Q] = {};
 #pragma unroll
   for (int w = 0; w < JT; ++w) n_care += __builtin_popcountll(kept_all[w]);
-  if (SEARCH && JT == 0)
-    for (int w = 0; w < l_J; ++w) n_care += valid ? __builtin_popcountll(P.mask[slot0 + 32 * w]) : 0;
   asm volatile("" : "+v"(n_care));  // (compared as 32 bits)
   if (JT && !__ballot(n_care > kFewCare)) {  // uniform
     if constexpr (JT != 0) {
@@ -368,6 +366,7 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P,
       uint64_t kept, bits[Q], patches[Q] = {};  // kept: care bits
       if constexpr (JT == 0) {
         kept = valid ? P.mask[slot] : 0ull;
+        if constexpr (SEARCH) n_care += __builtin_popcountll(kept);
 #pragma unroll
         for (int p = 0; p < Q; ++p) bits[p] = valid ? P.planes[p * P.n_slots + slot] : 0ull;
       } else {
