@@ -190,11 +190,12 @@ constexpr int kFewCare = 32;
 constexpr int kPivotBits = 5;
 constexpr bool has_few_care(int Q, int J) { return J * (1 + 2 * Q) <= 10; }  // (the words of wider ones fill the registers)
 
-template <int Q, int J>
+template <int Q, int J, bool LISTS>
 struct FewCare {
-  uint64_t kept[J], bits[J][Q];     // in: care bits, wanted bits
-  uint64_t patches[J][Q];           // out
-  uint32_t x[Q];                    // out: the solution with free variables 0
+  uint64_t kept[J], bits[J][Q];         // in: care bits, wanted bits
+  uint64_t patches[LISTS ? J : 1][Q];   // out, LISTS: the dropped equations
+  uint32_t dropped;                     // out, else: bit p: plane p has any
+  uint32_t x[Q];                        // out: the solution with free variables 0
 
   // rows: the network's, in LDS; n_care: of the lane's slice; steps: most care bits of a slice of the wave (uniform)
   __device__ inline void solve(const uint32_t *rows, int n_in, uint32_t coefs, int n_care, int steps) {
@@ -205,8 +206,9 @@ struct FewCare {
     uint64_t left = kept[0], now[Q];
 #pragma unroll
     for (int p = 0; p < Q; ++p) now[p] = bits[0][p];
+    dropped = 0;
 #pragma unroll
-    for (int w = 0; w < J; ++w)
+    for (int w = 0; w < (LISTS ? J : 0); ++w)
 #pragma unroll
       for (int p = 0; p < Q; ++p) patches[w][p] = 0;
     auto next_word = [&] {
@@ -254,11 +256,15 @@ struct FewCare {
         const bool gone = (r & coefs) == 0;
         if (__ballot(gone && r >> kPivotBits)) {  // uniform: the equation is dropped where its right-hand side is 1
           const uint32_t rhs = gone ? r >> n_in : 0u;
+          if constexpr (LISTS) {
 #pragma unroll
-          for (int w = 0; w < J; ++w)
+            for (int w = 0; w < J; ++w)
 #pragma unroll
-            for (int p = 0; p < Q; ++p)
-              if (J == 1 || w == w_i) patches[w][p] |= (uint64_t)((rhs >> p) & 1u) << i;
+              for (int p = 0; p < Q; ++p)
+                if (J == 1 || w == w_i) patches[w][p] |= (uint64_t)((rhs >> p) & 1u) << i;
+          } else {
+            dropped |= rhs;
+          }
         }
         const uint32_t pivots = 0xffffffffu >> (32 - kPivotBits);
         slot[t] = gone ? 0u : (r & ~pivots) | (uint32_t)__builtin_ctz((r & ~pivots) | 1u << 31);
@@ -296,9 +302,16 @@ struct FewCare {
 // the mismatch count set when syndromes gave the fewest patches, otherwise all ones, and the slice joins the list, whose
 // entry i is the high half of the first patch word of slice i of the pass's numbering; *list_len counts them.  The
 // workgroup's waves take turns at the slices that are tried by syndrome (syndrome_care says which).
+// The first pass for one and two words is kept to eight waves a SIMD: beyond 100 scalar or 64 vector registers a SIMD has room for
+// seven, and a launch of eight workgroups per CU ran in two rounds (us for the kernels of a search, as many registers as it
+// takes / eight waves: 16384 x 4096, two planes, n_out = 128, n_in = 16, S = 0.91 228 / 213, S = 0.85 1803 / 1703).  With three
+// words it takes 86 million weights to have so many workgroups, and fewer registers cost 0.6 us (one
+// plane, n_out = 192, n_in = 20 41.5 / 42.2).
+constexpr bool at_eight_waves(bool search, int JT) { return search && (JT == 1 || JT == 2); }
+
 template <int Q, bool PACKED, bool SEARCH, int JT>
-__global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P, int64_t first, int64_t n,
-                                                                   uint32_t *list_len, SyndromeCare care) {
+__global__ __launch_bounds__(ENC_THREADS, at_eight_waves(SEARCH, JT) ? 8 : 1) void encode_slices_kernel(
+    EncParams P, int64_t first, int64_t n, uint32_t *list_len, SyndromeCare care) {
   extern __shared__ uint32_t enc_lds[];  // [n_in][ENC_THREADS] basis, then the 64 J rows of the network
   __shared__ uint32_t block_total[Q];
   uint32_t *const rows = enc_lds + P.n_in * ENC_THREADS;
@@ -331,7 +344,8 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P,
   asm volatile("" : "+v"(n_care));  // (compared as 32 bits)
   if (JT && !__ballot(n_care > kFewCare)) {  // uniform
     if constexpr (JT != 0) {
-      FewCare<Q, JT> few;
+      constexpr bool LISTS = !at_eight_waves(SEARCH, JT);
+      FewCare<Q, JT, LISTS> few;
 #pragma unroll
       for (int w = 0; w < JT; ++w) {
         few.kept[w] = kept_all[w];
@@ -342,14 +356,19 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_slices_kernel(EncParams P,
       for (int s = 32; s > 0; s >>= 1) steps += __ballot(n_care >= steps + s) ? s : 0;
       few.solve(rows, n_in, coefs, n_care, steps);
 #pragma unroll
-      for (int p = 0; p < Q; ++p) x[p] = few.x[p];
+      for (int p = 0; p < Q; ++p) {
+        x[p] = few.x[p];
+        if constexpr (!LISTS) dropped[p] = (few.dropped >> p) & 1u;
+      }
+      if constexpr (LISTS) {
 #pragma unroll
-      for (int w = 0; w < JT; ++w) {
+        for (int w = 0; w < JT; ++w) {
 #pragma unroll
-        for (int p = 0; p < Q; ++p) {
-          dropped[p] = dropped[p] || few.patches[w][p] != 0;
-          if constexpr (!SEARCH)
-            put_patches(P.pbits, P.counts, p, p * P.n_slots + slot0 + 32 * w, few.patches[w][p], valid, block_total + p);
+          for (int p = 0; p < Q; ++p) {
+            dropped[p] = dropped[p] || few.patches[w][p] != 0;
+            if constexpr (!SEARCH)
+              put_patches(P.pbits, P.counts, p, p * P.n_slots + slot0 + 32 * w, few.patches[w][p], valid, block_total + p);
+          }
         }
       }
     }
