@@ -976,33 +976,33 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
   // what the multiplications did (16384 x 4096, B = 128 22.0 -> 22.4 us, B = 256 35.0 -> 35.7).
   constexpr bool SCALE_LAST = Q == 1 && !XF32 && TERMS == 1;
   constexpr bool REDO = SCALE_LAST && NREG < NW;
-  auto scale_sums = [&]() __attribute__((always_inline)) {
+  bool out_of_range = false;
+  for (bool scaled = !SCALE_LAST;; scaled = true) {
+    if (scaled) {
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
+      for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-      for (int j4 = 0; j4 < 4; ++j4) {
-        f32x4 a4[Q];
+        for (int j4 = 0; j4 < 4; ++j4) {
+          f32x4 a4[Q];
 #pragma unroll
-        for (int p = 0; p < Q; ++p)
-          a4[p] = *reinterpret_cast<const f32x4 *>(alpha_s + p * ROWS + rb * 32 + 8 * j4 + 4 * g);
+          for (int p = 0; p < Q; ++p)
+            a4[p] = *reinterpret_cast<const f32x4 *>(alpha_s + p * ROWS + rb * 32 + 8 * j4 + 4 * g);
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
+          for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            if constexpr (TERMS > 1) {
+            for (int k = 0; k < 4; ++k) {
+              if constexpr (TERMS > 1) {
 #pragma unroll
-              for (int p = 0; p < Q; ++p) acc[p][rb][cb][4 * j4 + k] += acc_low[p][rb][cb][4 * j4 + k];
+                for (int p = 0; p < Q; ++p) acc[p][rb][cb][4 * j4 + k] += acc_low[p][rb][cb][4 * j4 + k];
+              }
+              float v = a4[0][k] * acc[0][rb][cb][4 * j4 + k];
+#pragma unroll
+              for (int p = 1; p < Q; ++p) v += a4[p][k] * acc[p][rb][cb][4 * j4 + k];
+              acc[0][rb][cb][4 * j4 + k] = v;  // plane 0's accumulator now holds the scaled sum
             }
-            float v = a4[0][k] * acc[0][rb][cb][4 * j4 + k];
-#pragma unroll
-            for (int p = 1; p < Q; ++p) v += a4[p][k] * acc[p][rb][cb][4 * j4 + k];
-            acc[0][rb][cb][4 * j4 + k] = v;  // plane 0's accumulator now holds the scaled sum
-          }
-      }
-  };
-  if constexpr (!SCALE_LAST) scale_sums();
-  float *red = reinterpret_cast<float *>(xbuf_all);
-  auto add_up_waves = [&]() __attribute__((always_inline)) {
+        }
+    }
+    float *red = reinterpret_cast<float *>(xbuf_all);
     for (int round = 0; round < NW / NREG; ++round) {
       if (wave / NREG == round) {
         float *tile = red + (wave % NREG) * TILE;
@@ -1025,45 +1025,44 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
       }
       __syncthreads();
     }
-  };
-  add_up_waves();
-  // final pass: a thread owns four consecutive rows of one column; lanes run over columns, so each
-  // of its four stores is contiguous across the wave
-  bool out_of_range = false;
-  auto reduced4 = [&](int col, int rq, auto scaled) __attribute__((always_inline)) {
-    // (added in pairs, pairs of pairs, ...: fewer roundings on the way of each part than one after the other)
-    const float *src = red + col * TS + 4 * rq;
-    auto sum = [&](auto &&read) __attribute__((always_inline)) {
+    // final pass: a thread owns four consecutive rows of one column; lanes run over columns, so each
+    // of its four stores is contiguous across the wave
+    auto reduced4 = [&](int col, int rq) {
+      // (added in pairs, pairs of pairs, ...: fewer roundings on the way of each part than one after the other)
+      const float *src = red + col * TS + 4 * rq;
       f32x4 v[NREG];
 #pragma unroll
-      for (int r = 0; r < NREG; ++r) v[r] = read(r);
+      for (int r = 0; r < NREG; ++r) v[r] = *reinterpret_cast<const f32x4 *>(src + r * TILE);
 #pragma unroll
       for (int s = 1; s < NREG; s *= 2)
 #pragma unroll
         for (int r = 0; r + s < NREG; r += 2 * s) v[r] += v[r + s];
+      if constexpr (SCALE_LAST) {
+        if (scaled) return v[0];
+        const f32x4 a = *reinterpret_cast<const f32x4 *>(alpha_s + 4 * rq);
+        const bool in_range = fabsf(v[0][0]) + fabsf(v[0][1]) + fabsf(v[0][2]) + fabsf(v[0][3]) < __builtin_huge_valf();
+        v[0] *= a;
+        if (!in_range) {
+          out_of_range = true;
+          if constexpr (!REDO) {
+#pragma unroll
+            for (int r = 0; r < NREG; ++r) v[r] = *reinterpret_cast<const f32x4 *>(src + r * TILE) * a;
+#pragma unroll
+            for (int s = 1; s < NREG; s *= 2)
+#pragma unroll
+              for (int r = 0; r + s < NREG; r += 2 * s) v[r] += v[r + s];
+          }
+        }
+      }
       return v[0];
     };
-    auto part = [&](int r) { return *reinterpret_cast<const f32x4 *>(src + r * TILE); };
-    f32x4 v = sum(part);
-    if constexpr (!decltype(scaled)::value) {
-      const f32x4 a = *reinterpret_cast<const f32x4 *>(alpha_s + 4 * rq);
-      const bool in_range = fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]) < __builtin_huge_valf();
-      if constexpr (!REDO) {
-        if (!in_range) return sum([&](int r) { return part(r) * a; });
-      }
-      out_of_range = out_of_range || !in_range;
-      v *= a;
-    }
-    return v;
-  };
-  // n_splits > 1: this workgroup holds one of n_splits partial sums of its tile.  It parks the tile in the
-  // scratch area and takes a ticket; the workgroup that arrives last adds the parts in the order
-  // of their slice ranges (so the result does not depend on who was last) and writes Y.  No zero-fill, no
-  // atomics on Y, nobody waits for anybody.
-  float *const my_part =
-      n_splits > 1 ? L.split_part + ((int64_t)(blockIdx.y * gridDim.x + blockIdx.x) * n_splits + blockIdx.z) * kSplitTileFloats
-                   : nullptr;
-  auto store_sums = [&](auto scaled) __attribute__((always_inline)) {
+    // n_splits > 1: this workgroup holds one of n_splits partial sums of its tile.  It parks the tile in the
+    // scratch area and takes a ticket; the workgroup that arrives last adds the parts in the order
+    // of their slice ranges (so the result does not depend on who was last) and writes Y.  No zero-fill, no
+    // atomics on Y, nobody waits for anybody.
+    float *const my_part =
+        n_splits > 1 ? L.split_part + ((int64_t)(blockIdx.y * gridDim.x + blockIdx.x) * n_splits + blockIdx.z) * kSplitTileFloats
+                     : nullptr;
     for (int idx = tid; idx < (ROWS / 4) * NR; idx += NW * 64) {
       const int rq = idx / NR, nn = idx % NR;
       const int gc = col0 + nn;
@@ -1071,9 +1070,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
         f32x4 v;
         if (XF32) {
           const int c = 96 * (nn >> 5) + (nn & 31);
-          v = (reduced4(c, rq, scaled) + reduced4(c + 32, rq, scaled)) + reduced4(c + 64, rq, scaled);
+          v = (reduced4(c, rq) + reduced4(c + 32, rq)) + reduced4(c + 64, rq);
         } else {
-          v = reduced4(nn, rq, scaled);
+          v = reduced4(nn, rq);
         }
         if (n_splits > 1) {
           split_store4(split_rsrc(my_part), 16u * idx, __builtin_bit_cast(u32x4, v));
@@ -1086,14 +1085,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 4 && XFAST && !XF32) ? 2 : 1) void 
         }
       }
     }
-  };
-  store_sums(BoolC<!SCALE_LAST>{});
-  if constexpr (REDO) {
-    if (__syncthreads_or(out_of_range)) {  // uniform
-      scale_sums();
-      add_up_waves();
-      store_sums(BoolC<true>{});
-    }
+    if (!REDO || scaled || !__syncthreads_or(out_of_range)) break;  // uniform
   }
   if (n_splits > 1) {
     static_assert(ROWS * NR <= kSplitTileFloats || RB > 2, "a split launch's tile must fit its slot");
