@@ -242,7 +242,7 @@ XORENC_API int32_t xorenc_encode_exhaustive(int32_t m, int32_t n, int32_t n_in, 
  * xorenc_encode, or with fewest_patches != 0 xorenc_encode_exhaustive, for callers that need the patch total at once: waits
  * for hip_stream and leaves the total in *total_out, HOST memory that the GPU can write (hipHostMalloc), 4-byte aligned.
  * The last kernel writes it there, which spares the caller a copy of patch_off_out[q*n_units] behind the kernels
- * (about 9 us).  The only call that waits; not for streams that are being captured.
+ * (about 9 us).  This call and xorenc_encode_patches are the only ones that wait; not for streams that are being captured.
  */
 XORENC_API int32_t xorenc_encode_total(int32_t fewest_patches, int32_t m, int32_t n, int32_t n_in, int32_t q, int32_t n_out,
                                        const uint32_t *M_rows, const uint64_t *mask, const uint64_t *planes,

@@ -263,6 +263,9 @@ def test_encoder_with_more_counting_blocks_than_one_workgroup_adds_up():
     got = xe.decode(L, xe.OUT_PLANES).view(q, m // 32, 32, n // 64)
     want = (planes & mask).view(q, m // 32, n // 64, 32).transpose(2, 3)
     assert torch.equal(got, want)
+    # a first buffer that is too small: offsets and lists are written again from the scanned totals
+    again = xe.encode(m, n, n_in, q, M_rows, mask, planes, L.alpha, patch_capacity=L.patch.numel() // 2)
+    assert torch.equal(again.patch, L.patch) and torch.equal(again.patch_off, L.patch_off) and torch.equal(again.enc, L.enc)
 
 
 @pytest.mark.parametrize("q", [1, 2, 3, 4])

@@ -865,11 +865,13 @@ def test_threads_that_call_on_one_stream():
 
 
 @pytest.mark.parametrize("m,n,q,n_in", [(40, 1, 1, 8), (70, 33, 1, 16), (64, 95, 2, 16), (33, 130, 3, 20), (64, 2047, 4, 8),
-                                        (48, 4097, 2, 24), (80, 9001, 1, 16), (4500, 4001, 2, 8), (64, 16383, 1, 8)])
+                                        (48, 4097, 2, 24), (80, 9001, 1, 16), (4500, 4001, 2, 8), (64, 16383, 1, 8),
+                                        (4352, 8448, 1, 8), (8500, 4300, 2, 16)])
 def test_columns_without_gaps_are_the_columns_with_gaps(m, n, q, n_in):
     """One or two columns that follow each other without gaps go to the converting threads in 16-byte pieces, others element
     by element through LDS: the same conversion, so the same bits in Y, also where the last piece ends inside a dword and
-    what lies behind X is not a number.  (16 383 rows: the sums take the operands' place; 4500 rows of W: several rounds.)"""
+    what lies behind X is not a number.  (16 383 rows: the sums take the operands' place; the last two layers: several
+    rounds, see FEW_COLUMNS_IN_ROUNDS.)"""
     import torch
     import paper_1905_10138_amd as xe
     dev = torch.device("cuda:0")
