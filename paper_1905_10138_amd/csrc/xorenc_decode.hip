@@ -23,16 +23,29 @@ int32_t xorenc_internal_check_launch(void) { return xorenc_internal_hip_status((
 
 void xorenc_internal_begin_call(void) { (void)hipGetLastError(); }
 
-// bit i of out[j] = bit j of in[i]: halves of the square change places, then halves of the halves
-static void transpose_bits(const uint32_t *in, uint32_t *out) {
-  std::copy(in, in + 32, out);
-  uint32_t low = 0x0000ffffu;
-  for (int d = 16; d; d >>= 1, low ^= low << d)
-    for (int i = 0; i < 32; i = (i + d + 1) & ~d) {
-      const uint32_t t = ((out[i] >> d) ^ out[i + d]) & low;
-      out[i] ^= t << d;
-      out[i + d] ^= t;
+// Transposition of a 32 x 32 square of bits by blocks (J. O. Eklundh, A fast computer method for matrix transposing, 1972): in
+// every square of side 2 D on the diagonal the two blocks of side D off it change places, D = 16, 8, 4, 2, 1.
+template <int D>
+static void swap_blocks(uint32_t (&a)[32]) {
+  constexpr uint32_t kLeft = 0xffffffffu / ((1u << D) + 1u);  // the columns of the left blocks: D bits set, D clear, ...
+  for (int top = 0; top < 32; top += 2 * D)
+    for (int up = top; up < top + D; ++up) {
+      const uint32_t upper = a[up], lower = a[up + D];
+      a[up] = (upper & kLeft) | (lower & kLeft) << D;
+      a[up + D] = (upper >> D & kLeft) | (lower & ~kLeft);
     }
+}
+
+// bit i of out[j] = bit j of in[i]
+static void transpose_bits(const uint32_t *in, uint32_t *out) {
+  uint32_t a[32];
+  std::copy(in, in + 32, a);
+  swap_blocks<16>(a);
+  swap_blocks<8>(a);
+  swap_blocks<4>(a);
+  swap_blocks<2>(a);
+  swap_blocks<1>(a);
+  std::copy(a, a + 32, out);
 }
 
 int32_t xorenc_fill_dev_layer(const xorenc_layer *layer, DevLayer *D) {
