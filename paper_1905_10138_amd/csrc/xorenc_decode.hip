@@ -24,28 +24,28 @@ int32_t xorenc_internal_check_launch(void) { return xorenc_internal_hip_status((
 void xorenc_internal_begin_call(void) { (void)hipGetLastError(); }
 
 // Transposition of a 32 x 32 square of bits by blocks (J. O. Eklundh, A fast computer method for matrix transposing, 1972): in
-// every square of side 2 D on the diagonal the two blocks of side D off it change places, D = 16, 8, 4, 2, 1.
+// every square of side 2 D on the diagonal the two blocks of side D off it change places, D = 16, 8, 4, 2, 1.  (As loops 37 ns
+// for the five, unrolled 68.)
 template <int D>
-static void swap_blocks(uint32_t (&a)[32]) {
+static inline void swap_blocks(uint32_t *a) {
   constexpr uint32_t kLeft = 0xffffffffu / ((1u << D) + 1u);  // the columns of the left blocks: D bits set, D clear, ...
+#pragma clang loop unroll(disable)
   for (int top = 0; top < 32; top += 2 * D)
     for (int up = top; up < top + D; ++up) {
-      const uint32_t upper = a[up], lower = a[up + D];
-      a[up] = (upper & kLeft) | (lower & kLeft) << D;
-      a[up + D] = (upper >> D & kLeft) | (lower & ~kLeft);
+      const uint32_t differ = (a[up] >> D ^ a[up + D]) & kLeft;
+      a[up] ^= differ << D;
+      a[up + D] ^= differ;
     }
 }
 
 // bit i of out[j] = bit j of in[i]
 static void transpose_bits(const uint32_t *in, uint32_t *out) {
-  uint32_t a[32];
-  std::copy(in, in + 32, a);
-  swap_blocks<16>(a);
-  swap_blocks<8>(a);
-  swap_blocks<4>(a);
-  swap_blocks<2>(a);
-  swap_blocks<1>(a);
-  std::copy(a, a + 32, out);
+  std::copy(in, in + 32, out);
+  swap_blocks<16>(out);
+  swap_blocks<8>(out);
+  swap_blocks<4>(out);
+  swap_blocks<2>(out);
+  swap_blocks<1>(out);
 }
 
 int32_t xorenc_fill_dev_layer(const xorenc_layer *layer, DevLayer *D) {
