@@ -183,9 +183,9 @@ __device__ bool fewest_patches(uint32_t row, int n_care, int n_in, uint32_t *x_o
 //
 // Bound: instructions, about 34 and two per slot before it for an equation, of the slice with the most care bits in the
 // wave; with few waves the latency of the words' and the network's loads, which travel together.  us for the kernels of a call,
-// all in LDS / so: 2048 x 2048, S = 0.91, n_in = 16 15.4 / 11.8; 4096 x 4096, three planes, S = 0.8, n_in = 24 34.6 / 26.4;
-// 16384 x 4096, two planes, S = 0.95, n_in = 8 34.0 / 32.4; search, n_out = 192, n_in = 20 48.3 / 43.9.  Slices with more than
-// 32 care bits would need more registers than eight waves have (24 slots: 38 us for the second, a few slices had more).
+// all in LDS / so: 2048 x 2048, S = 0.91, n_in = 16 14.9 / 10.0; 4096 x 4096, three planes, S = 0.8, n_in = 24 33.2 / 26.0;
+// 16384 x 4096, two planes, S = 0.95, n_in = 8 33.2 / 31.6.  Slices with more than 32 care bits would need more registers than
+// eight waves have (24 slots: 38 us for the second, a few slices had more); what they cost beside the others stands below.
 constexpr int kFewCare = 32;
 constexpr int kPivotBits = 5;
 constexpr bool has_few_care(int Q, int J) { return J * (1 + 2 * Q) <= 10; }  // (the words of wider ones fill the registers)
@@ -295,7 +295,8 @@ struct FewCare {
 // Waves whose slices have few care bits keep everything in registers (FewCare).  The others' bound is the chain of dependent
 // LDS reads of a reduction (one per set pivot) and the longest of 64 slices in a wave.  The network's rows are read from LDS
 // (they used to be fetched from the kernel arguments with a vector load per equation), and the basis takes n_in KB of
-// LDS instead of 32.  Slices of 64 bits have a kernel of their own (JT = 1), all others share one (JT = 4).
+// LDS instead of 32.  JT: words per slice in the kernels that have the registers (one word with any number of planes, two with
+// one and two, three with one, see has_few_care, and n_in + Q <= 27); 0: any number of words, everything in LDS.
 //
 // SEARCH: first pass of the encoder with the fewest patches, over the slices [first, first + n).  The low half of a
 // slice's first patch word becomes its key: the solution x (below 2^24) when nothing was dropped, x with the lowest bit of

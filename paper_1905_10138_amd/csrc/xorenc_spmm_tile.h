@@ -38,8 +38,8 @@ struct TileLds {
 };
 
 // Results go past the L2: the lines that a launch leaves dirty there are written back after its last store, when nothing else
-// runs (16384 x 4096, one plane, B = 1024 106.2 -> 104.0 us,
-// two planes, n_out = 192, n_in = 20, B = 256 60.1 -> 58.4; in the kernels with smaller tiles it makes no difference).
+// runs (16384 x 4096, one plane, B = 1024 100.7 -> 99.2 us; two planes, n_out = 192, n_in = 20, B = 250 with the copy of X 61.7 ->
+// 61.1; in the kernels with smaller tiles it makes no difference).
 __device__ inline void store_past_l2(float *p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
