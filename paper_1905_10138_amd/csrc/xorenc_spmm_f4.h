@@ -52,7 +52,7 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 // takes).  X is converted and the tables are built once; the compressed words, patch offsets and scales of the next
 // round are requested before the current round's work (always the same number of requests, so that the waits
 // can count them: the last round asks for its own granule again), its patch entries after it.
-template <int Q, int NIBT, int PMAX, bool MR>
+template <int Q, int NIBT, int PMAX, bool MR, bool DIRECT>
 __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L, const uint16_t *__restrict__ X, int64_t ldx,
                                                                int B, float *__restrict__ Y, int64_t ldy, int PW, int KS,
                                                                int RG, int rounds, uint64_t kq_tab,
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   constexpr int NT = kF4Waves * 64;
   constexpr bool two_dw = NIBT == 3;
   constexpr int XR = 4;   // rows of X per thread, column and trip on the element-wise path
-  constexpr int MAXB = MR ? kF4MaxB : kF4MaxBOneRound;
+  constexpr int MAXB = MR && !DIRECT ? kF4MaxB : kF4MaxBOneRound;
   __shared__ __attribute__((aligned(16))) uint8_t xs[kF4XBytes];
   __shared__ __attribute__((aligned(16))) uint8_t scl[kF4SclBytes];        // scale bytes: (half-word, row of the A operand)
   __shared__ __attribute__((aligned(16))) uint32_t lut[NIBT * 2048];       // entry (table, value, half): four dwords
@@ -93,18 +93,19 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   const uint32_t CS = (uint32_t)(spr64 * 2 + 16);     // bytes between the columns of the raw copy of X
 
   // ---- X first: it is needed first.  One item = the 32 values of one half-word (blk) of one column (c), converted by one
-  // thread.  Columns that follow each other without gaps (ldx == B, at most two) are requested by that thread in 16-byte
-  // pieces and never pass through LDS unconverted: one trip to memory and two barriers fewer (us a launch, 4096 x 9216, two
-  // planes, B = 1 10.1 -> 8.8, B = 2 11.8 -> 9.8; 16384 x 4096, one plane, B = 1 8.2 -> 7.6).
+  // thread.  DIRECT: columns that follow each other without gaps (ldx == B, at most two) are requested by that thread in 16-byte
+  // pieces and never pass through LDS unconverted: one trip to memory and two barriers fewer (us a launch, with gaps / so:
+  // 4096 x 9216, two planes, B = 1 10.4 / 9.0; 16384 x 4096, one plane, B = 1 8.8 / 8.1).  A kernel of its own: as a branch
+  // it cost both kinds of calls 100 instructions before their first load (4096 x 4096, one plane, n_in = 8, B = 1, four layers
+  // 27.8 / 26.6 with the branch, 26.2 / 24.3 without).
   // Otherwise thread t takes rows t, t + NT, ... of every column (rows beyond n read as zero); the first XR rows per
   // column are requested now, the rest (long reductions of more columns) when those are parked.
-  const bool direct = B <= 2 && ldx == B && (reinterpret_cast<uintptr_t>(X) & 15) == 0;  // uniform
   const int nb = 2 * l_spr, nb_pad = 4 * ((l_spr + 1) >> 1);
   int cv_c, cv_blk;
-  if (MR && B >= 5) {
+  if (MAXB > 4 && B >= 5) {
     cv_c = tid & 7;
     cv_blk = tid >> 3;
-  } else if (B >= 3) {  // lanes c fastest, then blk%4: the 16-byte reads of 16 lanes fall into 16 different bank groups
+  } else if (MAXB > 2 && B >= 3) {  // lanes c fastest, then blk%4: the 16-byte reads of 16 lanes fall into 16 different bank groups
     cv_c = tid & 3;
     cv_blk = tid >> 2;
   } else {
@@ -114,11 +115,11 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   const bool cv_valid = cv_c < B && cv_blk < nb_pad;
   const uint32_t x_extent = (uint32_t)(((int64_t)(l_n - 1) * ldx + B) * 2);
   const __amdgpu_buffer_rsrc_t xrsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(X), 0, direct ? (x_extent + 3u) & ~3u : x_extent, kRsrcFlags);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(X), 0, DIRECT ? (x_extent + 3u) & ~3u : x_extent, kRsrcFlags);
   const uint32_t row_bytes = (uint32_t)(ldx * 2);
-  u32x4 xd[8];            // direct: the item's pieces (of both columns)
+  u32x4 xd[8];            // DIRECT: the item's pieces (of both columns)
   uint16_t xv[MAXB][XR];  // otherwise
-  if (direct) {
+  if constexpr (DIRECT) {
 #pragma unroll
     for (int i = 0; i < 8; ++i)
       if (i < 4 || B == 2)  // uniform
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   u32x4 V4[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) V4[i] = u32x4{0u, 0u, 0u, 0u};
-  if (!direct) {
+  if constexpr (!DIRECT) {
 #pragma unroll
     for (int c = 0; c < MAXB; ++c)
       if (c < B)  // uniform
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   // ---- X -> two e4m3 terms per value
   if (cv_valid) {
     uint32_t V[16];
-    if (direct) {
+    if constexpr (DIRECT) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         V[i] = xd[i >> 2][i & 3];
@@ -340,6 +341,10 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   // read from memory pair by pair instead); their offsets have arrived long ago
   uint32_t entv[Q];
   bool fast = true;
+  // (formed once for all planes: formed where a plane's entries are requested it takes a register that a load in flight may
+  // still write, and the requests wait for each other)
+  uint32_t entry_at = (uint32_t)lane * 2u;
+  asm volatile("" : "+v"(entry_at));
   auto load_entries = [&](const uint32_t(&off)[Q], uint32_t(&ent)[Q], bool &fst) __attribute__((always_inline)) {
     fst = true;
 #pragma unroll
@@ -348,7 +353,8 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
       const uint32_t total = __builtin_amdgcn_readlane(off[p], 2 * PW) - base;  // lane 2 PW: end of the range
       ent[p] = 0xFFFFu;
       if (total > 64u) fst = false;
-      if ((uint32_t)lane < min(total, 64u)) ent[p] = (l_patch + base)[lane];
+      if ((uint32_t)lane < min(total, 64u))
+        ent[p] = *reinterpret_cast<const uint16_t *>(reinterpret_cast<const uint8_t *>(l_patch + base) + entry_at);
     }
   };
   load_entries(offv, entv, fast);
@@ -418,8 +424,9 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
       auto flip_addr = [](uint32_t v) { return ((((v >> 6) & 15u) + ((v >> 1) & 16u)) << 4) + ((v & 3u) << 2); };
       auto flip_val = [](uint32_t v) { return 8u << (((v >> 2) & 7u) << 2); };
       // A group is G pairs of QI planes, as many as the flip area has room for: the mask's four arrangements are formed once
-      // for the planes of a pair (4096 x 9216, two planes, B = 1 8.8 -> 8.6 us).
-      constexpr int QI = Q <= FG ? Q : 1;
+      // for the planes of a pair (4096 x 9216, two planes, B = 1 8.8 -> 8.6 us).  Four planes go one after the other: a group
+      // of one pair would look for its lists pair by pair (16384 x 4096, n_in = 8, B = 1 81.5 us for four layers, 78.4 so).
+      constexpr int QI = Q <= 3 && Q <= FG ? Q : 1;
       constexpr int G = FG / QI;
 #pragma unroll
       for (int p0 = 0; p0 < Q; p0 += QI) {
@@ -542,17 +549,11 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
         float y = 0.f;
 #pragma unroll
         for (int p = 0; p < Q; ++p) {
-          // (four reads travel together)
-          float sum = 0.f;
-          for (int k0 = 0; k0 < KS; k0 += 4) {  // uniform
-            float v[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = src[(min(k0 + k, KS - 1) * Q + p) * 128];
-            sum = k0 ? sum + v[0] : v[0];
-#pragma unroll
-            for (int k = 1; k < 4; ++k) sum = k0 + k < KS ? sum + v[k] : sum;
-          }
-          const float a = -2.0f * al[p];
+          float sum = src[p * 128];
+          for (int k = 1; k < KS; ++k) sum += src[(k * Q + p) * 128];
+          float alpha = al[p];
+          asm volatile("" : "+v"(alpha));  // (multiplied where they arrive, the scales would be waited for before the loop)
+          const float a = -2.0f * alpha;
           y = p == 0 ? a * sum : y + a * sum;
         }
         Y[(int64_t)row * ldy + c] = y;
@@ -584,12 +585,24 @@ __global__ __launch_bounds__(kF4Waves * 64) void spmm_f4_kernel(DevLayerFor<1> L
   }
 }
 
+template <int Q, int NIBT, bool MR>
+void launch_f4_columns(const DevLayerFor<1> &A, const uint16_t *X, int64_t ldx, int B, float *Y, int64_t ldy, const F4Plan &P,
+                       uint64_t kq_tab, uint64_t rg_tab, hipStream_t st) {
+  constexpr int PMAX = MR ? f4_pmax_mr(Q, NIBT) : f4_pmax(Q);
+  const dim3 grid(P.grid), block(kF4Waves * 64);
+  if (B <= 2 && ldx == B && (reinterpret_cast<uintptr_t>(X) & 15) == 0)
+    hipLaunchKernelGGL((spmm_f4_kernel<Q, NIBT, PMAX, MR, true>), grid, block, 0, st, A, X, ldx, B, Y, ldy, P.PW, P.KS, P.RG,
+                       P.rounds, kq_tab, rg_tab);
+  else
+    hipLaunchKernelGGL((spmm_f4_kernel<Q, NIBT, PMAX, MR, false>), grid, block, 0, st, A, X, ldx, B, Y, ldy, P.PW, P.KS, P.RG,
+                       P.rounds, kq_tab, rg_tab);
+}
+
 template <int Q>
 int32_t launch_f4(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y, int64_t ldy, const F4Plan &P,
                   hipStream_t st) {
   const uint16_t *Xh = static_cast<const uint16_t *>(X);
   const DevLayerFor<1> A = layer_argument<1>(D);
-  const dim3 grid(P.grid), block(kF4Waves * 64);
   uint64_t kq_tab = 0, rg_tab = 0;  // wave w: K range w % KS of granule w / KS of the round
   for (int w = 0; w < kF4Waves; ++w) {
     kq_tab |= (uint64_t)(w % P.KS) << (4 * w);
@@ -597,17 +610,17 @@ int32_t launch_f4(const DevLayer &D, const void *X, int64_t ldx, int B, float *Y
   }
   if (P.rounds == 1 && B <= kF4MaxBOneRound) {
     switch (D.nib) {
-      case 1: hipLaunchKernelGGL((spmm_f4_kernel<Q, 1, f4_pmax(Q), false>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
-      case 2: hipLaunchKernelGGL((spmm_f4_kernel<Q, 2, f4_pmax(Q), false>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
-      case 3: hipLaunchKernelGGL((spmm_f4_kernel<Q, 3, f4_pmax(Q), false>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
-      default: hipLaunchKernelGGL((spmm_f4_kernel<Q, 4, f4_pmax(Q), false>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, 1, kq_tab, rg_tab); break;
+      case 1: launch_f4_columns<Q, 1, false>(A, Xh, ldx, B, Y, ldy, P, kq_tab, rg_tab, st); break;
+      case 2: launch_f4_columns<Q, 2, false>(A, Xh, ldx, B, Y, ldy, P, kq_tab, rg_tab, st); break;
+      case 3: launch_f4_columns<Q, 3, false>(A, Xh, ldx, B, Y, ldy, P, kq_tab, rg_tab, st); break;
+      default: launch_f4_columns<Q, 4, false>(A, Xh, ldx, B, Y, ldy, P, kq_tab, rg_tab, st); break;
     }
   } else {
     switch (D.nib) {
-      case 1: hipLaunchKernelGGL((spmm_f4_kernel<Q, 1, f4_pmax_mr(Q, 1), true>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
-      case 2: hipLaunchKernelGGL((spmm_f4_kernel<Q, 2, f4_pmax_mr(Q, 2), true>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
-      case 3: hipLaunchKernelGGL((spmm_f4_kernel<Q, 3, f4_pmax_mr(Q, 3), true>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
-      default: hipLaunchKernelGGL((spmm_f4_kernel<Q, 4, f4_pmax_mr(Q, 4), true>), grid, block, 0, st, A, Xh, ldx, B, Y, ldy, P.PW, P.KS, P.RG, P.rounds, kq_tab, rg_tab); break;
+      case 1: launch_f4_columns<Q, 1, true>(A, Xh, ldx, B, Y, ldy, P, kq_tab, rg_tab, st); break;
+      case 2: launch_f4_columns<Q, 2, true>(A, Xh, ldx, B, Y, ldy, P, kq_tab, rg_tab, st); break;
+      case 3: launch_f4_columns<Q, 3, true>(A, Xh, ldx, B, Y, ldy, P, kq_tab, rg_tab, st); break;
+      default: launch_f4_columns<Q, 4, true>(A, Xh, ldx, B, Y, ldy, P, kq_tab, rg_tab, st); break;
     }
   }
   return xorenc_internal_check_launch();
